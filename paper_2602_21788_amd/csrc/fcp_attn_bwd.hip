@@ -436,6 +436,28 @@ static int bwd_step(const void* q, const void* k, const void* v, const void* d_o
   void* region_kv = scratch;
   void* region_q = static_cast<char*>(scratch) + fcp::sched_region_bytes(n_work, cap_kv);
   float* stats = reinterpret_cast<float*>(static_cast<char*>(region_q) + fcp::sched_region_bytes(n_work, cap_q));
+  int dev = 0, n_cu = 0;
+  auto count_cus = [&]() -> int {
+    FCP_HIP_CHECK(hipGetDevice(&dev));
+    FCP_HIP_CHECK(hipDeviceGetAttribute(&n_cu, hipDeviceAttributeMultiprocessorCount, dev));
+    return FCP_OK;
+  };
+  // One pass or two.  The one-pass kernel (csrc/fcp_attn_bwd_fused.hip) forms S and dP once and needs no query-tile launch; it has the
+  // units of key tiles only, which take turns at the dQ rows of a sequence.  That pays where sequences are short, and not where many
+  // tiles follow each other through the same rows.  Lists of whole sequences (tq == tkv), measured:
+  //   256 rows or less per item: 1.1 to 2.4 times as fast at 8 to 64 query heads, down to a handful of items, except for
+  //       three or more heads per KV head and fewer tiles than CUs, where one longer sequence of the list sets the
+  //       time (0.82 to 1.0 there); at 333 to 400 rows 0.96 to 1.1;
+  //   one query head per KV head, up to 1024 tiles: 1.06 to 1.6 times as fast at any length; at 1500 tiles 1.0.
+  // Sharded lists (tq < tkv) have the whole sequence's tiles over a part of its rows: 0.63 to 1.1, they stay with two passes.
+  const int group = hq / hkv;
+  const int64_t key_units = (int64_t)tkv * hkv / fcp::kBwdBN;
+  bool fused = head_dim == 128 && hkv % fcp::kNumXcd == 0 && n_work >= 1 && n_work <= 1024 && tq == tkv;
+  if (fused) {
+    const int rcc = count_cus();
+    if (rcc != FCP_OK) return rcc;
+    fused = n_cu == 256 && ((tkv <= 256 * n_work && (group <= 2 || key_units >= n_cu)) || (group == 1 && key_units <= 4 * n_cu));
+  }
   // direct mode: where every row's result comes from (and the accumulator rows that are accumulated into cleared),
   // on extra blocks of the scheduling launch
   fcp::RowStates rs{};
@@ -460,7 +482,9 @@ static int bwd_step(const void* q, const void* k, const void* v, const void* d_o
   const int head_pair = ((hq / hkv) % 2 == 0) ? 1 : 0;
   int rc = fcp::launch_schedule_bwd((int64_t)hkv * head_dim * 2, q_limit, k_from, work, n_work, cu_seqlens_kv, n_seqs, tq, tkv,
                                     cap_kv, region_kv, head_pair ? fcp::kDqBM : 2 * fcp::kDqBM, cap_q, region_q, lse, delta, (int64_t)hq * tq, stats, st,
-                                    direct ? &rs : nullptr);
+                                    direct ? &rs : nullptr, fused ? fcp::bwd_chain(scratch, n_work, tq, tkv, hq) : nullptr,
+                                    fused ? fcp::bwd_chain_flags(scratch, n_work, tq, tkv, hq) : nullptr,
+                                    fused ? fcp::chain_flag_words(tq, hq, n_work) : 0);
   if (rc != FCP_OK) return rc;
 
   fcp::BwdParams p;
@@ -472,9 +496,7 @@ static int bwd_step(const void* q, const void* k, const void* v, const void* d_o
   p.tq = tq; p.hq = hq; p.hkv = hkv;
   p.scale = softmax_scale; p.scale_log2 = softmax_scale * fcp::kLog2e;
 
-  int dev = 0, n_cu = 256;
-  FCP_HIP_CHECK(hipGetDevice(&dev));
-  FCP_HIP_CHECK(hipDeviceGetAttribute(&n_cu, hipDeviceAttributeMultiprocessorCount, dev));
+  if (n_cu == 0 && (rc = count_cus()) != FCP_OK) return rc;
   auto grid_for = [&](int64_t units, int per_cu) {
     int64_t blocks = (int64_t)n_cu * per_cu;
     if (blocks > units) blocks = (units + 7) / 8 * 8;   // a multiple of the XCD count
@@ -482,6 +504,13 @@ static int bwd_step(const void* q, const void* k, const void* v, const void* d_o
     return dim3((unsigned)blocks);
   };
 
+  if (fused) {
+    p.chain = fcp::bwd_chain(scratch, n_work, tq, tkv, hq);
+    p.flags = fcp::bwd_chain_flags(scratch, n_work, tq, tkv, hq);
+    p.hdr = (fcp::SchedHeader*)region_kv;
+    p.tiles = fcp::sched_tiles(region_kv, n_work);
+    return fcp::launch_bwd_fused(p, cap_kv * hkv, n_cu, st);
+  }
   // dK/dV over key tiles
   p.hdr = (fcp::SchedHeader*)region_kv;
   p.tiles = fcp::sched_tiles(region_kv, n_work);

@@ -24,11 +24,18 @@ struct BwdParams {
   uint16_t* dq_out;
   uint16_t* dk_out;
   uint16_t* dv_out;
+  // One-pass kernel: the chain record of every tile (kChainWords words: rank, first block of the next tile, flag base,
+  // first block) and the flag words.
+  const int32_t* chain;
+  int32_t* flags;
   int32_t tq, hq, hkv;
   float scale, scale_log2;
 };
 
 // dK / dV over key tiles (csrc/fcp_attn_dkv.hip).  `units` = upper bound of (key tile, KV head) units.
 int launch_dkv(const BwdParams& p, int head_dim, int64_t units, int n_cu, hipStream_t stream);
+
+// dQ, dK and dV in one pass over key tiles (csrc/fcp_attn_bwd_fused.hip), 128 channels per head.
+int launch_bwd_fused(const BwdParams& p, int64_t units, int n_cu, hipStream_t stream);
 
 }  // namespace fcp

@@ -140,7 +140,7 @@ int launch_schedule_bwd(int64_t kv_row_bytes, const int32_t* q_limit, const int3
                         const fcp_work_desc* work, int64_t n_work, const int32_t* cu_seqlens_kv, int32_t n_seqs,
                         int32_t tq, int32_t tkv, int64_t cap_kv, void* region_kv, int32_t dq_tile, int64_t cap_q, void* region_q,
                         const float* lse, const float* delta, int64_t n_stats, float* stats, hipStream_t stream,
-                        const RowStates* states = nullptr);
+                        const RowStates* states = nullptr, int32_t* chain = nullptr, int32_t* flags = nullptr, int64_t n_flags = 0);
 
 // Direct modes: one state byte per query row and (backward: kv_state not NULL) per pool key: 0 untouched, 1 several
 // work items contribute (backward: accumulated in fp32, the accumulator row is cleared when the accumulators are
@@ -168,6 +168,24 @@ inline uint8_t* bwd_q_state(void* scratch, int64_t n_work, int32_t tq, int32_t t
 }
 inline uint8_t* bwd_kv_state(void* scratch, int64_t n_work, int32_t tq, int32_t tkv, int32_t hq) {
   return bwd_q_state(scratch, n_work, tq, tkv, hq) + pad_to((size_t)tq, 256);
+}
+
+// The one-pass backward (csrc/fcp_attn_bwd_fused.hip): per key tile its place in the chain of tiles that add to the same dQ rows, and
+// one flag word per (32-row block of a chain, head, half of the rows and 32-channel slice).
+constexpr int kChainWords = 4;            // rank (-1: atomics), first block of the next tile, the chain's first flag block, first block
+constexpr int kChainSlices = 8;
+inline int64_t chain_flag_words(int32_t tq, int32_t hq, int64_t n_work) { return ((int64_t)tq / 32 + 1 + n_work) * hq * kChainSlices; }
+inline size_t chain_bytes(int32_t tq, int32_t tkv, int32_t hq, int32_t head_dim, int64_t n_work) {
+  if (head_dim != 128) return 0;
+  return pad_to((size_t)kv_tile_cap(tkv, n_work) * kChainWords * sizeof(int32_t), 256) +
+         pad_to((size_t)chain_flag_words(tq, hq, n_work) * sizeof(int32_t), 256);
+}
+inline int32_t* bwd_chain(void* scratch, int64_t n_work, int32_t tq, int32_t tkv, int32_t hq) {
+  return reinterpret_cast<int32_t*>(bwd_kv_state(scratch, n_work, tq, tkv, hq) + pad_to((size_t)tkv, 256));
+}
+inline int32_t* bwd_chain_flags(void* scratch, int64_t n_work, int32_t tq, int32_t tkv, int32_t hq) {
+  return reinterpret_cast<int32_t*>(reinterpret_cast<char*>(bwd_chain(scratch, n_work, tq, tkv, hq)) +
+                                    pad_to((size_t)kv_tile_cap(tkv, n_work) * kChainWords * sizeof(int32_t), 256));
 }
 
 // The forward's row states follow its tile list in its scratch buffer.

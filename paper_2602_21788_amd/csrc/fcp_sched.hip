@@ -76,12 +76,15 @@ __device__ inline int32_t fwd_cost(const MaskTables& m, const fcp_work_desc& w, 
   return c;
 }
 
-// key tile kt (of `tile` keys) of segment s: cost = query blocks (of `inner` rows) that see its first key
+// key tile kt (of `tile` keys) of segment s: cost = query blocks (of `inner` rows) that see its first key; in a chained list blocks
+// counted from the item's first row, from the one with the first row that sees that key on
+template <bool Chain>
 __device__ inline int32_t bwd_cost(const MaskTables& m, const int32_t* cu, const fcp_work_desc& w, int s, int32_t kt,
                                    int32_t tile, int32_t inner) {
   const int64_t first_k_pos = (int64_t)w.k_seq_start[s] + (int64_t)kt * tile;
   int64_t first_row = m.from(w, cu, first_k_pos) - w.q_seq_start;
   if (first_row < 0) first_row = 0;
+  if constexpr (Chain) return max(1, ceil_div(w.q_len, inner) - (int32_t)min((int64_t)w.q_len, first_row / inner));
   const int64_t rows = (int64_t)w.q_len - first_row;
   return rows <= 0 ? 0 : (int32_t)((rows + inner - 1) / inner);
 }
@@ -284,13 +287,16 @@ struct SortArea {
 };
 
 // One tile list, built by one block.
+template <bool Chain>
 __device__ void build_list(
     int backward, int check_step, int32_t tile, int32_t inner, int32_t max_seg_keys, const MaskTables m,
     const fcp_work_desc* __restrict__ work, int32_t n_work,
     const int32_t* __restrict__ cu, int32_t n_seqs, int32_t tq, int32_t tkv, int32_t n_parts,
     int32_t tile_cap, SchedHeader* hdr, int32_t* item_off, int32_t* item_flags, Tile* tiles,
     int32_t (*s_rng)[7],                 // LDS, kMaxExclusiveScan rows: seq (-1 = invalid), q range, two key ranges
-    SortArea* area, int32_t* s_fl) {     // LDS: sort keys (later the histogram and the offsets), one flag word per item
+    int32_t (*s_flag0)[2],               // LDS, kMaxExclusiveScan rows: [0] = the item's first flag block
+    SortArea* area, int32_t* s_fl,       // LDS: sort keys (later the histogram and the offsets), one flag word per item
+    int32_t* chain) {                    // chain records of the key tiles, or NULL (then the order of equal costs is free)
   __shared__ int32_t s_wave[kSchedThreads / 64];
   __shared__ int32_t s_max, s_rej, s_carry;
   int32_t* const s_hist = area->later.hist;
@@ -313,6 +319,16 @@ __device__ void build_list(
   if (tid == 0) { s_max = 0; s_rej = 0; s_carry = 0; }
   for (int b = tid; b < kBuckets; b += kSchedThreads) s_hist[b] = 0;
   __syncthreads();
+
+  // Chains (key tiles only, at most kMaxExclusiveScan items): the flags of the query blocks of the items that own their rows.
+  if constexpr (Chain) {
+    const int32_t i = tid;
+    const int32_t nb = i < n_work && (s_fl[i] & kFlagQExclusive) ? ceil_div(s_rng[i][2] - s_rng[i][1], inner) : 0;
+    int32_t total;
+    const int32_t ex = block_exclusive_scan(nb, s_wave, total);
+    if (i < n_work) s_flag0[i][0] = ex;
+    __syncthreads();
+  }
 
   // Pass 1: validate, count tiles per item, exclusive offsets into item_off[0..n_work].
   for (int32_t base = 0; base < n_work; base += kSchedThreads) {
@@ -390,7 +406,54 @@ __device__ void build_list(
     k->q_seq_start = w.q_seq_start;
     k->q_len = w.q_len;
     k->flags = (fl & (sg ? kFlagSeg1Exclusive : kFlagSeg0Exclusive)) ? kFlagSeg0Exclusive : 0;
-    return bwd_cost(m, cu, w, sg, kt, tile, inner);
+    return bwd_cost<Chain>(m, cu, w, sg, kt, tile, inner);
+  };
+
+  // Place of key tile t in the chain of its item, if the item owns its query rows (else the tile adds with atomics, rank -1):
+  // rank = number of the item's tiles before it, `next` = first query block of the tile after it (or past the last block),
+  // `first` = its own first block, flag0 = the item's first flag block.  Order: by bucket (decreasing), then by flat number.  Inside a
+  // segment the buckets do not grow with the key, so the tiles of the other segment that come before are found by bisection.
+  // Blocks are counted so that tiles of one bucket start at the same one: a tile later in the chain never starts at an earlier block.
+  auto chain_place = [&](int32_t t, int32_t bucket, int32_t& rank, int32_t& next, int32_t& first, int32_t& flag0) {
+    int32_t lo = 0, hi = n_work - 1;
+    while (lo < hi) {
+      const int32_t mid = (lo + hi + 1) >> 1;
+      if (s_off[mid] <= t) lo = mid; else hi = mid - 1;
+    }
+    const fcp_work_desc w = work[lo];
+    const int32_t nqb = ceil_div(w.q_len, inner);
+    auto first_block = [&](int32_t b) {               // first block of the tiles of bucket b
+      const int64_t most = (((int64_t)b + 1) << shift) - 1;
+      return b >= kBuckets - 1 || most >= nqb ? 0 : nqb - (int32_t)most;
+    };
+    first = first_block(bucket);
+    next = nqb;
+    rank = -1;
+    flag0 = 0;
+    if (!(s_fl[lo] & kFlagQExclusive)) return;
+    flag0 = s_flag0[lo][0];
+    const int32_t nt0 = ceil_div(visible_len(m, w, 0, w.q_len - 1), tile);
+    const int32_t my_seg = t - s_off[lo] >= nt0 ? 1 : 0;
+    const int32_t my_kt = t - s_off[lo] - (my_seg ? nt0 : 0);
+    rank = my_kt;
+    for (int32_t sg = 0; sg < w.n_seg; ++sg) {
+      const int32_t nt = ceil_div(visible_len(m, w, sg, w.q_len - 1), tile);
+      auto bucket_of = [&](int32_t kt) { return min(bwd_cost<Chain>(m, cu, w, sg, kt, tile, inner) >> shift, kBuckets - 1); };
+      int32_t a;                                      // the segment's first tile after t
+      if (sg == my_seg) {
+        a = my_kt + 1;
+      } else {
+        int32_t b = nt;                               // first kt with bucket < `bucket` (ties stand before t) or <= `bucket`
+        a = 0;
+        while (a < b) {
+          const int32_t mid = (a + b) >> 1, bm = bucket_of(mid);
+          if (sg < my_seg ? bm < bucket : bm <= bucket) b = mid; else a = mid + 1;
+        }
+        rank += a;
+      }
+      if (a < nt) next = min(next, first_block(bucket_of(a)));
+    }
+    if (rank == 0) first = 0;                         // rows that see no key get their zeros from the item's first tile
   };
 
   // (a thread's first tile and its cost stay in registers for the scatter pass: with up to 1024 tiles, all of them)
@@ -415,13 +478,56 @@ __device__ void build_list(
     s_hist[b_lo] = ex + h_hi;
   }
   __syncthreads();
-  for (int32_t t = tid; t < n_tiles; t += kSchedThreads) {
-    Tile tl;
-    int32_t c;
-    if (t == tid) { tl = first_tile; c = first_cost; }
-    else c = decode(t, tl);
-    const int32_t pos = atomicAdd(&s_hist[min(c >> shift, kBuckets - 1)], 1);
-    tiles[pos] = tl;
+  if constexpr (!Chain) {
+    for (int32_t t = tid; t < n_tiles; t += kSchedThreads) {
+      Tile tl;
+      int32_t c;
+      if (t == tid) { tl = first_tile; c = first_cost; }
+      else c = decode(t, tl);
+      const int32_t pos = atomicAdd(&s_hist[min(c >> shift, kBuckets - 1)], 1);
+      tiles[pos] = tl;
+    }
+  } else {
+    // The tiles of a chain must stand in the list in the order in which they take turns: by bucket, then in the order of the
+    // flat tile numbers, i.e. the scatter has to be stable.  A wave groups its lanes by bucket, the waves
+    // take their places one after the other.
+    for (int32_t base = 0; base < n_tiles; base += kSchedThreads) {
+      const int32_t t = base + tid;
+      const bool live = t < n_tiles;
+      Tile tl;
+      int32_t bucket = -1 - tid, rank = -1, next = 0, first = 0, flag0 = 0;
+      if (live) {
+        int32_t c;
+        if (base == 0) { tl = first_tile; c = first_cost; }
+        else c = decode(t, tl);
+        bucket = min(c >> shift, kBuckets - 1);
+        chain_place(t, bucket, rank, next, first, flag0);
+      }
+      const int lane = tid & 63;
+      uint64_t mine = 0;                              // lanes of the wave with this lane's bucket
+      for (uint64_t todo = __builtin_amdgcn_ballot_w64(live); todo;) {
+        const int l = __builtin_ctzll(todo);
+        const int32_t bl = __builtin_amdgcn_readlane(bucket, l);
+        const uint64_t m = __builtin_amdgcn_ballot_w64(live && bucket == bl);
+        if (bucket == bl) mine = m;
+        todo &= ~m;
+      }
+      const int before = __builtin_popcountll(mine & (((uint64_t)1 << lane) - 1));
+      const int n_waves = min(kSchedThreads, n_tiles - base + 63) / 64;
+      int32_t pos = 0;
+      for (int w = 0; w < n_waves; ++w) {
+        if ((tid >> 6) == w && live) {
+          pos = s_hist[bucket] + before;
+          if (before == 0) s_hist[bucket] = pos + __builtin_popcountll(mine);
+        }
+        __syncthreads();
+      }
+      if (live) {
+        tiles[pos] = tl;
+        int32_t* r = chain + (int64_t)pos * kChainWords;
+        r[0] = rank; r[1] = next; r[2] = flag0; r[3] = first;
+      }
+    }
   }
   if (tid == 0) {
     hdr->n_tiles = n_tiles;
@@ -480,6 +586,7 @@ __device__ void row_states(
       s_rng[i][4] = s_rng[i][3] + s_vis[i][0];
       s_rng[i][5] += base;
       s_rng[i][6] = s_rng[i][5] + s_vis[i][1];
+      if (s_vis[i][0] + s_vis[i][1] == 0) s_rng[i][2] = s_rng[i][1];   // no key, no key tile: its rows are untouched
     }
   }
   __syncthreads();
@@ -612,8 +719,8 @@ __global__ __launch_bounds__(kSchedThreads) void sched_kernel(
   __shared__ SortArea s_area;
   const int b = blockIdx.x;
   if (b == 0) {
-    build_list(backward, check_step, tile, inner, max_seg_keys, m, work, n_work, cu, n_seqs, tq, tkv, n_parts, tile_cap,
-               hdr, item_off, item_flags, tiles, s_rng, &s_area, s_fl);
+    build_list<false>(backward, check_step, tile, inner, max_seg_keys, m, work, n_work, cu, n_seqs, tq, tkv, n_parts, tile_cap,
+               hdr, item_off, item_flags, tiles, s_rng, s_vis, &s_area, s_fl, nullptr);
   } else if (b <= fill_blocks) {
     const int64_t stride = (int64_t)fill_blocks * kSchedThreads;
     for (int64_t i = (int64_t)(b - 1) * kSchedThreads + threadIdx.x; i < lse_fill_n; i += stride)
@@ -635,12 +742,13 @@ struct ListJob {
   int32_t* item_flags;
   Tile* tiles;
 };
+template <bool Chain>
 __global__ __launch_bounds__(kSchedThreads) void sched_bwd_kernel(
     const ListJob kv, const ListJob qt, int32_t max_seg_keys, const MaskTables m,
     const fcp_work_desc* __restrict__ work, int32_t n_work,
     const int32_t* __restrict__ cu, int32_t n_seqs, int32_t tq, int32_t tkv,
     const float* __restrict__ lse, const float* __restrict__ delta, int64_t n_stats, float* __restrict__ stats,
-    int stat_blocks, const RowStateJob states) {
+    int stat_blocks, int32_t* __restrict__ chain, int32_t* __restrict__ flags, int64_t n_flags, const RowStateJob states) {
   __shared__ int32_t s_rng[kMaxExclusiveScan][7];
   __shared__ int32_t s_vis[kMaxExclusiveScan][2];
   __shared__ int32_t s_fl[kMaxExclusiveScan];
@@ -648,8 +756,9 @@ __global__ __launch_bounds__(kSchedThreads) void sched_bwd_kernel(
   const int b = blockIdx.x;
   if (b < 2) {
     const ListJob& j = b == 0 ? kv : qt;
-    build_list(b == 0 ? 1 : 0, 0, j.tile, j.inner, max_seg_keys, m, work, n_work, cu, n_seqs, tq, tkv, 1,
-               j.tile_cap, j.hdr, j.item_off, j.item_flags, j.tiles, s_rng, &s_area, s_fl);
+    if (Chain && b == 1) return;         // (the one-pass kernel has key tiles only)
+    build_list<Chain>(b == 0 ? 1 : 0, 0, j.tile, j.inner, max_seg_keys, m, work, n_work, cu, n_seqs, tq, tkv, 1,
+               j.tile_cap, j.hdr, j.item_off, j.item_flags, j.tiles, s_rng, s_vis, &s_area, s_fl, chain);
   } else if (b < 2 + stat_blocks) {
     const int64_t stride = (int64_t)stat_blocks * kSchedThreads;
     for (int64_t i = (int64_t)(b - 2) * kSchedThreads + threadIdx.x; i < n_stats; i += stride) {
@@ -657,6 +766,8 @@ __global__ __launch_bounds__(kSchedThreads) void sched_bwd_kernel(
       stats[i] = l == -INFINITY ? -INFINITY : -l * 1.4426950408889634f;
       stats[n_stats + i] = -delta[i];
     }
+    if constexpr (Chain)
+      for (int64_t i = (int64_t)(b - 2) * kSchedThreads + threadIdx.x; i < n_flags; i += stride) flags[i] = 0;
   } else {   // direct mode: the row states, and the accumulator rows that are accumulated into cleared
     row_states(2 + stat_blocks, gridDim.x - 2 - stat_blocks, states, max_seg_keys, m, work, n_work, cu, n_seqs, tq, tkv,
                s_rng, s_vis, s_fl, &s_area);
@@ -745,7 +856,7 @@ int launch_schedule_bwd(int64_t kv_row_bytes, const int32_t* q_limit, const int3
                         const fcp_work_desc* work, int64_t n_work, const int32_t* cu_seqlens_kv, int32_t n_seqs,
                         int32_t tq, int32_t tkv, int64_t cap_kv, void* region_kv, int32_t dq_tile, int64_t cap_q, void* region_q,
                         const float* lse, const float* delta, int64_t n_stats, float* stats, hipStream_t stream,
-                        const RowStates* states) {
+                        const RowStates* states, int32_t* chain, int32_t* flags, int64_t n_flags) {
   if (states) { const int rcs = check_row_states(n_work); if (rcs != FCP_OK) return rcs; }
   auto job = [&](void* region, int32_t tile, int32_t inner, int64_t cap) {
     ListJob j;
@@ -760,11 +871,12 @@ int launch_schedule_bwd(int64_t kv_row_bytes, const int32_t* q_limit, const int3
   if (stat_blocks > 1024) stat_blocks = 1024;
   if (stat_blocks < 1) stat_blocks = 1;
   const int state_blocks = states ? row_state_blocks(tq, states->kv_state ? tkv : 0) : 0;
-  hipLaunchKernelGGL(sched_bwd_kernel, dim3((unsigned)(2 + stat_blocks + state_blocks)), dim3(kSchedThreads), 0, stream,
+  const auto kernel = chain ? sched_bwd_kernel<true> : sched_bwd_kernel<false>;   // (two kernels: a longer one begins later)
+  hipLaunchKernelGGL(kernel, dim3((unsigned)(2 + stat_blocks + state_blocks)), dim3(kSchedThreads), 0, stream,
                      job(region_kv, kBwdBN, kBwdBM, cap_kv), job(region_q, dq_tile, kDqBN, cap_q),
                      max_segment_keys(kv_row_bytes), MaskTables{q_limit, k_from}, work,
                      (int32_t)n_work, cu_seqlens_kv, n_seqs, tq, tkv, lse, delta, n_stats, stats, (int)stat_blocks,
-                     make_job(states));
+                     chain, flags, n_flags, make_job(states));
   FCP_HIP_CHECK(hipGetLastError());
   return FCP_OK;
 }
@@ -773,14 +885,15 @@ int launch_schedule_bwd(int64_t kv_row_bytes, const int32_t* q_limit, const int3
 
 extern "C" size_t fcp_scratch_bytes(int which, int32_t tq, int32_t tkv, int32_t hq, int32_t hkv,
                                     int32_t head_dim, int64_t n_work, int32_t n_parts) {
-  (void)hkv; (void)head_dim;
+  (void)hkv;
   if (tq < 0 || tkv < 0 || n_work < 0 || n_parts < 0) return 0;
   if (which == FCP_SCRATCH_BWD)   // key-tile list (dK/dV kernel), query-tile list (dQ kernel), packed row statistics,
                                   // row states
     return fcp::sched_region_bytes(n_work, fcp::kv_tile_cap(tkv, n_work)) +
            fcp::sched_region_bytes(n_work, fcp::q_tile_cap(tq, tkv, n_work, 1 << 20)) +
            fcp::pad_to((size_t)hq * (size_t)tq * 8, 256) +
-           fcp::pad_to((size_t)tq, 256) + fcp::pad_to((size_t)tkv, 256);   // + row states of the direct mode
+           fcp::pad_to((size_t)tq, 256) + fcp::pad_to((size_t)tkv, 256) +  // + row states of the direct mode
+           fcp::chain_bytes(tq, tkv, hq, head_dim, n_work);                // + chains of the one-pass kernel
   return fcp::sched_region_bytes(n_work, fcp::q_tile_cap(tq, tkv, n_work, n_parts)) +
          fcp::pad_to((size_t)tq, 256);                                  // + row states of the direct mode
 }
