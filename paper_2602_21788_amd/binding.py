@@ -105,8 +105,17 @@ def _check(rc: int):
         raise FcpError(rc, lib().fcp_last_error().decode())
 
 
+_char_at, _addressof = ctypes.c_char.from_buffer, ctypes.addressof
+
+
 def _np_ptr(a):
-    return None if a is None else a.ctypes.data_as(ctypes.c_void_p)
+    """Address of a contiguous numpy array (by the buffer protocol: a third of the cost of a.ctypes.data)."""
+    if a is None:
+        return None
+    try:
+        return _addressof(_char_at(a))
+    except (TypeError, ValueError):               # read-only or empty
+        return a.ctypes.data
 
 
 def _dev_ptr(t):
@@ -136,12 +145,11 @@ def fcp_shard_plan(seq_lens, cp_degree, base_rank=None):
     if br is not None and br.shape != sl.shape:
         raise ValueError("base_rank must match seq_lens")
     nc, nw = ctypes.c_int64(0), ctypes.c_int64(0)
-    _check(lib().fcp_shard_plan(_np_ptr(sl), _np_ptr(cd), _np_ptr(br), len(sl), None, 0, ctypes.byref(nc),
-                                None, 0, ctypes.byref(nw)))
-    chunks = np.zeros(nc.value, CHUNK_DTYPE)
-    work = np.zeros(nw.value, WORK_DTYPE)
-    _check(lib().fcp_shard_plan(_np_ptr(sl), _np_ptr(cd), _np_ptr(br), len(sl), _np_ptr(chunks), nc.value,
-                                ctypes.byref(nc), _np_ptr(work), nw.value, ctypes.byref(nw)))
+    plan, lists, pc, pw = lib().fcp_shard_plan, (_np_ptr(sl), _np_ptr(cd), _np_ptr(br), len(sl)), ctypes.byref(nc), ctypes.byref(nw)
+    _check(plan(*lists, None, 0, pc, None, 0, pw))
+    chunks = np.empty(nc.value, CHUNK_DTYPE)      # (every field of every entry is written)
+    work = np.empty(nw.value, WORK_DTYPE)
+    _check(plan(*lists, _np_ptr(chunks), nc.value, pc, _np_ptr(work), nw.value, pw))
     return chunks, work
 
 
@@ -169,8 +177,8 @@ def fcp_shard_plan_mixed(seq_lens, cp_degree, spans, base_rank=None):
     nc, nw = ctypes.c_int64(0), ctypes.c_int64(0)
     _check(lib().fcp_shard_plan_mixed(_np_ptr(sl), _np_ptr(cd), _np_ptr(br), len(sl), _np_ptr(sp), len(sp), None, 0,
                                       ctypes.byref(nc), None, 0, ctypes.byref(nw)))
-    chunks = np.zeros(nc.value, CHUNK_DTYPE)
-    work = np.zeros(nw.value, WORK_DTYPE)
+    chunks = np.empty(nc.value, CHUNK_DTYPE)
+    work = np.empty(nw.value, WORK_DTYPE)
     _check(lib().fcp_shard_plan_mixed(_np_ptr(sl), _np_ptr(cd), _np_ptr(br), len(sl), _np_ptr(sp), len(sp),
                                       _np_ptr(chunks), nc.value, ctypes.byref(nc), _np_ptr(work), nw.value,
                                       ctypes.byref(nw)))
@@ -212,14 +220,13 @@ def fcp_plan_groups(seq_lens, n_ranks, tokens_per_rank, cost_model, eta=None):
         raise ValueError("eta must match seq_lens")
     cm = cost_model if isinstance(cost_model, CostModel) else CostModel(*[float(x) for x in cost_model])
     k = len(sl)
-    group_of = np.zeros(k, np.int32)
-    d_min, degree, base = (np.zeros(max(k, 1), np.int32) for _ in range(3))
+    group_of, d_min, degree, base = (np.empty(max(k, 1), np.int32) for _ in range(4))
     ng, mk = ctypes.c_int32(0), ctypes.c_double(0.0)
     _check(lib().fcp_plan_groups(_np_ptr(sl), _np_ptr(et), k, int(n_ranks), int(tokens_per_rank), ctypes.byref(cm),
                                  _np_ptr(group_of), ctypes.byref(ng), _np_ptr(d_min), _np_ptr(degree), _np_ptr(base),
                                  ctypes.byref(mk)))
     n = ng.value
-    return {"group_of_seq": group_of, "d_min": d_min[:n].copy(), "degree": degree[:n].copy(),
+    return {"group_of_seq": group_of[:k], "d_min": d_min[:n].copy(), "degree": degree[:n].copy(),
             "base_rank": base[:n].copy(), "makespan": mk.value}
 
 
@@ -230,7 +237,7 @@ def fcp_group_shard_args(group_of_seq, group_degree, group_base_rank):
     gb = np.ascontiguousarray(group_base_rank, dtype=np.int32)
     if gd.shape != gb.shape or go.ndim != 1 or gd.ndim != 1:
         raise ValueError("group_degree and group_base_rank must be 1-D and the same length")
-    cd, br = np.zeros(len(go), np.int32), np.zeros(len(go), np.int32)
+    cd, br = np.empty(len(go), np.int32), np.empty(len(go), np.int32)
     _check(lib().fcp_group_shard_args(_np_ptr(go), len(go), _np_ptr(gd), _np_ptr(gb), len(gd), _np_ptr(cd), _np_ptr(br)))
     return cd, br
 

@@ -2,7 +2,6 @@
 #include <algorithm>
 #include <cstdarg>
 #include <cstdio>
-#include <tuple>
 #include <vector>
 
 #include "fcp_internal.h"
@@ -90,84 +89,113 @@ static int shard_plan(const char* who, const int32_t* seq_lens, const int32_t* c
   SpanIndex mask;
   if (int rc = build_span_index(who, seq_lens, n_seqs, spans, n_spans, &mask)) return rc;
 
-  // Pass 1: chunk table in (seq, chunk) order.
-  std::vector<fcp_chunk_desc> cs;
-  std::vector<int64_t> first_chunk(n_seqs + 1, 0);   // index of a sequence's chunk 0 in `cs`
+  // Nothing below is sorted and no table is kept: chunk c of a sequence of L tokens at degree d starts at c q + min(c, r) (q, r: quotient and
+  // remainder of L / 2d), and walking the sequences in order visits the entries of every (rank) and (rank, step) in the order
+  // they are listed in, so that each entry can be written to its place once the entries per (rank) and (rank, step) have been
+  // counted.  (Building the two tables and sorting them took 86 % of the time of a plan of 512 sequences on 64 ranks.)
+  struct Cut {
+    int32_t n, quot, rem, d, base;                   // chunks of the sequence; degree, first rank
+    int64_t r;                                       // its dense number (below)
+    int32_t start(int32_t c) const { return c * quot + std::min(c, rem); }
+    int32_t len(int32_t c) const { return quot + (c < rem ? 1 : 0); }
+    int32_t filled() const { return quot > 0 ? n : rem; }       // chunks with tokens come first
+  };
+  std::vector<Cut> cuts(n_seqs);
+  // chunks that query chunk c of sequence s sees: those with a smaller number
+  auto n_seen = [&](int32_t s, const Cut& cut, int32_t c) -> int32_t {
+    if (n_spans == 0 || c >= cut.filled()) return c < cut.filled() ? c + 1 : 0;
+    const int32_t last_seen = mask.limit(s, cut.start(c) + cut.len(c) - 1);   // by the chunk's last row, hence by any
+    int32_t v = c + 1;
+    while (v < cut.filled() && cut.start(v) <= last_seen) ++v;
+    return v;
+  };
+
+  // Ranks as dense numbers: the ranks themselves from the least one on, or, where the base ranks lie far apart, their places
+  // among the ranks in use.
+  int64_t nc = 0, r_lo = INT64_MAX, r_hi = 0;
   for (int32_t s = 0; s < n_seqs; ++s) {
-    const int32_t L = seq_lens[s], d = cp_degree[s], base = base_rank ? base_rank[s] : 0;
-    first_chunk[s] = (int64_t)cs.size();
-    if (d == 1) {
-      cs.push_back({s, base, 0, 0, L, 0});
-    } else {
-      const int32_t n = 2 * d, quot = L / n, rem = L % n;
-      int32_t start = 0;
-      for (int32_t c = 0; c < n; ++c) {
-        const int32_t len = quot + (c < rem ? 1 : 0);
-        const int32_t local = c < d ? c : n - 1 - c;
-        cs.push_back({s, base + local, c, start, len, 0});
-        start += len;
-      }
+    const int32_t d = cp_degree[s], n = d == 1 ? 1 : 2 * d, base = base_rank ? base_rank[s] : 0;
+    const int32_t quot = seq_lens[s] / n;
+    cuts[s] = {n, quot, seq_lens[s] - quot * n, d, base, base};
+    nc += n;
+    r_lo = std::min<int64_t>(r_lo, base);
+    r_hi = std::max<int64_t>(r_hi, (int64_t)base + d);
+  }
+  int64_t n_dense = n_seqs == 0 ? 0 : r_hi - r_lo;
+  if (n_dense > 4 * nc + 1024) {
+    std::vector<int64_t> in_use;
+    for (const Cut& c : cuts)
+      for (int32_t i = 0; i < c.d; ++i) in_use.push_back((int64_t)c.base + i);
+    std::sort(in_use.begin(), in_use.end());
+    in_use.erase(std::unique(in_use.begin(), in_use.end()), in_use.end());
+    for (Cut& c : cuts) c.r = std::lower_bound(in_use.begin(), in_use.end(), (int64_t)c.base) - in_use.begin();
+    n_dense = (int64_t)in_use.size();
+  } else {
+    for (Cut& c : cuts) c.r -= r_lo;
+  }
+
+  // Entries per rank, and the first place of every rank's steps among the (rank, step) counters.  (An owner of empty
+  // chunks has no items, nor has any after it.)
+  std::vector<int64_t> chunk_at(n_dense + 1, 0), step_at(n_dense + 1, 0);
+  for (const Cut& c : cuts)
+    for (int32_t i = 0; i < c.d; ++i) {
+      chunk_at[c.r + i + 1] += c.d == 1 ? 1 : 2;
+      if (i < c.filled()) step_at[c.r + i + 1] = std::max<int64_t>(step_at[c.r + i + 1], c.d);
+    }
+  for (int64_t r = 0; r < n_dense; ++r) { chunk_at[r + 1] += chunk_at[r]; step_at[r + 1] += step_at[r]; }
+  // Items per (rank, step).  The step's keys belong to owner j; chunk j is its first one in memory, so a query chunk that sees
+  // j or more chunks has an item.
+  std::vector<int64_t> work_at(step_at[n_dense] + 1, 0);
+  for (int32_t s = 0; s < n_seqs; ++s) {
+    const Cut& c = cuts[s];
+    for (int32_t i = 0; i < std::min(c.d, c.filled()); ++i) {
+      const int32_t lo = n_seen(s, c, i), hi = c.d == 1 ? 0 : n_seen(s, c, 2 * c.d - 1 - i);
+      int64_t* const at = work_at.data() + step_at[c.r + i] + 1;
+      for (int32_t step = 0, j = i; step < c.d; ++step, j = j == 0 ? c.d - 1 : j - 1) at[step] += (j < lo) + (j < hi);
     }
   }
-  first_chunk[n_seqs] = (int64_t)cs.size();
+  for (size_t i = 1; i < work_at.size(); ++i) work_at[i] += work_at[i - 1];
+
+  *n_chunks = nc;
+  *n_work = work_at.back();
+  if ((chunks && chunk_cap < *n_chunks) || (work && work_cap < *n_work))
+    return fail(FCP_ERR_CAPACITY, "%s: need %lld chunk and %lld work entries", who,
+                (long long)*n_chunks, (long long)*n_work);
+  if (!chunks && !work) return FCP_OK;
 
   // Rank-local packed offsets: per rank, sequences in input order, early chunk before late.
-  std::vector<int64_t> order(cs.size());
-  for (size_t i = 0; i < order.size(); ++i) order[i] = (int64_t)i;
-  std::stable_sort(order.begin(), order.end(), [&](int64_t a, int64_t b) {
-    return std::tie(cs[a].rank, cs[a].seq, cs[a].chunk) < std::tie(cs[b].rank, cs[b].seq, cs[b].chunk);
-  });
-  {
-    int32_t cur_rank = -1, off = 0;
-    for (int64_t idx : order) {
-      if (cs[idx].rank != cur_rank) { cur_rank = cs[idx].rank; off = 0; }
-      cs[idx].local_off = off;
-      off += cs[idx].len;
-    }
-  }
-
-  // Pass 2: work items.
-  std::vector<fcp_work_desc> ws;
+  std::vector<int32_t> used(n_dense, 0);             // rows of the rank so far
   for (int32_t s = 0; s < n_seqs; ++s) {
-    const int32_t d = cp_degree[s];
-    const fcp_chunk_desc* c0 = cs.data() + first_chunk[s];
+    const Cut& cut = cuts[s];
+    const int32_t d = cut.d;
     for (int32_t i = 0; i < d; ++i) {
-      for (int32_t step = 0; step < d; ++step) {
-        const int32_t j = ((i - step) % d + d) % d;            // owner of this step's KV
-        const int32_t q_chunks[2] = {i, 2 * d - 1 - i};
-        const int32_t kv_chunks[2] = {j, 2 * d - 1 - j};       // increasing, j < 2d-1-j
-        const int32_t n_own = d == 1 ? 1 : 2;
-        for (int32_t qa = 0; qa < n_own; ++qa) {
-          const fcp_chunk_desc& qc = c0[d == 1 ? 0 : q_chunks[qa]];
-          if (qc.len == 0) continue;
-          fcp_work_desc w{};
-          w.seq = s; w.rank = qc.rank; w.step = step;
-          w.q_local_off = qc.local_off; w.q_seq_start = qc.seq_start; w.q_len = qc.len;
-          const int32_t last_seen = mask.limit(s, qc.seq_start + qc.len - 1);   // by the chunk's last row, hence by any
-          for (int32_t kb = 0; kb < n_own; ++kb) {
-            const int32_t b = d == 1 ? 0 : kv_chunks[kb];
-            if (c0[b].len == 0 || c0[b].seq_start > last_seen) continue;   // empty, or fully masked (a later chunk)
-            w.k_seq_start[w.n_seg] = c0[b].seq_start;
-            w.k_len[w.n_seg] = c0[b].len;
-            ++w.n_seg;
-          }
-          if (w.n_seg > 0) ws.push_back(w);
+      const int32_t ca = i, cb = 2 * d - 1 - i;      // the owner's chunks (the second one: d > 1)
+      const int32_t off = used[cut.r + i], len_a = cut.len(ca), len_b = d == 1 ? 0 : cut.len(cb);
+      used[cut.r + i] = off + len_a + len_b;
+      if (chunks) {
+        chunks[chunk_at[cut.r + i]++] = {s, cut.base + i, ca, cut.start(ca), len_a, off};
+        if (d > 1) chunks[chunk_at[cut.r + i]++] = {s, cut.base + i, cb, cut.start(cb), len_b, off + len_a};
+      }
+      if (!work || i >= cut.filled()) continue;
+      const int32_t lo = n_seen(s, cut, ca), hi = d == 1 ? 0 : n_seen(s, cut, cb);
+      int64_t* const at = work_at.data() + step_at[cut.r + i];
+      for (int32_t step = 0, j = i; step < d; ++step, j = j == 0 ? d - 1 : j - 1) {
+        const int32_t j2 = 2 * d - 1 - j;
+        fcp_work_desc w = {s, cut.base + i, step, off, cut.start(ca), len_a, 1, {cut.start(j), 0}, {cut.len(j), 0}};
+        const int32_t k1 = cut.start(j2), n1 = cut.len(j2);
+        if (j < lo) {
+          if (d > 1 && j2 < lo) { w.n_seg = 2; w.k_seq_start[1] = k1; w.k_len[1] = n1; }
+          work[at[step]++] = w;
+        }
+        if (j < hi) {
+          const bool two = j2 < hi;
+          w.q_local_off = off + len_a; w.q_seq_start = cut.start(cb); w.q_len = len_b;
+          w.n_seg = two ? 2 : 1; w.k_seq_start[1] = two ? k1 : 0; w.k_len[1] = two ? n1 : 0;
+          work[at[step]++] = w;
         }
       }
     }
   }
-  std::stable_sort(ws.begin(), ws.end(), [](const fcp_work_desc& a, const fcp_work_desc& b) {
-    return std::tie(a.rank, a.step, a.seq, a.q_seq_start) < std::tie(b.rank, b.step, b.seq, b.q_seq_start);
-  });
-
-  *n_chunks = (int64_t)cs.size();
-  *n_work = (int64_t)ws.size();
-  if ((chunks && chunk_cap < *n_chunks) || (work && work_cap < *n_work))
-    return fail(FCP_ERR_CAPACITY, "%s: need %lld chunk and %lld work entries", who,
-                (long long)*n_chunks, (long long)*n_work);
-  if (chunks)
-    for (size_t i = 0; i < order.size(); ++i) chunks[i] = cs[order[i]];
-  if (work) std::copy(ws.begin(), ws.end(), work);
   return FCP_OK;
 }
 

@@ -11,9 +11,9 @@
 //   * every table entry but DP[0][0] starts at +inf; Cond. 6 is "at most N ranks", so the answer is taken at the
 //     smallest rank count that attains the least makespan (with an exchange term more ranks can be slower).
 #include <algorithm>
+#include <array>
 #include <cmath>
 #include <limits>
-#include <numeric>
 #include <vector>
 
 #include "fcp.h"
@@ -22,19 +22,49 @@
 namespace {
 
 struct Group {
-  std::vector<int32_t> members;   // sequence indices in increasing order
   int64_t load = 0;               // tokens
   int32_t d_min = 0;
-  // sums that T(G, d) needs, accumulated in member order
+  // sums that T(G, d) needs, accumulated in increasing sequence index
   double quad = 0.0, lin = 0.0, tokens = 0.0;
 };
 
-// Eq. 8-10 for one group at degree d
-inline double group_time(const Group& g, int d, const fcp_cost_model& cm) {
-  const double t_cpa = g.quad / d;
-  const double t_cp = t_cpa + g.lin / d + cm.beta1;
-  const double t_cm = d == 1 ? 0.0 : cm.alpha3_over_v * g.tokens + cm.beta2;
-  return t_cp + t_cm - std::min(t_cpa, t_cm);
+// Eq. 8-10 for one group at degrees lo .. hi
+inline void group_times(const Group& g, int lo, int hi, const fcp_cost_model& cm, double* __restrict__ t) {
+  const double quad = g.quad, lin = g.lin, beta1 = cm.beta1, t_ring = cm.alpha3_over_v * g.tokens + cm.beta2;
+  for (int d = lo; d <= hi; ++d) {
+    const double t_cpa = quad / d, t_cm = d == 1 ? 0.0 : t_ring;
+    t[d] = t_cpa + lin / d + beta1 + t_cm - std::min(t_cpa, t_cm);
+  }
+}
+
+// One degree of a group against adjacent rank counts: the least makespan so far and its degree.
+inline void relax(const double* __restrict__ prev, double t, double d, double* __restrict__ best, double* __restrict__ degree, int n) {
+  for (int x = 0; x < n; ++x) {
+    const double cost = prev[x] < t ? t : prev[x];
+    const bool less = cost < best[x];
+    best[x] = less ? cost : best[x];
+    degree[x] = less ? d : degree[x];
+  }
+}
+
+// Sequence indices by decreasing length, equal lengths in input order: a byte-wise radix sort, least byte first, without the
+// bytes that all lengths share.
+std::vector<int32_t> longest_first(const int32_t* len, int32_t n) {
+  std::vector<int32_t> order(n), other(n);
+  std::array<std::array<int32_t, 256>, 4> count{};
+  for (int32_t k = 0; k < n; ++k) {
+    order[k] = k;
+    for (int b = 0; b < 4; ++b) ++count[b][~((uint32_t)len[k] >> (8 * b)) & 255];
+  }
+  for (int b = 0; b < 4; ++b) {
+    auto& at = count[b];
+    if (n == 0 || at[~((uint32_t)len[0] >> (8 * b)) & 255] == n) continue;
+    int32_t sum = 0;
+    for (int32_t& c : at) { const int32_t x = c; c = sum; sum += x; }
+    for (int32_t k : order) other[at[~((uint32_t)len[k] >> (8 * b)) & 255]++] = k;
+    std::swap(order, other);
+  }
+  return order;
 }
 
 }  // namespace
@@ -60,17 +90,18 @@ extern "C" int fcp_plan_groups(const int32_t* seq_lens, const float* eta, int32_
   // ---- Stage 1: best-fit decreasing.  Longest first (equal lengths in input order); a sequence goes to the open
   // group with the least headroom that still holds it (the group opened first among equals), else opens a group
   // of d_min = ceil(len / capacity) ranks.
-  std::vector<int32_t> order(n_seqs);
-  std::iota(order.begin(), order.end(), 0);
-  std::stable_sort(order.begin(), order.end(), [&](int32_t a, int32_t b) { return seq_lens[a] > seq_lens[b]; });
+  // (The rooms of the open groups lie side by side, so that the search is one pass over a few cache lines.)
+  const std::vector<int32_t> order = longest_first(seq_lens, n_seqs);
   std::vector<Group> groups;
+  std::vector<int64_t> room_of;
   for (int32_t k : order) {
     const int64_t s = seq_lens[k];
     int best = -1;
-    int64_t best_room = 0;
-    for (size_t g = 0; g < groups.size(); ++g) {
-      const int64_t room = (int64_t)groups[g].d_min * tokens_per_rank - groups[g].load;
-      if (room >= s && (best < 0 || room < best_room)) { best = (int)g; best_room = room; }
+    int64_t best_room = INT64_MAX;
+    for (size_t g = 0; g < room_of.size(); ++g) {
+      const bool better = room_of[g] >= s && room_of[g] < best_room;
+      best = better ? (int)g : best;
+      best_room = better ? room_of[g] : best_room;
     }
     if (best < 0) {
       Group g;
@@ -82,17 +113,18 @@ extern "C" int fcp_plan_groups(const int32_t* seq_lens, const float* eta, int32_
       }
       g.d_min = (int32_t)dm;
       groups.push_back(g);
+      room_of.push_back(dm * tokens_per_rank);
       best = (int)groups.size() - 1;
     }
-    groups[best].load += s;
+    room_of[best] -= s;
     group_of_seq[k] = best;
   }
   const int kp = (int)groups.size();
   *n_groups = kp;
-  // members and cost sums in increasing sequence index
+  // cost sums in increasing sequence index
   for (int32_t k = 0; k < n_seqs; ++k) {
     Group& g = groups[group_of_seq[k]];
-    g.members.push_back(k);
+    g.load += seq_lens[k];
     const double s = (double)seq_lens[k];
     g.quad += cm->alpha1 * (1.0 + (eta ? (double)eta[k] : 0.0)) * s * s;
     g.lin += cm->alpha2 * s;
@@ -118,17 +150,21 @@ extern "C" int fcp_plan_groups(const int32_t* seq_lens, const float* eta, int32_
   std::vector<int32_t> path((size_t)kp * (N + 1), 0);
   prev[0] = 0.0;
   int64_t before = 0;                       // sum of d_min of the groups before group i
-  std::vector<double> t(N + 1);
+  std::vector<double> t(N + 1), pick(N + 1);   // (degrees as doubles: lanes of one width)
   for (int i = 0; i < kp; ++i) {
     const int dm = groups[i].d_min;
-    const int d_hi = N - (int)before;       // no j leaves more than this for group i
-    for (int d = dm; d <= d_hi; ++d) t[d] = group_time(groups[i], d, *cm);
+    const int d_hi = N - (int)(need - dm);  // no count leaves more than this for group i
+    group_times(groups[i], dm, d_hi, *cm, t.data());
+    // Rank counts from before + dm (less is infeasible) to what leaves the later groups their minimum.  The degree is the
+    // outer loop, so that the inner one runs over adjacent entries without a dependence and is vectorised; for each count the
+    // degrees are still tried in increasing order and the first of equals stays.
+    const int j_lo = (int)before + dm, j_hi = N - (int)(need - before - dm);
     std::fill(cur.begin(), cur.end(), inf);
-    for (int j = 0; j <= N; ++j)
-      for (int d = dm; d <= j - (int)before; ++d) {
-        const double cost = std::max(prev[j - d], t[d]);
-        if (cost < cur[j]) { cur[j] = cost; path[(size_t)i * (N + 1) + j] = d; }
-      }
+    std::fill(pick.begin(), pick.end(), 0.0);
+    for (int d = dm; d <= j_hi - (int)before; ++d) {
+      relax(prev.data() + before, t[d], d, cur.data() + before + d, pick.data() + before + d, j_hi - (int)before - d + 1);
+    }
+    for (int j = j_lo; j <= j_hi; ++j) path[(size_t)i * (N + 1) + j] = (int32_t)pick[j];
     before += dm;
     std::swap(prev, cur);
   }
