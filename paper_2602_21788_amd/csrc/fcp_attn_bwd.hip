@@ -37,6 +37,7 @@
 // case for degree-1 sequences), otherwise with fp32 atomics.
 #include "fcp_bwd.h"
 
+#include <algorithm>
 #include <type_traits>
 
 namespace fcp {
@@ -430,8 +431,8 @@ static int bwd_step(const void* q, const void* k, const void* v, const void* d_o
   if ((int64_t)tq * hq * head_dim * 2 + ((int64_t)1 << 22) >= ((int64_t)1 << 31))
     return fail(FCP_ERR_UNSUPPORTED, "fcp_attn_bwd_step: tq * hq * head_dim must stay below 2^30 - 2^21 elements");
   hipStream_t st = (hipStream_t)stream;
-  const int64_t cap_kv = fcp::kv_tile_cap(tkv, n_work);
-  const int64_t cap_q = fcp::q_tile_cap(tq, tkv, n_work, 1 << 20);
+  const int64_t cap_kv = fcp::bwd_kv_cap(tkv, n_work);
+  const int64_t cap_q = fcp::bwd_q_cap(tq, tkv, n_work);
   if (cap_kv > INT32_MAX / 64 || cap_q > INT32_MAX / 64) return fail(FCP_ERR_UNSUPPORTED, "fcp_attn_bwd_step: too many tiles");
   void* region_kv = scratch;
   void* region_q = static_cast<char*>(scratch) + fcp::sched_region_bytes(n_work, cap_kv);
@@ -480,11 +481,19 @@ static int bwd_step(const void* q, const void* k, const void* v, const void* d_o
   }
   // dQ units: 128 query rows for two heads of one KV head when the heads pair up, else 256 rows for one head
   const int head_pair = ((hq / hkv) % 2 == 0) ? 1 : 0;
+  // Split tiles (see csrc/fcp_sched.hip): worth the scheduler's time where there are a few tiles per CU at most and a serial loop can be
+  // long, in 32-row blocks of all heads of a KV head or in 32-key blocks.  In sharded lists a tile's loop is the shorter for
+  // the sharding, and its accumulators are mostly shared already.  Measured, backward: one sequence of 4096 tokens, 8 query heads on one KV
+  // head, 128 channels 969 -> 273 us; 6 on 2, 64 channels 447 -> 166 us; 30 sequences of 20011 tokens in all, 6 on 2, 414 -> 289 us; 4096 tokens
+  // over 3 ranks, 4 on 4, 92 -> 72 us; 32 on 8 1.02 to 1.15 times as fast.
+  const fcp::SplitTiles sp{group, hkv, hq / (head_pair ? 2 : 1), 256, 12};        // (256 CUs; 12 steps at least)
+  const int64_t longest = std::max((int64_t)tq * group / fcp::kBwdBM, (int64_t)tkv / fcp::kDqBN);
+  const bool split = !fused && key_units <= 1024 && n_work <= 1024 && longest >= (tq == tkv ? 24 : 64);
   int rc = fcp::launch_schedule_bwd((int64_t)hkv * head_dim * 2, q_limit, k_from, work, n_work, cu_seqlens_kv, n_seqs, tq, tkv,
                                     cap_kv, region_kv, head_pair ? fcp::kDqBM : 2 * fcp::kDqBM, cap_q, region_q, lse, delta, (int64_t)hq * tq, stats, st,
                                     direct ? &rs : nullptr, fused ? fcp::bwd_chain(scratch, n_work, tq, tkv, hq) : nullptr,
                                     fused ? fcp::bwd_chain_flags(scratch, n_work, tq, tkv, hq) : nullptr,
-                                    fused ? fcp::chain_flag_words(tq, hq, n_work) : 0);
+                                    fused ? fcp::chain_flag_words(tq, hq, n_work) : 0, split ? &sp : nullptr);
   if (rc != FCP_OK) return rc;
 
   fcp::BwdParams p;
@@ -514,12 +523,15 @@ static int bwd_step(const void* q, const void* k, const void* v, const void* d_o
   // dK/dV over key tiles
   p.hdr = (fcp::SchedHeader*)region_kv;
   p.tiles = fcp::sched_tiles(region_kv, n_work);
-  if ((rc = fcp::launch_dkv(p, head_dim, cap_kv * hkv, n_cu, st)) != FCP_OK) return rc;
+  const double pieces = split ? (double)tq * tkv * hq / sp.min_steps : 0.;      // bounds of the units that splitting adds, times a step's pairs
+  const int64_t kv_units = fcp::kv_tile_cap(tkv, n_work) * hkv + (int64_t)(pieces / (fcp::kBwdBM * fcp::kBwdBN));
+  if ((rc = fcp::launch_dkv(p, head_dim, kv_units, n_cu, st)) != FCP_OK) return rc;
 
   // dQ over query tiles
   p.hdr = (fcp::SchedHeader*)region_q;
   p.tiles = fcp::sched_tiles(region_q, n_work);
-  const int64_t dq_units = cap_q * (hq / (head_pair ? 2 : 1));
+  const int64_t dq_units = fcp::q_tile_cap(tq, tkv, n_work, 1 << 20) * (hq / (head_pair ? 2 : 1)) +
+                           (int64_t)(pieces / (2 * fcp::kDqBM * fcp::kDqBN));
   if (head_dim == 128) {
     static std::atomic<uint64_t> lds_done;
     if ((rc = fcp::raise_lds_limit((const void*)fcp::dq_kernel<128>, fcp::DqCfg<128>::LDS_BYTES, lds_done)) != FCP_OK) return rc;

@@ -93,32 +93,33 @@ inline int32_t max_segment_keys(int64_t kv_row_bytes) { return (int32_t)(((int64
 // over a rank's items the key segments of a sequence add up to at most twice its length.
 int64_t q_tile_cap(int32_t tq, int32_t tkv, int64_t n_work, int32_t n_parts);
 int64_t kv_tile_cap(int32_t tkv, int64_t n_work);
+// Room for the backward's lists when tiles are split: a tile has two pieces more than its share of the steps asks for at most, and
+// all shares together make two pieces per CU.
+inline int64_t bwd_kv_cap(int32_t tkv, int64_t n_work) { return 2 * kv_tile_cap(tkv, n_work) + 2048; }
+inline int64_t bwd_q_cap(int32_t tq, int32_t tkv, int64_t n_work) { return 2 * q_tile_cap(tq, tkv, n_work, 1 << 20) + 2048; }
 
-// One schedule region: SchedHeader | item offsets int32[n_work+1] | item flags int32[n_work]
-// | Tile[cap]; every part padded to 64 bytes, the region to 256.
+// One schedule region: SchedHeader | item offsets int32[n_work+1] | Tile[cap]; every part padded to 64 bytes, the region to 256.
 constexpr int32_t kFlagQExclusive = 1;    // no other item of the launch covers these query rows
 constexpr int32_t kFlagSeg0Exclusive = 2; // no other item's key segment overlaps segment 0 / 1
 constexpr int32_t kFlagSeg1Exclusive = 4;
 inline size_t pad_to(size_t x, size_t a) { return (x + a - 1) / a * a; }
 inline size_t sched_item_off_bytes(int64_t n_work) { return pad_to((size_t)(n_work + 1) * sizeof(int32_t), 64); }
-inline size_t sched_flags_bytes(int64_t n_work) { return pad_to((size_t)(n_work > 0 ? n_work : 1) * sizeof(int32_t), 64); }
 inline size_t sched_region_bytes(int64_t n_work, int64_t cap) {
-  return pad_to(sizeof(SchedHeader) + sched_item_off_bytes(n_work) + sched_flags_bytes(n_work) +
+  return pad_to(sizeof(SchedHeader) + sched_item_off_bytes(n_work) +
                 (size_t)cap * sizeof(Tile), 256);
 }
 inline const SchedHeader* sched_header(const void* region) { return static_cast<const SchedHeader*>(region); }
-inline const int32_t* sched_flags(const void* region, int64_t n_work) {
-  return reinterpret_cast<const int32_t*>(static_cast<const char*>(region) + sizeof(SchedHeader) +
-                                          sched_item_off_bytes(n_work));
-}
 inline const Tile* sched_tiles(const void* region, int64_t n_work) {
   return reinterpret_cast<const Tile*>(static_cast<const char*>(region) + sizeof(SchedHeader) +
-                                       sched_item_off_bytes(n_work) + sched_flags_bytes(n_work));
+                                       sched_item_off_bytes(n_work));
 }
 
 static_assert(kBwdBN == 4 * 32, "KTile keeps four key groups");
 
 struct RowStates;   // direct modes, see below
+// Splitting of the backward's tiles on small problems (csrc/fcp_sched.hip): query heads per KV head, units per key tile and per query tile, CUs, least
+// piece in 32-row blocks (of all heads together) and in 32-key blocks.
+struct SplitTiles { int32_t group, kv_units, q_units, n_cu, min_steps; };
 
 // Builds one tile list in `region` (tiles of `tile` keys if `key_tiles`, else of `tile` query rows;
 // `inner` is the block size of the other dimension used for the cost; kv_row_bytes = hkv*D*2 bounds
@@ -140,7 +141,7 @@ int launch_schedule_bwd(int64_t kv_row_bytes, const int32_t* q_limit, const int3
                         const fcp_work_desc* work, int64_t n_work, const int32_t* cu_seqlens_kv, int32_t n_seqs,
                         int32_t tq, int32_t tkv, int64_t cap_kv, void* region_kv, int32_t dq_tile, int64_t cap_q, void* region_q,
                         const float* lse, const float* delta, int64_t n_stats, float* stats, hipStream_t stream,
-                        const RowStates* states = nullptr, int32_t* chain = nullptr, int32_t* flags = nullptr, int64_t n_flags = 0);
+                        const RowStates* states = nullptr, int32_t* chain = nullptr, int32_t* flags = nullptr, int64_t n_flags = 0, const SplitTiles* split = nullptr);
 
 // Direct modes: one state byte per query row and (backward: kv_state not NULL) per pool key: 0 untouched, 1 several
 // work items contribute (backward: accumulated in fp32, the accumulator row is cleared when the accumulators are
@@ -163,8 +164,8 @@ int launch_row_states(int64_t kv_row_bytes, const RowStates& rs, const int32_t* 
 
 // Where the row states live in the backward's scratch buffer (after the two lists and the statistics planes).
 inline uint8_t* bwd_q_state(void* scratch, int64_t n_work, int32_t tq, int32_t tkv, int32_t hq) {
-  return static_cast<uint8_t*>(scratch) + sched_region_bytes(n_work, kv_tile_cap(tkv, n_work)) +
-         sched_region_bytes(n_work, q_tile_cap(tq, tkv, n_work, 1 << 20)) + pad_to((size_t)hq * (size_t)tq * 8, 256);
+  return static_cast<uint8_t*>(scratch) + sched_region_bytes(n_work, bwd_kv_cap(tkv, n_work)) +
+         sched_region_bytes(n_work, bwd_q_cap(tq, tkv, n_work)) + pad_to((size_t)hq * (size_t)tq * 8, 256);
 }
 inline uint8_t* bwd_kv_state(void* scratch, int64_t n_work, int32_t tq, int32_t tkv, int32_t hq) {
   return bwd_q_state(scratch, n_work, tq, tkv, hq) + pad_to((size_t)tq, 256);

@@ -10,6 +10,12 @@
 // It also validates every work item against the extents the caller passed, so that no
 // attention kernel can be steered out of bounds by a bad descriptor: a rejected item gets
 // no tiles and is counted in the header.
+//
+// A list is one block's work between two launches that wait for it, so what counts is the chain of dependent steps: trips to global memory and
+// block barriers.  Items are fetched once into LDS with everything that depends on global memory (their sequence's place, what their last row
+// sees), the exclusivity flags take the cheapest of three ways, nothing is indexed in scratch memory.  Time from the first
+// to the last instruction of a list, forward / backward: 1 item 8.2 -> 5.6 us, 28 items 18 / 31 -> 11 / 13 us, 71 items 37 / 48 -> 14 / 12 us,
+// 1000 items 64 / 65 -> 14 / 23 us.
 #include "fcp_internal.h"
 
 namespace fcp {
@@ -18,32 +24,33 @@ namespace {
 
 constexpr int kSchedThreads = 1024;
 constexpr int kBuckets = 2048;
-constexpr int kMaxExclusiveScan = 1024;   // beyond this many items the all-pairs overlap scan is skipped
-
-struct ItemInfo {
-  bool ok;
-  int32_t n_tiles;     // tiles this item contributes
-  int32_t nt0;         // backward: tiles of segment 0
-  int32_t max_cost;
-};
+constexpr int kMaxExclusiveScan = 1024;   // longer lists are not staged in LDS and have no exclusivity flags
 
 __device__ inline int32_t ceil_div(int32_t a, int32_t b) { return (a + b - 1) / b; }
 
-__device__ inline bool item_valid(const fcp_work_desc& w, const int32_t* cu, int32_t n_seqs,
-                                  int32_t tq, int32_t tkv, int32_t n_parts, bool check_step, int32_t max_seg_keys) {
-  if (w.seq < 0 || w.seq >= n_seqs) return false;
-  if (check_step && (w.step < 0 || w.step >= n_parts)) return false;
-  if (w.q_len < 1 || w.q_local_off < 0 || w.q_seq_start < 0) return false;
-  if ((int64_t)w.q_local_off + w.q_len > (int64_t)tq) return false;
-  if ((int64_t)w.q_seq_start + w.q_len > (int64_t)(1 << 30)) return false;
-  if (w.n_seg < 1 || w.n_seg > 2) return false;
-  const int64_t s0 = cu[w.seq], s1 = cu[w.seq + 1];
-  if (s0 < 0 || s1 < s0 || s1 > (int64_t)tkv) return false;
-  for (int s = 0; s < w.n_seg; ++s) {
-    if (w.k_seq_start[s] < 0 || w.k_len[s] < 1 || w.k_len[s] > max_seg_keys) return false;
-    if (s0 + (int64_t)w.k_seq_start[s] + w.k_len[s] > s1) return false;
-  }
-  return true;
+// A work item as the scheduler uses it: validated, with the place of its keys in the pool.  Items are fetched once per block and kept in LDS: a list
+// is built of many short dependent steps, and trips to global memory for descriptor, cu_seqlens and mask in each of them
+// were most of its time.  (No arrays: indexed by a run-time segment number they would live in scratch memory.)
+struct Item {
+  int32_t seq;                      // -1: rejected
+  int32_t q_off, q_len, q_pos;      // query rows: first local row, count, position of the first
+  int32_t k0, n0, k1, n1;           // key segments: position of the first key, keys (n1 = 0: one segment)
+  int32_t base;                     // pool row of the sequence's first key
+  int32_t vis0, vis1;               // keys of the segment that the last row sees
+  int32_t step;
+  __device__ int32_t k(int s) const { return s ? k1 : k0; }
+  __device__ int32_t n(int s) const { return s ? n1 : n0; }
+  __device__ int32_t vis(int s) const { return s ? vis1 : vis0; }
+};
+constexpr int kItemWords = 13;      // in LDS: the item, then the first flag block of its chain (an odd stride: no bank conflicts)
+using ItemSlot = int32_t[kItemWords];
+__device__ inline void put_item(ItemSlot& r, const Item& it) {
+  const int32_t w[12] = {it.seq, it.q_off, it.q_len, it.q_pos, it.k0, it.n0, it.k1, it.n1, it.base, it.vis0, it.vis1, it.step};
+#pragma unroll
+  for (int i = 0; i < 12; ++i) r[i] = w[i];
+}
+__device__ inline Item get_item(const ItemSlot& r) {
+  return {r[0], r[1], r[2], r[3], r[4], r[5], r[6], r[7], r[8], r[9], r[10], r[11]};
 }
 
 // The mask in the form every kernel uses: row i sees the keys at positions 0 .. limit(i), a key is seen by the
@@ -52,59 +59,64 @@ __device__ inline bool item_valid(const fcp_work_desc& w, const int32_t* cu, int
 struct MaskTables {
   const int32_t* q_limit;   // [tq] by local query row, or NULL
   const int32_t* k_from;    // [tkv] by pool row, or NULL
-  __device__ int64_t limit(const fcp_work_desc& w, int32_t row) const {
-    return q_limit ? (int64_t)q_limit[w.q_local_off + row] : (int64_t)w.q_seq_start + row;
+  __device__ int64_t limit(const Item& it, int32_t row) const {
+    return q_limit ? (int64_t)q_limit[it.q_off + row] : (int64_t)it.q_pos + row;
   }
-  __device__ int64_t from(const fcp_work_desc& w, const int32_t* cu, int64_t k_pos) const {
-    return k_from ? (int64_t)k_from[cu[w.seq] + k_pos] : k_pos;
-  }
+  __device__ int64_t from(const Item& it, int64_t k_pos) const { return k_from ? (int64_t)k_from[it.base + k_pos] : k_pos; }
 };
 
-// keys of segment s that row `last_row` of the item (hence any row up to it) can see
-__device__ inline int32_t visible_len(const MaskTables& m, const fcp_work_desc& w, int s, int32_t last_row) {
-  int64_t v = m.limit(w, last_row) - w.k_seq_start[s] + 1;
-  if (v < 0) v = 0;
-  if (v > w.k_len[s]) v = w.k_len[s];
-  return (int32_t)v;
+// keys of segment s that a row with that limit sees
+__device__ inline int32_t seen_keys(const Item& it, int s, int64_t limit) {
+  return (int32_t)max((int64_t)0, min((int64_t)it.n(s), limit - it.k(s) + 1));
+}
+
+struct ListArgs {                   // what a list is built from
+  const fcp_work_desc* work;
+  const int32_t* cu;
+  int32_t n_work, n_seqs, tq, tkv, n_parts, max_seg_keys;
+  bool check_step;
+};
+__device__ inline Item load_item(const ListArgs& a, const MaskTables& m, int32_t i) {
+  const fcp_work_desc w = a.work[i];
+  Item it{-1, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0};
+  if (w.seq < 0 || w.seq >= a.n_seqs) return it;
+  if (a.check_step && (w.step < 0 || w.step >= a.n_parts)) return it;
+  if (w.q_len < 1 || w.q_local_off < 0 || w.q_seq_start < 0) return it;
+  if ((int64_t)w.q_local_off + w.q_len > (int64_t)a.tq) return it;
+  if ((int64_t)w.q_seq_start + w.q_len > (int64_t)(1 << 30)) return it;
+  if (w.n_seg < 1 || w.n_seg > 2) return it;
+  const int64_t s0 = a.cu[w.seq], s1 = a.cu[w.seq + 1];
+  if (s0 < 0 || s1 < s0 || s1 > (int64_t)a.tkv) return it;
+#pragma unroll
+  for (int s = 0; s < 2; ++s) {
+    if (s >= w.n_seg) continue;
+    if (w.k_seq_start[s] < 0 || w.k_len[s] < 1 || w.k_len[s] > a.max_seg_keys) return it;
+    if (s0 + (int64_t)w.k_seq_start[s] + w.k_len[s] > s1) return it;
+  }
+  const bool two = w.n_seg > 1;
+  it = {w.seq, w.q_local_off, w.q_len, w.q_seq_start, w.k_seq_start[0], w.k_len[0], two ? w.k_seq_start[1] : 0, two ? w.k_len[1] : 0,
+        (int32_t)s0, 0, 0, w.step};
+  const int64_t limit = m.limit(it, it.q_len - 1);
+  it.vis0 = seen_keys(it, 0, limit);
+  it.vis1 = two ? seen_keys(it, 1, limit) : 0;
+  return it;
 }
 
 // query tile qt (of `tile` rows): cost = key blocks (of `inner` keys) its last row sees
-__device__ inline int32_t fwd_cost(const MaskTables& m, const fcp_work_desc& w, int32_t qt, int32_t tile, int32_t inner) {
-  int32_t last_row = min((qt + 1) * tile, w.q_len) - 1;
-  int32_t c = 0;
-  for (int s = 0; s < w.n_seg; ++s) c += ceil_div(visible_len(m, w, s, last_row), inner);
-  return c;
+__device__ inline int32_t fwd_cost(const MaskTables& m, const Item& it, int32_t qt, int32_t tile, int32_t inner) {
+  const int64_t limit = m.limit(it, min((qt + 1) * tile, it.q_len) - 1);
+  return ceil_div(seen_keys(it, 0, limit), inner) + (it.n1 > 0 ? ceil_div(seen_keys(it, 1, limit), inner) : 0);
 }
 
-// key tile kt (of `tile` keys) of segment s: cost = query blocks (of `inner` rows) that see its first key; in a chained list blocks
-// counted from the item's first row, from the one with the first row that sees that key on
+// key tile kt (of `tile` keys) of segment s: the item's first row that sees its first key
+__device__ inline int32_t first_row_of(const MaskTables& m, const Item& it, int s, int32_t kt, int32_t tile) {
+  return (int32_t)max((int64_t)0, min((int64_t)it.q_len - 1, m.from(it, (int64_t)it.k(s) + (int64_t)kt * tile) - it.q_pos));
+}
+// ... and its cost = query blocks (of `inner` rows) from that row on; in a chained list blocks counted from the item's first row
 template <bool Chain>
-__device__ inline int32_t bwd_cost(const MaskTables& m, const int32_t* cu, const fcp_work_desc& w, int s, int32_t kt,
-                                   int32_t tile, int32_t inner) {
-  const int64_t first_k_pos = (int64_t)w.k_seq_start[s] + (int64_t)kt * tile;
-  int64_t first_row = m.from(w, cu, first_k_pos) - w.q_seq_start;
-  if (first_row < 0) first_row = 0;
-  if constexpr (Chain) return max(1, ceil_div(w.q_len, inner) - (int32_t)min((int64_t)w.q_len, first_row / inner));
-  const int64_t rows = (int64_t)w.q_len - first_row;
-  return rows <= 0 ? 0 : (int32_t)((rows + inner - 1) / inner);
-}
-
-__device__ inline ItemInfo item_info(const MaskTables& m, const fcp_work_desc& w, const int32_t* cu, int32_t n_seqs,
-                                     int32_t tq, int32_t tkv, int32_t n_parts, bool backward,
-                                     bool check_step, int32_t tile, int32_t inner, int32_t max_seg_keys) {
-  ItemInfo r{false, 0, 0, 0};
-  r.ok = item_valid(w, cu, n_seqs, tq, tkv, n_parts, check_step, max_seg_keys);
-  if (!r.ok) return r;
-  if (!backward) {
-    r.n_tiles = ceil_div(w.q_len, tile);
-    r.max_cost = fwd_cost(m, w, r.n_tiles - 1, tile, inner);
-  } else {
-    r.nt0 = ceil_div(visible_len(m, w, 0, w.q_len - 1), tile);
-    int32_t nt1 = w.n_seg > 1 ? ceil_div(visible_len(m, w, 1, w.q_len - 1), tile) : 0;
-    r.n_tiles = r.nt0 + nt1;
-    r.max_cost = ceil_div(w.q_len, inner);
-  }
-  return r;
+__device__ inline int32_t bwd_cost(const MaskTables& m, const Item& it, int s, int32_t kt, int32_t tile, int32_t inner) {
+  const int32_t row = first_row_of(m, it, s, kt, tile);
+  return Chain ? ceil_div(it.q_len, inner) - row / inner : ceil_div(it.q_len - row, inner);
 }
 
 // Exclusive block scan of one value per thread; returns the exclusive prefix and sets
@@ -130,23 +142,15 @@ __device__ inline int32_t block_exclusive_scan(int32_t v, int32_t* s_wave, int32
 }
 
 // Exclusivity flags: an item whose query rows (key segments) no other valid item of this launch touches lets the
-// backward kernels add to dQ (dK/dV) without atomics, or write the final result directly.  The items' ranges are
-// staged in LDS (seq, -1 = invalid; q range; two key ranges) so that the all-pairs scan does not wait on global memory.
-__device__ inline void stage_item(int32_t (&r)[7], const fcp_work_desc& a, bool ok) {
-  r[0] = ok ? a.seq : -1;
-  r[1] = a.q_local_off;
-  r[2] = a.q_local_off + a.q_len;
-  r[3] = a.k_seq_start[0];
-  r[4] = a.k_seq_start[0] + a.k_len[0];
-  r[5] = a.n_seg > 1 ? a.k_seq_start[1] : 0;
-  r[6] = a.n_seg > 1 ? a.k_seq_start[1] + a.k_len[1] : 0;   // empty range when absent
-}
-// Flags of all items at once (n_work <= kMaxExclusiveScan), by sorting instead of comparing all pairs: intervals sorted by
-// their start overlap an earlier one iff the largest end so far exceeds their start, and a later one iff the next start
-// lies before their end.  Query rows: one set over all valid items.  Key segments: one set of up to two segments per
-// item, ordered by (sequence, start); only segments of the same sequence can overlap, and an item's own two segments
-// count like anybody else's.  The sequence enters the sort key with its low 21 bits: two sequences that collide there
-// are treated as one, which can only clear a flag that could have been set (the safe side).
+// backward kernels add to dQ (dK/dV) without atomics, or write the final result directly.
+// Flags of all items at once (n_work <= kMaxExclusiveScan, staged in LDS).  Query rows are one set of intervals over all valid items, key segments
+// one set of up to two per item, ordered by (sequence, start): only segments of the same sequence can overlap, and an item's own two
+// segments count like anybody else's.  Three ways:
+//   * a list in row order, every interval behind the one before (packed whole sequences): one look at the neighbour finds that out;
+//   * up to kSmallList items: all pairs;
+//   * else by sorting: intervals sorted by their start overlap an earlier one iff the largest end so far exceeds their start, and a
+//     later one iff the next start lies before their end.  The sequence enters the sort key with its low 21 bits: two
+//     sequences that collide there are treated as one, which can only clear a flag that could have been set (the safe side).
 // `key`: LDS work area of 2 * kMaxExclusiveScan entries; `fl`: LDS, one word per item, written here.
 __device__ inline void bitonic_sort(uint64_t* key, int32_t n_pow2) {
   // A list written in row order (the usual case: items by sequence, chunks by position) is sorted already: one pass
@@ -184,29 +188,42 @@ __device__ inline void block_running_max(uint64_t v0, uint64_t v1, uint64_t* s_w
   before1 = before0 > v0 ? before0 : v0;        // ... before v1
 }
 
-constexpr int kSmallList = 64;   // up to this many items the flags come from a comparison of all pairs
+constexpr int kSmallList = 256;   // (all pairs take about 5 us there, the two sorts 25 at any length)
 
-__device__ inline void exclusive_flags_all(const int32_t (*rng)[7], int32_t n_work, uint64_t* key, uint64_t* s_wmax, int32_t* fl) {
+__device__ inline void exclusive_flags_all(const ItemSlot* item, int32_t n_work, uint64_t* key, uint64_t* s_wmax, int32_t* fl) {
   const int tid = threadIdx.x;
   constexpr uint64_t kNone = ~(uint64_t)0;
-  for (int32_t i = tid; i < n_work; i += kSchedThreads)
-    fl[i] = rng[i][0] < 0 ? 0 : (kFlagQExclusive | kFlagSeg0Exclusive | kFlagSeg1Exclusive);
+  constexpr int32_t kAll = kFlagQExclusive | kFlagSeg0Exclusive | kFlagSeg1Exclusive;
+  static_assert(kMaxExclusiveScan <= kSchedThreads, "one item per thread");
+  bool in_order = true;
+  if (tid < n_work) {
+    const Item a = get_item(item[tid]);
+    fl[tid] = a.seq < 0 ? 0 : kAll;
+    in_order = a.seq >= 0 && (a.n1 == 0 || a.k1 >= a.k0 + a.n0);
+    if (tid > 0) {
+      const Item b = get_item(item[tid - 1]);
+      in_order &= a.q_off >= b.q_off + b.q_len && (a.seq > b.seq || (a.seq == b.seq && a.k0 >= (b.n1 > 0 ? b.k1 + b.n1 : b.k0 + b.n0)));
+    }
+  }
+  if (__syncthreads_and(in_order)) return;
   if (n_work <= kSmallList) {
-    // Short lists (a packed micro-batch of a few dozen sequences): all pairs of segment slots, 16 or fewer per thread -
-    // the two sorts below are 36 or more rounds of LDS traffic and block barriers, 10 us where this takes 1.  The same
-    // rules: empty segments and invalid items take no part, sequences compare by their low 21 bits, an item's own
-    // other segment counts, query rows are compared once per pair of items.
-    __syncthreads();
-    const int32_t m = 2 * n_work;
-    for (int32_t idx = tid; idx < m * m; idx += kSchedThreads) {
-      const int32_t a = idx / m, b = idx - a * m;
-      if (a == b) continue;
-      const int32_t ia = a >> 1, sa = a & 1, ib = b >> 1, sb = b & 1;
-      if (rng[ia][0] < 0 || rng[ib][0] < 0) continue;
-      const int32_t a0 = rng[ia][3 + 2 * sa], a1 = rng[ia][4 + 2 * sa], b0 = rng[ib][3 + 2 * sb], b1 = rng[ib][4 + 2 * sb];
-      if (a1 > a0 && b1 > b0 && ((rng[ia][0] ^ rng[ib][0]) & 0x1FFFFF) == 0 && a0 < b1 && b0 < a1)
-        atomicAnd(&fl[ia], ~(sa ? kFlagSeg1Exclusive : kFlagSeg0Exclusive));
-      if (sa == 0 && sb == 0 && rng[ia][1] < rng[ib][2] && rng[ib][1] < rng[ia][2]) atomicAnd(&fl[ia], ~kFlagQExclusive);
+    // thread = (item, share of the others); the lanes of a wave look at the same other item
+    int32_t p = 1;
+    while (p < n_work) p <<= 1;
+    const int32_t ia = tid & (p - 1), parts = kSchedThreads / p;
+    if (ia < n_work && fl[ia] != 0) {
+      const Item a = get_item(item[ia]);
+      int32_t lost = a.n1 > 0 && a.k0 < a.k1 + a.n1 && a.k1 < a.k0 + a.n0 ? kFlagSeg0Exclusive | kFlagSeg1Exclusive : 0;
+      for (int32_t ib = tid / p; ib < n_work; ib += parts) {
+        const Item b = get_item(item[ib]);
+        if (ib == ia || b.seq < 0) continue;
+        if (a.q_off < b.q_off + b.q_len && b.q_off < a.q_off + a.q_len) lost |= kFlagQExclusive;
+        if (a.seq != b.seq) continue;
+        auto meets = [](int32_t k, int32_t n, int32_t ks, int32_t ns) { return n > 0 && ns > 0 && k < ks + ns && ks < k + n; };
+        if (meets(a.k0, a.n0, b.k0, b.n0) || meets(a.k0, a.n0, b.k1, b.n1)) lost |= kFlagSeg0Exclusive;
+        if (meets(a.k1, a.n1, b.k0, b.n0) || meets(a.k1, a.n1, b.k1, b.n1)) lost |= kFlagSeg1Exclusive;
+      }
+      if (lost) atomicAnd(&fl[ia], ~lost);
     }
     __syncthreads();
     return;
@@ -215,22 +232,22 @@ __device__ inline void exclusive_flags_all(const int32_t (*rng)[7], int32_t n_wo
   int32_t np = 2;
   while (np < n_work) np <<= 1;
   for (int32_t i = tid; i < np; i += kSchedThreads)
-    key[i] = (i < n_work && rng[i][0] >= 0) ? ((uint64_t)(uint32_t)rng[i][1] << 11) | (uint64_t)i : kNone;
+    key[i] = (i < n_work && item[i][0] >= 0) ? ((uint64_t)(uint32_t)item[i][1] << 11) | (uint64_t)i : kNone;
   __syncthreads();
   bitonic_sort(key, np);
   {
     // one element per thread (np <= kSchedThreads): value of the running maximum = end
     const uint64_t k0 = tid < np ? key[tid] : kNone;
     const bool live = k0 != kNone;
-    const int32_t item = live ? (int32_t)(k0 & 2047) : 0;
-    const uint64_t end = live ? (uint64_t)(uint32_t)rng[item][2] : 0;
+    const int32_t i = live ? (int32_t)(k0 & 2047) : 0;
+    const uint64_t end = live ? (uint64_t)(uint32_t)(item[i][1] + item[i][2]) : 0;
     uint64_t before, unused;
     block_running_max(end, 0, s_wmax, before, unused);
     if (live) {
       const uint64_t start = k0 >> 11;
       const uint64_t nxt = tid + 1 < np ? key[tid + 1] : kNone;
       const bool hit = before > start || (nxt != kNone && (nxt >> 11) < end);
-      if (hit) atomicAnd(&fl[item], ~kFlagQExclusive);
+      if (hit) atomicAnd(&fl[i], ~kFlagQExclusive);
     }
   }
   __syncthreads();
@@ -240,10 +257,8 @@ __device__ inline void exclusive_flags_all(const int32_t (*rng)[7], int32_t n_wo
   for (int32_t sl = tid; sl < np2; sl += kSchedThreads) {
     const int32_t i = sl >> 1, sg = sl & 1;
     uint64_t k = kNone;
-    if (i < n_work && rng[i][0] >= 0) {
-      const int32_t a = rng[i][3 + 2 * sg], b = rng[i][4 + 2 * sg];
-      if (b > a) k = ((uint64_t)(rng[i][0] & 0x1FFFFF) << 43) | ((uint64_t)(uint32_t)a << 12) | (uint64_t)sl;
-    }
+    if (i < n_work && item[i][0] >= 0 && item[i][5 + 2 * sg] > 0)
+      k = ((uint64_t)(item[i][0] & 0x1FFFFF) << 43) | ((uint64_t)(uint32_t)item[i][4 + 2 * sg] << 12) | (uint64_t)sl;
     key[sl] = k;
   }
   __syncthreads();
@@ -254,7 +269,8 @@ __device__ inline void exclusive_flags_all(const int32_t (*rng)[7], int32_t n_wo
       slot = (int32_t)(k & 4095);
       start = (k >> 12) & 0x7FFFFFFFu;
       seqm = k >> 43;
-      val = (seqm << 32) | (uint64_t)(uint32_t)rng[slot >> 1][4 + 2 * (slot & 1)];
+      const ItemSlot& r = item[slot >> 1];
+      val = (seqm << 32) | (uint64_t)(uint32_t)(r[4 + 2 * (slot & 1)] + r[5 + 2 * (slot & 1)]);
     };
     const int32_t p0 = 2 * tid, p1 = 2 * tid + 1;
     const uint64_t k0 = p0 < np2 ? key[p0] : kNone, k1 = p1 < np2 ? key[p1] : kNone;
@@ -277,6 +293,85 @@ __device__ inline void exclusive_flags_all(const int32_t (*rng)[7], int32_t n_wo
   __syncthreads();
 }
 
+// What the key-tile and query-tile lists of a backward are like: one unit per tile; the chains of the one-pass kernel; tiles split where
+// whole ones would leave most of the chip idle (see split_sizes).
+enum ListMode { kWhole, kChained, kSplit };
+
+// Split tiles.  A unit is a serial loop over the 32-row blocks (key tiles: of every query head of the KV head) or the 32-key
+// blocks (query tiles) that the tile meets.  On small problems the longest of these loops, not the sum of the work, sets the time: a
+// sequence of 4096 tokens with 3 query heads per KV head has a key tile of 384 steps where an even spread over the CUs would
+// be 37.  So a key tile's rows are cut into pieces of `rows` rows of the item, a query tile's keys into pieces of `keys` keys of a segment, and
+// every piece is a unit; the pieces of a tile add to its accumulators with atomics.
+// Size of a piece, in steps: a CU's even share of all steps; not less than sqrt(steps / 8), where the loop of a piece and the atomics of all of them
+// take the same time (a piece's 32 K elements go at one element per L2 channel and clock, an eighth of a step's time); not less
+// than min_steps, a unit's own beginning and end.  Nothing is split unless the longest loop is clearly longer than what the pieces
+// take: the share, half a piece at the end of the list, the atomics of the items whose tiles are longer than a piece.
+struct SplitArgs { int32_t group, kv_units, q_units, dq_tile, n_cu, min_steps; };
+struct SplitSizes { int32_t rows, keys; };
+constexpr int32_t kNoPieces = 1 << 24;
+constexpr float kSplitGain = 1.15f;
+
+// Called by every thread of the block, with its item (rejected: none).  Every block that asks gets the same answer: sums are formed in a fixed order.
+__device__ inline SplitSizes split_sizes(const SplitArgs& a, const MaskTables& m, const Item& it, int32_t n_work) {
+  __shared__ float s_part[kSchedThreads / 64][6];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, n_waves = (n_work + 63) >> 6;
+  // the item's steps (the average of its first and last tile times the tiles) and its longest tile: key tiles, query tiles
+  float steps[2] = {0.f, 0.f}, longest[2] = {0.f, 0.f};
+  if (it.seq >= 0) {
+#pragma unroll
+    for (int s = 0; s < 2; ++s) {
+      const int32_t nt = ceil_div(it.vis(s), kBwdBN);
+      if (nt == 0) continue;
+      const int32_t c0 = bwd_cost<false>(m, it, s, 0, kBwdBN, kBwdBM), c1 = bwd_cost<false>(m, it, s, nt - 1, kBwdBN, kBwdBM);
+      steps[0] += 0.5f * nt * (c0 + c1) * a.group * a.kv_units;
+      longest[0] = fmaxf(longest[0], c0 * a.group);
+    }
+    const int32_t nq = ceil_div(it.q_len, a.dq_tile);
+    longest[1] = ceil_div(it.vis0, kDqBN) + ceil_div(it.vis1, kDqBN);
+    steps[1] = 0.5f * nq * (fwd_cost(m, it, 0, a.dq_tile, kDqBN) + longest[1]) * a.q_units;
+  }
+  auto wave_sum = [](float v) { for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64); return v; };
+  auto wave_max = [](float v) { for (int o = 32; o > 0; o >>= 1) v = fmaxf(v, __shfl_xor(v, o, 64)); return v; };
+  if (wave < n_waves) {
+    const float p[4] = {wave_sum(steps[0]), wave_sum(steps[1]), wave_max(longest[0]), wave_max(longest[1])};
+    if (lane == 0)
+#pragma unroll
+      for (int i = 0; i < 4; ++i) s_part[wave][i] = p[i];
+  }
+  __syncthreads();
+  float all[2] = {0.f, 0.f}, top[2] = {0.f, 0.f}, piece[2];
+  for (int w = 0; w < n_waves; ++w)
+#pragma unroll
+    for (int l = 0; l < 2; ++l) {
+      all[l] += s_part[w][l];
+      top[l] = fmaxf(top[l], s_part[w][2 + l]);
+    }
+#pragma unroll
+  for (int l = 0; l < 2; ++l) piece[l] = fmaxf(fmaxf(all[l] / a.n_cu, sqrtf(all[l] * 0.125f)), (float)a.min_steps);
+  if (wave < n_waves) {
+    const float p[2] = {wave_sum(longest[0] > piece[0] ? steps[0] : 0.f), wave_sum(longest[1] > piece[1] ? steps[1] : 0.f)};
+    if (lane == 0) { s_part[wave][4] = p[0]; s_part[wave][5] = p[1]; }
+  }
+  __syncthreads();
+#pragma unroll
+  for (int l = 0; l < 2; ++l) {
+    float heavy = 0.f;
+    for (int w = 0; w < n_waves; ++w) heavy += s_part[w][4 + l];
+    const float pieces = all[l] / a.n_cu + 0.5f * piece[l] + 0.125f * heavy / piece[l] + 4.f;
+    if (top[l] < kSplitGain * pieces) piece[l] = kNoPieces;
+  }
+  return {piece[0] < kNoPieces ? 32 * max(1, (int32_t)piece[0] / a.group) : 32 * kNoPieces, 32 * (int32_t)piece[1]};
+}
+
+// Pieces of a query tile: up to this many, those of segment 0 first (one for a tile that is not split).
+__device__ inline int32_t key_slots(const Item& it, int32_t keys) { return max(1, ceil_div(it.vis0, keys) + ceil_div(it.vis1, keys)); }
+// The pieces of a key tile: numbers first .. first + count - 1.  A later tile of the segment lacks the leading ones.
+struct RowPieces { int32_t first, count; };
+__device__ inline RowPieces row_pieces(const MaskTables& m, const Item& it, int s, int32_t kt, int32_t rows) {
+  const int32_t first = first_row_of(m, it, s, kt, kBwdBN) / rows;
+  return {first, ceil_div(it.q_len, rows) - first};
+}
+
 // LDS shared between the flags' sort (first) and the list builder's histogram and offsets (afterwards).
 struct SortArea {
   union {
@@ -287,126 +382,188 @@ struct SortArea {
 };
 
 // One tile list, built by one block.
-template <bool Chain>
+template <ListMode Mode>
 __device__ void build_list(
-    int backward, int check_step, int32_t tile, int32_t inner, int32_t max_seg_keys, const MaskTables m,
-    const fcp_work_desc* __restrict__ work, int32_t n_work,
-    const int32_t* __restrict__ cu, int32_t n_seqs, int32_t tq, int32_t tkv, int32_t n_parts,
-    int32_t tile_cap, SchedHeader* hdr, int32_t* item_off, int32_t* item_flags, Tile* tiles,
-    int32_t (*s_rng)[7],                 // LDS, kMaxExclusiveScan rows: seq (-1 = invalid), q range, two key ranges
-    int32_t (*s_flag0)[2],               // LDS, kMaxExclusiveScan rows: [0] = the item's first flag block
+    bool backward, int32_t tile, int32_t inner, const ListArgs& args, const MaskTables& m,
+    int32_t tile_cap, SchedHeader* hdr, int32_t* item_off, Tile* tiles,
+    ItemSlot* s_item,                    // LDS, kMaxExclusiveScan slots
     SortArea* area, int32_t* s_fl,       // LDS: sort keys (later the histogram and the offsets), one flag word per item
-    int32_t* chain) {                    // chain records of the key tiles, or NULL (then the order of equal costs is free)
+    int32_t* chain,                      // kChained: the tiles' chain records
+    const SplitArgs& sargs) {            // kSplit
   __shared__ int32_t s_wave[kSchedThreads / 64];
-  __shared__ int32_t s_max, s_rej, s_carry;
+  __shared__ int32_t s_max, s_rej;
+  constexpr bool Chain = Mode == kChained;
   int32_t* const s_hist = area->later.hist;
-  int32_t* const s_off = area->later.off;          // copy of item_off for short work lists: the tile decode below
-  const bool off_in_lds = n_work <= kMaxExclusiveScan;   // searches it, and a search in global memory is a chain of misses
-  const int tid = threadIdx.x;
-  // The exclusivity flags first: their sort keys share LDS with the histogram and the offsets.
-  if (n_work <= kMaxExclusiveScan) {
-    for (int32_t i = tid; i < n_work; i += kSchedThreads) {
-      const fcp_work_desc a = work[i];
-      stage_item(s_rng[i], a, item_valid(a, cu, n_seqs, tq, tkv, n_parts, check_step != 0, max_seg_keys));
+  int32_t* const s_off = area->later.off;          // item_off for staged lists
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int32_t n_work = args.n_work;
+  const bool staged = n_work <= kMaxExclusiveScan;
+  SplitSizes split{};
+  bool cut = false;                                // tiles are split (the same for every thread)
+  Item mine{-1, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0};
+  if (tid == 0) { s_max = 0; s_rej = 0; }
+  if (staged) {
+    if (tid < n_work) {
+      mine = load_item(args, m, tid);
+      put_item(s_item[tid], mine);
     }
     __syncthreads();
-    exclusive_flags_all(s_rng, n_work, area->key, area->wmax, s_fl);
-    for (int32_t i = tid; i < n_work; i += kSchedThreads) item_flags[i] = s_fl[i];
-  } else {
-    for (int32_t i = tid; i < n_work; i += kSchedThreads) item_flags[i] = 0;
+    exclusive_flags_all(s_item, n_work, area->key, area->wmax, s_fl);
+    if constexpr (Mode == kSplit) {
+      split = split_sizes(sargs, m, mine, n_work);
+      cut = (backward ? split.rows : split.keys) < 32 * kNoPieces;
+    }
   }
-  __syncthreads();
-  if (tid == 0) { s_max = 0; s_rej = 0; s_carry = 0; }
-  for (int b = tid; b < kBuckets; b += kSchedThreads) s_hist[b] = 0;
-  __syncthreads();
+  auto fetch = [&](int32_t i) { return staged ? get_item(s_item[i]) : load_item(args, m, i); };
+  for (int b = tid; b < kBuckets; b += kSchedThreads) s_hist[b] = 0;   // (the sort keys are done with)
 
   // Chains (key tiles only, at most kMaxExclusiveScan items): the flags of the query blocks of the items that own their rows.
   if constexpr (Chain) {
-    const int32_t i = tid;
-    const int32_t nb = i < n_work && (s_fl[i] & kFlagQExclusive) ? ceil_div(s_rng[i][2] - s_rng[i][1], inner) : 0;
+    const int32_t nb = tid < n_work && (s_fl[tid] & kFlagQExclusive) ? ceil_div(mine.q_len, inner) : 0;
     int32_t total;
     const int32_t ex = block_exclusive_scan(nb, s_wave, total);
-    if (i < n_work) s_flag0[i][0] = ex;
-    __syncthreads();
+    if (tid < n_work) s_item[tid][12] = ex;
   }
 
-  // Pass 1: validate, count tiles per item, exclusive offsets into item_off[0..n_work].
+  // Pass 1: count tiles per item, exclusive offsets.
+  int32_t total_tiles = 0;
   for (int32_t base = 0; base < n_work; base += kSchedThreads) {
     const int32_t i = base + tid;
-    int32_t cnt = 0;
+    int32_t cnt = 0, cost = 0, bad = 0;
     if (i < n_work) {
-      const fcp_work_desc w = work[i];
-      const ItemInfo info = item_info(m, w, cu, n_seqs, tq, tkv, n_parts, backward != 0, check_step != 0, tile, inner, max_seg_keys);
-      if (!info.ok) atomicAdd(&s_rej, 1);
-      cnt = info.n_tiles;
-      if (info.max_cost > 0) atomicMax(&s_max, info.max_cost);
+      const Item it = staged ? mine : load_item(args, m, i);
+      if (it.seq < 0) {
+        bad = 1;
+      } else if (!backward) {
+        cnt = ceil_div(it.q_len, tile);
+        cost = ceil_div(it.vis0, inner) + ceil_div(it.vis1, inner);
+        if (Mode == kSplit && cut) cnt *= key_slots(it, split.keys);
+      } else {
+        const int32_t nt0 = ceil_div(it.vis0, tile), nt1 = ceil_div(it.vis1, tile);
+        cnt = nt0 + nt1;
+        cost = ceil_div(it.q_len, inner);
+        if (Mode == kSplit && cut)
+          cnt = (nt0 > 0 ? nt0 * row_pieces(m, it, 0, 0, split.rows).count : 0) + (nt1 > 0 ? nt1 * row_pieces(m, it, 1, 0, split.rows).count : 0);
+      }
+    }
+    for (int o = 32; o > 0; o >>= 1) cost = max(cost, __shfl_xor(cost, o, 64));
+    const uint64_t n_bad = __builtin_amdgcn_ballot_w64(bad != 0);
+    if (lane == 0) {
+      if (cost > 0) atomicMax(&s_max, cost);
+      if (n_bad) atomicAdd(&s_rej, __builtin_popcountll(n_bad));
     }
     int32_t total;
     const int32_t ex = block_exclusive_scan(cnt, s_wave, total);
-    const int32_t carry = s_carry;
-    if (i < n_work) {
-      item_off[i] = carry + ex;
-      if (off_in_lds) s_off[i] = carry + ex;
-    }
-    __syncthreads();
-    if (tid == 0) s_carry = carry + total;
-    __syncthreads();
+    if (i < n_work) (staged ? s_off : item_off)[i] = total_tiles + ex;
+    total_tiles += total;
   }
-  const int32_t total_tiles = s_carry;
+  __syncthreads();
   const int32_t n_tiles = min(total_tiles, tile_cap);
-  if (tid == 0) {
-    item_off[n_work] = total_tiles;
-    if (total_tiles > tile_cap) atomicAdd(&s_rej, total_tiles - tile_cap);
-  }
+  if (tid == 0 && total_tiles > tile_cap) s_rej += total_tiles - tile_cap;
   int shift = 0;
   while ((s_max >> shift) >= kBuckets) ++shift;
-  __syncthreads();
 
   // Pass 2 and 3 share the decode of a flat tile number into its resolved record and cost.
-  auto decode = [&](int32_t t, Tile& out) -> int32_t {
+  auto item_of = [&](int32_t t) {
     int32_t lo = 0, hi = n_work - 1;               // last item with item_off <= t
     while (lo < hi) {
       const int32_t mid = (lo + hi + 1) >> 1;
-      if ((off_in_lds ? s_off[mid] : item_off[mid]) <= t) lo = mid; else hi = mid - 1;
+      if ((staged ? s_off[mid] : item_off[mid]) <= t) lo = mid; else hi = mid - 1;
     }
-    const fcp_work_desc w = work[lo];
-    const int32_t local = t - (off_in_lds ? s_off[lo] : item_off[lo]);
-    const int32_t row0_kv = cu[w.seq];
-    const int32_t fl = off_in_lds ? s_fl[lo] : 0;
-    for (int i = 0; i < 16; ++i) out.w[i] = 0;
+    return lo;
+  };
+  auto decode = [&](int32_t t, Tile& out) -> int32_t {
+    const int32_t at = item_of(t);
+    const Item it = fetch(at);
+    const int32_t local = t - (staged ? s_off[at] : item_off[at]);
+    const int32_t fl = staged ? s_fl[at] : 0;
     if (!backward) {
-      QTile* q = reinterpret_cast<QTile*>(&out);
-      const int32_t r0 = local * tile;
-      q->q_row0 = w.q_local_off + r0;
-      q->q_pos0 = w.q_seq_start + r0;
-      q->rows = min(tile, w.q_len - r0);
-      q->step = w.step;
-      for (int sg = 0; sg < 2; ++sg) {
-        q->kv_row0[sg] = sg < w.n_seg ? row0_kv + w.k_seq_start[sg] : 0;
-        q->k_pos0[sg] = sg < w.n_seg ? w.k_seq_start[sg] : 0;
-        q->vis[sg] = sg < w.n_seg ? visible_len(m, w, sg, r0 + q->rows - 1) : 0;
+      int32_t slots = 1, qt = local;
+      if (Mode == kSplit && cut) {
+        slots = key_slots(it, split.keys);
+        qt = local / slots;
       }
-      q->flags = fl;
-      return fwd_cost(m, w, local, tile, inner);
+      QTile q{};
+      const int32_t r0 = qt * tile;
+      q.q_row0 = it.q_off + r0;
+      q.q_pos0 = it.q_pos + r0;
+      q.rows = min(tile, it.q_len - r0);
+      q.step = it.step;
+      const int64_t limit = m.limit(it, r0 + q.rows - 1);
+      const int32_t v0 = seen_keys(it, 0, limit), v1 = it.n1 > 0 ? seen_keys(it, 1, limit) : 0;
+      q.kv_row0[0] = it.base + it.k0;
+      q.k_pos0[0] = it.k0;
+      q.vis[0] = v0;
+      q.kv_row0[1] = it.n1 > 0 ? it.base + it.k1 : 0;
+      q.k_pos0[1] = it.k1;
+      q.vis[1] = v1;
+      q.flags = fl;
+      int32_t cost = ceil_div(v0, inner) + ceil_div(v1, inner);
+      if (Mode == kSplit && cut) {
+        int32_t slot = local - qt * slots;
+        if (v0 + v1 > split.keys) {
+          const int32_t c0 = ceil_div(it.vis0, split.keys);
+          const int sg = slot < c0 ? 0 : 1;
+          const int32_t first = (slot - (sg ? c0 : 0)) * split.keys;
+          const int32_t vis = min(split.keys, (sg ? v1 : v0) - first);
+          q.kv_row0[0] = it.base + it.k(sg) + first;
+          q.k_pos0[0] = it.k(sg) + first;
+          q.vis[0] = vis;
+          q.kv_row0[1] = q.k_pos0[1] = q.vis[1] = 0;
+          q.flags = fl & ~kFlagQExclusive;
+          cost = vis > 0 ? ceil_div(vis, inner) : -1;
+        } else if (slot > 0) {
+          cost = -1;
+        }
+      }
+      out = __builtin_bit_cast(Tile, q);
+      return cost;
     }
-    const int32_t nt0 = ceil_div(visible_len(m, w, 0, w.q_len - 1), tile);
-    const int sg = local >= nt0 ? 1 : 0;
-    const int32_t kt = local - (sg ? nt0 : 0);
-    KTile* k = reinterpret_cast<KTile*>(&out);
-    k->kv_row0 = row0_kv + w.k_seq_start[sg] + kt * tile;
-    k->k_pos0 = w.k_seq_start[sg] + kt * tile;
-    k->n_keys = min(tile, visible_len(m, w, sg, w.q_len - 1) - kt * tile);
-    const int64_t last_q_pos = (int64_t)w.q_seq_start + w.q_len - 1;
-    for (int g = 0; g < 4; ++g) {
-      const int32_t first_key = min(32 * g, k->n_keys - 1), last_key = min(32 * g + 31, k->n_keys - 1);
-      k->from_first[g] = (int32_t)min(last_q_pos, m.from(w, cu, (int64_t)k->k_pos0 + first_key));
-      k->from_last[g] = (int32_t)min(last_q_pos, m.from(w, cu, (int64_t)k->k_pos0 + last_key));
+    const int32_t nt0 = ceil_div(it.vis0, tile);
+    int sg = local >= nt0 ? 1 : 0;
+    int32_t kt = local - (sg ? nt0 : 0);
+    int32_t row0 = 0, row1 = it.q_len;               // the unit's rows of the item
+    bool whole = true;
+    if (Mode == kSplit && cut) {
+      RowPieces pc = nt0 > 0 ? row_pieces(m, it, 0, 0, split.rows) : RowPieces{0, 1};
+      sg = local >= nt0 * pc.count ? 1 : 0;
+      const int32_t l = local - (sg ? nt0 * pc.count : 0);
+      if (sg) pc = row_pieces(m, it, 1, 0, split.rows);
+      kt = l / pc.count;
+      row0 = (pc.first + l - kt * pc.count) * split.rows;
+      row1 = min(it.q_len, row0 + split.rows);
+      if (first_row_of(m, it, sg, kt, tile) >= row1) return -1;
+      whole = row_pieces(m, it, sg, kt, split.rows).count == 1;
+      if (whole) { row0 = 0; row1 = it.q_len; }
     }
-    k->q_local_off = w.q_local_off;
-    k->q_seq_start = w.q_seq_start;
-    k->q_len = w.q_len;
-    k->flags = (fl & (sg ? kFlagSeg1Exclusive : kFlagSeg0Exclusive)) ? kFlagSeg0Exclusive : 0;
-    return bwd_cost<Chain>(m, cu, w, sg, kt, tile, inner);
+    KTile k{};
+    k.k_pos0 = it.k(sg) + kt * tile;
+    k.kv_row0 = it.base + k.k_pos0;
+    k.n_keys = min(tile, it.vis(sg) - kt * tile);
+    const int64_t last_q_pos = (int64_t)it.q_pos + row1 - 1;
+    int32_t from[8];                                 // of every group's first and last key
+#pragma unroll
+    for (int g = 0; g < 8; ++g) from[g] = min(16 * (g & ~1) + 31 * (g & 1), k.n_keys - 1);
+    if (m.k_from) {                                  // (one branch: the eight loads are in flight together)
+#pragma unroll
+      for (int g = 0; g < 8; ++g) from[g] = m.k_from[k.kv_row0 + from[g]];
+    } else {
+#pragma unroll
+      for (int g = 0; g < 8; ++g) from[g] += k.k_pos0;
+    }
+#pragma unroll
+    for (int g = 0; g < 8; ++g) {
+      const int32_t f = (int32_t)min(last_q_pos, (int64_t)from[g]);
+      if (g & 1) k.from_last[g / 2] = f; else k.from_first[g / 2] = f;
+    }
+    k.q_local_off = it.q_off + row0;
+    k.q_seq_start = it.q_pos + row0;
+    k.q_len = row1 - row0;
+    k.flags = whole && (fl & (sg ? kFlagSeg1Exclusive : kFlagSeg0Exclusive)) ? kFlagSeg0Exclusive : 0;
+    out = __builtin_bit_cast(Tile, k);
+    const int32_t first = k.from_first[0] - it.q_pos;      // (first_row_of, before it is clamped)
+    if (Chain) return ceil_div(it.q_len, inner) - max(0, first) / inner;
+    return ceil_div(row1 - max(row0, first), inner);
   };
 
   // Place of key tile t in the chain of its item, if the item owns its query rows (else the tile adds with atomics, rank -1):
@@ -415,13 +572,9 @@ __device__ void build_list(
   // segment the buckets do not grow with the key, so the tiles of the other segment that come before are found by bisection.
   // Blocks are counted so that tiles of one bucket start at the same one: a tile later in the chain never starts at an earlier block.
   auto chain_place = [&](int32_t t, int32_t bucket, int32_t& rank, int32_t& next, int32_t& first, int32_t& flag0) {
-    int32_t lo = 0, hi = n_work - 1;
-    while (lo < hi) {
-      const int32_t mid = (lo + hi + 1) >> 1;
-      if (s_off[mid] <= t) lo = mid; else hi = mid - 1;
-    }
-    const fcp_work_desc w = work[lo];
-    const int32_t nqb = ceil_div(w.q_len, inner);
+    const int32_t at = item_of(t);
+    const Item it = get_item(s_item[at]);
+    const int32_t nqb = ceil_div(it.q_len, inner);
     auto first_block = [&](int32_t b) {               // first block of the tiles of bucket b
       const int64_t most = (((int64_t)b + 1) << shift) - 1;
       return b >= kBuckets - 1 || most >= nqb ? 0 : nqb - (int32_t)most;
@@ -430,15 +583,16 @@ __device__ void build_list(
     next = nqb;
     rank = -1;
     flag0 = 0;
-    if (!(s_fl[lo] & kFlagQExclusive)) return;
-    flag0 = s_flag0[lo][0];
-    const int32_t nt0 = ceil_div(visible_len(m, w, 0, w.q_len - 1), tile);
-    const int32_t my_seg = t - s_off[lo] >= nt0 ? 1 : 0;
-    const int32_t my_kt = t - s_off[lo] - (my_seg ? nt0 : 0);
+    if (!(s_fl[at] & kFlagQExclusive)) return;
+    flag0 = s_item[at][12];
+    const int32_t nt0 = ceil_div(it.vis0, tile);
+    const int32_t my_seg = t - s_off[at] >= nt0 ? 1 : 0;
+    const int32_t my_kt = t - s_off[at] - (my_seg ? nt0 : 0);
     rank = my_kt;
-    for (int32_t sg = 0; sg < w.n_seg; ++sg) {
-      const int32_t nt = ceil_div(visible_len(m, w, sg, w.q_len - 1), tile);
-      auto bucket_of = [&](int32_t kt) { return min(bwd_cost<Chain>(m, cu, w, sg, kt, tile, inner) >> shift, kBuckets - 1); };
+#pragma unroll
+    for (int sg = 0; sg < 2; ++sg) {
+      const int32_t nt = ceil_div(it.vis(sg), tile);
+      auto bucket_of = [&](int32_t kt) { return min(bwd_cost<Chain>(m, it, sg, kt, tile, inner) >> shift, kBuckets - 1); };
       int32_t a;                                      // the segment's first tile after t
       if (sg == my_seg) {
         a = my_kt + 1;
@@ -463,16 +617,16 @@ __device__ void build_list(
     Tile tl;
     const int32_t c = decode(t, tl);
     if (t == tid) { first_tile = tl; first_cost = c; }
-    atomicAdd(&s_hist[min(c >> shift, kBuckets - 1)], 1);
+    if (Mode != kSplit || c >= 0) atomicAdd(&s_hist[min(c >> shift, kBuckets - 1)], 1);   // (-1: no such piece)
   }
   __syncthreads();
   // Descending-cost start offset of every bucket: scan the histogram from the top.
+  int32_t n_listed;
   {
     static_assert(kBuckets == 2 * kSchedThreads, "two buckets per thread");
     const int b_hi = kBuckets - 1 - 2 * tid, b_lo = b_hi - 1;
     const int32_t h_hi = s_hist[b_hi], h_lo = s_hist[b_lo];
-    int32_t total;
-    const int32_t ex = block_exclusive_scan(h_hi + h_lo, s_wave, total);
+    const int32_t ex = block_exclusive_scan(h_hi + h_lo, s_wave, n_listed);
     __syncthreads();
     s_hist[b_hi] = ex;
     s_hist[b_lo] = ex + h_hi;
@@ -484,6 +638,7 @@ __device__ void build_list(
       int32_t c;
       if (t == tid) { tl = first_tile; c = first_cost; }
       else c = decode(t, tl);
+      if (Mode == kSplit && c < 0) continue;
       const int32_t pos = atomicAdd(&s_hist[min(c >> shift, kBuckets - 1)], 1);
       tiles[pos] = tl;
     }
@@ -530,7 +685,7 @@ __device__ void build_list(
     }
   }
   if (tid == 0) {
-    hdr->n_tiles = n_tiles;
+    hdr->n_tiles = n_listed;
     hdr->n_rejected = s_rej;
     hdr->max_cost = s_max;
     hdr->pad0 = 0;
@@ -552,43 +707,35 @@ struct RowStateJob {
   int32_t q_row_elems, kv_row_elems;
   int32_t n_parts, check_step;   // the validity rules of the list the states go with
 };
-// The blocks `first` .. `first + count - 1` of the launch share the rows; LDS arrays come from the kernel.
-__device__ void row_states(
-    int first, int count, const RowStateJob& job, int32_t max_seg_keys, const MaskTables& m,
-    const fcp_work_desc* __restrict__ work, int32_t n_work, const int32_t* __restrict__ cu, int32_t n_seqs, int32_t tq,
-    int32_t tkv, int32_t (*s_rng)[7], int32_t (*s_vis)[2], int32_t* s_fl, SortArea* area) {
+// The blocks `first` .. `first + count - 1` of the launch share the rows; LDS arrays come from the kernel.  `split`: the rows of split tiles are
+// accumulated into.
+template <bool Split>
+__device__ void row_states(int first, int count, const RowStateJob& job, const ListArgs& args, const MaskTables& m, ItemSlot* s_item,
+                           int32_t* s_fl, SortArea* area, const SplitArgs& sargs) {
   uint8_t* __restrict__ q_state = job.q_state;
   uint8_t* __restrict__ kv_state = job.kv_state;
   float* __restrict__ dq_acc = job.dq_acc;
   float* __restrict__ dk_acc = job.dk_acc;
   float* __restrict__ dv_acc = job.dv_acc;
   const int32_t q_row_elems = job.q_row_elems, kv_row_elems = job.kv_row_elems;
-  const int32_t n_kv_rows = kv_state ? tkv : 0;
+  const int32_t tq = args.tq, n_work = args.n_work, n_kv_rows = kv_state ? args.tkv : 0;
   const int tid = threadIdx.x, lane = tid & 63;
-  for (int32_t i = tid; i < n_work; i += kSchedThreads) {
-    const fcp_work_desc a = work[i];
-    const bool ok = item_valid(a, cu, n_seqs, tq, tkv, job.n_parts, job.check_step != 0, max_seg_keys);
-    stage_item(s_rng[i], a, ok);
-    s_vis[i][0] = ok ? visible_len(m, a, 0, a.q_len - 1) : 0;
-    s_vis[i][1] = ok && a.n_seg > 1 ? visible_len(m, a, 1, a.q_len - 1) : 0;
+  Item mine{-1, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0};
+  if (tid < n_work) {
+    mine = load_item(args, m, tid);
+    put_item(s_item[tid], mine);
   }
   __syncthreads();
-  exclusive_flags_all(s_rng, n_work, area->key, area->wmax, s_fl);
-  // The key ranges as pool rows [first, end of the visible part): a pool row then needs no search for its sequence
-  // (a binary search of cu_seqlens per row, ten dependent trips to global memory, was most of this pass).  A rejected
-  // item gets empty ranges, so the passes over the list below carry no test of validity.
-  for (int32_t i = tid; i < n_work; i += kSchedThreads) {
-    if (s_rng[i][0] < 0) {
-      for (int c = 1; c < 7; ++c) s_rng[i][c] = 0;
-    } else if (n_kv_rows > 0) {
-      const int32_t base = cu[s_rng[i][0]];
-      s_rng[i][3] += base;
-      s_rng[i][4] = s_rng[i][3] + s_vis[i][0];
-      s_rng[i][5] += base;
-      s_rng[i][6] = s_rng[i][5] + s_vis[i][1];
-      if (s_vis[i][0] + s_vis[i][1] == 0) s_rng[i][2] = s_rng[i][1];   // no key, no key tile: its rows are untouched
-    }
+  exclusive_flags_all(s_item, n_work, area->key, area->wmax, s_fl);
+  SplitSizes split{};
+  bool cut = false;
+  if constexpr (Split) {
+    split = split_sizes(sargs, m, mine, n_work);
+    cut = min(split.rows, split.keys) < 32 * kNoPieces;
   }
+  // Only the keys that some row sees matter here.  A rejected item has empty ranges, so the passes over the list below carry no test
+  // of validity.  An item without such keys has no key tile: in the backward its rows are untouched.
+  if (n_kv_rows > 0 && tid < n_work && mine.vis0 + mine.vis1 == 0) s_item[tid][2] = 0;
   __syncthreads();
 
   // Rows are taken in batches of 64, one LANE per row.  Batch f belongs to block f mod count, so every block's batches
@@ -608,19 +755,18 @@ __device__ void row_states(
   if (tid == 0) s_cnt[0] = 0;
   __syncthreads();
   {
-    // does the range of rows [s, e) meet a batch of this block?  The first batch at or after s / 64 that is ours.
-    auto mine = [&](int64_t s0, int64_t e0) {
-      if (e0 <= s0) return false;
+    // do the n rows from s0 on meet a batch of this block?  The first batch at or after s0 / 64 that is ours.
+    auto ours = [&](int64_t s0, int32_t n) {
+      if (n <= 0) return false;
       const int64_t fs = s0 >> 6;
       int64_t d = (blk - fs) % count;
       if (d < 0) d += count;
-      return ((fs + d) << 6) < e0;
+      return ((fs + d) << 6) < s0 + n;
     };
     for (int32_t i = tid; i < n_work; i += kSchedThreads) {
-      bool hit = mine(s_rng[i][1], s_rng[i][2]);                                 // (a rejected item has empty ranges)
-      if (n_kv_rows > 0)
-        hit = hit || mine((int64_t)tq + s_rng[i][3], (int64_t)tq + s_rng[i][4]) ||
-              mine((int64_t)tq + s_rng[i][5], (int64_t)tq + s_rng[i][6]);
+      const Item it = get_item(s_item[i]);
+      bool hit = ours(it.q_off, it.q_len);
+      if (n_kv_rows > 0) hit = hit || ours((int64_t)tq + it.base + it.k0, it.vis0) || ours((int64_t)tq + it.base + it.k1, it.vis1);
       if (hit) s_pick[atomicAdd(&s_cnt[0], 1)] = i;
     }
   }
@@ -633,6 +779,7 @@ __device__ void row_states(
     const int64_t f = f0 + (int64_t)wave * count + blk;
     const int64_t r0 = f << 6, r = r0 + lane;
     const bool live = r < n_rows;
+    int32_t at = 0, at_seg = 0;          // the last one found (kSplit)
     int32_t cnt = 0, own = 0;            // covering (item, segment) pairs; flags bit of the last one found
     // (no branch inside these loops: the reads of several items are in flight together)
     if (r0 + 63 < tq) {                  // 64 query rows
@@ -640,9 +787,10 @@ __device__ void row_states(
 #pragma unroll 4
       for (int32_t c = 0; c < n_cand; ++c) {
         const int32_t j = s_pick[c];
-        const bool hit = s_rng[j][1] <= x && x < s_rng[j][2];
+        const bool hit = (uint32_t)(x - s_item[j][1]) < (uint32_t)s_item[j][2];
         cnt += hit;
         own = hit ? s_fl[j] & kFlagQExclusive : own;
+        if constexpr (Split) at = hit ? j : at;
       }
     } else if (r0 < n_rows) {            // pool rows, or the batch with the last query rows and the first pool rows
       const bool is_q = r < tq;
@@ -651,13 +799,29 @@ __device__ void row_states(
       for (int32_t c = 0; c < n_cand; ++c) {
         const int32_t j = s_pick[c];
         const int32_t fj = s_fl[j];
-        const bool hq = is_q && s_rng[j][1] <= x && x < s_rng[j][2];
-        const bool h0 = !is_q && s_rng[j][3] <= x && x < s_rng[j][4];
-        const bool h1 = !is_q && s_rng[j][5] <= x && x < s_rng[j][6];
+        const int32_t (&it)[kItemWords] = s_item[j];
+        const int32_t y = x - it[8];
+        const bool hq = is_q && (uint32_t)(x - it[1]) < (uint32_t)it[2];
+        const bool h0 = !is_q && (uint32_t)(y - it[4]) < (uint32_t)it[9];
+        const bool h1 = !is_q && (uint32_t)(y - it[6]) < (uint32_t)it[10];
         cnt += (int)hq + (int)h0 + (int)h1;
         own = hq ? fj & kFlagQExclusive : own;
         own = h0 ? fj & kFlagSeg0Exclusive : own;
         own = h1 ? fj & kFlagSeg1Exclusive : own;
+        if constexpr (Split) { at = hq || h0 || h1 ? j : at; at_seg = h1 ? 1 : h0 ? 0 : at_seg; }
+      }
+    }
+    if (Split && cut) {
+      if (cnt == 1 && own != 0) {        // is the row's tile one of several units?
+        const Item it = get_item(s_item[at]);
+        if (r < tq) {
+          const int32_t last = min(((int32_t)r - it.q_off) / sargs.dq_tile * sargs.dq_tile + sargs.dq_tile, it.q_len) - 1;
+          const int64_t limit = m.limit(it, last);
+          if (seen_keys(it, 0, limit) + (it.n1 > 0 ? seen_keys(it, 1, limit) : 0) > split.keys) own = 0;
+        } else {
+          const int32_t kt = ((int32_t)(r - tq) - it.base - it.k(at_seg)) / kBwdBN;
+          if (row_pieces(m, it, at_seg, kt, split.rows).count > 1) own = 0;
+        }
       }
     }
     const int state = cnt == 0 ? 0 : (cnt == 1 && own != 0) ? 2 : 1;
@@ -695,39 +859,37 @@ __device__ void row_states(
 }
 
 // The row states alone (launches that build no list).
-__global__ __launch_bounds__(kSchedThreads) void row_state_kernel(
-    const RowStateJob job, int32_t max_seg_keys, const MaskTables m, const fcp_work_desc* __restrict__ work,
-    int32_t n_work, const int32_t* __restrict__ cu, int32_t n_seqs, int32_t tq, int32_t tkv) {
-  __shared__ int32_t s_rng[kMaxExclusiveScan][7];
-  __shared__ int32_t s_vis[kMaxExclusiveScan][2];   // keys of each segment that the item's last row sees
+__global__ __launch_bounds__(kSchedThreads) void row_state_kernel(const RowStateJob job, const ListArgs args, const MaskTables m) {
+  __shared__ ItemSlot s_item[kMaxExclusiveScan];
   __shared__ int32_t s_fl[kMaxExclusiveScan];
   __shared__ SortArea s_area;
-  row_states(0, gridDim.x, job, max_seg_keys, m, work, n_work, cu, n_seqs, tq, tkv, s_rng, s_vis, s_fl, &s_area);
+  row_states<false>(0, gridDim.x, job, args, m, s_item, s_fl, &s_area, SplitArgs{});
 }
 
-// Forward: block 0 builds the query-tile list, the next `fill_blocks` blocks pre-fill the partial LSE with -inf,
+struct ListJob {
+  int32_t tile, inner, tile_cap;
+  SchedHeader* hdr;
+  int32_t* item_off;
+  Tile* tiles;
+};
+
+// Forward (and the lists of empty calls): block 0 builds the list, the next `fill_blocks` blocks pre-fill the partial LSE with -inf,
 // the blocks after those classify the rows (direct mode).
 __global__ __launch_bounds__(kSchedThreads) void sched_kernel(
-    int backward, int check_step, int32_t tile, int32_t inner, int32_t max_seg_keys, const MaskTables m,
-    const fcp_work_desc* __restrict__ work, int32_t n_work,
-    const int32_t* __restrict__ cu, int32_t n_seqs, int32_t tq, int32_t tkv, int32_t n_parts,
-    int32_t tile_cap, SchedHeader* hdr, int32_t* item_off, int32_t* item_flags, Tile* tiles,
+    int backward, const ListJob j, const ListArgs args, const MaskTables m,
     float* lse_fill, int64_t lse_fill_n, int fill_blocks, const RowStateJob states) {
-  __shared__ int32_t s_rng[kMaxExclusiveScan][7];
-  __shared__ int32_t s_vis[kMaxExclusiveScan][2];
+  __shared__ ItemSlot s_item[kMaxExclusiveScan];
   __shared__ int32_t s_fl[kMaxExclusiveScan];
   __shared__ SortArea s_area;
   const int b = blockIdx.x;
   if (b == 0) {
-    build_list<false>(backward, check_step, tile, inner, max_seg_keys, m, work, n_work, cu, n_seqs, tq, tkv, n_parts, tile_cap,
-               hdr, item_off, item_flags, tiles, s_rng, s_vis, &s_area, s_fl, nullptr);
+    build_list<kWhole>(backward != 0, j.tile, j.inner, args, m, j.tile_cap, j.hdr, j.item_off, j.tiles, s_item, &s_area, s_fl, nullptr, SplitArgs{});
   } else if (b <= fill_blocks) {
     const int64_t stride = (int64_t)fill_blocks * kSchedThreads;
     for (int64_t i = (int64_t)(b - 1) * kSchedThreads + threadIdx.x; i < lse_fill_n; i += stride)
       lse_fill[i] = -INFINITY;
   } else {
-    row_states(1 + fill_blocks, gridDim.x - 1 - fill_blocks, states, max_seg_keys, m, work, n_work, cu, n_seqs, tq, tkv,
-               s_rng, s_vis, s_fl, &s_area);
+    row_states<false>(1 + fill_blocks, gridDim.x - 1 - fill_blocks, states, args, m, s_item, s_fl, &s_area, SplitArgs{});
   }
 }
 
@@ -735,30 +897,20 @@ __global__ __launch_bounds__(kSchedThreads) void sched_kernel(
 // (dK/dV kernel), block 1 the query-tile list (dQ kernel), the other blocks write the row statistics in the form
 // the kernels consume: plane 0 = -LSE log2 e (-inf for a row without keys, so that its probabilities vanish),
 // plane 1 = -delta.
-struct ListJob {
-  int32_t tile, inner, tile_cap;
-  SchedHeader* hdr;
-  int32_t* item_off;
-  int32_t* item_flags;
-  Tile* tiles;
-};
-template <bool Chain>
+template <ListMode Mode>
 __global__ __launch_bounds__(kSchedThreads) void sched_bwd_kernel(
-    const ListJob kv, const ListJob qt, int32_t max_seg_keys, const MaskTables m,
-    const fcp_work_desc* __restrict__ work, int32_t n_work,
-    const int32_t* __restrict__ cu, int32_t n_seqs, int32_t tq, int32_t tkv,
+    const ListJob kv, const ListJob qt, const ListArgs args, const MaskTables m,
     const float* __restrict__ lse, const float* __restrict__ delta, int64_t n_stats, float* __restrict__ stats,
-    int stat_blocks, int32_t* __restrict__ chain, int32_t* __restrict__ flags, int64_t n_flags, const RowStateJob states) {
-  __shared__ int32_t s_rng[kMaxExclusiveScan][7];
-  __shared__ int32_t s_vis[kMaxExclusiveScan][2];
+    int stat_blocks, int32_t* __restrict__ chain, int32_t* __restrict__ flags, int64_t n_flags, const SplitArgs split,
+    const RowStateJob states) {
+  __shared__ ItemSlot s_item[kMaxExclusiveScan];
   __shared__ int32_t s_fl[kMaxExclusiveScan];
   __shared__ SortArea s_area;
   const int b = blockIdx.x;
   if (b < 2) {
     const ListJob& j = b == 0 ? kv : qt;
-    if (Chain && b == 1) return;         // (the one-pass kernel has key tiles only)
-    build_list<Chain>(b == 0 ? 1 : 0, 0, j.tile, j.inner, max_seg_keys, m, work, n_work, cu, n_seqs, tq, tkv, 1,
-               j.tile_cap, j.hdr, j.item_off, j.item_flags, j.tiles, s_rng, s_vis, &s_area, s_fl, chain);
+    if (Mode == kChained && b == 1) return;         // (the one-pass kernel has key tiles only)
+    build_list<Mode>(b == 0, j.tile, j.inner, args, m, j.tile_cap, j.hdr, j.item_off, j.tiles, s_item, &s_area, s_fl, chain, split);
   } else if (b < 2 + stat_blocks) {
     const int64_t stride = (int64_t)stat_blocks * kSchedThreads;
     for (int64_t i = (int64_t)(b - 2) * kSchedThreads + threadIdx.x; i < n_stats; i += stride) {
@@ -766,11 +918,10 @@ __global__ __launch_bounds__(kSchedThreads) void sched_bwd_kernel(
       stats[i] = l == -INFINITY ? -INFINITY : -l * 1.4426950408889634f;
       stats[n_stats + i] = -delta[i];
     }
-    if constexpr (Chain)
+    if constexpr (Mode == kChained)
       for (int64_t i = (int64_t)(b - 2) * kSchedThreads + threadIdx.x; i < n_flags; i += stride) flags[i] = 0;
   } else {   // direct mode: the row states, and the accumulator rows that are accumulated into cleared
-    row_states(2 + stat_blocks, gridDim.x - 2 - stat_blocks, states, max_seg_keys, m, work, n_work, cu, n_seqs, tq, tkv,
-               s_rng, s_vis, s_fl, &s_area);
+    row_states<Mode == kSplit>(2 + stat_blocks, gridDim.x - 2 - stat_blocks, states, args, m, s_item, s_fl, &s_area, split);
   }
 }
 
@@ -797,6 +948,15 @@ static RowStateJob make_job(const RowStates* rs) {
   return j;
 }
 
+static ListArgs list_args(int64_t kv_row_bytes, const fcp_work_desc* work, int64_t n_work, const int32_t* cu, int32_t n_seqs, int32_t tq,
+                          int32_t tkv, int32_t n_parts, bool check_step) {
+  return {work, cu, (int32_t)n_work, n_seqs, tq, tkv, n_parts, max_segment_keys(kv_row_bytes), check_step};
+}
+static ListJob list_job(void* region, int64_t n_work, int32_t tile, int32_t inner, int64_t cap) {
+  return {tile, inner, (int32_t)cap, reinterpret_cast<SchedHeader*>(region),
+          reinterpret_cast<int32_t*>(static_cast<char*>(region) + sizeof(SchedHeader)), const_cast<Tile*>(sched_tiles(region, n_work))};
+}
+
 int check_row_states(int64_t n_work) {
   if (n_work > kMaxExclusiveScan)
     return fail(FCP_ERR_UNSUPPORTED, "direct mode: more than %d work items (use the plain entry point)", kMaxExclusiveScan);
@@ -809,8 +969,8 @@ int launch_row_states(int64_t kv_row_bytes, const RowStates& rs, const int32_t* 
   int rc = check_row_states(n_work);
   if (rc != FCP_OK) return rc;
   hipLaunchKernelGGL(row_state_kernel, dim3((unsigned)row_state_blocks(tq, rs.kv_state ? tkv : 0)), dim3(kSchedThreads), 0,
-                     stream, make_job(&rs), max_segment_keys(kv_row_bytes),
-                     MaskTables{q_limit, k_from}, work, (int32_t)n_work, cu_seqlens_kv, n_seqs, tq, tkv);
+                     stream, make_job(&rs), list_args(kv_row_bytes, work, n_work, cu_seqlens_kv, n_seqs, tq, tkv, rs.n_parts, rs.check_step),
+                     MaskTables{q_limit, k_from});
   FCP_HIP_CHECK(hipGetLastError());
   return FCP_OK;
 }
@@ -832,11 +992,6 @@ int launch_schedule(bool backward, int32_t tile, int32_t inner, int64_t kv_row_b
                     int32_t n_parts, int64_t tile_cap, void* region, float* lse_fill,
                     int64_t lse_fill_n, hipStream_t stream, const RowStates* states) {
   if (states) { const int rcs = check_row_states(n_work); if (rcs != FCP_OK) return rcs; }
-  char* base = static_cast<char*>(region);
-  SchedHeader* hdr = reinterpret_cast<SchedHeader*>(base);
-  int32_t* item_off = reinterpret_cast<int32_t*>(base + sizeof(SchedHeader));
-  int32_t* item_flags = const_cast<int32_t*>(sched_flags(region, n_work));
-  Tile* tiles = const_cast<Tile*>(sched_tiles(region, n_work));
   int fill_blocks = 0;
   if (lse_fill && lse_fill_n > 0) {
     fill_blocks = (int)((lse_fill_n + kSchedThreads * 4 - 1) / (kSchedThreads * 4));
@@ -845,9 +1000,9 @@ int launch_schedule(bool backward, int32_t tile, int32_t inner, int64_t kv_row_b
   }
   const int state_blocks = states ? row_state_blocks(tq, states->kv_state ? tkv : 0) : 0;
   hipLaunchKernelGGL(sched_kernel, dim3(1 + fill_blocks + state_blocks), dim3(kSchedThreads), 0, stream,
-                     backward ? 1 : 0, lse_fill ? 1 : 0, tile, inner,
-                     max_segment_keys(kv_row_bytes), MaskTables{q_limit, k_from}, work, (int32_t)n_work, cu_seqlens_kv, n_seqs, tq, tkv, n_parts,
-                     (int32_t)tile_cap, hdr, item_off, item_flags, tiles, lse_fill, lse_fill_n, fill_blocks, make_job(states));
+                     backward ? 1 : 0, list_job(region, n_work, tile, inner, tile_cap),
+                     list_args(kv_row_bytes, work, n_work, cu_seqlens_kv, n_seqs, tq, tkv, n_parts, lse_fill != nullptr),
+                     MaskTables{q_limit, k_from}, lse_fill, lse_fill_n, fill_blocks, make_job(states));
   FCP_HIP_CHECK(hipGetLastError());
   return FCP_OK;
 }
@@ -856,27 +1011,20 @@ int launch_schedule_bwd(int64_t kv_row_bytes, const int32_t* q_limit, const int3
                         const fcp_work_desc* work, int64_t n_work, const int32_t* cu_seqlens_kv, int32_t n_seqs,
                         int32_t tq, int32_t tkv, int64_t cap_kv, void* region_kv, int32_t dq_tile, int64_t cap_q, void* region_q,
                         const float* lse, const float* delta, int64_t n_stats, float* stats, hipStream_t stream,
-                        const RowStates* states, int32_t* chain, int32_t* flags, int64_t n_flags) {
+                        const RowStates* states, int32_t* chain, int32_t* flags, int64_t n_flags, const SplitTiles* split) {
   if (states) { const int rcs = check_row_states(n_work); if (rcs != FCP_OK) return rcs; }
-  auto job = [&](void* region, int32_t tile, int32_t inner, int64_t cap) {
-    ListJob j;
-    j.tile = tile; j.inner = inner; j.tile_cap = (int32_t)cap;
-    j.hdr = reinterpret_cast<SchedHeader*>(region);
-    j.item_off = reinterpret_cast<int32_t*>(static_cast<char*>(region) + sizeof(SchedHeader));
-    j.item_flags = const_cast<int32_t*>(sched_flags(region, n_work));
-    j.tiles = const_cast<Tile*>(sched_tiles(region, n_work));
-    return j;
-  };
   int64_t stat_blocks = (n_stats + kSchedThreads * 4 - 1) / (kSchedThreads * 4);
   if (stat_blocks > 1024) stat_blocks = 1024;
   if (stat_blocks < 1) stat_blocks = 1;
   const int state_blocks = states ? row_state_blocks(tq, states->kv_state ? tkv : 0) : 0;
-  const auto kernel = chain ? sched_bwd_kernel<true> : sched_bwd_kernel<false>;   // (two kernels: a longer one begins later)
+  SplitArgs sp{};
+  if (split) sp = {split->group, split->kv_units, split->q_units, dq_tile, split->n_cu, split->min_steps};
+  // (a kernel of its own for each mode: a longer one begins later)
+  const auto kernel = chain ? sched_bwd_kernel<kChained> : split ? sched_bwd_kernel<kSplit> : sched_bwd_kernel<kWhole>;
   hipLaunchKernelGGL(kernel, dim3((unsigned)(2 + stat_blocks + state_blocks)), dim3(kSchedThreads), 0, stream,
-                     job(region_kv, kBwdBN, kBwdBM, cap_kv), job(region_q, dq_tile, kDqBN, cap_q),
-                     max_segment_keys(kv_row_bytes), MaskTables{q_limit, k_from}, work,
-                     (int32_t)n_work, cu_seqlens_kv, n_seqs, tq, tkv, lse, delta, n_stats, stats, (int)stat_blocks,
-                     chain, flags, n_flags, make_job(states));
+                     list_job(region_kv, n_work, kBwdBN, kBwdBM, cap_kv), list_job(region_q, n_work, dq_tile, kDqBN, cap_q),
+                     list_args(kv_row_bytes, work, n_work, cu_seqlens_kv, n_seqs, tq, tkv, 1, false),
+                     MaskTables{q_limit, k_from}, lse, delta, n_stats, stats, (int)stat_blocks, chain, flags, n_flags, sp, make_job(states));
   FCP_HIP_CHECK(hipGetLastError());
   return FCP_OK;
 }
@@ -889,8 +1037,8 @@ extern "C" size_t fcp_scratch_bytes(int which, int32_t tq, int32_t tkv, int32_t 
   if (tq < 0 || tkv < 0 || n_work < 0 || n_parts < 0) return 0;
   if (which == FCP_SCRATCH_BWD)   // key-tile list (dK/dV kernel), query-tile list (dQ kernel), packed row statistics,
                                   // row states
-    return fcp::sched_region_bytes(n_work, fcp::kv_tile_cap(tkv, n_work)) +
-           fcp::sched_region_bytes(n_work, fcp::q_tile_cap(tq, tkv, n_work, 1 << 20)) +
+    return fcp::sched_region_bytes(n_work, fcp::bwd_kv_cap(tkv, n_work)) +
+           fcp::sched_region_bytes(n_work, fcp::bwd_q_cap(tq, tkv, n_work)) +
            fcp::pad_to((size_t)hq * (size_t)tq * 8, 256) +
            fcp::pad_to((size_t)tq, 256) + fcp::pad_to((size_t)tkv, 256) +  // + row states of the direct mode
            fcp::chain_bytes(tq, tkv, hq, head_dim, n_work);                // + chains of the one-pass kernel
