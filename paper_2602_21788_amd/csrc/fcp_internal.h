@@ -176,17 +176,17 @@ inline uint8_t* bwd_kv_state(void* scratch, int64_t n_work, int32_t tq, int32_t 
 constexpr int kChainWords = 4;            // rank (-1: atomics), first block of the next tile, the chain's first flag block, first block
 constexpr int kChainSlices = 8;
 inline int64_t chain_flag_words(int32_t tq, int32_t hq, int64_t n_work) { return ((int64_t)tq / 32 + 1 + n_work) * hq * kChainSlices; }
+// (a record for every tile that the key-tile list has room for)
+inline size_t chain_table_bytes(int32_t tkv, int64_t n_work) { return pad_to((size_t)bwd_kv_cap(tkv, n_work) * kChainWords * sizeof(int32_t), 256); }
 inline size_t chain_bytes(int32_t tq, int32_t tkv, int32_t hq, int32_t head_dim, int64_t n_work) {
   if (head_dim != 128) return 0;
-  return pad_to((size_t)kv_tile_cap(tkv, n_work) * kChainWords * sizeof(int32_t), 256) +
-         pad_to((size_t)chain_flag_words(tq, hq, n_work) * sizeof(int32_t), 256);
+  return chain_table_bytes(tkv, n_work) + pad_to((size_t)chain_flag_words(tq, hq, n_work) * sizeof(int32_t), 256);
 }
 inline int32_t* bwd_chain(void* scratch, int64_t n_work, int32_t tq, int32_t tkv, int32_t hq) {
   return reinterpret_cast<int32_t*>(bwd_kv_state(scratch, n_work, tq, tkv, hq) + pad_to((size_t)tkv, 256));
 }
 inline int32_t* bwd_chain_flags(void* scratch, int64_t n_work, int32_t tq, int32_t tkv, int32_t hq) {
-  return reinterpret_cast<int32_t*>(reinterpret_cast<char*>(bwd_chain(scratch, n_work, tq, tkv, hq)) +
-                                    pad_to((size_t)kv_tile_cap(tkv, n_work) * kChainWords * sizeof(int32_t), 256));
+  return reinterpret_cast<int32_t*>(reinterpret_cast<char*>(bwd_chain(scratch, n_work, tq, tkv, hq)) + chain_table_bytes(tkv, n_work));
 }
 
 // The forward's row states follow its tile list in its scratch buffer.

@@ -583,7 +583,8 @@ __device__ void build_list(
     next = nqb;
     rank = -1;
     flag0 = 0;
-    if (!(s_fl[at] & kFlagQExclusive)) return;
+    // (a list that is cut lacks tiles that others would wait for: all of it adds with atomics)
+    if (!(s_fl[at] & kFlagQExclusive) || total_tiles > tile_cap) return;
     flag0 = s_item[at][12];
     const int32_t nt0 = ceil_div(it.vis0, tile);
     const int32_t my_seg = t - s_off[at] >= nt0 ? 1 : 0;
