@@ -402,12 +402,12 @@ __device__ void build_list(
   bool cut = false;                                // tiles are split (the same for every thread)
   Item mine{-1, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0};
   if (tid == 0) { s_max = 0; s_rej = 0; }
+  if (staged && tid < n_work) {
+    mine = load_item(args, m, tid);
+    put_item(s_item[tid], mine);
+  }
+  __syncthreads();                                 // (for every list: the other waves add to s_max and s_rej below)
   if (staged) {
-    if (tid < n_work) {
-      mine = load_item(args, m, tid);
-      put_item(s_item[tid], mine);
-    }
-    __syncthreads();
     exclusive_flags_all(s_item, n_work, area->key, area->wmax, s_fl);
     if constexpr (Mode == kSplit) {
       split = split_sizes(sargs, m, mine, n_work);

@@ -117,3 +117,36 @@ def test_tensors_as_views_inside_larger_buffers_are_not_overrun(family):
             tail = bigs[name][getattr(ra, name).shape[0]:]
             assert bool((tail == sentinel).all()), (family, rank, name, "rows after the tensor were written")
         assert bool((bigs["o_part"][ra.o_part.numel():] == sentinel).all()), (family, rank, "o_part overrun")
+
+
+def test_rejected_items_of_a_list_of_more_than_1024_items_are_all_counted():
+    """3000 items, every seventh with a descriptor that the scheduler refuses, so that every wave of its block counts some of them: the
+    forward's and the backward's count is exact, call after call."""
+    import torch
+    import paper_2602_21788_amd.binding as B
+    n, hq, hkv, D = 3000, 2, 1, 64
+    dev = "cuda:0"
+    cu = np.arange(0, 8 * n + 1, 8).astype(np.int32)      # 3000 sequences of eight tokens
+    T = 8 * n
+    work = np.zeros(n, B.WORK_DTYPE)
+    work["seq"], work["q_local_off"], work["q_len"], work["n_seg"] = np.arange(n), cu[:-1], 8, 1
+    work["k_len"][:, 0] = 8
+    bad = np.arange(3, n, 7)
+    work["q_len"][bad[::3]] = 0
+    work["k_len"][bad[1::3], 0] = 9                       # past the sequence's end
+    work["seq"][bad[2::3]] = n
+    work_d = torch.from_numpy(work.view(np.uint8).copy()).to(dev)
+    cu_d = torch.from_numpy(cu).to(dev)
+    q, do = (torch.randn(T, hq, D, device=dev).to(torch.bfloat16) for _ in range(2))
+    k, v = (torch.randn(T, hkv, D, device=dev).to(torch.bfloat16) for _ in range(2))
+    o_part, lse_part = torch.empty(1, T, hq, D, device=dev), torch.empty(1, hq, T, device=dev)
+    lse, delta = (torch.zeros(hq, T, device=dev) for _ in range(2))
+    acc = [torch.zeros(T, h, D, device=dev) for h in (hq, hkv, hkv)]
+    scratch = [torch.empty(B.fcp_scratch_bytes(w, T, T, hq, hkv, D, n, 1), dtype=torch.uint8, device=dev)
+               for w in (B.FCP_SCRATCH_FWD, B.FCP_SCRATCH_BWD)]
+    _say(f"long work list: {len(bad)} of {n} items refused")
+    for _ in range(20):
+        B.fcp_attn_fwd_step(q, k, v, cu_d, work_d, 1, D ** -0.5, o_part, lse_part, scratch[0])
+        B.fcp_attn_bwd_step(q, k, v, do, lse, delta, cu_d, work_d, D ** -0.5, *acc, scratch[1])
+        for s in scratch:
+            assert B.fcp_scratch_status(s) == (n - len(bad), len(bad))
