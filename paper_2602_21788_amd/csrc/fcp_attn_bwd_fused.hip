@@ -288,22 +288,17 @@ __global__ __launch_bounds__(768, 1) void bwd_fused_kernel(const BwdParams p0) {
         if (act) {
 #pragma unroll
           for (int q = 0; q < 4; ++q) nl[q] = *reinterpret_cast<const f32x4*>(stat + 8 * q);
-          // P = exp2(c S - LSE log2 e).  Rows past the item's last need no mask: their dO and statistics arrive as zeros, so P = 1 meets
-          // zeros in dV and dS.  That leaves the causal edge and the keys past the tile's last.
-          if (j < j_unmasked) {
-            const int q_pos0 = u.t.q_seq_start + (u.qb0 + j) * C::BM;
-            int lo = my_key_from - q_pos0;          // register i is masked below it (a key past the tile's last: always)
-            asm volatile("; masked variant" : "+v"(lo));
-#pragma unroll
-            for (int i = 0; i < 16; ++i) if (8 * (i / 4) + (i % 4) < lo) sacc[i] = -INFINITY;
-          }
         }
-        auto p_pair = [&](int x) {
+        // The masked variants: the causal edge and the keys past the tile's last (always masked).  Rows past the item's last need no mask:
+        // their dO and statistics arrive as zeros, so P = 1 meets zeros in dV and dS.  A masked pair is selected away, not multiplied by zero:
+        // a row must not see what a key after it holds, an infinity or a NaN included.
+        const bool masked = act && j < j_unmasked;
+        auto clear_masked = [&](f32x16& x) {
+          const int q_pos0 = u.t.q_seq_start + (u.qb0 + j) * C::BM;
+          int lo = my_key_from - q_pos0;            // register i is masked below it
+          asm volatile("; masked variant" : "+v"(lo));
 #pragma unroll
-          for (int i = 2 * x; i < 2 * x + 2; ++i) {
-            pr[i] = __builtin_amdgcn_exp2f(fmaf(sacc[i], p.scale_log2, nl[i / 4][i % 4]));
-            pb[i / 8][i % 8] = (__bf16)pr[i];
-          }
+          for (int i = 0; i < 16; ++i) x[i] = 8 * (i / 4) + (i % 4) < lo ? 0.f : x[i];
         };
         auto ds_pair = [&](int x) {
 #pragma unroll
@@ -314,7 +309,10 @@ __global__ __launch_bounds__(768, 1) void bwd_fused_kernel(const BwdParams p0) {
 #pragma unroll
           for (int x = 0; x < A; ++x) fr[x] = rows(at, x);
 #pragma unroll
-          for (int x = 0; x < C::NS; ++x) p_pair(x);
+          for (int i = 0; i < 16; ++i) pr[i] = __builtin_amdgcn_exp2f(fmaf(sacc[i], p.scale_log2, nl[i / 4][i % 4]));
+          if (masked) clear_masked(pr);
+#pragma unroll
+          for (int i = 0; i < 16; ++i) pb[i / 8][i % 8] = (__bf16)pr[i];
 #pragma unroll
           for (int q = 0; q < 2; ++q) *reinterpret_cast<bf16x8*>(smem + fresh(lane) * 16 + (x_p + (it & 1) * C::PB) + q * 1024) = pb[q];
 #pragma unroll
@@ -342,10 +340,15 @@ __global__ __launch_bounds__(768, 1) void bwd_fused_kernel(const BwdParams p0) {
           for (int x = 0; x < C::NS; ++x) {
             sacc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fr[x], kf[x], x == 0 ? zero16() : sacc, 0, 0, 0);
             if (x + A < C::NS) fr[x + A] = rows(at1, x + A);
-            ds_pair(x);
+            // (dP has arrived by now; right after its own instructions the selection costs 3 % on 1000 sequences of 128 tokens)
+            if (x == 1 && masked) clear_masked(dp);
+            if (x == 2) ds_pair(0);
+            if (x >= 2) ds_pair(x - 1);
+            if (x == 7) ds_pair(7);
             __builtin_amdgcn_sched_barrier(0);
           }
         } else if (act) {
+          if (masked) clear_masked(dp);
 #pragma unroll
           for (int x = 0; x < C::NS; ++x) ds_pair(x);
         }
@@ -494,15 +497,21 @@ __global__ __launch_bounds__(768, 1) void bwd_fused_kernel(const BwdParams p0) {
         // ---- dQ of step it - 1
         f32x4 dq[2];
         if (live1) {
-          if (j1 < j_all) {                         // rare, as above
+          if (j1 < j_all) {                         // rare: a group that the block does not see is left out (its keys may hold anything)
+            dq[0] = dq[1] = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-            for (int x = 0; x < 4; ++x) if (j1 < j_actg[x]) ds[x] = bf16x8{0, 0, 0, 0, 0, 0, 0, 0};
+            for (int x = 0; x < 4; ++x)
+              if (j1 >= j_actg[x]) {
+#pragma unroll
+                for (int c = 0; c < 2; ++c) dq[c] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kt[x][c], ds[x], dq[c], 0, 0, 0);
+              }
+          } else {
+#pragma unroll
+            for (int x = 0; x < 4; ++x)
+#pragma unroll
+              for (int c = 0; c < 2; ++c)
+                dq[c] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kt[x][c], ds[x], x == 0 ? f32x4{0.f, 0.f, 0.f, 0.f} : dq[c], 0, 0, 0);
           }
-#pragma unroll
-          for (int x = 0; x < 4; ++x)
-#pragma unroll
-            for (int c = 0; c < 2; ++c)
-              dq[c] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kt[x][c], ds[x], x == 0 ? f32x4{0.f, 0.f, 0.f, 0.f} : dq[c], 0, 0, 0);
         }
         __builtin_amdgcn_sched_barrier(0);
         // operands of step it - 1: its P and dS are visible since this iteration's barrier

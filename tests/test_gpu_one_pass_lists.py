@@ -20,3 +20,36 @@ def test_rows_of_one_sequence_in_many_items(family):
     got, scratch = listed.run_backward(B, family, lens, listed.work_list(B, lens, items), q, k, v, do, lse, delta, D ** -0.5)
     assert B.fcp_scratch_status(scratch) == (528, 0)
     listed.check(got, ref, TOL_BF16_REL, family)
+
+
+@pytest.mark.parametrize("what", ["k", "v", "q"])
+@pytest.mark.parametrize("bad", [float("nan"), float("inf")])
+def test_rows_do_not_see_what_later_keys_hold(what, bad):
+    """A key row or value row that is not finite reaches only the dQ rows that see it (a key row also those of the same 32-row block, through
+    the zeros that it is multiplied with), and a query row whose scores are not finite leaves the dV of later keys alone."""
+    import torch
+    import paper_2602_21788_amd.binding as B
+    lens, hq, hkv, D = [300, 77, 160], 8, 8, 128
+    items = [(s, 0, n, [(0, n)]) for s, n in enumerate(lens)]
+    cu = listed.offsets(lens)
+    q, k, v, do = listed.draw(lens, hq, hkv, D, 12)
+    lse, delta, ref = listed.reference(lens, items, q, k, v, do, D ** -0.5)
+    at = {0: 150, 1: 70, 2: 127}                          # the bad row of each sequence
+    for s, j in at.items():
+        {"k": k, "v": v, "q": q}[what][cu[s] + j] = bad
+        if what == "q":
+            lse[:, cu[s] + j] = float("nan")
+    print(f"one-pass backward with {bad} in {what}", flush=True)
+    for family in ("plain", "direct"):
+        got, _ = listed.run_backward(B, family, lens, listed.work_list(B, lens, items), q, k, v, do, lse, delta, D ** -0.5)
+        dq, _, dv = (x.float().cpu() for x in got)
+        for s, n in enumerate(lens):
+            j = at[s]
+            if what == "q":
+                a, b = dv[cu[s] + j + 1:cu[s] + n], ref[2][cu[s] + j + 1:cu[s] + n]
+            else:
+                last = j if what == "v" else j // 32 * 32
+                a, b = dq[cu[s]:cu[s] + last], ref[0][cu[s]:cu[s] + last]
+                assert not torch.isfinite(dq[cu[s] + j:cu[s] + n]).all()     # (those that see it do)
+            assert torch.isfinite(a).all(), (family, s)
+            assert float((a - b).abs().max() / b.abs().max()) <= TOL_BF16_REL, (family, s)
