@@ -40,11 +40,14 @@ struct SchedHeader {
   int32_t n_tiles;              // tiles in the list (sorted by decreasing cost)
   int32_t n_rejected;           // work items that failed validation
   int32_t max_cost;
-  int32_t pad0;
+  int32_t path;                 // backward, key-tile list: how the call is worked (kPath* bits), for tests and profiles
   int32_t counter[kNumXcd];     // next unit per XCD (or counter[0] alone)
   int32_t pad1[4];
 };                               // 64 bytes
 static_assert(sizeof(SchedHeader) == 64, "header size");
+constexpr int32_t kPathOnePass = 1;     // one pass over key tiles (csrc/fcp_attn_bwd_fused.hip)
+constexpr int32_t kPathSplitKeys = 2;   // key tiles in pieces of rows
+constexpr int32_t kPathSplitRows = 4;   // query tiles in pieces of keys
 
 // One schedulable tile, fully resolved by the scheduler so that an attention kernel needs a
 // single 64-byte read per unit (no dependent loads of work item and cu_seqlens).

@@ -400,6 +400,7 @@ __device__ void build_list(
   const bool staged = n_work <= kMaxExclusiveScan;
   SplitSizes split{};
   bool cut = false;                                // tiles are split (the same for every thread)
+  int32_t path = Mode == kChained ? kPathOnePass : 0;
   Item mine{-1, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0};
   if (tid == 0) { s_max = 0; s_rej = 0; }
   if (staged && tid < n_work) {
@@ -412,6 +413,7 @@ __device__ void build_list(
     if constexpr (Mode == kSplit) {
       split = split_sizes(sargs, m, mine, n_work);
       cut = (backward ? split.rows : split.keys) < 32 * kNoPieces;
+      path = (split.rows < 32 * kNoPieces ? kPathSplitKeys : 0) | (split.keys < 32 * kNoPieces ? kPathSplitRows : 0);
     }
   }
   auto fetch = [&](int32_t i) { return staged ? get_item(s_item[i]) : load_item(args, m, i); };
@@ -689,7 +691,7 @@ __device__ void build_list(
     hdr->n_tiles = n_listed;
     hdr->n_rejected = s_rej;
     hdr->max_cost = s_max;
-    hdr->pad0 = 0;
+    hdr->path = path;
     for (int c = 0; c < 4; ++c) hdr->pad1[c] = 0;
     for (int c = 0; c < kNumXcd; ++c) hdr->counter[c] = 0;
   }

@@ -104,6 +104,14 @@ def run_backward(B, family, lens, work, q, k, v, do, lse, delta, scale, spans=No
     return got, scratch
 
 
+ONE_PASS, SPLIT_KEYS, SPLIT_ROWS = 1, 2, 4
+
+
+def backward_path(scratch):
+    """How the last backward on `scratch` was worked: the path word of its key-tile list's header."""
+    return int(scratch[:16].cpu().view(torch.int32)[3])
+
+
 def check(got, ref, tol, label=""):
     for name, a, b in zip(("dQ", "dK", "dV"), got, ref):
         a = a.float().cpu()

@@ -7,6 +7,7 @@ bf16 tensors O, dQ, dK, dV; max|LSE_gpu - LSE_ref| <= 1e-3 (absolute) for fp32 L
 import numpy as np
 
 import fcp_synth as synth
+from listed import backward_path
 from oracle import attn as oattn
 from oracle import plan as oplan
 
@@ -95,6 +96,7 @@ def check_rank(wl, q, k, v, do, rank, backward=True, check_partials=False, label
             assert np.isfinite(got[name]).all(), (label, name)
             res[name] = rel_err(got[name], ref)
             assert res[name] <= TOL_BF16_REL, (label, name, res)
+        res["_path"] = backward_path(ra.scratch_b)
         res["_dK_acc"] = ra.dk_acc.cpu().numpy().astype(np.float64)
         res["_dV_acc"] = ra.dv_acc.cpu().numpy().astype(np.float64)
         # The direct backward (rows owned by one unit written as bf16 by their kernel) on poisoned buffers: it must

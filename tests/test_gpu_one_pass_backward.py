@@ -5,6 +5,7 @@ item does not own its rows, add with atomics."""
 import numpy as np
 import pytest
 
+from listed import ONE_PASS, backward_path
 from parity import TOL_BF16_REL
 
 pytestmark = pytest.mark.gpu
@@ -96,7 +97,7 @@ def test_one_pass_backward(family, hq, hkv, kind):
         B.fcp_attn_bwd_step_direct(*t, lse, delta, cu_d, work_d, scale, *acc, *got, scratch)
         B.fcp_grad_finalize_direct(*acc, *got, scratch, len(work))
     torch.cuda.synchronize()
-    assert B.fcp_scratch_status(scratch)[1] == 0
+    assert B.fcp_scratch_status(scratch)[1] == 0 and backward_path(scratch) == ONE_PASS
     for name, a, b in zip(("dQ", "dK", "dV"), got, ref):
         a = a.float().cpu()
         assert torch.isfinite(a).all(), name

@@ -18,7 +18,7 @@ def test_rows_of_one_sequence_in_many_items(family):
     lse, delta, ref = listed.reference(lens, items, q, k, v, do, D ** -0.5)
     print(f"rows of one sequence in {len(items)} items, {family}", flush=True)
     got, scratch = listed.run_backward(B, family, lens, listed.work_list(B, lens, items), q, k, v, do, lse, delta, D ** -0.5)
-    assert B.fcp_scratch_status(scratch) == (528, 0)
+    assert B.fcp_scratch_status(scratch) == (528, 0) and listed.backward_path(scratch) == listed.ONE_PASS
     listed.check(got, ref, TOL_BF16_REL, family)
 
 
@@ -41,7 +41,8 @@ def test_rows_do_not_see_what_later_keys_hold(what, bad):
             lse[:, cu[s] + j] = float("nan")
     print(f"one-pass backward with {bad} in {what}", flush=True)
     for family in ("plain", "direct"):
-        got, _ = listed.run_backward(B, family, lens, listed.work_list(B, lens, items), q, k, v, do, lse, delta, D ** -0.5)
+        got, scratch = listed.run_backward(B, family, lens, listed.work_list(B, lens, items), q, k, v, do, lse, delta, D ** -0.5)
+        assert listed.backward_path(scratch) == listed.ONE_PASS
         dq, _, dv = (x.float().cpu() for x in got)
         for s, n in enumerate(lens):
             j = at[s]
