@@ -48,6 +48,7 @@ extern "C" {
 #define FCP_ERR_CAPACITY (-2)
 #define FCP_ERR_UNSUPPORTED (-3)
 #define FCP_ERR_HIP (-4)
+#define FCP_ERR_STALLED (-5)   /* fcp_scratch_status only */
 
 /* One per (sequence, zigzag chunk), sorted by (rank, seq, chunk).  24 bytes. */
 typedef struct fcp_chunk_desc {
@@ -377,6 +378,10 @@ int fcp_group_shard_args(const int32_t* group_of_seq, int32_t n_seqs, const int3
  * Reads back what the last fwd/bwd step that used `scratch` recorded: the number of
  * scheduled tiles and the number of rejected work items.  Synchronises `stream`.
  * Either output pointer (host) may be NULL.
+ * Units of a backward that add to the same rows in a fixed order wait for each other.  The waits are bounded (about half a
+ * second of polling): should one run out, the units end, every dQ, dK or dV row whose sum lacks a contribution holds NaN, and
+ * this call returns FCP_ERR_STALLED (the counts are still written).  In a list in the order that the scheduler
+ * writes, a unit only waits for units that were begun earlier.
  */
 int fcp_scratch_status(const void* scratch, void* stream, int32_t* n_tiles, int32_t* n_rejected);
 

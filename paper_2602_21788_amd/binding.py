@@ -15,7 +15,7 @@ import numpy as np
 _PKG = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.path.join(_PKG, "libfcp.so")
 
-FCP_OK, FCP_ERR_INVALID_ARG, FCP_ERR_CAPACITY, FCP_ERR_UNSUPPORTED, FCP_ERR_HIP = 0, -1, -2, -3, -4
+FCP_OK, FCP_ERR_INVALID_ARG, FCP_ERR_CAPACITY, FCP_ERR_UNSUPPORTED, FCP_ERR_HIP, FCP_ERR_STALLED = 0, -1, -2, -3, -4, -5
 FCP_SCRATCH_FWD, FCP_SCRATCH_BWD = 0, 1
 
 CHUNK_DTYPE = np.dtype([("seq", "<i4"), ("rank", "<i4"), ("chunk", "<i4"),
@@ -382,7 +382,8 @@ def fcp_grad_finalize(acc, out_bf16, stream=None):
 
 
 def fcp_scratch_status(scratch, stream=None):
-    """(n_tiles, n_rejected) recorded by the last step that used `scratch`; synchronises."""
+    """(n_tiles, n_rejected) recorded by the last step that used `scratch`; synchronises.  Raises FcpError
+    (FCP_ERR_STALLED) if units of a backward waited for each other in vain."""
     a, b = ctypes.c_int32(0), ctypes.c_int32(0)
     _check(lib().fcp_scratch_status(_dev_ptr(scratch), _stream(stream), ctypes.byref(a), ctypes.byref(b)))
     return a.value, b.value

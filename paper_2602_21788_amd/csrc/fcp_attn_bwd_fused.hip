@@ -95,7 +95,8 @@ __device__ inline BwdParams args_again() {
   return __builtin_bit_cast(BwdParams, r);
 }
 constexpr int kClaimed = 1 << 30;      // counter of a claimed queue: past every unit
-constexpr int kSpinLimit = 1 << 18;    // polls of a wave per unit, about half a second: a chain that cannot go on ends, and is reported
+constexpr int kSpinLimit = 1 << 18;    // polls of a wave per unit, about half a second: a chain that cannot go on ends, its rows become NaN and the
+                                       // header says so
 
 // A unit as every role sees it.
 struct FusedUnit {
@@ -546,18 +547,19 @@ __global__ __launch_bounds__(768, 1) void bwd_fused_kernel(const BwdParams p0) {
           const int l = fresh(lane);
           const int at = old_buf + ((it - 1) & 1) * 2048 + (l & 15) * 128 + (((l >> 4) ^ ((l >> 1) & 7)) << 4);   // chunk 4 c + b at ^ (c << 6)
           const int dq_voff = (l & 15) * dq_row_bytes + 16 * (l >> 4);
+          const float dq_mul = spin_left > 0 ? p.scale : NAN;          // (see kSpinLimit)
           if (loads) {
 #pragma unroll
             for (int c = 0; c < 2; ++c) {
               const f32x4 v = *reinterpret_cast<const f32x4*>(smem + (at ^ (c << 6)));
 #pragma unroll
-              for (int e = 0; e < 4; ++e) dq[c][e] = fmaf(dq[c][e], p.scale, v[e]);
+              for (int e = 0; e < 4; ++e) dq[c][e] = fmaf(dq[c][e], dq_mul, v[e]);
             }
           } else {
 #pragma unroll
             for (int c = 0; c < 2; ++c)
 #pragma unroll
-              for (int e = 0; e < 4; ++e) dq[c][e] *= p.scale;
+              for (int e = 0; e < 4; ++e) dq[c][e] *= dq_mul;
           }
           if (is_last(j1)) {
             const __amdgpu_buffer_rsrc_t rb = __builtin_amdgcn_make_buffer_rsrc((void*)(p.dq_out + dq0), (short)0, (uint32_t)dq_bytes / 2, 0x00020000);
@@ -595,7 +597,7 @@ __global__ __launch_bounds__(768, 1) void bwd_fused_kernel(const BwdParams p0) {
           fo0 -= fblk;
         }
       }
-      if (spin_left <= 0 && lane == 0) atomicAdd(&p.hdr->n_rejected, 1);
+      if (spin_left <= 0 && lane == 0) atomicAdd(&p.hdr->n_stalled, 1);
       // ---- epilogue
       int row_bytes = p.hkv * D * (direct ? 2 : 4);
       asm volatile("" : "+s"(row_bytes));

@@ -42,7 +42,8 @@ struct SchedHeader {
   int32_t max_cost;
   int32_t path;                 // backward, key-tile list: how the call is worked (kPath* bits), for tests and profiles
   int32_t counter[kNumXcd];     // next unit per XCD (or counter[0] alone)
-  int32_t pad1[4];
+  int32_t n_stalled;            // backward, key-tile list: waits for another unit's turn that ran out (their rows are NaN)
+  int32_t pad[3];
 };                               // 64 bytes
 static_assert(sizeof(SchedHeader) == 64, "header size");
 constexpr int32_t kPathOnePass = 1;     // one pass over key tiles (csrc/fcp_attn_bwd_fused.hip)

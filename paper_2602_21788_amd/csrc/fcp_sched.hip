@@ -692,7 +692,8 @@ __device__ void build_list(
     hdr->n_rejected = s_rej;
     hdr->max_cost = s_max;
     hdr->path = path;
-    for (int c = 0; c < 4; ++c) hdr->pad1[c] = 0;
+    hdr->n_stalled = 0;
+    for (int c = 0; c < 3; ++c) hdr->pad[c] = 0;
     for (int c = 0; c < kNumXcd; ++c) hdr->counter[c] = 0;
   }
 }
@@ -1057,5 +1058,7 @@ extern "C" int fcp_scratch_status(const void* scratch, void* stream, int32_t* n_
   FCP_HIP_CHECK(hipStreamSynchronize((hipStream_t)stream));
   if (n_tiles) *n_tiles = h.n_tiles;
   if (n_rejected) *n_rejected = h.n_rejected;
+  if (h.n_stalled != 0)
+    return fcp::fail(FCP_ERR_STALLED, "fcp_scratch_status: %d waits for another unit's turn ran out; the rows concerned are NaN", (int)h.n_stalled);
   return FCP_OK;
 }

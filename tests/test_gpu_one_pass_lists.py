@@ -54,3 +54,20 @@ def test_rows_do_not_see_what_later_keys_hold(what, bad):
                 assert not torch.isfinite(dq[cu[s] + j:cu[s] + n]).all()     # (those that see it do)
             assert torch.isfinite(a).all(), (family, s)
             assert float((a - b).abs().max() / b.abs().max()) <= TOL_BF16_REL, (family, s)
+
+
+def test_status_reports_waits_that_ran_out():
+    """A wait for another unit's turn that ran out is not a rejected work item: the status call has an error of its own for it (the header
+    word that the kernels count them in is set here by hand)."""
+    import torch
+    import paper_2602_21788_amd.binding as B
+    lens, hq, hkv, D = [300, 200], 8, 8, 128
+    items = [(s, 0, n, [(0, n)]) for s, n in enumerate(lens)]
+    q, k, v, do = listed.draw(lens, hq, hkv, D, 13)
+    lse, delta, _ = listed.reference(lens, items, q, k, v, do, D ** -0.5)
+    _, scratch = listed.run_backward(B, "plain", lens, listed.work_list(B, lens, items), q, k, v, do, lse, delta, D ** -0.5)
+    assert B.fcp_scratch_status(scratch) == (5, 0)
+    scratch[:64].view(torch.int32)[12] = 3
+    with pytest.raises(B.FcpError) as e:
+        B.fcp_scratch_status(scratch)
+    assert e.value.code == B.FCP_ERR_STALLED and "3 waits" in str(e.value)
