@@ -188,9 +188,10 @@ int fcp_attn_bwd_delta(const void* o, const void* d_o, int32_t tq, int32_t hq, i
  *   dV += P^T dO,  dP = dO V^T,  dS = P o (dP - delta),  dQ += scale dS K,  dK += scale dS^T Q,
  * dK/dV summed over the hq/hkv query heads of a KV head.  The three fp32 accumulators are
  * ADDED to (caller zeroes them before the first step): dq_acc [tq,hq,D], dk_acc, dv_acc
- * [tkv,hkv,D].  Rows (keys) that only one work item of the call touches are read, added to and
- * written back with plain loads and stores; the others use fp32 atomics, so their summation
- * order varies run to run.  While the call runs nobody else may write the accumulators.
+ * [tkv,hkv,D].  Rows (keys) that only one work item of the call touches are summed in a fixed order, so
+ * that their results repeat bit for bit: with plain loads and stores, or, where the work on them is cut into
+ * pieces, with fp32 atomics of one piece after the other.  The others use fp32 atomics in any order, which
+ * varies run to run.  While the call runs nobody else may read or write the accumulators.
  * Limits: tq*hq*head_dim below 2^30 - 2^21 elements (the bf16 rows of a work item are addressed with 32-bit byte
  * offsets), n_work <= 2^24 items (FCP_ERR_UNSUPPORTED).
  * Other arguments as in fcp_attn_fwd_step; scratch sized with FCP_SCRATCH_BWD.

@@ -34,7 +34,7 @@
 // on a 16384-token sequence, 4 % on the packed workload.)
 // The result is added to the caller's fp32 accumulator once per unit: with plain
 // load-add-store when the scheduler found that no other item of the launch touches the same rows (always the
-// case for degree-1 sequences), otherwise with fp32 atomics.
+// case for degree-1 sequences), otherwise with fp32 atomics; the pieces of a split tile in turn.
 #include "fcp_bwd.h"
 
 #include <algorithm>
@@ -380,14 +380,22 @@ __global__ __launch_bounds__(512, 1) void dq_kernel(const BwdParams p, const int
                                                 (8 * (i / 4) + (i % 4)) * out_row_bytes + 64 * db, 0);
         }
     } else {
+      const bool in_turn = (t.flags & kFlagInTurn) != 0;
+      int32_t* const turn = p.turns + ((int64_t)t.turn * (p.hq / hpu) + head / hpu) * kTurnWaves + wave;
+      float mul_e = p.scale;
+      if (in_turn && !wait_turn(turn, t.flags >> kPieceShift)) {
+        mul_e = NAN;
+        if (lane_e == 0) atomicAdd(p.n_stalled, 1);
+      }
 #pragma unroll
       for (int db = 0; db < C::NCB; ++db)
 #pragma unroll
         for (int i = 0; i < 16; ++i) {
-          const float val = acc[db][i] * p.scale;
+          const float val = acc[db][i] * mul_e;
           if (exclusive) __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(unsigned, val), racc, acc_voff, acc_soff(db, i), 0);
           else __builtin_amdgcn_raw_ptr_buffer_atomic_fadd_f32(val, racc, acc_voff, acc_soff(db, i), 0);
         }
+      if (in_turn) pass_turn(turn);
     }
     uq.advance(&s_next_unit, s_rec);   // barrier: the LDS stages are free for the next unit's fills
   }
@@ -483,20 +491,22 @@ static int bwd_step(const void* q, const void* k, const void* v, const void* d_o
   const int head_pair = ((hq / hkv) % 2 == 0) ? 1 : 0;
   // Split tiles (see csrc/fcp_sched.hip): worth the scheduler's time where there are a few tiles per CU at most and a serial loop can be
   // long, in 32-row blocks of all heads of a KV head or in 32-key blocks.  In sharded lists a tile's loop is the shorter for
-  // the sharding, and its accumulators are mostly shared already.  Measured, backward: one sequence of 4096 tokens, 8 query heads on one KV
-  // head, 128 channels 969 -> 273 us; 6 on 2, 64 channels 447 -> 166 us; 30 sequences of 20011 tokens in all, 6 on 2, 414 -> 289 us; 4096 tokens
-  // over 3 ranks, 4 on 4, 92 -> 72 us; 32 on 8 1.02 to 1.15 times as fast.
-  const fcp::SplitTiles sp{group, hkv, hq / (head_pair ? 2 : 1), 256, 12};        // (256 CUs; 12 steps at least)
+  // the sharding, and its accumulators are mostly shared already.  Measured, scheduling and attention launches: one sequence of 4096 tokens, 8 query
+  // heads on one KV head, 128 channels 950 -> 312 us; 6 on 2, 64 channels 395 -> 177 us; 30 sequences of 20011 tokens in all, 6 on 2, 505 -> 343 us
+  // whole and 305 -> 246 us with the longest one over 3 ranks; 4096 tokens over 3 ranks, 4 on 4, 107 -> 84 us; 4096 tokens, 32 on 8, 628 -> 580 us.
+  const fcp::SplitTiles sp{group, hkv, hq / (head_pair ? 2 : 1), 256, 12,          // (256 CUs; 12 steps at least)
+                           (int32_t)fcp::key_turns(tkv, n_work), (int32_t)fcp::row_turns(tq, n_work)};
   const int64_t longest = std::max((int64_t)tq * group / fcp::kBwdBM, (int64_t)tkv / fcp::kDqBN);
   const bool split = !fused && key_units <= 1024 && n_work <= 1024 && longest >= (tq == tkv ? 24 : 64);
   int rc = fcp::launch_schedule_bwd((int64_t)hkv * head_dim * 2, q_limit, k_from, work, n_work, cu_seqlens_kv, n_seqs, tq, tkv,
                                     cap_kv, region_kv, head_pair ? fcp::kDqBM : 2 * fcp::kDqBM, cap_q, region_q, lse, delta, (int64_t)hq * tq, stats, st,
-                                    direct ? &rs : nullptr, fused ? fcp::bwd_chain(scratch, n_work, tq, tkv, hq) : nullptr,
-                                    fused ? fcp::bwd_chain_flags(scratch, n_work, tq, tkv, hq) : nullptr,
-                                    fused ? fcp::chain_flag_words(tq, hq, n_work) : 0, split ? &sp : nullptr);
+                                    direct ? &rs : nullptr, fused ? fcp::bwd_chain(scratch, n_work, tq, tkv, hq, hkv) : nullptr,
+                                    fused ? fcp::bwd_chain_flags(scratch, n_work, tq, tkv, hq, hkv) : split ? fcp::bwd_turns(scratch, n_work, tq, tkv, hq) : nullptr,
+                                    fused ? fcp::chain_flag_words(tq, hq, n_work) : split ? fcp::turn_words(tq, tkv, hq, hkv, n_work) : 0,
+                                    split ? &sp : nullptr);
   if (rc != FCP_OK) return rc;
 
-  fcp::BwdParams p;
+  fcp::BwdParams p{};
   p.q = (const uint16_t*)q; p.k = (const uint16_t*)k; p.v = (const uint16_t*)v; p.d_o = (const uint16_t*)d_o;
   p.lse = lse; p.delta = delta; p.stats = stats;
   p.q_limit = q_limit; p.k_from = k_from;
@@ -514,13 +524,15 @@ static int bwd_step(const void* q, const void* k, const void* v, const void* d_o
   };
 
   if (fused) {
-    p.chain = fcp::bwd_chain(scratch, n_work, tq, tkv, hq);
-    p.flags = fcp::bwd_chain_flags(scratch, n_work, tq, tkv, hq);
+    p.chain = fcp::bwd_chain(scratch, n_work, tq, tkv, hq, hkv);
+    p.flags = fcp::bwd_chain_flags(scratch, n_work, tq, tkv, hq, hkv);
     p.hdr = (fcp::SchedHeader*)region_kv;
     p.tiles = fcp::sched_tiles(region_kv, n_work);
     return fcp::launch_bwd_fused(p, cap_kv * hkv, n_cu, st);
   }
   // dK/dV over key tiles
+  p.turns = fcp::bwd_turns(scratch, n_work, tq, tkv, hq);
+  p.n_stalled = &((fcp::SchedHeader*)region_kv)->n_stalled;
   p.hdr = (fcp::SchedHeader*)region_kv;
   p.tiles = fcp::sched_tiles(region_kv, n_work);
   const double pieces = split ? (double)tq * tkv * hq / sp.min_steps : 0.;      // bounds of the units that splitting adds, times a step's pairs
@@ -528,6 +540,7 @@ static int bwd_step(const void* q, const void* k, const void* v, const void* d_o
   if ((rc = fcp::launch_dkv(p, head_dim, kv_units, n_cu, st)) != FCP_OK) return rc;
 
   // dQ over query tiles
+  p.turns += fcp::key_turns(tkv, n_work) * hkv * fcp::kTurnWaves;
   p.hdr = (fcp::SchedHeader*)region_q;
   p.tiles = fcp::sched_tiles(region_q, n_work);
   const int64_t dq_units = fcp::q_tile_cap(tq, tkv, n_work, 1 << 20) * (hq / (head_pair ? 2 : 1)) +

@@ -34,7 +34,7 @@
 //   * inside the matrix phases every LDS fragment is requested several MFMAs before its use;
 //   * the caller's fp32 accumulators: when the scheduler found that no other item of the launch touches the tile's
 //     keys, the waves' accumulators start from the caller's values and the epilogue stores whole 128-byte lines;
-//     otherwise they start at zero and the epilogue adds with fp32 atomics.
+//     otherwise they start at zero and the epilogue adds with fp32 atomics; the pieces of a split tile in turn.
 #include "fcp_bwd.h"
 
 namespace fcp {
@@ -108,7 +108,7 @@ __global__ __launch_bounds__(1024, 1) void dkv_kernel(const BwdParams p) {
   for (;;) {
     const int unit = uq.current(&s_next_unit);
     if (unit >= uq.n_units) break;
-    const KTile t = read_record<KTile, 15>(s_rec);
+    const KTile t = read_record<KTile, 16>(s_rec);
     const int kvh = xcd * kvh_here + unit % kvh_here;
     uq.prefetch();
 
@@ -447,16 +447,24 @@ __global__ __launch_bounds__(1024, 1) void dkv_kernel(const BwdParams p) {
                                                     (32 * kb + 8 * (i / 4) + (i % 4)) * out_row_bytes + 64 * db, 0);
             }
       } else {
+        const bool in_turn = (t.flags & kFlagInTurn) != 0;
+        int32_t* const turn = p.turns + ((int64_t)t.turn * p.hkv + kvh) * kTurnWaves + (role == 3 ? 4 : 0) + pw;
+        float mul_e = mul;
+        if (in_turn && !wait_turn(turn, t.flags >> kPieceShift)) {
+          mul_e = NAN;
+          if (lane == 0) atomicAdd(p.n_stalled, 1);
+        }
 #pragma unroll
         for (int kb = 0; kb < 2; ++kb)
 #pragma unroll
           for (int db = 0; db < C::NVA; ++db)
 #pragma unroll
             for (int i = 0; i < 16; ++i) {
-              const float val = acc[db][kb][i] * mul;
+              const float val = acc[db][kb][i] * mul_e;
               if (exclusive) __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(unsigned, val), racc, acc_voff, acc_soff(kb, db, i), 0);
               else __builtin_amdgcn_raw_ptr_buffer_atomic_fadd_f32(val, racc, acc_voff, acc_soff(kb, db, i), 0);
             }
+        if (in_turn) pass_turn(turn);
       }
     }
     uq.advance(&s_next_unit, s_rec);   // barrier: the LDS stages are free for the next unit's fills

@@ -61,7 +61,8 @@ struct QTile {                   // a block of query rows of one work item (forw
   int32_t k_pos0[2];             // its position in the sequence
   int32_t vis[2];                // keys of the segment that the block's last row sees (0 = none)
   int32_t flags;                 // kFlag* of the work item
-  int32_t pad[5];
+  int32_t turn;                  // kFlagInTurn: number of the tile's turn words
+  int32_t pad[4];
 };
 struct KTile {                   // a block of keys of one segment of one work item (dK/dV)
   int32_t kv_row0;               // pool row of the first key
@@ -73,7 +74,7 @@ struct KTile {                   // a block of keys of one segment of one work i
   // first query that sees its last key (of the tile's n_keys), both capped at the item's last row.  With the
   // causal mask these are the two keys' own positions; with full-attention spans the start of the key's span.
   int32_t from_first[4], from_last[4];
-  int32_t pad;
+  int32_t turn;                  // kFlagInTurn: number of the tile's turn words
 };
 static_assert(sizeof(QTile) == 64 && sizeof(KTile) == 64, "tile records are 16 words");
 struct Tile { int32_t w[16]; };  // storage type of the list
@@ -106,6 +107,8 @@ inline int64_t bwd_q_cap(int32_t tq, int32_t tkv, int64_t n_work) { return 2 * q
 constexpr int32_t kFlagQExclusive = 1;    // no other item of the launch covers these query rows
 constexpr int32_t kFlagSeg0Exclusive = 2; // no other item's key segment overlaps segment 0 / 1
 constexpr int32_t kFlagSeg1Exclusive = 4;
+constexpr int32_t kFlagInTurn = 8;        // tile records only: the unit is piece (flags >> kPieceShift) of a tile that the launch owns (split tiles)
+constexpr int kPieceShift = 8;
 inline size_t pad_to(size_t x, size_t a) { return (x + a - 1) / a * a; }
 inline size_t sched_item_off_bytes(int64_t n_work) { return pad_to((size_t)(n_work + 1) * sizeof(int32_t), 64); }
 inline size_t sched_region_bytes(int64_t n_work, int64_t cap) {
@@ -122,8 +125,8 @@ static_assert(kBwdBN == 4 * 32, "KTile keeps four key groups");
 
 struct RowStates;   // direct modes, see below
 // Splitting of the backward's tiles on small problems (csrc/fcp_sched.hip): query heads per KV head, units per key tile and per query tile, CUs, least
-// piece in 32-row blocks (of all heads together) and in 32-key blocks.
-struct SplitTiles { int32_t group, kv_units, q_units, n_cu, min_steps; };
+// piece in 32-row blocks (of all heads together) and in 32-key blocks; numbers that the turn words have room for.
+struct SplitTiles { int32_t group, kv_units, q_units, n_cu, min_steps, key_turns, row_turns; };
 
 // Builds one tile list in `region` (tiles of `tile` keys if `key_tiles`, else of `tile` query rows;
 // `inner` is the block size of the other dimension used for the cost; kv_row_bytes = hkv*D*2 bounds
@@ -175,6 +178,23 @@ inline uint8_t* bwd_kv_state(void* scratch, int64_t n_work, int32_t tq, int32_t 
   return bwd_q_state(scratch, n_work, tq, tkv, hq) + pad_to((size_t)tq, 256);
 }
 
+// Turn words of split tiles: kTurnWaves per (key tile, KV head), then as many per (query tile, head).  Only tiles whose rows one item owns have them: the
+// key segments of these do not overlap, nor do their query rows, so there are at most this many (a tile begins every kBwdBN keys or
+// kMinQTile rows and at every segment or item).
+constexpr int kTurnWaves = 8;                // waves of a unit that add
+constexpr int32_t kMaxFlaggedItems = 1024;   // longer lists have no exclusivity flags
+inline int64_t key_turns(int32_t tkv, int64_t n_work) { return tkv / kBwdBN + 2 * (n_work < kMaxFlaggedItems ? n_work : kMaxFlaggedItems); }
+inline int64_t row_turns(int32_t tq, int64_t n_work) { return tq / kMinQTile + (n_work < kMaxFlaggedItems ? n_work : kMaxFlaggedItems); }
+inline int64_t turn_words(int32_t tq, int32_t tkv, int32_t hq, int32_t hkv, int64_t n_work) {
+  return (key_turns(tkv, n_work) * hkv + row_turns(tq, n_work) * hq) * kTurnWaves;
+}
+inline size_t turn_bytes(int32_t tq, int32_t tkv, int32_t hq, int32_t hkv, int64_t n_work) {
+  return pad_to((size_t)turn_words(tq, tkv, hq, hkv, n_work) * sizeof(int32_t), 256);
+}
+inline int32_t* bwd_turns(void* scratch, int64_t n_work, int32_t tq, int32_t tkv, int32_t hq) {
+  return reinterpret_cast<int32_t*>(bwd_kv_state(scratch, n_work, tq, tkv, hq) + pad_to((size_t)tkv, 256));
+}
+
 // The one-pass backward (csrc/fcp_attn_bwd_fused.hip): per key tile its place in the chain of tiles that add to the same dQ rows, and
 // one flag word per (32-row block of a chain, head, half of the rows and 32-channel slice).
 constexpr int kChainWords = 4;            // rank (-1: atomics), first block of the next tile, the chain's first flag block, first block
@@ -186,11 +206,11 @@ inline size_t chain_bytes(int32_t tq, int32_t tkv, int32_t hq, int32_t head_dim,
   if (head_dim != 128) return 0;
   return chain_table_bytes(tkv, n_work) + pad_to((size_t)chain_flag_words(tq, hq, n_work) * sizeof(int32_t), 256);
 }
-inline int32_t* bwd_chain(void* scratch, int64_t n_work, int32_t tq, int32_t tkv, int32_t hq) {
-  return reinterpret_cast<int32_t*>(bwd_kv_state(scratch, n_work, tq, tkv, hq) + pad_to((size_t)tkv, 256));
+inline int32_t* bwd_chain(void* scratch, int64_t n_work, int32_t tq, int32_t tkv, int32_t hq, int32_t hkv) {
+  return reinterpret_cast<int32_t*>(reinterpret_cast<char*>(bwd_turns(scratch, n_work, tq, tkv, hq)) + turn_bytes(tq, tkv, hq, hkv, n_work));
 }
-inline int32_t* bwd_chain_flags(void* scratch, int64_t n_work, int32_t tq, int32_t tkv, int32_t hq) {
-  return reinterpret_cast<int32_t*>(reinterpret_cast<char*>(bwd_chain(scratch, n_work, tq, tkv, hq)) + chain_table_bytes(tkv, n_work));
+inline int32_t* bwd_chain_flags(void* scratch, int64_t n_work, int32_t tq, int32_t tkv, int32_t hq, int32_t hkv) {
+  return reinterpret_cast<int32_t*>(reinterpret_cast<char*>(bwd_chain(scratch, n_work, tq, tkv, hq, hkv)) + chain_table_bytes(tkv, n_work));
 }
 
 // The forward's row states follow its tile list in its scratch buffer.

@@ -24,7 +24,7 @@ namespace {
 
 constexpr int kSchedThreads = 1024;
 constexpr int kBuckets = 2048;
-constexpr int kMaxExclusiveScan = 1024;   // longer lists are not staged in LDS and have no exclusivity flags
+constexpr int kMaxExclusiveScan = kMaxFlaggedItems;   // longer lists are not staged in LDS and have no exclusivity flags
 
 __device__ inline int32_t ceil_div(int32_t a, int32_t b) { return (a + b - 1) / b; }
 
@@ -42,7 +42,7 @@ struct Item {
   __device__ int32_t n(int s) const { return s ? n1 : n0; }
   __device__ int32_t vis(int s) const { return s ? vis1 : vis0; }
 };
-constexpr int kItemWords = 13;      // in LDS: the item, then the first flag block of its chain (an odd stride: no bank conflicts)
+constexpr int kItemWords = 13;      // in LDS: the item, then the first flag block of its chain or the first turn number of its tiles (an odd stride: no bank conflicts)
 using ItemSlot = int32_t[kItemWords];
 __device__ inline void put_item(ItemSlot& r, const Item& it) {
   const int32_t w[12] = {it.seq, it.q_off, it.q_len, it.q_pos, it.k0, it.n0, it.k1, it.n1, it.base, it.vis0, it.vis1, it.step};
@@ -301,22 +301,27 @@ enum ListMode { kWhole, kChained, kSplit };
 // blocks (query tiles) that the tile meets.  On small problems the longest of these loops, not the sum of the work, sets the time: a
 // sequence of 4096 tokens with 3 query heads per KV head has a key tile of 384 steps where an even spread over the CUs would
 // be 37.  So a key tile's rows are cut into pieces of `rows` rows of the item, a query tile's keys into pieces of `keys` keys of a segment, and
-// every piece is a unit; the pieces of a tile add to its accumulators with atomics.
+// every piece is a unit; the pieces of a tile add to its accumulators with atomics, and where one item owns the rows they take turns
+// (see wait_turn in csrc/fcp_bwd.h), so that the sums of such rows repeat bit for bit as those of whole tiles do.
 // Size of a piece, in steps: a CU's even share of all steps; not less than sqrt(steps / 8), where the loop of a piece and the atomics of all of them
 // take the same time (a piece's 32 K elements go at one element per L2 channel and clock, an eighth of a step's time); not less
+// than sqrt(kTurnSteps longest loop), where the loop of a piece and the turns of its tile take the same time; not less
 // than min_steps, a unit's own beginning and end.  Nothing is split unless the longest loop is clearly longer than what the pieces
-// take: the share, half a piece at the end of the list, the atomics of the items whose tiles are longer than a piece.
-struct SplitArgs { int32_t group, kv_units, q_units, dq_tile, n_cu, min_steps; };
+// take: the share, half a piece at the end of the list, the atomics of the items whose tiles are longer than a piece, the turns.
+struct SplitArgs { int32_t group, kv_units, q_units, dq_tile, n_cu, min_steps, key_turns, row_turns; };
 struct SplitSizes { int32_t rows, keys; };
 constexpr int32_t kNoPieces = 1 << 24;
 constexpr float kSplitGain = 1.15f;
+constexpr float kTurnSteps = 4.f;      // one piece's turn, in steps: its atomics, their acknowledgement, the word (1.5 to 6 within 5 % of each other)
 
-// Called by every thread of the block, with its item (rejected: none).  Every block that asks gets the same answer: sums are formed in a fixed order.
-__device__ inline SplitSizes split_sizes(const SplitArgs& a, const MaskTables& m, const Item& it, int32_t n_work) {
-  __shared__ float s_part[kSchedThreads / 64][6];
+// Called by every thread of the block, with its item (rejected: none).  Every block that asks gets the same answer: sums are formed in a fixed
+// order, and nothing is contracted differently where the function is inlined twice.
+__device__ inline SplitSizes split_sizes(const SplitArgs& a, const MaskTables& m, const Item& it, int32_t fl, int32_t n_work) {
+#pragma clang fp contract(off)
+  __shared__ float s_part[kSchedThreads / 64][8];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, n_waves = (n_work + 63) >> 6;
-  // the item's steps (the average of its first and last tile times the tiles) and its longest tile: key tiles, query tiles
-  float steps[2] = {0.f, 0.f}, longest[2] = {0.f, 0.f};
+  // the item's steps (the average of its first and last tile times the tiles) and its longest tile, also among those it owns: key tiles, query tiles
+  float steps[2] = {0.f, 0.f}, longest[2] = {0.f, 0.f}, owned[2] = {0.f, 0.f};
   if (it.seq >= 0) {
 #pragma unroll
     for (int s = 0; s < 2; ++s) {
@@ -325,39 +330,43 @@ __device__ inline SplitSizes split_sizes(const SplitArgs& a, const MaskTables& m
       const int32_t c0 = bwd_cost<false>(m, it, s, 0, kBwdBN, kBwdBM), c1 = bwd_cost<false>(m, it, s, nt - 1, kBwdBN, kBwdBM);
       steps[0] += 0.5f * nt * (c0 + c1) * a.group * a.kv_units;
       longest[0] = fmaxf(longest[0], c0 * a.group);
+      if (fl & (s ? kFlagSeg1Exclusive : kFlagSeg0Exclusive)) owned[0] = fmaxf(owned[0], c0 * a.group);
     }
     const int32_t nq = ceil_div(it.q_len, a.dq_tile);
     longest[1] = ceil_div(it.vis0, kDqBN) + ceil_div(it.vis1, kDqBN);
+    if (fl & kFlagQExclusive) owned[1] = longest[1];
     steps[1] = 0.5f * nq * (fwd_cost(m, it, 0, a.dq_tile, kDqBN) + longest[1]) * a.q_units;
   }
   auto wave_sum = [](float v) { for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64); return v; };
   auto wave_max = [](float v) { for (int o = 32; o > 0; o >>= 1) v = fmaxf(v, __shfl_xor(v, o, 64)); return v; };
   if (wave < n_waves) {
-    const float p[4] = {wave_sum(steps[0]), wave_sum(steps[1]), wave_max(longest[0]), wave_max(longest[1])};
+    const float p[6] = {wave_sum(steps[0]), wave_sum(steps[1]), wave_max(longest[0]), wave_max(longest[1]), wave_max(owned[0]), wave_max(owned[1])};
     if (lane == 0)
 #pragma unroll
-      for (int i = 0; i < 4; ++i) s_part[wave][i] = p[i];
+      for (int i = 0; i < 6; ++i) s_part[wave][i] = p[i];
   }
   __syncthreads();
-  float all[2] = {0.f, 0.f}, top[2] = {0.f, 0.f}, piece[2];
+  float all[2] = {0.f, 0.f}, top[2] = {0.f, 0.f}, turns[2] = {0.f, 0.f}, piece[2];
   for (int w = 0; w < n_waves; ++w)
 #pragma unroll
     for (int l = 0; l < 2; ++l) {
       all[l] += s_part[w][l];
       top[l] = fmaxf(top[l], s_part[w][2 + l]);
+      turns[l] = fmaxf(turns[l], kTurnSteps * s_part[w][4 + l]);
     }
 #pragma unroll
-  for (int l = 0; l < 2; ++l) piece[l] = fmaxf(fmaxf(all[l] / a.n_cu, sqrtf(all[l] * 0.125f)), (float)a.min_steps);
+  for (int l = 0; l < 2; ++l)
+    piece[l] = fmaxf(fmaxf(all[l] / a.n_cu, sqrtf(all[l] * 0.125f)), fmaxf(sqrtf(turns[l]), (float)a.min_steps));
   if (wave < n_waves) {
     const float p[2] = {wave_sum(longest[0] > piece[0] ? steps[0] : 0.f), wave_sum(longest[1] > piece[1] ? steps[1] : 0.f)};
-    if (lane == 0) { s_part[wave][4] = p[0]; s_part[wave][5] = p[1]; }
+    if (lane == 0) { s_part[wave][6] = p[0]; s_part[wave][7] = p[1]; }
   }
   __syncthreads();
 #pragma unroll
   for (int l = 0; l < 2; ++l) {
     float heavy = 0.f;
-    for (int w = 0; w < n_waves; ++w) heavy += s_part[w][4 + l];
-    const float pieces = all[l] / a.n_cu + 0.5f * piece[l] + 0.125f * heavy / piece[l] + 4.f;
+    for (int w = 0; w < n_waves; ++w) heavy += s_part[w][6 + l];
+    const float pieces = all[l] / a.n_cu + 0.5f * piece[l] + 0.125f * heavy / piece[l] + turns[l] / piece[l] + 4.f;
     if (top[l] < kSplitGain * pieces) piece[l] = kNoPieces;
   }
   return {piece[0] < kNoPieces ? 32 * max(1, (int32_t)piece[0] / a.group) : 32 * kNoPieces, 32 * (int32_t)piece[1]};
@@ -370,6 +379,20 @@ struct RowPieces { int32_t first, count; };
 __device__ inline RowPieces row_pieces(const MaskTables& m, const Item& it, int s, int32_t kt, int32_t rows) {
   const int32_t first = first_row_of(m, it, s, kt, kBwdBN) / rows;
   return {first, ceil_div(it.q_len, rows) - first};
+}
+
+// Pieces of a tile stand in the list by bucket (decreasing), then in the order of their flat numbers.  How many stand before piece `offset` of
+// run `at`, for pieces that come in runs of equal buckets.
+struct PieceRun { int32_t count, bucket; };
+template <int N>
+__device__ inline int32_t pieces_before(const PieceRun (&run)[N], int at, int32_t offset) {
+  int32_t n = offset, mine = 0;
+#pragma unroll
+  for (int i = 0; i < N; ++i) mine = i == at ? run[i].bucket : mine;
+#pragma unroll
+  for (int i = 0; i < N; ++i)
+    if (i != at && (run[i].bucket > mine || (i < at && run[i].bucket == mine))) n += run[i].count;
+  return n;
 }
 
 // LDS shared between the flags' sort (first) and the list builder's histogram and offsets (afterwards).
@@ -411,7 +434,7 @@ __device__ void build_list(
   if (staged) {
     exclusive_flags_all(s_item, n_work, area->key, area->wmax, s_fl);
     if constexpr (Mode == kSplit) {
-      split = split_sizes(sargs, m, mine, n_work);
+      split = split_sizes(sargs, m, mine, tid < n_work ? s_fl[tid] : 0, n_work);
       cut = (backward ? split.rows : split.keys) < 32 * kNoPieces;
       path = (split.rows < 32 * kNoPieces ? kPathSplitKeys : 0) | (split.keys < 32 * kNoPieces ? kPathSplitRows : 0);
     }
@@ -424,6 +447,19 @@ __device__ void build_list(
     const int32_t nb = tid < n_work && (s_fl[tid] & kFlagQExclusive) ? ceil_div(mine.q_len, inner) : 0;
     int32_t total;
     const int32_t ex = block_exclusive_scan(nb, s_wave, total);
+    if (tid < n_work) s_item[tid][12] = ex;
+  }
+
+  // Split tiles: the first turn number of the tiles of the items that own their rows (query tiles) or of the segments that own their keys.
+  if (Mode == kSplit && cut) {
+    int32_t nt = 0;
+    if (tid < n_work) {
+      const int32_t fl = s_fl[tid];
+      if (backward) nt = (fl & kFlagSeg0Exclusive ? ceil_div(mine.vis0, tile) : 0) + (fl & kFlagSeg1Exclusive ? ceil_div(mine.vis1, tile) : 0);
+      else nt = fl & kFlagQExclusive ? ceil_div(mine.q_len, tile) : 0;
+    }
+    int32_t total;
+    const int32_t ex = block_exclusive_scan(nt, s_wave, total);
     if (tid < n_work) s_item[tid][12] = ex;
   }
 
@@ -474,6 +510,7 @@ __device__ void build_list(
     }
     return lo;
   };
+  auto bucket_of = [&](int32_t cost) { return min(cost >> shift, kBuckets - 1); };
   auto decode = [&](int32_t t, Tile& out) -> int32_t {
     const int32_t at = item_of(t);
     const Item it = fetch(at);
@@ -514,6 +551,16 @@ __device__ void build_list(
           q.kv_row0[1] = q.k_pos0[1] = q.vis[1] = 0;
           q.flags = fl & ~kFlagQExclusive;
           cost = vis > 0 ? ceil_div(vis, inner) : -1;
+          q.turn = s_item[at][12] + qt;
+          if (vis > 0 && (fl & kFlagQExclusive) && q.turn < sargs.row_turns && total_tiles <= tile_cap) {
+            // runs: the full pieces of segment 0, its last one, those of segment 1
+            const int32_t n0 = ceil_div(v0, split.keys), n1 = ceil_div(v1, split.keys), full = split.keys / inner;
+            const int32_t t0 = ceil_div(v0 - (n0 - 1) * split.keys, inner), t1 = ceil_div(v1 - (n1 - 1) * split.keys, inner);
+            const PieceRun run[4] = {{max(0, n0 - 1), bucket_of(full)}, {min(n0, 1), bucket_of(t0)},
+                                     {max(0, n1 - 1), bucket_of(full)}, {min(n1, 1), bucket_of(t1)}};
+            const int32_t i = slot - (sg ? c0 : 0), last = (sg ? n1 : n0) - 1;
+            q.flags |= kFlagInTurn | pieces_before(run, 2 * sg + (i == last ? 1 : 0), i == last ? 0 : i) << kPieceShift;
+          }
         } else if (slot > 0) {
           cost = -1;
         }
@@ -561,7 +608,21 @@ __device__ void build_list(
     k.q_local_off = it.q_off + row0;
     k.q_seq_start = it.q_pos + row0;
     k.q_len = row1 - row0;
-    k.flags = whole && (fl & (sg ? kFlagSeg1Exclusive : kFlagSeg0Exclusive)) ? kFlagSeg0Exclusive : 0;
+    const bool owned = (fl & (sg ? kFlagSeg1Exclusive : kFlagSeg0Exclusive)) != 0;
+    k.flags = whole && owned ? kFlagSeg0Exclusive : 0;
+    if (Mode == kSplit && !whole && owned) {
+      k.turn = s_item[at][12] + (sg && (fl & kFlagSeg0Exclusive) ? nt0 : 0) + kt;
+      if (k.turn < sargs.key_turns && total_tiles <= tile_cap) {
+        // runs: the first piece (from the first row that sees the tile on), the full ones, the last one
+        const RowPieces pc = row_pieces(m, it, sg, kt, split.rows);
+        const int32_t end = (pc.first + 1) * split.rows, last0 = (pc.first + pc.count - 1) * split.rows;
+        const PieceRun run[3] = {{1, bucket_of(ceil_div(end - first_row_of(m, it, sg, kt, tile), inner))}, {pc.count - 2, bucket_of(split.rows / inner)},
+                                 {1, bucket_of(ceil_div(it.q_len - last0, inner))}};
+        const int32_t i = row0 / split.rows - pc.first;
+        const int ra = i == 0 ? 0 : i == pc.count - 1 ? 2 : 1;
+        k.flags = kFlagInTurn | pieces_before(run, ra, ra == 1 ? i - 1 : 0) << kPieceShift;
+      }
+    }
     out = __builtin_bit_cast(Tile, k);
     const int32_t first = k.from_first[0] - it.q_pos;      // (first_row_of, before it is clamped)
     if (Chain) return ceil_div(it.q_len, inner) - max(0, first) / inner;
@@ -595,7 +656,7 @@ __device__ void build_list(
 #pragma unroll
     for (int sg = 0; sg < 2; ++sg) {
       const int32_t nt = ceil_div(it.vis(sg), tile);
-      auto bucket_of = [&](int32_t kt) { return min(bwd_cost<Chain>(m, it, sg, kt, tile, inner) >> shift, kBuckets - 1); };
+      auto tile_bucket = [&](int32_t kt) { return bucket_of(bwd_cost<Chain>(m, it, sg, kt, tile, inner)); };
       int32_t a;                                      // the segment's first tile after t
       if (sg == my_seg) {
         a = my_kt + 1;
@@ -603,12 +664,12 @@ __device__ void build_list(
         int32_t b = nt;                               // first kt with bucket < `bucket` (ties stand before t) or <= `bucket`
         a = 0;
         while (a < b) {
-          const int32_t mid = (a + b) >> 1, bm = bucket_of(mid);
+          const int32_t mid = (a + b) >> 1, bm = tile_bucket(mid);
           if (sg < my_seg ? bm < bucket : bm <= bucket) b = mid; else a = mid + 1;
         }
         rank += a;
       }
-      if (a < nt) next = min(next, first_block(bucket_of(a)));
+      if (a < nt) next = min(next, first_block(tile_bucket(a)));
     }
     if (rank == 0) first = 0;                         // rows that see no key get their zeros from the item's first tile
   };
@@ -620,7 +681,7 @@ __device__ void build_list(
     Tile tl;
     const int32_t c = decode(t, tl);
     if (t == tid) { first_tile = tl; first_cost = c; }
-    if (Mode != kSplit || c >= 0) atomicAdd(&s_hist[min(c >> shift, kBuckets - 1)], 1);   // (-1: no such piece)
+    if (Mode != kSplit || c >= 0) atomicAdd(&s_hist[bucket_of(c)], 1);   // (-1: no such piece)
   }
   __syncthreads();
   // Descending-cost start offset of every bucket: scan the histogram from the top.
@@ -635,31 +696,31 @@ __device__ void build_list(
     s_hist[b_lo] = ex + h_hi;
   }
   __syncthreads();
-  if constexpr (!Chain) {
+  if (Mode == kWhole || (Mode == kSplit && !cut)) {
     for (int32_t t = tid; t < n_tiles; t += kSchedThreads) {
       Tile tl;
       int32_t c;
       if (t == tid) { tl = first_tile; c = first_cost; }
       else c = decode(t, tl);
-      if (Mode == kSplit && c < 0) continue;
-      const int32_t pos = atomicAdd(&s_hist[min(c >> shift, kBuckets - 1)], 1);
+      const int32_t pos = atomicAdd(&s_hist[bucket_of(c)], 1);
       tiles[pos] = tl;
     }
   } else {
-    // The tiles of a chain must stand in the list in the order in which they take turns: by bucket, then in the order of the
-    // flat tile numbers, i.e. the scatter has to be stable.  A wave groups its lanes by bucket, the waves
+    // The tiles of a chain, and the pieces of a tile, must stand in the list in the order in which they take turns: by bucket, then in the
+    // order of the flat tile numbers, i.e. the scatter has to be stable.  A wave groups its lanes by bucket, the waves
     // take their places one after the other.
     for (int32_t base = 0; base < n_tiles; base += kSchedThreads) {
       const int32_t t = base + tid;
-      const bool live = t < n_tiles;
       Tile tl;
-      int32_t bucket = -1 - tid, rank = -1, next = 0, first = 0, flag0 = 0;
-      if (live) {
-        int32_t c;
+      int32_t c = -1, bucket = -1 - tid, rank = -1, next = 0, first = 0, flag0 = 0;
+      if (t < n_tiles) {
         if (base == 0) { tl = first_tile; c = first_cost; }
         else c = decode(t, tl);
-        bucket = min(c >> shift, kBuckets - 1);
-        chain_place(t, bucket, rank, next, first, flag0);
+      }
+      const bool live = c >= 0;                       // (kSplit, -1: no such piece)
+      if (live) {
+        bucket = bucket_of(c);
+        if constexpr (Chain) chain_place(t, bucket, rank, next, first, flag0);
       }
       const int lane = tid & 63;
       uint64_t mine = 0;                              // lanes of the wave with this lane's bucket
@@ -682,8 +743,10 @@ __device__ void build_list(
       }
       if (live) {
         tiles[pos] = tl;
-        int32_t* r = chain + (int64_t)pos * kChainWords;
-        r[0] = rank; r[1] = next; r[2] = flag0; r[3] = first;
+        if constexpr (Chain) {
+          int32_t* r = chain + (int64_t)pos * kChainWords;
+          r[0] = rank; r[1] = next; r[2] = flag0; r[3] = first;
+        }
       }
     }
   }
@@ -734,7 +797,7 @@ __device__ void row_states(int first, int count, const RowStateJob& job, const L
   SplitSizes split{};
   bool cut = false;
   if constexpr (Split) {
-    split = split_sizes(sargs, m, mine, n_work);
+    split = split_sizes(sargs, m, mine, tid < n_work ? s_fl[tid] : 0, n_work);
     cut = min(split.rows, split.keys) < 32 * kNoPieces;
   }
   // Only the keys that some row sees matter here.  A rejected item has empty ranges, so the passes over the list below carry no test
@@ -922,7 +985,7 @@ __global__ __launch_bounds__(kSchedThreads) void sched_bwd_kernel(
       stats[i] = l == -INFINITY ? -INFINITY : -l * 1.4426950408889634f;
       stats[n_stats + i] = -delta[i];
     }
-    if constexpr (Mode == kChained)
+    if constexpr (Mode != kWhole)
       for (int64_t i = (int64_t)(b - 2) * kSchedThreads + threadIdx.x; i < n_flags; i += stride) flags[i] = 0;
   } else {   // direct mode: the row states, and the accumulator rows that are accumulated into cleared
     row_states<Mode == kSplit>(2 + stat_blocks, gridDim.x - 2 - stat_blocks, states, args, m, s_item, s_fl, &s_area, split);
@@ -1022,7 +1085,7 @@ int launch_schedule_bwd(int64_t kv_row_bytes, const int32_t* q_limit, const int3
   if (stat_blocks < 1) stat_blocks = 1;
   const int state_blocks = states ? row_state_blocks(tq, states->kv_state ? tkv : 0) : 0;
   SplitArgs sp{};
-  if (split) sp = {split->group, split->kv_units, split->q_units, dq_tile, split->n_cu, split->min_steps};
+  if (split) sp = {split->group, split->kv_units, split->q_units, dq_tile, split->n_cu, split->min_steps, split->key_turns, split->row_turns};
   // (a kernel of its own for each mode: a longer one begins later)
   const auto kernel = chain ? sched_bwd_kernel<kChained> : split ? sched_bwd_kernel<kSplit> : sched_bwd_kernel<kWhole>;
   hipLaunchKernelGGL(kernel, dim3((unsigned)(2 + stat_blocks + state_blocks)), dim3(kSchedThreads), 0, stream,
@@ -1037,7 +1100,6 @@ int launch_schedule_bwd(int64_t kv_row_bytes, const int32_t* q_limit, const int3
 
 extern "C" size_t fcp_scratch_bytes(int which, int32_t tq, int32_t tkv, int32_t hq, int32_t hkv,
                                     int32_t head_dim, int64_t n_work, int32_t n_parts) {
-  (void)hkv;
   if (tq < 0 || tkv < 0 || n_work < 0 || n_parts < 0) return 0;
   if (which == FCP_SCRATCH_BWD)   // key-tile list (dK/dV kernel), query-tile list (dQ kernel), packed row statistics,
                                   // row states
@@ -1045,6 +1107,7 @@ extern "C" size_t fcp_scratch_bytes(int which, int32_t tq, int32_t tkv, int32_t 
            fcp::sched_region_bytes(n_work, fcp::bwd_q_cap(tq, tkv, n_work)) +
            fcp::pad_to((size_t)hq * (size_t)tq * 8, 256) +
            fcp::pad_to((size_t)tq, 256) + fcp::pad_to((size_t)tkv, 256) +  // + row states of the direct mode
+           fcp::turn_bytes(tq, tkv, hq, hkv, n_work) +                     // + turns of split tiles
            fcp::chain_bytes(tq, tkv, hq, head_dim, n_work);                // + chains of the one-pass kernel
   return fcp::sched_region_bytes(n_work, fcp::q_tile_cap(tq, tkv, n_work, n_parts)) +
          fcp::pad_to((size_t)tq, 256);                                  // + row states of the direct mode
