@@ -301,14 +301,17 @@ int fcp_grad_finalize(const float* acc, void* out_bf16, int64_t n, void* stream)
  * their whole result from one unit of work (every sequence that is not sharded, Sec. 4.1): the kernel that computes
  * such a row writes it as bf16 at once.  Per query row and per pool key:
  *   - no work item of the call touches it: the result is zero;
- *   - one work item owns it (no other item of the call covers the same query rows / key segment): written to
- *     dq_out / dk_out / dv_out directly, the fp32 accumulator row is neither read nor written;
+ *   - one work item owns it (no other item of the call covers the same query rows / key segment): summed in a fixed
+ *     order (results repeat bit for bit) and mostly written to dq_out / dk_out / dv_out by the kernel that computes
+ *     it.  Where the work on the row is cut into several units (key tiles that take turns at dQ rows, pieces of a
+ *     tile) the fp32 accumulator row carries the sum from one to the next;
  *   - otherwise: accumulated in fp32 in dq_acc / dk_acc / dv_acc (this call clears those rows first; the caller need
  *     not) with atomics.
  * fcp_grad_finalize_direct then completes the outputs: accumulated rows are converted (round to nearest even),
  * untouched rows zeroed, directly written rows left alone.  The row states stay in `scratch` between the two calls.
- *   dq_acc [tq,hq,D], dk_acc, dv_acc [tkv,hkv,D] fp32 device, contents on entry irrelevant, on exit defined only
- *   for the accumulated rows;  dq_out [tq,hq,D], dk_out, dv_out [tkv,hkv,D] bf16 device, complete after the finalize.
+ *   dq_acc [tq,hq,D], dk_acc, dv_acc [tkv,hkv,D] fp32 device: work space of the call, any row of it; contents on entry
+ *   irrelevant, on exit defined only for the rows that several items accumulate into;  dq_out [tq,hq,D], dk_out,
+ *   dv_out [tkv,hkv,D] bf16 device, complete after the finalize.
  * Limits: those of fcp_attn_bwd_step, and n_work <= 1024 (FCP_ERR_UNSUPPORTED beyond: use the accumulating call).
  * Other arguments, alignment and errors as in fcp_attn_bwd_step; scratch sized with FCP_SCRATCH_BWD.
  */

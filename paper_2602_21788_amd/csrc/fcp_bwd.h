@@ -20,7 +20,7 @@ struct BwdParams {
   float* dk;
   float* dv;
   // Direct mode (all three set, or all NULL): a unit that owns its rows / keys in this launch (the scheduler's
-  // exclusivity flags) writes its final bf16 result here and leaves the fp32 accumulator alone.
+  // exclusivity flags) writes its final bf16 result here; dq also carries the one-pass kernel's running sums.
   uint16_t* dq_out;
   uint16_t* dk_out;
   uint16_t* dv_out;

@@ -151,7 +151,7 @@ int launch_schedule_bwd(int64_t kv_row_bytes, const int32_t* q_limit, const int3
                         const RowStates* states = nullptr, int32_t* chain = nullptr, int32_t* flags = nullptr, int64_t n_flags = 0, const SplitTiles* split = nullptr);
 
 // Direct modes: one state byte per query row and (backward: kv_state not NULL) per pool key: 0 untouched, 1 several
-// work items contribute (backward: accumulated in fp32, the accumulator row is cleared when the accumulators are
+// work items contribute, or several pieces of a split tile (backward: accumulated in fp32, the accumulator row is cleared when the accumulators are
 // given; forward: partial results, merged afterwards), 2 written directly as bf16 by the unit that owns it.
 // n_parts / check_step: the validity rules of the list the states go with.  The scheduling launches below compute
 // them on additional blocks when `states` is given; launch_row_states() is the same work as a launch of its own.
