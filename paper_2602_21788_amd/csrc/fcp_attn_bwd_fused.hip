@@ -72,6 +72,13 @@ __device__ inline void wait_vmem() { asm volatile("s_waitcnt vmcnt(%0)" :: "n"(N
 // A copy that the compiler cannot see through: what is derived from it inside a loop is formed there and holds no registers across
 // the loop's other parts.
 __device__ inline int fresh(int v) { asm volatile("" : "+v"(v)); return v; }
+__device__ inline int fresh_uniform(int v) { asm volatile("" : "+s"(v)); return v; }
+// The lane, formed anew: no register holds it, or the thread's number, from the kernel's beginning on.
+__device__ inline int lane_id() {
+  int l;
+  asm volatile("v_mbcnt_lo_u32_b32 %0, -1, 0\n\tv_mbcnt_hi_u32_b32 %0, -1, %0" : "=v"(l));
+  return l;
+}
 constexpr int kCacheBypass = 16;   // sc1: the load goes past the CU's vector cache, which may hold what the line was when this CU last read it
 // Two wave-wide LDS-direct loads of 16 bytes per lane (see lds_fill_b128), 1 KB apart in LDS and `step` bytes apart in memory; v0, v1 = lane offsets.
 template <bool Bypass>
@@ -94,7 +101,9 @@ __device__ inline BwdParams args_again() {
   for (int i = 0; i < (int)(sizeof(BwdParams) / 8); ++i) r.w[i] = a[i];
   return __builtin_bit_cast(BwdParams, r);
 }
-constexpr int kClaimed = 1 << 30;      // counter of a claimed queue: past every unit
+constexpr int kClaimed = 1 << 30;      // counter of a claimed queue: past every unit; the claiming XCD from bit kClaimShift on (home blocks count below it)
+constexpr int kClaimShift = 24;
+constexpr int kClaimPolls = 16;
 constexpr int kSpinLimit = 1 << 18;    // polls of a wave per unit, about half a second: a chain that cannot go on ends, its rows become NaN and the
                                        // header says so
 
@@ -125,7 +134,7 @@ __global__ __launch_bounds__(768, 1) void bwd_fused_kernel(const BwdParams p0) {
   using DT = typename C::DT;
   extern __shared__ __attribute__((aligned(256))) unsigned char smem[];
   __shared__ int32_t s_next_unit;
-  __shared__ int32_t s_queue[2];                   // queue; next unit of a queue that this block works off alone, or -1
+  __shared__ int32_t s_queue[2];                   // queue that units are taken from; this block's XCD
   __shared__ int32_t s_rec[20];                    // tile record, then chain record
 
   const BwdParams& p = p0;
@@ -136,39 +145,14 @@ __global__ __launch_bounds__(768, 1) void bwd_fused_kernel(const BwdParams p0) {
   const int G = p.hq / p.hkv;
   const uint32_t lds0 = lds_offset(smem);
   // the queue of the XCD this block really runs on: see the head of the file
-  if (tid == 0) {
-    s_queue[0] = __builtin_amdgcn_s_getreg(20 | (0 << 6) | (3 << 11)) & (kNumXcd - 1);   // HW_REG_XCC_ID, bits 3:0
-    s_queue[1] = -1;
-  }
+  if (tid == 0) s_queue[0] = s_queue[1] = __builtin_amdgcn_s_getreg(20 | (0 << 6) | (3 << 11)) & (kNumXcd - 1);   // HW_REG_XCC_ID, bits 3:0
   const int kvh_here = p.hkv / kNumXcd;
   const int n_units = p.hdr->n_tiles * kvh_here;
 
   // Units are taken one at a time, when the block is about to need one: a unit that a block holds in reserve would
-  // hold up the units after it in its chains.  Blocks are dealt to the XCDs in turn, so every queue has its blocks; should an XCD
-  // get none, a block that has run out of units claims the whole queue that nobody has begun.
-  auto take_unit = [&]() {
-    const int lane = fresh(tid) & 63;
-    int32_t v0 = __builtin_amdgcn_readfirstlane(s_queue[1]);
-    if (v0 >= 0) {
-      if (lane == 0) s_queue[1] = v0 + 1;
-    } else if (lane == 0) {
-      v0 = atomicAdd(&p.hdr->counter[s_queue[0]], 1);
-    }
-    int unit = __builtin_amdgcn_readfirstlane(v0);
-    if (unit >= n_units && n_units > 0) {
-      int32_t c = 1;
-      if (lane < kNumXcd) c = __hip_atomic_load(&p.hdr->counter[lane], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      for (uint64_t idle = __builtin_amdgcn_ballot_w64(c == 0); idle; idle &= idle - 1) {
-        const int q = __builtin_ctzll(idle);
-        int32_t old = 0;
-        if (lane == 0) old = atomicCAS(&p.hdr->counter[q], 0, kClaimed);
-        if (__builtin_amdgcn_readfirstlane(old) == 0) {
-          if (lane == 0) { s_queue[0] = q; s_queue[1] = 1; }
-          unit = 0;
-          break;
-        }
-      }
-    }
+  // hold up the units after it in its chains.
+  auto publish = [&](int unit) {
+    const int lane = lane_id();
     if (unit < n_units) {
       const int64_t tile = unit / kvh_here;
       if (lane < 16) s_rec[lane] = reinterpret_cast<const int32_t*>(p.tiles)[tile * 16 + lane];
@@ -176,7 +160,45 @@ __global__ __launch_bounds__(768, 1) void bwd_fused_kernel(const BwdParams p0) {
     }
     if (lane == 0) s_next_unit = unit;
   };
-  if (wave == 0) take_unit();
+  auto take_unit = [&]() {
+    const int home = __builtin_amdgcn_readfirstlane(s_queue[1]), q = __builtin_amdgcn_readfirstlane(s_queue[0]);
+    int32_t v0 = 0;
+    if (lane_id() == 0) v0 = atomicAdd(q == home ? &p.hdr->counter[q] : &p.hdr->claimed[q], 1);
+    publish(__builtin_amdgcn_readfirstlane(v0));
+  };
+  // Blocks are dealt to the XCDs in turn, so every queue has its blocks.  An XCD that has begun nothing while a block of another one
+  // has run out of units is late (its CUs are held by something else) or got no block: after a few polls (about 30 us) its
+  // queue is claimed as a whole for the XCD of that block, and all blocks of that XCD which run out work it off together.  None of them
+  // leaves before the last claim: a block leaves when every queue is begun.
+  auto take_elsewhere = [&]() {
+    const int home = __builtin_amdgcn_readfirstlane(s_queue[1]);
+    int unit = __builtin_amdgcn_readfirstlane(s_next_unit);
+    if (unit < n_units || n_units == 0) return;
+    const int lane = lane_id();
+    for (int polls = 0;; ++polls) {
+      int32_t c = 1;
+      if (lane < kNumXcd) c = __hip_atomic_load(&p.hdr->counter[lane], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      uint64_t ours = __builtin_amdgcn_ballot_w64(c >= kClaimed && (c - kClaimed) >> kClaimShift == home);
+      const uint64_t idle = __builtin_amdgcn_ballot_w64(c == 0);
+      if (idle && polls >= kClaimPolls) {
+        const int q = __builtin_ctzll(idle);
+        int32_t old = 0;
+        if (lane == 0) old = atomicCAS(&p.hdr->counter[q], 0, kClaimed + (home << kClaimShift));
+        if (__builtin_amdgcn_readfirstlane(old) == 0) ours |= (uint64_t)1 << q;
+      }
+      for (; ours && unit >= n_units; ours &= ours - 1) {
+        const int q = __builtin_ctzll(ours);
+        int32_t v = 0;
+        if (lane == 0) v = atomicAdd(&p.hdr->claimed[q], 1);
+        unit = __builtin_amdgcn_readfirstlane(v);
+        if (lane == 0) s_queue[0] = q;
+      }
+      if (unit < n_units || !idle) break;
+      __builtin_amdgcn_s_sleep(32);
+    }
+    publish(unit);
+  };
+  if (wave == 0) { take_unit(); take_elsewhere(); }
   __syncthreads();
   auto next_unit = [&](FusedUnit& u) {
     const int unit = __builtin_amdgcn_readfirstlane(s_next_unit);
@@ -207,8 +229,7 @@ __global__ __launch_bounds__(768, 1) void bwd_fused_kernel(const BwdParams p0) {
     const int fill_row0 = 16 * (pw & 1);
     while (next_unit(u)) {
       const BwdParams p = args_again();
-      int lane = tid & 63;                          // per-lane values are formed here, not ahead of the unit loop (registers)
-      asm volatile("" : "+v"(lane));
+      const int lane = lane_id();                   // per-lane values are formed here, not ahead of the unit loop (registers)
       const int l32 = lane & 31, g2 = lane >> 5;
       const int n_keys = u.t.n_keys, n_iter = u.n_iter;
       // ---- fills: instruction i covers rows fill_row0 + 4 i + lane / 16 (its chunk permutation differs by i)
@@ -237,7 +258,7 @@ __global__ __launch_bounds__(768, 1) void bwd_fused_kernel(const BwdParams p0) {
         const int tf = fresh(tfill);
         lds_fill_x2<false>(f_r, f_dst, tf, tf ^ 16, f_soff, 4 * q_row_bytes);
         lds_fill_x2<false>(f_r, f_dst + 2048, tf ^ 32, tf ^ 48, f_soff + 8 * q_row_bytes, 4 * q_row_bytes);
-        if (pw < 2) lds_fill_b32(f_rs, f_dst + (2 * C::TILE - DT::row_base(fill_row0)) + pw * C::SLOT, 4 * lane, f_ssoff);
+        if (fresh_uniform(pw) < 2) lds_fill_b32(f_rs, f_dst + (2 * C::TILE - DT::row_base(fill_row0)) + pw * C::SLOT, 4 * lane, f_ssoff);
         --f_left;
         f_soff -= C::BM * q_row_bytes;
         f_ssoff -= C::BM * 4;
@@ -362,6 +383,7 @@ __global__ __launch_bounds__(768, 1) void bwd_fused_kernel(const BwdParams p0) {
         st = st1;
         j = j1;
       }
+      if (wave == 0) take_elsewhere();              // (rare; here, where the unit's registers are free)
       wait_vmem<0>();                               // the fills past the last step (zeros) have landed: the next unit's V tile passes through their stages
       lds_barrier();                                // the LDS is free for the next unit
     }
@@ -372,8 +394,7 @@ __global__ __launch_bounds__(768, 1) void bwd_fused_kernel(const BwdParams p0) {
     const int dq_row_bytes = p.hq * D * 4;
     while (next_unit(u)) {
       const BwdParams p = args_again();
-      int lane = tid & 63;
-      asm volatile("" : "+v"(lane));
+      const int lane = lane_id();
       const int l32 = lane & 31, g2 = lane >> 5;
       const int n_keys = u.t.n_keys, n_iter = u.n_iter;
       const int64_t kv_row0 = u.t.kv_row0;

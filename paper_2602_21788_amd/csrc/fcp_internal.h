@@ -44,8 +44,10 @@ struct SchedHeader {
   int32_t counter[kNumXcd];     // next unit per XCD (or counter[0] alone)
   int32_t n_stalled;            // backward, key-tile list: waits for another unit's turn that ran out (their rows are NaN)
   int32_t pad[3];
-};                               // 64 bytes
-static_assert(sizeof(SchedHeader) == 64, "header size");
+  int32_t claimed[kNumXcd];     // one-pass backward: next unit of a queue that another XCD's blocks have claimed
+  int32_t pad2[8];
+};                               // 128 bytes
+static_assert(sizeof(SchedHeader) == 128, "header size");
 constexpr int32_t kPathOnePass = 1;     // one pass over key tiles (csrc/fcp_attn_bwd_fused.hip)
 constexpr int32_t kPathSplitKeys = 2;   // key tiles in pieces of rows
 constexpr int32_t kPathSplitRows = 4;   // query tiles in pieces of keys

@@ -757,7 +757,7 @@ __device__ void build_list(
     hdr->path = path;
     hdr->n_stalled = 0;
     for (int c = 0; c < 3; ++c) hdr->pad[c] = 0;
-    for (int c = 0; c < kNumXcd; ++c) hdr->counter[c] = 0;
+    for (int c = 0; c < kNumXcd; ++c) hdr->counter[c] = hdr->claimed[c] = 0;
   }
 }
 

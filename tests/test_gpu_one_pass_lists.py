@@ -71,3 +71,40 @@ def test_status_reports_waits_that_ran_out():
     with pytest.raises(B.FcpError) as e:
         B.fcp_scratch_status(scratch)
     assert e.value.code == B.FCP_ERR_STALLED and "3 waits" in str(e.value)
+
+
+def test_one_pass_beside_another_streams_work():
+    """Blocks of the kernel that start late or unevenly, because another stream's kernels hold CUs, change nothing: not the sums, whichever
+    XCD works a queue of units off, and no wait runs out."""
+    import torch
+    import paper_2602_21788_amd.binding as B
+    from paper_2602_21788_amd.rank import RankAttention
+    dev = "cuda:0"
+    lens = [3000] + [60] * 20                              # 24 of the 44 units of a queue are one chain
+    D, hq, hkv = 128, 8, 8
+    items = [(s, 0, n, [(0, n)]) for s, n in enumerate(lens)]
+    q, k, v, do = listed.draw(lens, hq, hkv, D, 14)
+    lse, delta, ref = listed.reference(lens, items, q, k, v, do, D ** -0.5)
+    work = listed.work_list(B, lens, items)
+    first, scratch = listed.run_backward(B, "plain", lens, work, q, k, v, do, lse, delta, D ** -0.5)
+    assert listed.backward_path(scratch) == listed.ONE_PASS
+    listed.check(first, ref, TOL_BF16_REL, "alone")
+    other = RankAttention([8192], [1], 0, 16, 8, D)
+    other.set_random_inputs(3)
+    side, mine = torch.cuda.Stream(), torch.cuda.Stream()
+    t = [x.to(dev) for x in (q, k, v, do, lse, delta)] + [torch.from_numpy(listed.offsets(lens)).to(dev)]
+    work_d = torch.from_numpy(work.view("u1").copy()).to(dev)
+    unused = torch.empty_like(t[5])
+    for call in range(12):
+        got = [torch.zeros_like(x) for x in first]
+        torch.cuda.synchronize()
+        print(f"one-pass backward beside another stream, call {call}", flush=True)
+        for _ in range(3):
+            other.forward_direct(stream=side)
+        for _ in range(call % 3):                          # (starts at different places of the other stream's work)
+            B.fcp_attn_bwd_delta(t[0], t[3], unused, stream=mine)
+        B.fcp_attn_bwd_step(*t, work_d, D ** -0.5, *got, scratch, stream=mine)
+        torch.cuda.synchronize()
+        assert B.fcp_scratch_status(scratch)[1] == 0
+        for a, b in zip(got, first):
+            assert torch.equal(a, b), call
