@@ -528,7 +528,7 @@ static int bwd_step(const void* q, const void* k, const void* v, const void* d_o
     p.flags = fcp::bwd_chain_flags(scratch, n_work, tq, tkv, hq, hkv);
     p.hdr = (fcp::SchedHeader*)region_kv;
     p.tiles = fcp::sched_tiles(region_kv, n_work);
-    return fcp::launch_bwd_fused(p, cap_kv * hkv, n_cu, st);
+    return fcp::launch_bwd_fused(p, fcp::kv_tile_cap(tkv, n_work) * hkv, n_cu, st);   // (more units, of keys shared by many items: the blocks take them in turn)
   }
   // dK/dV over key tiles
   p.turns = fcp::bwd_turns(scratch, n_work, tq, tkv, hq);
