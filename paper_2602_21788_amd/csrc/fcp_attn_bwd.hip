@@ -446,11 +446,8 @@ static int bwd_step(const void* q, const void* k, const void* v, const void* d_o
   void* region_q = static_cast<char*>(scratch) + fcp::sched_region_bytes(n_work, cap_kv);
   float* stats = reinterpret_cast<float*>(static_cast<char*>(region_q) + fcp::sched_region_bytes(n_work, cap_q));
   int dev = 0, n_cu = 0;
-  auto count_cus = [&]() -> int {
-    FCP_HIP_CHECK(hipGetDevice(&dev));
-    FCP_HIP_CHECK(hipDeviceGetAttribute(&n_cu, hipDeviceAttributeMultiprocessorCount, dev));
-    return FCP_OK;
-  };
+  FCP_HIP_CHECK(hipGetDevice(&dev));
+  FCP_HIP_CHECK(hipDeviceGetAttribute(&n_cu, hipDeviceAttributeMultiprocessorCount, dev));
   // One pass or two.  The one-pass kernel (csrc/fcp_attn_bwd_fused.hip) forms S and dP once and needs no query-tile launch; it has the
   // units of key tiles only, which take turns at the dQ rows of a sequence.  That pays where sequences are short, and not where many
   // tiles follow each other through the same rows.  Lists of whole sequences (tq == tkv), measured:
@@ -461,12 +458,9 @@ static int bwd_step(const void* q, const void* k, const void* v, const void* d_o
   // Sharded lists (tq < tkv) have the whole sequence's tiles over a part of its rows: 0.63 to 1.1, they stay with two passes.
   const int group = hq / hkv;
   const int64_t key_units = (int64_t)tkv * hkv / fcp::kBwdBN;
-  bool fused = head_dim == 128 && hkv % fcp::kNumXcd == 0 && n_work >= 1 && n_work <= 1024 && tq == tkv;
-  if (fused) {
-    const int rcc = count_cus();
-    if (rcc != FCP_OK) return rcc;
-    fused = n_cu == 256 && ((tkv <= 256 * n_work && (group <= 2 || key_units >= n_cu)) || (group == 1 && key_units <= 4 * n_cu));
-  }
+  // (The kernel's queues are those of eight XCDs: not on a part of the chip.)
+  const bool fused = head_dim == 128 && hkv % fcp::kNumXcd == 0 && n_work >= 1 && n_work <= 1024 && tq == tkv && n_cu == 256 &&
+                     ((tkv <= 256 * n_work && (group <= 2 || key_units >= n_cu)) || (group == 1 && key_units <= 4 * n_cu));
   // direct mode: where every row's result comes from (and the accumulator rows that are accumulated into cleared),
   // on extra blocks of the scheduling launch
   fcp::RowStates rs{};
@@ -494,7 +488,7 @@ static int bwd_step(const void* q, const void* k, const void* v, const void* d_o
   // the sharding, and its accumulators are mostly shared already.  Measured, scheduling and attention launches: one sequence of 4096 tokens, 8 query
   // heads on one KV head, 128 channels 950 -> 312 us; 6 on 2, 64 channels 395 -> 177 us; 30 sequences of 20011 tokens in all, 6 on 2, 505 -> 343 us
   // whole and 305 -> 246 us with the longest one over 3 ranks; 4096 tokens over 3 ranks, 4 on 4, 107 -> 84 us; 4096 tokens, 32 on 8, 628 -> 580 us.
-  const fcp::SplitTiles sp{group, hkv, hq / (head_pair ? 2 : 1), 256, 12,          // (256 CUs; 12 steps at least)
+  const fcp::SplitTiles sp{group, hkv, hq / (head_pair ? 2 : 1), n_cu, 12,         // (12 steps at least)
                            (int32_t)fcp::key_turns(tkv, n_work), (int32_t)fcp::row_turns(tq, n_work)};
   const int64_t longest = std::max((int64_t)tq * group / fcp::kBwdBM, (int64_t)tkv / fcp::kDqBN);
   const bool split = !fused && key_units <= 1024 && n_work <= 1024 && longest >= (tq == tkv ? 24 : 64);
@@ -515,7 +509,6 @@ static int bwd_step(const void* q, const void* k, const void* v, const void* d_o
   p.tq = tq; p.hq = hq; p.hkv = hkv;
   p.scale = softmax_scale; p.scale_log2 = softmax_scale * fcp::kLog2e;
 
-  if (n_cu == 0 && (rc = count_cus()) != FCP_OK) return rc;
   auto grid_for = [&](int64_t units, int per_cu) {
     int64_t blocks = (int64_t)n_cu * per_cu;
     if (blocks > units) blocks = (units + 7) / 8 * 8;   // a multiple of the XCD count
