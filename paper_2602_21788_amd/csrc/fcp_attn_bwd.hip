@@ -459,7 +459,7 @@ static int bwd_step(const void* q, const void* k, const void* v, const void* d_o
   const int group = hq / hkv;
   const int64_t key_units = (int64_t)tkv * hkv / fcp::kBwdBN;
   // (The kernel's queues are those of eight XCDs: not on a part of the chip.)
-  const bool fused = head_dim == 128 && hkv % fcp::kNumXcd == 0 && n_work >= 1 && n_work <= 1024 && tq == tkv && n_cu == 256 &&
+  const bool fused = fcp::one_pass_heads(hkv, head_dim) && n_work >= 1 && n_work <= 1024 && tq == tkv && n_cu == 256 &&
                      ((tkv <= 256 * n_work && (group <= 2 || key_units >= n_cu)) || (group == 1 && key_units <= 4 * n_cu));
   // direct mode: where every row's result comes from (and the accumulator rows that are accumulated into cleared),
   // on extra blocks of the scheduling launch

@@ -1108,7 +1108,7 @@ extern "C" size_t fcp_scratch_bytes(int which, int32_t tq, int32_t tkv, int32_t 
            fcp::pad_to((size_t)hq * (size_t)tq * 8, 256) +
            fcp::pad_to((size_t)tq, 256) + fcp::pad_to((size_t)tkv, 256) +  // + row states of the direct mode
            fcp::turn_bytes(tq, tkv, hq, hkv, n_work) +                     // + turns of split tiles
-           fcp::chain_bytes(tq, tkv, hq, head_dim, n_work);                // + chains of the one-pass kernel
+           fcp::chain_bytes(tq, tkv, hq, hkv, head_dim, n_work);                // + chains of the one-pass kernel
   return fcp::sched_region_bytes(n_work, fcp::q_tile_cap(tq, tkv, n_work, n_parts)) +
          fcp::pad_to((size_t)tq, 256);                                  // + row states of the direct mode
 }

@@ -20,4 +20,19 @@ def test_chain_records_for_every_tile_of_a_full_list():
         tkv = tq + int(rng.integers(0, 2)) * int(rng.integers(0, 40000))
         size = [B.fcp_scratch_bytes(B.FCP_SCRATCH_BWD, tq, tkv, hq, hkv, D, n_work, 1) for D in (64, 128)]
         flags = (tq // 32 + 1 + n_work) * hq * 8 * 4
-        assert size[1] - size[0] >= _list_capacity(tkv, n_work) * 16 + flags, (tq, tkv, hq, hkv, n_work)
+        if hkv % 8 == 0:
+            assert size[1] - size[0] >= _list_capacity(tkv, n_work) * 16 + flags, (tq, tkv, hq, hkv, n_work)
+        else:                                                 # the one-pass backward does not take such heads
+            assert size[1] == size[0], (tq, tkv, hq, hkv, n_work)
+
+
+def test_a_buffer_for_the_largest_call_has_room_for_smaller_ones():
+    """Programs size the scratch once: a call with fewer rows, keys or items of the same heads never needs more."""
+    rng = np.random.default_rng(2)
+    for _ in range(400):
+        hkv = int(rng.choice([1, 2, 3, 8, 16]))
+        hq, D = hkv * int(rng.integers(1, 5)), int(rng.choice([64, 128]))
+        big = [int(rng.integers(1, 70000)), int(rng.integers(1, 70000)), int(rng.integers(1, 3000))]
+        small = [int(rng.integers(1, x + 1)) if rng.integers(0, 3) else x for x in big]
+        size = [B.fcp_scratch_bytes(B.FCP_SCRATCH_BWD, tq, tkv, hq, hkv, D, n_work, 1) for tq, tkv, n_work in (big, small)]
+        assert size[1] <= size[0], (big, small, hq, hkv, D)
