@@ -85,6 +85,7 @@ __global__ __launch_bounds__(512, 1) void dq_kernel(const BwdParams p, const int
   const int xcd = per_xcd ? (int)(blockIdx.x % kNumXcd) : 0;
   const int heads_here = per_xcd ? p.hq / kNumXcd : p.hq;
   const int units_per_tile = heads_here / hpu;
+  if (p.either && (p.hdr->path & kPathOnePass)) return;
   UnitQueue uq;
   uq.init(p.hdr, p.tiles, xcd, units_per_tile, &s_next_unit, s_rec);
 
@@ -456,11 +457,20 @@ static int bwd_step(const void* q, const void* k, const void* v, const void* d_o
   //       time (0.82 to 1.0 there); at 333 to 400 rows 0.96 to 1.1;
   //   one query head per KV head, up to 1024 tiles: 1.06 to 1.6 times as fast at any length; at 1500 tiles 1.0.
   // Sharded lists (tq < tkv) have the whole sequence's tiles over a part of its rows: 0.63 to 1.1, they stay with two passes.
+  // The rows per item are an average, and the items are in device memory: where one of them could be long enough to turn the comparison
+  // round (16384 rows with one query head per KV head, else 2048 and 512 rows of two and four heads), the scheduler decides when it sees them
+  // (one_pass_pays in csrc/fcp_sched.hip), and the launches of the other way end at once: 3 to 5 us, which lists of two heads per KV
+  // head and less than 8 K tokens on 8 KV heads are spared (0.92 to 0.95 at worst).
+  // One sequence among 30 short ones (mean 64 and 128 tokens), 32 query heads on 8, one pass / two: 512 tokens 99 / 110 and 105 / 140 us, 1024 187 / 144
+  // and 193 / 162, 2048 375 / 243 and 380 / 250; among 1000 (mean 128), 4096 tokens 2177 / 2560, 16384 10611 / 8846; 8 heads on 8 among 1000,
+  // 16384 tokens 2435 / 2496, 32768 7978 / 7367.
   const int group = hq / hkv;
   const int64_t key_units = (int64_t)tkv * hkv / fcp::kBwdBN;
   // (The kernel's queues are those of eight XCDs: not on a part of the chip.)
   const bool fused = fcp::one_pass_heads(hkv, head_dim) && n_work >= 1 && n_work <= 1024 && tq == tkv && n_cu == 256 &&
                      ((tkv <= 256 * n_work && (group <= 2 || key_units >= n_cu)) || (group == 1 && key_units <= 4 * n_cu));
+  const int64_t longest_item = (int64_t)tkv - n_work + 1;      // (with a row at least in each of the others)
+  const bool either = fused && group * longest_item > (group == 1 ? 16384 : group == 2 ? 4096 : 2048) && (group > 2 || key_units >= 2 * n_cu);
   // direct mode: where every row's result comes from (and the accumulator rows that are accumulated into cleared),
   // on extra blocks of the scheduling launch
   fcp::RowStates rs{};
@@ -488,16 +498,18 @@ static int bwd_step(const void* q, const void* k, const void* v, const void* d_o
   // the sharding, and its accumulators are mostly shared already.  Measured, scheduling and attention launches: one sequence of 4096 tokens, 8 query
   // heads on one KV head, 128 channels 950 -> 312 us; 6 on 2, 64 channels 395 -> 177 us; 30 sequences of 20011 tokens in all, 6 on 2, 505 -> 343 us
   // whole and 305 -> 246 us with the longest one over 3 ranks; 4096 tokens over 3 ranks, 4 on 4, 107 -> 84 us; 4096 tokens, 32 on 8, 628 -> 580 us.
-  const fcp::SplitTiles sp{group, hkv, hq / (head_pair ? 2 : 1), n_cu, 12,         // (12 steps at least)
-                           (int32_t)fcp::key_turns(tkv, n_work), (int32_t)fcp::row_turns(tq, n_work)};
   const int64_t longest = std::max((int64_t)tq * group / fcp::kBwdBM, (int64_t)tkv / fcp::kDqBN);
-  const bool split = !fused && key_units <= 1024 && n_work <= 1024 && longest >= (tq == tkv ? 24 : 64);
+  const bool split = (!fused || either) && key_units <= 1024 && n_work <= 1024 && longest >= (tq == tkv ? 24 : 64);
+  const fcp::SplitTiles sp{group, hkv, hq / (head_pair ? 2 : 1), n_cu, 12,         // (12 steps at least)
+                           (int32_t)fcp::key_turns(tkv, n_work), (int32_t)fcp::row_turns(tq, n_work), split};
+  int32_t* const turns = fcp::bwd_turns(scratch, n_work, tq, tkv, hq);
+  int32_t* const flags = fcp::bwd_chain_flags(scratch, n_work, tq, tkv, hq, hkv);
+  const int64_t n_flags = fused ? fcp::chain_flag_words(tq, hq, n_work) : 0;
+  int32_t* const clear = split ? turns : flags;
+  const int64_t n_clear = !split ? n_flags : !fused ? fcp::turn_words(tq, tkv, hq, hkv, n_work) : flags - turns + n_flags;
   int rc = fcp::launch_schedule_bwd((int64_t)hkv * head_dim * 2, q_limit, k_from, work, n_work, cu_seqlens_kv, n_seqs, tq, tkv,
                                     cap_kv, region_kv, head_pair ? fcp::kDqBM : 2 * fcp::kDqBM, cap_q, region_q, lse, delta, (int64_t)hq * tq, stats, st,
-                                    direct ? &rs : nullptr, fused ? fcp::bwd_chain(scratch, n_work, tq, tkv, hq, hkv) : nullptr,
-                                    fused ? fcp::bwd_chain_flags(scratch, n_work, tq, tkv, hq, hkv) : split ? fcp::bwd_turns(scratch, n_work, tq, tkv, hq) : nullptr,
-                                    fused ? fcp::chain_flag_words(tq, hq, n_work) : split ? fcp::turn_words(tq, tkv, hq, hkv, n_work) : 0,
-                                    split ? &sp : nullptr);
+                                    direct ? &rs : nullptr, fused ? fcp::bwd_chain(scratch, n_work, tq, tkv, hq, hkv) : nullptr, clear, n_clear, &sp, either);
   if (rc != FCP_OK) return rc;
 
   fcp::BwdParams p{};
@@ -516,15 +528,17 @@ static int bwd_step(const void* q, const void* k, const void* v, const void* d_o
     return dim3((unsigned)blocks);
   };
 
+  p.either = either;
   if (fused) {
     p.chain = fcp::bwd_chain(scratch, n_work, tq, tkv, hq, hkv);
-    p.flags = fcp::bwd_chain_flags(scratch, n_work, tq, tkv, hq, hkv);
+    p.flags = flags;
     p.hdr = (fcp::SchedHeader*)region_kv;
     p.tiles = fcp::sched_tiles(region_kv, n_work);
-    return fcp::launch_bwd_fused(p, fcp::kv_tile_cap(tkv, n_work) * hkv, n_cu, st);   // (more units, of keys shared by many items: the blocks take them in turn)
+    rc = fcp::launch_bwd_fused(p, fcp::kv_tile_cap(tkv, n_work) * hkv, n_cu, st);     // (more units, of keys shared by many items: the blocks take them in turn)
+    if (rc != FCP_OK || !either) return rc;
   }
   // dK/dV over key tiles
-  p.turns = fcp::bwd_turns(scratch, n_work, tq, tkv, hq);
+  p.turns = turns;
   p.n_stalled = &((fcp::SchedHeader*)region_kv)->n_stalled;
   p.hdr = (fcp::SchedHeader*)region_kv;
   p.tiles = fcp::sched_tiles(region_kv, n_work);

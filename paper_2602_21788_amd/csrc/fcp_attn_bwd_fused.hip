@@ -138,6 +138,7 @@ __global__ __launch_bounds__(768, 1) void bwd_fused_kernel(const BwdParams p0) {
   __shared__ int32_t s_rec[20];                    // tile record, then chain record
 
   const BwdParams& p = p0;
+  if (p.either && !(p.hdr->path & kPathOnePass)) return;
   const int tid = threadIdx.x;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int role = wave >> 2;                      // 0: score wave, 1: dV, 2: dK

@@ -85,6 +85,7 @@ __global__ __launch_bounds__(1024, 1) void dkv_kernel(const BwdParams p) {
   const bool per_xcd = (p.hkv % kNumXcd) == 0;
   const int xcd = per_xcd ? (int)(blockIdx.x % kNumXcd) : 0;
   const int kvh_here = per_xcd ? p.hkv / kNumXcd : p.hkv;
+  if (p.either && (p.hdr->path & kPathOnePass)) return;
   UnitQueue uq;
   uq.init(p.hdr, p.tiles, xcd, kvh_here, &s_next_unit, s_rec);
 

@@ -32,6 +32,7 @@ struct BwdParams {
   int32_t* turns;
   int32_t* n_stalled;
   int32_t tq, hq, hkv;
+  int32_t either;            // the list decided which kernels work it (path word): the others of the launches have nothing to do
   float scale, scale_log2;
 };
 

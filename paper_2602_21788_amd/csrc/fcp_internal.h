@@ -127,8 +127,8 @@ static_assert(kBwdBN == 4 * 32, "KTile keeps four key groups");
 
 struct RowStates;   // direct modes, see below
 // Splitting of the backward's tiles on small problems (csrc/fcp_sched.hip): query heads per KV head, units per key tile and per query tile, CUs, least
-// piece in 32-row blocks (of all heads together) and in 32-key blocks; numbers that the turn words have room for.
-struct SplitTiles { int32_t group, kv_units, q_units, n_cu, min_steps, key_turns, row_turns; };
+// piece in 32-row blocks (of all heads together) and in 32-key blocks; numbers that the turn words have room for; whether tiles may be split.
+struct SplitTiles { int32_t group, kv_units, q_units, n_cu, min_steps, key_turns, row_turns; bool cuts; };
 
 // Builds one tile list in `region` (tiles of `tile` keys if `key_tiles`, else of `tile` query rows;
 // `inner` is the block size of the other dimension used for the cost; kv_row_bytes = hkv*D*2 bounds
@@ -145,12 +145,13 @@ int launch_schedule(bool key_tiles, int32_t tile, int32_t inner, int64_t kv_row_
 
 // Everything that precedes the backward's attention kernels in one launch: both tile lists (key tiles of kBwdBN
 // keys in region_kv, query tiles of dq_tile rows in region_q) and the row statistics (stats: two planes of n_stats
-// floats, -LSE log2 e and -delta).
+// floats, -LSE log2 e and -delta).  chain: for the one-pass kernel, or (either) for the one or the other, as the list decides: the path word says
+// which, and the header of the query-tile list has no tiles for one pass.  `flags`: words to clear.
 int launch_schedule_bwd(int64_t kv_row_bytes, const int32_t* q_limit, const int32_t* k_from,
                         const fcp_work_desc* work, int64_t n_work, const int32_t* cu_seqlens_kv, int32_t n_seqs,
                         int32_t tq, int32_t tkv, int64_t cap_kv, void* region_kv, int32_t dq_tile, int64_t cap_q, void* region_q,
                         const float* lse, const float* delta, int64_t n_stats, float* stats, hipStream_t stream,
-                        const RowStates* states = nullptr, int32_t* chain = nullptr, int32_t* flags = nullptr, int64_t n_flags = 0, const SplitTiles* split = nullptr);
+                        const RowStates* states = nullptr, int32_t* chain = nullptr, int32_t* flags = nullptr, int64_t n_flags = 0, const SplitTiles* split = nullptr, bool either = false);
 
 // Direct modes: one state byte per query row and (backward: kv_state not NULL) per pool key: 0 untouched, 1 several
 // work items contribute, or several pieces of a split tile (backward: accumulated in fp32, the accumulator row is cleared when the accumulators are
@@ -210,11 +211,12 @@ inline size_t chain_bytes(int32_t tq, int32_t tkv, int32_t hq, int32_t hkv, int3
   if (!one_pass_heads(hkv, head_dim)) return 0;
   return chain_table_bytes(tkv, n_work) + pad_to((size_t)chain_flag_words(tq, hq, n_work) * sizeof(int32_t), 256);
 }
-inline int32_t* bwd_chain(void* scratch, int64_t n_work, int32_t tq, int32_t tkv, int32_t hq, int32_t hkv) {
-  return reinterpret_cast<int32_t*>(reinterpret_cast<char*>(bwd_turns(scratch, n_work, tq, tkv, hq)) + turn_bytes(tq, tkv, hq, hkv, n_work));
-}
+// (the flags right behind the turn words: a list that may be worked either way clears both as one range)
 inline int32_t* bwd_chain_flags(void* scratch, int64_t n_work, int32_t tq, int32_t tkv, int32_t hq, int32_t hkv) {
-  return reinterpret_cast<int32_t*>(reinterpret_cast<char*>(bwd_chain(scratch, n_work, tq, tkv, hq, hkv)) + chain_table_bytes(tkv, n_work));
+  return bwd_turns(scratch, n_work, tq, tkv, hq) + turn_bytes(tq, tkv, hq, hkv, n_work) / sizeof(int32_t);
+}
+inline int32_t* bwd_chain(void* scratch, int64_t n_work, int32_t tq, int32_t tkv, int32_t hq, int32_t hkv) {
+  return bwd_chain_flags(scratch, n_work, tq, tkv, hq, hkv) + pad_to((size_t)chain_flag_words(tq, hq, n_work) * sizeof(int32_t), 256) / sizeof(int32_t);
 }
 
 // The forward's row states follow its tile list in its scratch buffer.

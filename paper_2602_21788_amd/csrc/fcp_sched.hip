@@ -102,6 +102,12 @@ __device__ inline Item load_item(const ListArgs& a, const MaskTables& m, int32_t
   return it;
 }
 
+// The thread's item of a list that is staged in LDS (none: rejected).
+__device__ inline Item my_item(const ListArgs& a, const MaskTables& m) {
+  if (a.n_work <= kMaxExclusiveScan && (int32_t)threadIdx.x < a.n_work) return load_item(a, m, threadIdx.x);
+  return {-1, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0};
+}
+
 // query tile qt (of `tile` rows): cost = key blocks (of `inner` keys) its last row sees
 __device__ inline int32_t fwd_cost(const MaskTables& m, const Item& it, int32_t qt, int32_t tile, int32_t inner) {
   const int64_t limit = m.limit(it, min((qt + 1) * tile, it.q_len) - 1);
@@ -372,6 +378,53 @@ __device__ inline SplitSizes split_sizes(const SplitArgs& a, const MaskTables& m
   return {piece[0] < kNoPieces ? 32 * max(1, (int32_t)piece[0] / a.group) : 32 * kNoPieces, 32 * (int32_t)piece[1]};
 }
 
+// One pass or two, where the longest item decides (lists of several short items that the caller may have put a long one among).  Estimated times
+// in us, from the list: tiles and steps per CU and the longest tile's loop.  In one pass a chain is a serial loop as long as its first tile's, and with
+// several query heads per KV head its other tiles keep that tile's pace through all heads: `idle` steps, those that they lack
+// against it.  Fitted to 124 lists of 30 to 1000 short sequences and one of 512 to 65536 tokens, 1, 2 and 4 heads per KV head (5 and 10 % off on
+// average).  On these and on 117 others (log-normal lengths, several long ones, 1 to 8 heads per KV head) the way chosen takes 0.4 % longer than the
+// faster one on average and 17 % at most; one pass for all of them 4 % and 57 %.
+// Called by every thread of the block, with its item.  Every block that asks gets the same answer.
+__device__ inline bool one_pass_pays(const SplitArgs& a, const MaskTables& m, const Item& it, int32_t n_work) {
+#pragma clang fp contract(off)
+  __shared__ float s_part[kSchedThreads / 64][4];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, n_waves = (n_work + 63) >> 6;
+  float units = 0.f, steps = 0.f, idle = 0.f, longest = 0.f;
+  if (it.seq >= 0) {
+#pragma unroll
+    for (int s = 0; s < 2; ++s) {
+      const int32_t nt = ceil_div(it.vis(s), kBwdBN);
+      if (nt == 0) continue;
+      const int32_t c0 = bwd_cost<true>(m, it, s, 0, kBwdBN, kBwdBM), c1 = bwd_cost<true>(m, it, s, nt - 1, kBwdBN, kBwdBM);
+      units += nt;
+      steps += 0.5f * nt * (c0 + c1) * a.group;
+      idle += 0.5f * nt * (c0 - c1) * a.group;
+      longest = fmaxf(longest, (float)(c0 * a.group));
+    }
+  }
+  if (wave < n_waves) {
+    for (int o = 32; o > 0; o >>= 1) {
+      units += __shfl_xor(units, o, 64);
+      steps += __shfl_xor(steps, o, 64);
+      idle += __shfl_xor(idle, o, 64);
+      longest = fmaxf(longest, __shfl_xor(longest, o, 64));
+    }
+    if (lane == 0) { s_part[wave][0] = units; s_part[wave][1] = steps; s_part[wave][2] = idle; s_part[wave][3] = longest; }
+  }
+  __syncthreads();
+  units = steps = idle = longest = 0.f;
+  for (int w = 0; w < n_waves; ++w) {
+    units += s_part[w][0];
+    steps += s_part[w][1];
+    idle += s_part[w][2];
+    longest = fmaxf(longest, s_part[w][3]);
+  }
+  const float per_cu = (float)a.kv_units / a.n_cu;
+  const float one = 21.f + fmaxf((7.9f * units + 1.36f * steps + (a.group > 1 ? 0.64f : 0.41f) * idle) * per_cu, 1.46f * longest);
+  const float two = 47.f + fmaxf((12.9f * units + 1.65f * steps) * per_cu, 1.12f * longest);
+  return one <= two;
+}
+
 // Pieces of a query tile: up to this many, those of segment 0 first (one for a tile that is not split).
 __device__ inline int32_t key_slots(const Item& it, int32_t keys) { return max(1, ceil_div(it.vis0, keys) + ceil_div(it.vis1, keys)); }
 // The pieces of a key tile: numbers first .. first + count - 1.  A later tile of the segment lacks the leading ones.
@@ -412,7 +465,8 @@ __device__ void build_list(
     ItemSlot* s_item,                    // LDS, kMaxExclusiveScan slots
     SortArea* area, int32_t* s_fl,       // LDS: sort keys (later the histogram and the offsets), one flag word per item
     int32_t* chain,                      // kChained: the tiles' chain records
-    const SplitArgs& sargs) {            // kSplit
+    const SplitArgs& sargs,              // kSplit
+    const Item& mine) {                  // staged lists: the thread's item, or a rejected one
   __shared__ int32_t s_wave[kSchedThreads / 64];
   __shared__ int32_t s_max, s_rej;
   constexpr bool Chain = Mode == kChained;
@@ -424,12 +478,8 @@ __device__ void build_list(
   SplitSizes split{};
   bool cut = false;                                // tiles are split (the same for every thread)
   int32_t path = Mode == kChained ? kPathOnePass : 0;
-  Item mine{-1, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0};
   if (tid == 0) { s_max = 0; s_rej = 0; }
-  if (staged && tid < n_work) {
-    mine = load_item(args, m, tid);
-    put_item(s_item[tid], mine);
-  }
+  if (staged && tid < n_work) put_item(s_item[tid], mine);
   __syncthreads();                                 // (for every list: the other waves add to s_max and s_rej below)
   if (staged) {
     exclusive_flags_all(s_item, n_work, area->key, area->wmax, s_fl);
@@ -778,7 +828,7 @@ struct RowStateJob {
 // accumulated into.
 template <bool Split>
 __device__ void row_states(int first, int count, const RowStateJob& job, const ListArgs& args, const MaskTables& m, ItemSlot* s_item,
-                           int32_t* s_fl, SortArea* area, const SplitArgs& sargs) {
+                           int32_t* s_fl, SortArea* area, const SplitArgs& sargs, const Item& item) {
   uint8_t* __restrict__ q_state = job.q_state;
   uint8_t* __restrict__ kv_state = job.kv_state;
   float* __restrict__ dq_acc = job.dq_acc;
@@ -787,22 +837,18 @@ __device__ void row_states(int first, int count, const RowStateJob& job, const L
   const int32_t q_row_elems = job.q_row_elems, kv_row_elems = job.kv_row_elems;
   const int32_t tq = args.tq, n_work = args.n_work, n_kv_rows = kv_state ? args.tkv : 0;
   const int tid = threadIdx.x, lane = tid & 63;
-  Item mine{-1, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0};
-  if (tid < n_work) {
-    mine = load_item(args, m, tid);
-    put_item(s_item[tid], mine);
-  }
+  if (tid < n_work) put_item(s_item[tid], item);
   __syncthreads();
   exclusive_flags_all(s_item, n_work, area->key, area->wmax, s_fl);
   SplitSizes split{};
   bool cut = false;
   if constexpr (Split) {
-    split = split_sizes(sargs, m, mine, tid < n_work ? s_fl[tid] : 0, n_work);
+    split = split_sizes(sargs, m, item, tid < n_work ? s_fl[tid] : 0, n_work);
     cut = min(split.rows, split.keys) < 32 * kNoPieces;
   }
   // Only the keys that some row sees matter here.  A rejected item has empty ranges, so the passes over the list below carry no test
   // of validity.  An item without such keys has no key tile: in the backward its rows are untouched.
-  if (n_kv_rows > 0 && tid < n_work && mine.vis0 + mine.vis1 == 0) s_item[tid][2] = 0;
+  if (n_kv_rows > 0 && tid < n_work && item.vis0 + item.vis1 == 0) s_item[tid][2] = 0;
   __syncthreads();
 
   // Rows are taken in batches of 64, one LANE per row.  Batch f belongs to block f mod count, so every block's batches
@@ -930,7 +976,7 @@ __global__ __launch_bounds__(kSchedThreads) void row_state_kernel(const RowState
   __shared__ ItemSlot s_item[kMaxExclusiveScan];
   __shared__ int32_t s_fl[kMaxExclusiveScan];
   __shared__ SortArea s_area;
-  row_states<false>(0, gridDim.x, job, args, m, s_item, s_fl, &s_area, SplitArgs{});
+  row_states<false>(0, gridDim.x, job, args, m, s_item, s_fl, &s_area, SplitArgs{}, my_item(args, m));
 }
 
 struct ListJob {
@@ -950,13 +996,13 @@ __global__ __launch_bounds__(kSchedThreads) void sched_kernel(
   __shared__ SortArea s_area;
   const int b = blockIdx.x;
   if (b == 0) {
-    build_list<kWhole>(backward != 0, j.tile, j.inner, args, m, j.tile_cap, j.hdr, j.item_off, j.tiles, s_item, &s_area, s_fl, nullptr, SplitArgs{});
+    build_list<kWhole>(backward != 0, j.tile, j.inner, args, m, j.tile_cap, j.hdr, j.item_off, j.tiles, s_item, &s_area, s_fl, nullptr, SplitArgs{}, my_item(args, m));
   } else if (b <= fill_blocks) {
     const int64_t stride = (int64_t)fill_blocks * kSchedThreads;
     for (int64_t i = (int64_t)(b - 1) * kSchedThreads + threadIdx.x; i < lse_fill_n; i += stride)
       lse_fill[i] = -INFINITY;
   } else {
-    row_states<false>(1 + fill_blocks, gridDim.x - 1 - fill_blocks, states, args, m, s_item, s_fl, &s_area, SplitArgs{});
+    row_states<false>(1 + fill_blocks, gridDim.x - 1 - fill_blocks, states, args, m, s_item, s_fl, &s_area, SplitArgs{}, my_item(args, m));
   }
 }
 
@@ -964,7 +1010,8 @@ __global__ __launch_bounds__(kSchedThreads) void sched_kernel(
 // (dK/dV kernel), block 1 the query-tile list (dQ kernel), the other blocks write the row statistics in the form
 // the kernels consume: plane 0 = -LSE log2 e (-inf for a row without keys, so that its probabilities vanish),
 // plane 1 = -delta.
-template <ListMode Mode>
+// Other != Mode: the list decides which of the two it is (see one_pass_pays).
+template <ListMode Mode, ListMode Other = Mode>
 __global__ __launch_bounds__(kSchedThreads) void sched_bwd_kernel(
     const ListJob kv, const ListJob qt, const ListArgs args, const MaskTables m,
     const float* __restrict__ lse, const float* __restrict__ delta, int64_t n_stats, float* __restrict__ stats,
@@ -976,8 +1023,17 @@ __global__ __launch_bounds__(kSchedThreads) void sched_bwd_kernel(
   const int b = blockIdx.x;
   if (b < 2) {
     const ListJob& j = b == 0 ? kv : qt;
-    if (Mode == kChained && b == 1) return;         // (the one-pass kernel has key tiles only)
-    build_list<Mode>(b == 0, j.tile, j.inner, args, m, j.tile_cap, j.hdr, j.item_off, j.tiles, s_item, &s_area, s_fl, chain, split);
+    const Item mine = my_item(args, m);
+    if (Other != Mode && !one_pass_pays(split, m, mine, args.n_work)) {
+      build_list<Other>(b == 0, j.tile, j.inner, args, m, j.tile_cap, j.hdr, j.item_off, j.tiles, s_item, &s_area, s_fl, nullptr, split, mine);
+    } else if (Mode == kChained && b == 1) {        // the one-pass kernel has key tiles only
+      if (Other != Mode && threadIdx.x == 0) {
+        j.hdr->n_tiles = 0;
+        j.hdr->path = kPathOnePass;
+      }
+    } else {
+      build_list<Mode>(b == 0, j.tile, j.inner, args, m, j.tile_cap, j.hdr, j.item_off, j.tiles, s_item, &s_area, s_fl, chain, split, mine);
+    }
   } else if (b < 2 + stat_blocks) {
     const int64_t stride = (int64_t)stat_blocks * kSchedThreads;
     for (int64_t i = (int64_t)(b - 2) * kSchedThreads + threadIdx.x; i < n_stats; i += stride) {
@@ -988,7 +1044,12 @@ __global__ __launch_bounds__(kSchedThreads) void sched_bwd_kernel(
     if constexpr (Mode != kWhole)
       for (int64_t i = (int64_t)(b - 2) * kSchedThreads + threadIdx.x; i < n_flags; i += stride) flags[i] = 0;
   } else {   // direct mode: the row states, and the accumulator rows that are accumulated into cleared
-    row_states<Mode == kSplit>(2 + stat_blocks, gridDim.x - 2 - stat_blocks, states, args, m, s_item, s_fl, &s_area, split);
+    const Item mine = my_item(args, m);
+    const int first = 2 + stat_blocks, count = gridDim.x - first;
+    if (Other == kSplit && Other != Mode && !one_pass_pays(split, m, mine, args.n_work))
+      row_states<true>(first, count, states, args, m, s_item, s_fl, &s_area, split, mine);
+    else
+      row_states<Mode == kSplit>(first, count, states, args, m, s_item, s_fl, &s_area, split, mine);
   }
 }
 
@@ -1078,7 +1139,7 @@ int launch_schedule_bwd(int64_t kv_row_bytes, const int32_t* q_limit, const int3
                         const fcp_work_desc* work, int64_t n_work, const int32_t* cu_seqlens_kv, int32_t n_seqs,
                         int32_t tq, int32_t tkv, int64_t cap_kv, void* region_kv, int32_t dq_tile, int64_t cap_q, void* region_q,
                         const float* lse, const float* delta, int64_t n_stats, float* stats, hipStream_t stream,
-                        const RowStates* states, int32_t* chain, int32_t* flags, int64_t n_flags, const SplitTiles* split) {
+                        const RowStates* states, int32_t* chain, int32_t* flags, int64_t n_flags, const SplitTiles* split, bool either) {
   if (states) { const int rcs = check_row_states(n_work); if (rcs != FCP_OK) return rcs; }
   int64_t stat_blocks = (n_stats + kSchedThreads * 4 - 1) / (kSchedThreads * 4);
   if (stat_blocks > 1024) stat_blocks = 1024;
@@ -1087,7 +1148,9 @@ int launch_schedule_bwd(int64_t kv_row_bytes, const int32_t* q_limit, const int3
   SplitArgs sp{};
   if (split) sp = {split->group, split->kv_units, split->q_units, dq_tile, split->n_cu, split->min_steps, split->key_turns, split->row_turns};
   // (a kernel of its own for each mode: a longer one begins later)
-  const auto kernel = chain ? sched_bwd_kernel<kChained> : split ? sched_bwd_kernel<kSplit> : sched_bwd_kernel<kWhole>;
+  const bool cuts = split && split->cuts;
+  const auto kernel = chain && either ? (cuts ? sched_bwd_kernel<kChained, kSplit> : sched_bwd_kernel<kChained, kWhole>)
+                      : chain ? sched_bwd_kernel<kChained> : cuts ? sched_bwd_kernel<kSplit> : sched_bwd_kernel<kWhole>;
   hipLaunchKernelGGL(kernel, dim3((unsigned)(2 + stat_blocks + state_blocks)), dim3(kSchedThreads), 0, stream,
                      list_job(region_kv, n_work, kBwdBN, kBwdBM, cap_kv), list_job(region_q, n_work, dq_tile, kDqBN, cap_q),
                      list_args(kv_row_bytes, work, n_work, cu_seqlens_kv, n_seqs, tq, tkv, 1, false),

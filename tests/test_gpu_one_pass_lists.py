@@ -1,4 +1,5 @@
 """GPU parity of the one-pass backward on lists that callers write themselves."""
+import numpy as np
 import pytest
 
 import listed
@@ -108,3 +109,72 @@ def test_one_pass_beside_another_streams_work():
         assert B.fcp_scratch_status(scratch)[1] == 0
         for a, b in zip(got, first):
             assert torch.equal(a, b), call
+
+
+_SHORT = [int(x) for x in np.random.default_rng(7).integers(20, 120, 59)]
+
+
+@pytest.mark.parametrize("lens,hq,path", [
+    ([90] + _SHORT, 32, listed.ONE_PASS),
+    ([1500] + _SHORT[:30] + [40] * 20, 32, listed.SPLIT_KEYS),                       # two passes, key tiles in pieces
+    ([4000] + _SHORT[:30], 24, 0),                                                   # two passes, whole tiles
+    ([3000] + _SHORT + [100] * 10, 8, listed.ONE_PASS),                              # one query head per KV head: one pass, whatever the lengths
+])
+@pytest.mark.parametrize("family", ["plain", "direct"])
+def test_the_longest_sequence_decides_between_one_pass_and_two(family, lens, hq, path):
+    """The mean length is short in all of these lists; the scheduler sees the longest one."""
+    import paper_2602_21788_amd.binding as B
+    hkv, D = 8, 128
+    assert sum(lens) <= 256 * len(lens) and sum(lens) >= 4096
+    items = [(s, 0, n, [(0, n)]) for s, n in enumerate(lens)]
+    q, k, v, do = listed.draw(lens, hq, hkv, D, 15)
+    lse, delta, ref = listed.reference(lens, items, q, k, v, do, D ** -0.5)
+    print(f"one pass or two: {len(lens)} sequences, the longest of {max(lens)}, {hq} heads, {family}", flush=True)
+    got, scratch = listed.run_backward(B, family, lens, listed.work_list(B, lens, items), q, k, v, do, lse, delta, D ** -0.5)
+    assert B.fcp_scratch_status(scratch)[1] == 0 and listed.backward_path(scratch) == path
+    listed.check(got, ref, TOL_BF16_REL, family)
+
+
+def test_a_captured_backward_decides_anew_at_every_replay():
+    """The choice between one pass and two is made on the device: a graph replayed on another list of the same size takes that list's way."""
+    import torch
+    import paper_2602_21788_amd.binding as B
+    hq, hkv, D, dev = 32, 8, 128, "cuda:0"
+    lists = {}
+    for name, lens in (("short", [100] * 45), ("long", [1500] + [60] * 43 + [420])):
+        items = [(s, 0, n, [(0, n)]) for s, n in enumerate(lens)]
+        q, k, v, do = listed.draw(lens, hq, hkv, D, 16)
+        lse, delta, ref = listed.reference(lens, items, q, k, v, do, D ** -0.5)
+        lists[name] = ([x.to(dev) for x in (q, k, v, do, lse, delta, torch.from_numpy(listed.offsets(lens)))] +
+                       [torch.from_numpy(listed.work_list(B, lens, items).view("u1").copy()).to(dev)], ref)
+    t = [x.clone() for x in lists["short"][0]]
+    T = t[0].shape[0]
+    scratch = listed.scratch_for(B, T, hq, hkv, D, 45)
+    shapes = ((T, hq, D), (T, hkv, D), (T, hkv, D))
+    acc = [torch.full(s, float("nan"), device=dev) for s in shapes]
+    out = [torch.full(s, float("nan"), device=dev, dtype=torch.bfloat16) for s in shapes]
+
+    def backward():
+        B.fcp_attn_bwd_step_direct(*t, D ** -0.5, *acc, *out, scratch)
+        B.fcp_grad_finalize_direct(*acc, *out, scratch, 45)
+
+    backward()
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        backward()
+    for name in ("short", "long", "long", "short", "long"):
+        tensors, ref = lists[name]
+        for a, b in zip(t, tensors):
+            a.copy_(b)
+        torch.cuda.synchronize()
+        print(f"captured backward, {name} list", flush=True)
+        graph.replay()
+        torch.cuda.synchronize()
+        replayed = [x.clone() for x in out]
+        assert listed.backward_path(scratch) == (listed.ONE_PASS if name == "short" else listed.SPLIT_KEYS)
+        listed.check(replayed, ref, TOL_BF16_REL, name)
+        backward()
+        torch.cuda.synchronize()
+        for a, b in zip(replayed, out):
+            assert torch.equal(a.view(torch.int16), b.view(torch.int16)), name
