@@ -446,7 +446,8 @@ static int bwd_step(const void* q, const void* k, const void* v, const void* d_o
   void* region_kv = scratch;
   void* region_q = static_cast<char*>(scratch) + fcp::sched_region_bytes(n_work, cap_kv);
   float* stats = reinterpret_cast<float*>(static_cast<char*>(region_q) + fcp::sched_region_bytes(n_work, cap_q));
-  int dev = 0, n_cu = 0;
+  if (direct) { const int rcs = fcp::check_row_states(n_work); if (rcs != FCP_OK) return rcs; }
+  int dev = 0, n_cu = 0;                            // (arguments are refused without a device)
   FCP_HIP_CHECK(hipGetDevice(&dev));
   FCP_HIP_CHECK(hipDeviceGetAttribute(&n_cu, hipDeviceAttributeMultiprocessorCount, dev));
   // One pass or two.  The one-pass kernel (csrc/fcp_attn_bwd_fused.hip) forms S and dP once and needs no query-tile launch; it has the

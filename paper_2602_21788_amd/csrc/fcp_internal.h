@@ -168,6 +168,7 @@ struct RowStates {
   int32_t n_parts;
   bool check_step;
 };
+int check_row_states(int64_t n_work);   // error of a list that is too long for them
 int launch_row_states(int64_t kv_row_bytes, const RowStates& rs, const int32_t* q_limit, const int32_t* k_from,
                       const fcp_work_desc* work, int64_t n_work, const int32_t* cu_seqlens_kv, int32_t n_seqs,
                       int32_t tq, int32_t tkv, hipStream_t stream);

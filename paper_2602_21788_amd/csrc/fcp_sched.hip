@@ -1140,7 +1140,6 @@ int launch_schedule_bwd(int64_t kv_row_bytes, const int32_t* q_limit, const int3
                         int32_t tq, int32_t tkv, int64_t cap_kv, void* region_kv, int32_t dq_tile, int64_t cap_q, void* region_q,
                         const float* lse, const float* delta, int64_t n_stats, float* stats, hipStream_t stream,
                         const RowStates* states, int32_t* chain, int32_t* flags, int64_t n_flags, const SplitTiles* split, bool either) {
-  if (states) { const int rcs = check_row_states(n_work); if (rcs != FCP_OK) return rcs; }
   int64_t stat_blocks = (n_stats + kSchedThreads * 4 - 1) / (kSchedThreads * 4);
   if (stat_blocks > 1024) stat_blocks = 1024;
   if (stat_blocks < 1) stat_blocks = 1;
