@@ -178,3 +178,65 @@ def test_a_captured_backward_decides_anew_at_every_replay():
         torch.cuda.synchronize()
         for a, b in zip(replayed, out):
             assert torch.equal(a.view(torch.int16), b.view(torch.int16)), name
+
+
+@pytest.mark.parametrize("hq,hkv,segments", [(8, 8, 1), (16, 8, 2), (16, 16, 1), (24, 8, 1)])
+@pytest.mark.parametrize("family", ["plain", "direct"])
+def test_one_pass_with_full_attention_spans(family, hq, hkv, segments):
+    """Spans that cross the borders of 32-row blocks, key groups and key tiles, a sequence that is one span (its tiles all begin at the
+    first block) and spans at a sequence's ends: the order of a chain and the blocks that its tiles begin at follow from the mask."""
+    import paper_2602_21788_amd.binding as B
+    D = 128
+    lens = [300, 1, 129, 513, 260, 64, 400] + [150] * (19 if hq == 24 else 2)        # (three heads per KV head: 256 key tiles at least)
+    spans = [(0, 20, 200), (2, 127, 2), (3, 0, 513), (4, 0, 40), (4, 120, 20), (4, 250, 10), (6, 31, 2), (6, 95, 66), (6, 255, 140)]
+    items = [(s, 0, n, [(0, n)] if segments == 1 or n < 4 else [(n // 3, n - n // 3), (0, n // 3)]) for s, n in enumerate(lens)]
+    q, k, v, do = listed.draw(lens, hq, hkv, D, 17)
+    lse, delta, ref = listed.reference(lens, items, q, k, v, do, D ** -0.5, spans)
+    print(f"one-pass backward with spans: {hq}/{hkv} heads, {segments} segments, {family}", flush=True)
+    got, scratch = listed.run_backward(B, family, lens, listed.work_list(B, lens, items), q, k, v, do, lse, delta, D ** -0.5, spans=spans)
+    assert B.fcp_scratch_status(scratch)[1] == 0 and listed.backward_path(scratch) == listed.ONE_PASS
+    listed.check(got, ref, TOL_BF16_REL, family)
+
+
+@pytest.mark.parametrize("family", ["plain", "direct"])
+def test_one_pass_inside_larger_buffers_is_not_overrun(family):
+    """Every tensor is the front of a larger allocation: the rows after the inputs hold NaN, those after the accumulators and outputs a
+    sentinel; the last sequence is no multiple of any tile.  Rows past the end read as zero, stores past it are dropped."""
+    import torch
+    import paper_2602_21788_amd.binding as B
+    dev, hq, hkv, D, pad, sentinel = "cuda:0", 16, 8, 128, 300, 1024.0
+    lens = [129, 300, 1, 77, 203]
+    items = [(s, 0, n, [(0, n)]) for s, n in enumerate(lens)]
+    cpu = listed.draw(lens, hq, hkv, D, 18)
+    lse, delta, ref = listed.reference(lens, items, *cpu, D ** -0.5)
+    T = cpu[0].shape[0]
+
+    def front(x, fill):
+        big = torch.full((T + pad,) + tuple(x.shape[1:]), fill, dtype=x.dtype, device=dev)
+        big[:T].copy_(x)
+        return big
+    ins = [front(x, float("nan")) for x in cpu]
+    acc = [front(torch.zeros_like(x), sentinel) for x in ref]
+    out = [front(torch.zeros(x.shape, dtype=torch.bfloat16), sentinel) for x in ref]
+    guard = [torch.full((hq * T + 4096,), float("nan"), device=dev) for _ in range(2)]     # statistics: [hq, T], NaN behind them
+    for g, x in zip(guard, (lse, delta)):
+        g[:hq * T].copy_(x.reshape(-1))
+    size = B.fcp_scratch_bytes(B.FCP_SCRATCH_BWD, T, T, hq, hkv, D, len(lens), 1)
+    room = torch.full((size + 4096,), 165, dtype=torch.uint8, device=dev)
+    scratch = room[:size]
+    t = [x[:T] for x in ins] + [g[:hq * T].view(hq, T) for g in guard] + [torch.from_numpy(listed.offsets(lens)).to(dev)]
+    work_d = torch.from_numpy(listed.work_list(B, lens, items).view("u1").copy()).to(dev)
+    print(f"one-pass backward inside larger buffers, {family}", flush=True)
+    if family == "plain":
+        B.fcp_attn_bwd_step(*t, work_d, D ** -0.5, *[x[:T] for x in acc], scratch)
+        got = acc
+    else:
+        B.fcp_attn_bwd_step_direct(*t, work_d, D ** -0.5, *[x[:T] for x in acc], *[x[:T] for x in out], scratch)
+        B.fcp_grad_finalize_direct(*[x[:T] for x in acc], *[x[:T] for x in out], scratch, len(lens))
+        got = out
+    torch.cuda.synchronize()
+    assert B.fcp_scratch_status(scratch)[1] == 0 and listed.backward_path(scratch) == listed.ONE_PASS
+    listed.check([x[:T] for x in got], ref, TOL_BF16_REL, family)
+    for x in acc + out:
+        assert bool((x[T:] == sentinel).all()), "rows after a tensor were written"
+    assert bool((room[size:] == 165).all()), "bytes after the scratch were written"
