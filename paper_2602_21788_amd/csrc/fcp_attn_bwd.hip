@@ -497,8 +497,9 @@ static int bwd_step(const void* q, const void* k, const void* v, const void* d_o
   // Split tiles (see csrc/fcp_sched.hip): worth the scheduler's time where there are a few tiles per CU at most and a serial loop can be
   // long, in 32-row blocks of all heads of a KV head or in 32-key blocks.  In sharded lists a tile's loop is the shorter for
   // the sharding, and its accumulators are mostly shared already.  Measured, scheduling and attention launches: one sequence of 4096 tokens, 8 query
-  // heads on one KV head, 128 channels 950 -> 312 us; 6 on 2, 64 channels 395 -> 177 us; 30 sequences of 20011 tokens in all, 6 on 2, 505 -> 343 us
-  // whole and 305 -> 246 us with the longest one over 3 ranks; 4096 tokens over 3 ranks, 4 on 4, 107 -> 84 us; 4096 tokens, 32 on 8, 628 -> 580 us.
+  // heads on one KV head, 128 channels 952 -> 296 us; 6 on 2, 64 channels 445 -> 175 us; 30 sequences of 20011 tokens in all, 6 on 2, 489 -> 357 us
+  // whole and 316 -> 245 us with the longest one over 3 ranks; 4096 tokens over 3 ranks, 4 on 4, 106 -> 86 us; 4096 tokens, 32 on 8, 609 -> 575 us.
+  // (At the edge the estimate can miss: 9000 tokens over 4 ranks, 12 on 4, 128 channels 367 -> 375 us.)
   const int64_t longest = std::max((int64_t)tq * group / fcp::kBwdBM, (int64_t)tkv / fcp::kDqBN);
   const bool split = (!fused || either) && key_units <= 1024 && n_work <= 1024 && longest >= (tq == tkv ? 24 : 64);
   const fcp::SplitTiles sp{group, hkv, hq / (head_pair ? 2 : 1), n_cu, 12,         // (12 steps at least)
