@@ -69,10 +69,6 @@ __device__ inline void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_b
 template <int N>
 __device__ inline void wait_vmem() { asm volatile("s_waitcnt vmcnt(%0)" :: "n"(N) : "memory"); }
 
-// A copy that the compiler cannot see through: what is derived from it inside a loop is formed there and holds no registers across
-// the loop's other parts.
-__device__ inline int fresh(int v) { asm volatile("" : "+v"(v)); return v; }
-__device__ inline int fresh_uniform(int v) { asm volatile("" : "+s"(v)); return v; }
 // The lane, formed anew: no register holds it, or the thread's number, from the kernel's beginning on.
 __device__ inline int lane_id() {
   int l;

@@ -5,7 +5,7 @@
 // packed sequences of heterogeneous length (Sec. 4.1).  Per row the kernel emits the
 // locally normalised output and LSE = ln sum exp(scaled scores).
 //
-// gfx950 design
+// gfx950 design (128 channels per head, long items; the other lists: csrc/fcp_attn_fwd_small.hip, the rule is at fwd_form below)
 //   * persistent 512-thread blocks (8 wave64, one block per CU, two waves per SIMD) pull
 //     (query tile, head) units from per-XCD counters; the tile list is sorted longest-first by
 //     the scheduler kernel;
@@ -33,34 +33,18 @@
 //   * key tiles completely below the diagonal skip the mask; key tiles completely above a
 //     wave's rows are not computed by that wave (it only keeps the barriers).
 
-#include "fcp_device.h"
+#include "fcp_fwd.h"
+
+#include <algorithm>
 
 namespace fcp {
 namespace {
 
-struct FwdParams {
-  const uint16_t* q;
-  const uint16_t* k;
-  const uint16_t* v;
-  SchedHeader* hdr;
-  const Tile* tiles;
-  float* o_part;
-  float* lse_part;
-  const int32_t* q_limit;   // [tq] last key position each local query row sees, NULL = its own position (causal)
-  uint16_t* o_out;          // running and direct mode: final O as bf16 [tq,hq,D], or NULL
-  float* lse_out;           // direct mode: final LSE [hq,tq]
-  int32_t running;          // 1: slot 0 of o_part / lse_part is the caller's running result, continued and rewritten
-  int32_t direct;           // 1: a tile whose rows no other item of the launch covers writes o_out / lse_out, no partial
-  int32_t tq, hq, hkv;
-  int32_t head_pair;  // 1: a unit is a 128-row tile for TWO heads of one KV head; 0: a 256-row tile for one head
-  float scale_log2;   // softmax_scale * log2(e)
-};
-
-constexpr float kRescaleThreshold = 8.f;   // log2 units
 constexpr int kFwdAhead = 4;               // LDS fragments requested this many MFMAs before their use (3 and 6 measured: no better)
 
 template <int D>
 struct FwdCfg {
+  static_assert(D == 128, "64 channels: csrc/fcp_attn_fwd_small.hip is faster at every size");
   static constexpr int BM = kFwdBM;               // 256 query rows per unit (32 per wave)
   static constexpr int BN = kFwdBN;               // 64 keys per LDS tile
   static constexpr int NWAVE = 8;
@@ -74,7 +58,7 @@ struct FwdCfg {
   static constexpr int RPW = BN / NWAVE;          // tile rows each wave fills
   static constexpr int IPT = RPW / KT::RPI;       // fill instructions per wave per tile and tensor
   static constexpr int FILLS = 2 * IPT;           // ... per tile
-  static constexpr int NKA = D == 128 ? 2 : 4;    // distinct per-lane K read addresses
+  static constexpr int NKA = 2;                   // distinct per-lane K read addresses
   static constexpr int NVA = D / 32;              // distinct per-lane V^T read addresses
   static constexpr int NS = D / 16;               // MFMAs of one 32 x 32 score block
   static constexpr int KB_STRIDE = KT::row_base(32);
@@ -107,7 +91,8 @@ __global__ __launch_bounds__(512, 1) void fwd_kernel(const FwdParams p) {
   const int heads_here = per_xcd ? p.hq / kNumXcd : p.hq;
   const int units_per_tile = heads_here / hpu;
   UnitQueue uq;
-  uq.init(p.hdr, p.tiles, xcd, units_per_tile, &s_next_unit, s_rec);
+  uq.init_dealt(p.hdr, p.tiles, xcd, units_per_tile, per_xcd ? blockIdx.x / kNumXcd : blockIdx.x, per_xcd ? gridDim.x / kNumXcd : gridDim.x, p.tile_cap,
+                &s_next_unit, s_rec);
 
   // ---- per-lane constants -----------------------------------------------------------------
   const int kv_row_bytes = p.hkv * D * 2;
@@ -494,13 +479,43 @@ __global__ __launch_bounds__(512, 1) void fwd_kernel(const FwdParams p) {
 
 using fcp::fail;
 
+// What the static work area must hold: the tile list of the eight-wave kernel (the lists of smaller tiles are taken where they fit too).
+static size_t static_need(int32_t tq, int32_t tkv, int64_t n_work, int32_t n_parts) {
+  return fcp::sched_region_bytes(n_work, fcp::q_tile_cap(tq, tkv, n_work, n_parts)) + fcp::pad_to((size_t)tq, 256);
+}
+
+// Which form works a list.  The items are in device memory; the host has their mean length and the work per CU (units of 128 rows of one head, a
+// row counted once per item that covers it).  Measured, forward step with its scheduling launch, wide / the form chosen, us:
+//   few units, and loops long enough to be divided: the longest unit's loop sets the time.  128 channels, 8 heads: 2000 tokens 56 / 36 (four waves
+//     a row), 4096 tokens 98 / 73 (two), 4096 tokens over 3 ranks 47 / 39.  64 channels, 4 heads: 512 tokens 23 / 18, 4096 82 / 41; several sequences
+//     have a longer longest loop for the same work: 16 of 16384 tokens 125 / 82.  (At twice the bounds the divided form is slower: 16384
+//     tokens over 5 ranks, 6 heads on 2 of 64 channels 75 / 88.)
+//   64 channels otherwise: blocks of four waves, three per CU, at every size: 60000 tokens in 16 sequences, 40 heads on 8 4100 / 3760; 1000 of 128 1050 / 737.
+//   128 channels: short items are mostly beginnings and ends of units, which other blocks of the CU cover: 1000 of 128, 32 heads on 8 922 / 694, 200
+//     of 400 690 / 608, 30 of 667 over 3 ranks 317 / 300; with few units per CU two blocks with 64-key tiles do better than three with 32-key tiles: 4000
+//     tokens in 8 sequences 84 / 77 (three: 85), 8192 tokens of 8 heads 190 / 182 (205).  Long items: the wide form (60000 tokens in 16
+//     sequences 4900; 5020 with three blocks, 5180 with two).
+static fcp::FwdForm fwd_form(int head_dim, int hq, int64_t tq, int64_t tkv, int64_t n_work, int64_t n_parts, int n_cu) {
+  const int64_t rows = std::min(n_parts * tq, tkv);          // of all items together, at most
+  const int64_t mean = n_work > 0 ? rows / n_work : 0;
+  const double per_cu = (double)rows * hq / (128. * n_cu);
+  if (head_dim == 64) {
+    if (mean >= 256 && (per_cu <= 0.5 || (per_cu <= 1. && mean >= 1024))) return fcp::kFwdSplit4;
+    return mean >= 256 && per_cu <= (tq == tkv && n_work >= 8 ? 2.5 : 1.6) ? fcp::kFwdSplit2 : fcp::kFwdSmall;
+  }
+  if (mean >= 256 && per_cu <= 1.1) return per_cu <= 0.55 ? fcp::kFwdSplit4 : fcp::kFwdSplit2;
+  const int64_t units = (rows / 128 + n_work) * hq;
+  if (mean <= 640) return units <= 12 * (int64_t)n_cu ? fcp::kFwdSmall : fcp::kFwdShort;
+  return units <= 6 * (int64_t)n_cu ? fcp::kFwdSmall : fcp::kFwdWide;
+}
+
 // Both entry points; q_limit == NULL is the causal mask.
 static int fwd_step(const void* q, const void* k, const void* v, const int32_t* cu_seqlens_kv,
                     int32_t n_seqs, const fcp_work_desc* work, int64_t n_work, int32_t n_parts,
                     int32_t tq, int32_t tkv, int32_t hq, int32_t hkv, int32_t head_dim,
                     float softmax_scale, const int32_t* q_limit, float* o_part, float* lse_part, void* scratch,
                     size_t scratch_bytes, void* stream, bool running = false, void* o_out = nullptr,
-                    float* lse_out = nullptr) {
+                    float* lse_out = nullptr, bool static_area = false) {
   fcp::clear_error();
   if (!q || !k || !v || !cu_seqlens_kv || !o_part || !lse_part || !scratch)
     return fail(FCP_ERR_INVALID_ARG, "fcp_attn_fwd_step: null pointer");
@@ -515,16 +530,24 @@ static int fwd_step(const void* q, const void* k, const void* v, const int32_t* 
                                reinterpret_cast<uintptr_t>(v) | reinterpret_cast<uintptr_t>(o_part);
   if (align_mask & 15u) return fail(FCP_ERR_INVALID_ARG, "fcp_attn_fwd_step: q/k/v/o_part must be 16-byte aligned");
   if (reinterpret_cast<uintptr_t>(scratch) & 255u) return fail(FCP_ERR_INVALID_ARG, "fcp_attn_fwd_step: scratch must be 256-byte aligned");
-  const size_t need = fcp_scratch_bytes(FCP_SCRATCH_FWD, tq, tkv, hq, hkv, head_dim, n_work, n_parts);
+  const size_t need = static_area ? static_need(tq, tkv, n_work, n_parts)
+                                  : fcp_scratch_bytes(FCP_SCRATCH_FWD, tq, tkv, hq, hkv, head_dim, n_work, n_parts);
   if (scratch_bytes < need) return fail(FCP_ERR_CAPACITY, "fcp_attn_fwd_step: scratch %zu < %zu bytes", scratch_bytes, need);
   if ((int64_t)tq * hq * head_dim * (int64_t)n_parts > ((int64_t)1 << 40))
     return fail(FCP_ERR_UNSUPPORTED, "fcp_attn_fwd_step: partial output too large");
 
   hipStream_t st = (hipStream_t)stream;
-  const int64_t cap = fcp::q_tile_cap(tq, tkv, n_work, n_parts);
-  if (cap > INT32_MAX / 64) return fail(FCP_ERR_UNSUPPORTED, "fcp_attn_fwd_step: too many tiles");
+  if (fcp::q_tile_cap(tq, tkv, n_work, n_parts) > INT32_MAX / 64) return fail(FCP_ERR_UNSUPPORTED, "fcp_attn_fwd_step: too many tiles");
+  if (lse_out) { const int rcs = fcp::check_row_states(n_work); if (rcs != FCP_OK) return rcs; }
+  int dev = 0, n_cu = 256;                          // (arguments are refused without a device)
+  FCP_HIP_CHECK(hipGetDevice(&dev));
+  FCP_HIP_CHECK(hipDeviceGetAttribute(&n_cu, hipDeviceAttributeMultiprocessorCount, dev));
+  const fcp::FwdForm form = fwd_form(head_dim, hq, tq, tkv, n_work, n_parts, n_cu);
+  const int unit_rows = fcp::fwd_unit_rows(form, head_dim);
   // two heads of one KV head per unit when the heads pair up, else twice the rows for one head
-  const int head_pair = ((hq / hkv) % 2 == 0) ? 1 : 0;
+  const int head_pair = ((hq / hkv) % 2 == 0) && unit_rows > 32 ? 1 : 0;
+  const int32_t tile = unit_rows >> head_pair;
+  const int64_t cap = fcp::q_tile_cap(tq, tkv, n_work, n_parts, tile);
   const bool direct = lse_out != nullptr;
   // direct mode: which rows get their final result from one unit and which are merged from partials is worked out on
   // extra blocks of the scheduling launch
@@ -534,7 +557,7 @@ static int fwd_step(const void* q, const void* k, const void* v, const int32_t* 
     rs.q_row_elems = hq * head_dim; rs.kv_row_elems = hkv * head_dim;
     rs.n_parts = n_parts; rs.check_step = true;
   }
-  int rc = fcp::launch_schedule(false, head_pair ? fcp::kFwdBM / 2 : fcp::kFwdBM, fcp::kFwdBN, (int64_t)hkv * head_dim * 2, q_limit, nullptr, work, n_work, cu_seqlens_kv, n_seqs, tq, tkv, n_parts, cap, scratch,
+  int rc = fcp::launch_schedule(false, tile, fcp::kFwdBN, (int64_t)hkv * head_dim * 2, q_limit, nullptr, work, n_work, cu_seqlens_kv, n_seqs, tq, tkv, n_parts, cap, scratch,
                                 running ? nullptr : lse_part, (int64_t)n_parts * hq * tq, st, direct ? &rs : nullptr);
   if (rc != FCP_OK) return rc;
   if (tq == 0 || n_work == 0) return FCP_OK;
@@ -550,24 +573,18 @@ static int fwd_step(const void* q, const void* k, const void* v, const int32_t* 
   p.lse_out = lse_out;
   p.direct = direct ? 1 : 0;
   p.tq = tq; p.hq = hq; p.hkv = hkv;
+  p.tile_cap = (int32_t)cap;
   p.head_pair = head_pair;
   p.scale_log2 = softmax_scale * 1.4426950408889634f;
 
-  int dev = 0, n_cu = 256;
-  FCP_HIP_CHECK(hipGetDevice(&dev));
-  FCP_HIP_CHECK(hipDeviceGetAttribute(&n_cu, hipDeviceAttributeMultiprocessorCount, dev));
   int64_t units = cap * (hq / (head_pair ? 2 : 1));
+  if (form != fcp::kFwdWide) return fcp::launch_fwd_small(p, head_dim, form, units, n_cu, st);
   int64_t blocks = n_cu;                               // one 512-thread block per CU
   if (blocks > units) blocks = (units + 7) / 8 * 8;   // keep a multiple of the XCD count
   if (blocks < 8) blocks = 8;
-  static std::atomic<uint64_t> lds_done[2];
-  if (head_dim == 128) {
-    if ((rc = fcp::raise_lds_limit((const void*)fcp::fwd_kernel<128>, fcp::FwdCfg<128>::LDS_BYTES, lds_done[0])) != FCP_OK) return rc;
-    hipLaunchKernelGGL(fcp::fwd_kernel<128>, dim3((unsigned)blocks), dim3(512), fcp::FwdCfg<128>::LDS_BYTES, st, p);
-  } else {
-    if ((rc = fcp::raise_lds_limit((const void*)fcp::fwd_kernel<64>, fcp::FwdCfg<64>::LDS_BYTES, lds_done[1])) != FCP_OK) return rc;
-    hipLaunchKernelGGL(fcp::fwd_kernel<64>, dim3((unsigned)blocks), dim3(512), fcp::FwdCfg<64>::LDS_BYTES, st, p);
-  }
+  static std::atomic<uint64_t> lds_done;
+  if ((rc = fcp::raise_lds_limit((const void*)fcp::fwd_kernel<128>, fcp::FwdCfg<128>::LDS_BYTES, lds_done)) != FCP_OK) return rc;
+  hipLaunchKernelGGL(fcp::fwd_kernel<128>, dim3((unsigned)blocks), dim3(512), fcp::FwdCfg<128>::LDS_BYTES, st, p);
   FCP_HIP_CHECK(hipGetLastError());
   return FCP_OK;
 }
@@ -600,7 +617,7 @@ extern "C" int fcp_attn_fwd_step_static(const void* q, const void* k, const void
   fcp::clear_error();
   if (tq < 0 || tkv < 1 || n_work < 0 || n_parts < 1 || hq < 1 || hkv < 1)
     return fail(FCP_ERR_INVALID_ARG, "fcp_attn_fwd_step_static: bad sizes");
-  const size_t need = fcp_scratch_bytes(FCP_SCRATCH_FWD, tq, tkv, hq, hkv, head_dim, n_work, n_parts);
+  const size_t need = static_need(tq, tkv, n_work, n_parts);
   if (need > (size_t)FCP_STATIC_SCRATCH_BYTES)
     return fail(FCP_ERR_CAPACITY, "fcp_attn_fwd_step_static: this call needs a work area of %zu bytes, the static one has %zu "
                                   "(use fcp_attn_fwd_step with a caller-owned scratch buffer)", need, (size_t)FCP_STATIC_SCRATCH_BYTES);
@@ -610,7 +627,7 @@ extern "C" int fcp_attn_fwd_step_static(const void* q, const void* k, const void
   // every part of the area that the kernels read is written first by the scheduling launch of the same call (header,
   // counters, offsets, flags, tile records), so what the previous call left needs no clearing
   return fwd_step(q, k, v, cu_seqlens_kv, n_seqs, work, n_work, n_parts, tq, tkv, hq, hkv, head_dim, softmax_scale,
-                  nullptr, o_part, lse_part, area, (size_t)FCP_STATIC_SCRATCH_BYTES, stream);
+                  nullptr, o_part, lse_part, area, (size_t)FCP_STATIC_SCRATCH_BYTES, stream, false, nullptr, nullptr, true);
 }
 
 extern "C" int fcp_attn_fwd_step(const void* q, const void* k, const void* v, const int32_t* cu_seqlens_kv,

@@ -1,0 +1,468 @@
+// The forward's forms for short documents, small problems and 64 channels per head: blocks of four waves, two or three blocks per CU.
+//
+// Same function as fwd_kernel (csrc/fcp_attn_fwd.hip).  There a CU works on one unit at a time, eight waves in lock step: the best form for a
+// long row of key tiles of 128 channels, but whatever the unit waits for at its two ends (record, first tiles and Q rows on their way in, O
+// rows on their way out) the whole CU waits for, and a unit of 256 rows x heads is a serial loop over all their keys while most
+// of the chip may have no unit at all.  Here
+//   * a block has one wave per SIMD and two LDS stages: several blocks share a CU without any lock step, one's beginning and end meet the others'
+//     matrix work, and so do one's exponentials.  64 channels: three blocks of 140 registers (four, with two of them spilled, are as
+//     fast).  128 channels: two with 64-key stages, or three of 168 registers with 32-key stages, which is what the LDS holds;
+//   * a unit = 64 rows x two query heads of one KV head (even number of heads per KV head) or 128 rows of one head; every wave owns 32 rows, all
+//     share the stages, one barrier per stage: scores, softmax and P V of a stage in turn (the fragments requested AH matrix instructions ahead;
+//     all at once is slower with three blocks, the compiler's own order with two);
+//   * SPLIT = 2, 4: groups of SPLIT waves own the same 32 rows and divide the keys of every stage among them, 32 keys each; their
+//     (maximum, sum, O) meet in LDS at the unit's end.  Half (a quarter) of the rows per unit, half (a quarter) of the serial loop, for problems
+//     that would otherwise leave CUs without a unit.  A stage's fills then serve fewer matrix instructions, so it does not pay where units
+//     abound (60000 tokens in 16 sequences, 32 heads on 8: 5180 -> 6300 us with two).
+// Priorities as in fwd_kernel (matrix stream first) gain 1 % on long items and lose 1 to 3 % elsewhere; none are set.
+// Times of the forms beside each other and where each is taken: fwd_form in csrc/fcp_attn_fwd.hip.
+#include "fcp_fwd.h"
+
+namespace fcp {
+namespace {
+
+template <int D, int NW, int SPLIT, int SKEYS>
+struct SmallCfg {
+  static constexpr int NWAVE = NW;
+  static constexpr int RG = NWAVE / SPLIT;        // groups of 32 rows (of one or two heads)
+  static constexpr int SK = SKEYS;                // keys per stage
+  static constexpr int NB = SK / 32 / SPLIT;      // 32-key blocks of a stage per wave
+  using KT = RowTile<D>;
+  using VT = TrTile<D>;
+  using QT = DualTile<D>;
+  static constexpr int KBYTES = KT::bytes(SK);
+  static constexpr int STAGE = KBYTES + VT::bytes(SK);
+  static constexpr int max_of(int a, int b) { return a > b ? a : b; }
+  static constexpr int LDS_BYTES = max_of(max_of(2 * STAGE, STAGE + NWAVE * QT::bytes(32)), SPLIT > 1 ? NWAVE * 32 * D * 4 : NWAVE * RowStage<D>::BYTES);
+  static constexpr int RPW = SK / NWAVE;          // tile rows each wave fills
+  static constexpr int IPT = RPW / KT::RPI;       // fill instructions per wave, stage and tensor
+  static constexpr int NKF = D == 128 || IPT == 1 ? 1 : 2;    // distinct lane offsets of K fills (the row permutation of D = 64 has a period of 16 rows)
+  static constexpr int NKA = D == 128 ? 2 : 4;    // distinct per-lane K read addresses
+  static constexpr int NVA = D / 32;              // distinct per-lane V^T read addresses
+  static constexpr int NS = D / 16;               // MFMAs of one 32 x 32 score block
+  static constexpr int KB_STRIDE = KT::row_base(32);
+  static constexpr int PARTS = SPLIT < NVA ? SPLIT : NVA;   // waves of a group that combine, each NVA / PARTS channel blocks
+  static_assert(RPW % KT::RPI == 0 && KT::row_base(RPW * 3 + KT::RPI) == KT::row_base(RPW * 3) + KT::row_base(KT::RPI), "a wave's rows start on a padding group boundary");
+};
+
+template <int D, int NW, int SPLIT, int SKEYS, int OCC, int AH>
+__global__ __launch_bounds__(64 * NW, OCC) void fwd_small_kernel(const FwdParams p) {
+  using C = SmallCfg<D, NW, SPLIT, SKEYS>;
+  using KT = typename C::KT;
+  using VT = typename C::VT;
+  using QT = typename C::QT;
+  extern __shared__ __attribute__((aligned(256))) unsigned char smem[];
+  __shared__ int32_t s_next_unit;
+  __shared__ int32_t s_rec[16];
+  __shared__ __attribute__((aligned(16))) float s_rowf[C::NWAVE][32];   // per wave: one factor per query row
+  __shared__ __attribute__((aligned(16))) float s_rowl[C::NWAVE][32];   // SPLIT > 1: ... and its share of the row sum
+
+  const int tid = threadIdx.x;
+  const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int share = wave % SPLIT;                 // which 32 (or 64) keys of a stage
+  const int group = wave / SPLIT;
+  const int l32 = lane & 31, g2 = lane >> 5;
+  const int G = p.hq / p.hkv;
+  const uint32_t lds0 = lds_offset(smem);
+
+  // unit numbering as in fwd_kernel: each XCD owns a contiguous eighth of the heads where they split evenly
+  const int hpu = p.head_pair ? 2 : 1;
+  const bool per_xcd = (p.hq % (kNumXcd * hpu)) == 0;
+  const int xcd = per_xcd ? (int)(blockIdx.x % kNumXcd) : 0;
+  const int heads_here = per_xcd ? p.hq / kNumXcd : p.hq;
+  const int units_per_tile = heads_here / hpu;
+  UnitQueue uq;
+  uq.init_dealt(p.hdr, p.tiles, xcd, units_per_tile, per_xcd ? blockIdx.x / kNumXcd : blockIdx.x, per_xcd ? gridDim.x / kNumXcd : gridDim.x, p.tile_cap,
+                &s_next_unit, s_rec);
+
+  const int kv_row_bytes = p.hkv * D * 2;
+  int kfill[C::NKF];
+#pragma unroll
+  for (int i = 0; i < C::NKF; ++i) kfill[i] = fill_voff<KT>(C::RPW, wave, i, lane, kv_row_bytes) - i * KT::RPI * kv_row_bytes;
+  const int vfill = fill_voff<VT>(C::RPW, wave, 0, lane, kv_row_bytes);
+  // fragment addresses as in fwd_kernel, from the wave's first key block of a stage on
+  int kaddr[C::NKA];
+#pragma unroll
+  for (int j = 0; j < C::NKA; ++j) kaddr[j] = tile_off<KT>(l32, 2 * j + g2) + (SPLIT > 1 ? share * C::KB_STRIDE : 0);
+  int vaddr[C::NVA];
+  {
+    const int row0 = 4 * g2 + ((lane & 15) >> 2);
+    const int chunk0 = 2 * ((lane >> 4) & 1) + ((lane & 3) >> 1);
+#pragma unroll
+    for (int db = 0; db < C::NVA; ++db)
+      vaddr[db] = C::KBYTES + tile_off<VT>(row0, 4 * db + chunk0) + 8 * (lane & 1) + (SPLIT > 1 ? share * VT::row_base(32) : 0);
+  }
+
+  for (;;) {
+    const int unit = uq.current(&s_next_unit);
+    if (unit >= uq.n_units) break;
+    const QTile t = read_record<QTile, 12>(s_rec);
+    const int second = p.head_pair && C::RG > 1 ? group / (C::RG / 2 > 0 ? C::RG / 2 : 1) : 0;
+    const int head = xcd * heads_here + (unit % units_per_tile) * hpu + second;
+    const int kvh = head / G;
+
+    const int wave_r0 = 32 * (p.head_pair ? group % (C::RG / 2 > 0 ? C::RG / 2 : 1) : group);
+    const bool wave_active = wave_r0 < t.rows;
+    const int my_row = wave_r0 + l32;
+    const bool row_valid = my_row < t.rows;
+    const int row_ld = min(my_row, t.rows - 1);
+    // last key position the lane's row sees, and the least and greatest such limit among the wave's rows
+    int q_lim = t.q_pos0 + my_row;
+    int wave_first_lim = t.q_pos0 + wave_r0;
+    int wave_last_lim = t.q_pos0 + min(wave_r0 + 31, t.rows - 1);
+    if (p.q_limit) {
+      const int32_t* ql = p.q_limit + t.q_row0;
+      q_lim = ql[row_ld];
+      wave_first_lim = __builtin_amdgcn_readfirstlane(ql[min(wave_r0, t.rows - 1)]);
+      wave_last_lim = __builtin_amdgcn_readfirstlane(ql[min(wave_r0 + 31, t.rows - 1)]);
+      __builtin_amdgcn_s_waitcnt(kWaitVm0);
+    }
+    // the two segments' fields as scalars (indexed with a run-time segment number the record would land in scratch memory)
+    const int vis0 = t.vis[0], vis1 = t.vis[1], kpos0 = t.k_pos0[0], kpos1 = t.k_pos0[1];
+    const int nt0 = (vis0 + C::SK - 1) / C::SK, nt1 = (vis1 + C::SK - 1) / C::SK;
+    const int n_iter = nt0 + nt1;
+
+    // ---- fills: as in fwd_kernel, stage by stage in list order
+    i32x4 f_rk, f_rv;
+    auto f_resources = [&](int64_t row0, int vis) {
+      const int64_t off = (row0 * p.hkv + kvh) * D;
+      const int bytes = vis > 0 ? (vis - 1) * kv_row_bytes + D * 2 : 0;
+      f_rk = buffer_rsrc(p.k + off, bytes);
+      f_rv = buffer_rsrc(p.v + off, bytes);
+    };
+    f_resources(t.kv_row0[0], vis0);
+    int f_left = nt0, f_soff = 0;
+    bool f_seg0 = true;
+    uint32_t f_dst = 0;
+    const uint32_t f_k = lds0 + KT::row_base(C::RPW * wave), f_v = lds0 + C::KBYTES + VT::row_base(C::RPW * wave);
+    auto fill_next = [&]() {
+      if (f_seg0 && f_left == 0) { f_resources(t.kv_row0[1], vis1); f_seg0 = false; f_soff = 0; }
+#pragma unroll
+      for (int i = 0; i < C::IPT; ++i) {
+        const int so = f_soff + i * KT::RPI * kv_row_bytes;
+        lds_fill_b128(f_rk, f_k + f_dst + KT::row_base(KT::RPI * i), kfill[i % C::NKF], so);
+        lds_fill_b128(f_rv, f_v + f_dst + VT::row_base(VT::RPI * i), vfill, so);
+      }
+      --f_left;
+      f_soff += C::SK * kv_row_bytes;
+      f_dst = C::STAGE - f_dst;
+    };
+
+    // Prologue: the first stage and the wave's Q rows (whole rows through the second stage, which the first fill of the loop takes over
+    // after the barrier that ends the reads here).
+    if (n_iter > 0) fill_next();
+    bf16x8 qf[C::NS];
+    {
+      int lane_p = lane;                            // addresses formed here, not ahead of the unit loop (registers)
+      asm volatile("" : "+v"(lane_p));
+      const int q_row_bytes = p.hq * D * 2;
+      const int n_wave_rows = t.rows - wave_r0;
+      const i32x4 rq = buffer_rsrc(p.q + ((int64_t)(t.q_row0 + wave_r0) * p.hq + head) * D,
+                                   n_wave_rows > 0 ? (min(n_wave_rows, 32) - 1) * q_row_bytes + D * 2 : 0);
+      const int area = C::STAGE + wave * QT::bytes(32);
+#pragma unroll
+      for (int i = 0; i < 32 / QT::RPI; ++i)
+        lds_fill_b128(rq, lds0 + area + QT::row_base(QT::RPI * i), fill_voff<QT>(32, 0, i, lane_p, q_row_bytes), 0);
+      __builtin_amdgcn_s_waitcnt(kWaitVm0);
+#pragma unroll
+      for (int ks = 0; ks < C::NS; ++ks)
+        qf[ks] = *reinterpret_cast<const bf16x8*>(smem + area + tile_off<QT>(lane_p & 31, 2 * ks + (lane_p >> 5)));
+      __builtin_amdgcn_s_waitcnt(0xC07F);           // lgkmcnt(0): in registers before anybody fills the second stage
+    }
+    f32x16 oacc[C::NVA];
+#pragma unroll
+    for (int db = 0; db < C::NVA; ++db) oacc[db] = zero16();
+    float m_run = -INFINITY;   // running maximum in log2 units (score * scale_log2)
+    float l_run = 0.f;         // this lane's share of the running sum
+    const int slot = p.running ? 0 : t.step;
+    if (p.running && share == 0) {                  // the caller's merged result is one more block of keys, see fwd_kernel
+      const float lse_prev = p.lse_part[(int64_t)head * p.tq + t.q_row0 + row_ld];
+      const int row_bytes = fresh_uniform(p.hq * D * 4);   // (the rows' offsets are formed here, not ahead of the unit loop)
+      const int n_wave_rows = t.rows - wave_r0;
+      const __amdgpu_buffer_rsrc_t ri = __builtin_amdgcn_make_buffer_rsrc(
+          (void*)(p.o_part + ((int64_t)(t.q_row0 + wave_r0) * p.hq + head) * D), (short)0,
+          n_wave_rows > 0 ? (n_wave_rows - 1) * row_bytes + D * 4 : 0, 0x00020000);
+      const int o_voff = 4 * g2 * row_bytes + 4 * l32;
+#pragma unroll
+      for (int db = 0; db < C::NVA; ++db)
+#pragma unroll
+        for (int i = 0; i < 16; ++i)
+          oacc[db][i] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(
+              ri, o_voff, (8 * (i / 4) + (i % 4)) * row_bytes + 128 * db, 0));
+      const bool has_prev = lse_prev > -INFINITY;
+      if (has_prev) {
+        m_run = lse_prev * kLog2e;
+        l_run = g2 == 0 ? 1.f : 0.f;
+      }
+      __builtin_amdgcn_s_waitcnt(kWaitVm0);
+      s_rowf[wave][l32] = has_prev ? 1.f : 0.f;
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        const f32x4 a = *reinterpret_cast<const f32x4*>(&s_rowf[wave][8 * j + 4 * g2]);
+#pragma unroll
+        for (int db = 0; db < C::NVA; ++db)
+#pragma unroll
+          for (int e = 0; e < 4; ++e) oacc[db][4 * j + e] = a[e] != 0.f ? oacc[db][4 * j + e] : 0.f;
+      }
+    }
+    auto scale_rows = [&](float f) {                // see fwd_kernel
+      s_rowf[wave][l32] = f;
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        const f32x4 a = *reinterpret_cast<const f32x4*>(&s_rowf[wave][8 * j + 4 * g2]);
+#pragma unroll
+        for (int db = 0; db < C::NVA; ++db)
+#pragma unroll
+          for (int e = 0; e < 4; ++e) oacc[db][4 * j + e] *= a[e];
+      }
+    };
+
+    // ---- the unit: per stage one barrier, then scores, softmax and P V of the wave's keys.  At the barrier the wave's part of the stage has
+    // landed; the other stage was last read before it.
+    for (int it = 0; it < n_iter; ++it) {
+      __builtin_amdgcn_s_waitcnt(kWaitVm0);
+      __syncthreads();
+      if (it + 1 < n_iter) fill_next();
+      const bool seg1 = it >= nt0;
+      const int k0 = (it - (seg1 ? nt0 : 0)) * C::SK + (SPLIT > 1 ? 32 * share : 0);    // the wave's first key of the segment
+      const int k_pos = (seg1 ? kpos1 : kpos0) + k0;
+      const int n_valid = (seg1 ? vis1 : vis0) - k0;
+      if (!wave_active || n_valid <= 0 || k_pos > wave_last_lim) continue;
+      const unsigned char* const stage = smem + (it & 1) * C::STAGE;
+      constexpr int kAhead = AH;
+      f32x16 sacc[C::NB];
+      {
+        constexpr int N = C::NB * C::NS;
+        bf16x8 fr[N];
+        auto request = [&](int f) {
+          if (f >= N) return;
+          const int kb = f / C::NS, ks = f % C::NS;
+          fr[f] = *reinterpret_cast<const bf16x8*>(stage + kaddr[ks % C::NKA] + (ks / C::NKA) * (C::NKA * 32) + kb * C::KB_STRIDE);
+        };
+#pragma unroll
+        for (int x = 0; x < kAhead; ++x) request(x);
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int x = 0; x < N; ++x) {
+          sacc[x / C::NS] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fr[x], qf[x % C::NS], x % C::NS == 0 ? zero16() : sacc[x / C::NS], 0, 0, 0);
+          request(x + kAhead);
+          __builtin_amdgcn_sched_barrier(0);
+        }
+      }
+      constexpr int NV = 2 * C::NB * C::NVA;
+      bf16x8 vf[NV];
+      auto v_request = [&](int f) {
+        if (f >= NV) return;
+        const int tt = f / C::NVA, db = f % C::NVA;
+        vf[f] = tr_read_8(stage + vaddr[db] + tt * (16 * VT::row_base(1)), 8 * VT::row_base(1));
+      };
+#pragma unroll
+      for (int x = 0; x < kAhead; ++x) v_request(x);
+      // mask, lazy running maximum, exponentials, row sum, conversion: see fwd_kernel
+      if (k_pos + 32 * C::NB - 1 > wave_first_lim || n_valid < 32 * C::NB) {
+        const int lim = min(n_valid, q_lim - k_pos + 1) - 4 * g2;
+#pragma unroll
+        for (int kb = 0; kb < C::NB; ++kb)
+#pragma unroll
+          for (int i = 0; i < 16; ++i)
+            if (32 * kb + 8 * (i / 4) + (i % 4) >= lim) sacc[kb][i] = -INFINITY;
+      }
+      float mx = max3(sacc[0][0], sacc[0][1], sacc[C::NB - 1][0]);
+#pragma unroll
+      for (int kb = 0; kb < C::NB; ++kb)
+#pragma unroll
+        for (int i = kb == 0 ? 2 : 0; i < 16; i += 2) mx = max3(mx, sacc[kb][i], sacc[kb][i + 1]);
+      mx = lane32_partner_max(mx) * p.scale_log2;
+      if (__builtin_amdgcn_ballot_w64(mx > m_run + kRescaleThreshold) != 0) {
+        const float m_new = fmaxf(m_run, mx);
+        const float alpha = __builtin_amdgcn_exp2f(m_run - (m_new == -INFINITY ? 0.f : m_new));
+        m_run = m_new;
+        l_run *= alpha;
+        scale_rows(alpha);
+      }
+      const float m_use = m_run == -INFINITY ? 0.f : m_run;
+      float psum = 0.f;
+      bf16x8 pf[2 * C::NB];
+#pragma unroll
+      for (int e = 0; e < 16 * C::NB; e += 2) {
+        const float e0 = __builtin_amdgcn_exp2f(fmaf(sacc[e / 16][e % 16], p.scale_log2, -m_use));
+        const float e1 = __builtin_amdgcn_exp2f(fmaf(sacc[e / 16][e % 16 + 1], p.scale_log2, -m_use));
+        psum += e0;
+        psum += e1;
+        pf[e / 8][e % 8] = (__bf16)e0;
+        pf[e / 8][e % 8 + 1] = (__bf16)e1;
+      }
+      l_run += psum;
+      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int x = 0; x < NV; ++x) {
+        oacc[x % C::NVA] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(pf[x / C::NVA], vf[x], oacc[x % C::NVA], 0, 0, 0);
+        v_request(x + kAhead);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+    }
+    __syncthreads();                                // the stages are free
+    uq.prefetch();                                  // ahead of the epilogue's stores, see fwd_kernel
+
+    // ---- epilogue
+    float l_tot = lane32_partner_sum(l_run);
+    if constexpr (SPLIT > 1) {
+      // The group's waves leave (maximum, sum, O) in LDS, lane by lane in the accumulator layout; wave `share` of PARTS combines its channel blocks.
+      s_rowf[wave][l32] = m_run;
+      s_rowl[wave][l32] = l_tot;
+      unsigned char* const mine = smem + wave * (32 * D * 4);
+#pragma unroll
+      for (int db = 0; db < C::NVA; ++db)
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+          f32x4 v;
+#pragma unroll
+          for (int e = 0; e < 4; ++e) v[e] = oacc[db][4 * j + e];
+          *reinterpret_cast<f32x4*>(mine + (db * 4 + j) * 1024 + lane * 16) = v;
+        }
+      __syncthreads();
+      const int w0 = group * SPLIT;
+      auto at = [&](const float (*a)[32], int w, int j) { return *reinterpret_cast<const f32x4*>(&a[w0 + w][8 * j + 4 * g2]); };
+      m_run = s_rowf[w0][l32];
+#pragma unroll
+      for (int w = 1; w < SPLIT; ++w) m_run = fmaxf(m_run, s_rowf[w0 + w][l32]);
+      l_tot = 0.f;
+#pragma unroll
+      for (int w = 0; w < SPLIT; ++w) l_tot += s_rowl[w0 + w][l32] * __builtin_amdgcn_exp2f(s_rowf[w0 + w][l32] - (m_run == -INFINITY ? 0.f : m_run));
+      constexpr int NO = C::NVA / C::PARTS;         // channel blocks per combining wave: db = share * NO + o
+      f32x16 out[NO];
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {                 // four rows at a time, see scale_rows
+        f32x4 m4 = at(s_rowf, 0, j), f4[SPLIT], l4 = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int w = 1; w < SPLIT; ++w)
+#pragma unroll
+          for (int e = 0; e < 4; ++e) m4[e] = fmaxf(m4[e], at(s_rowf, w, j)[e]);
+#pragma unroll
+        for (int w = 0; w < SPLIT; ++w)
+#pragma unroll
+          for (int e = 0; e < 4; ++e) {
+            f4[w][e] = __builtin_amdgcn_exp2f(at(s_rowf, w, j)[e] - (m4[e] == -INFINITY ? 0.f : m4[e]));
+            l4[e] += f4[w][e] * at(s_rowl, w, j)[e];
+          }
+#pragma unroll
+        for (int e = 0; e < 4; ++e) l4[e] = l4[e] > 0.f ? 1.f / l4[e] : 0.f;
+#pragma unroll
+        for (int o = 0; o < NO; ++o) {
+          f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+          const int db = (share < C::PARTS ? share : 0) * NO + o;
+#pragma unroll
+          for (int w = 0; w < SPLIT; ++w) {
+            const f32x4 v = *reinterpret_cast<const f32x4*>(smem + (w0 + w) * (32 * D * 4) + (db * 4 + j) * 1024 + lane * 16);
+#pragma unroll
+            for (int e = 0; e < 4; ++e) acc[e] += f4[w][e] * v[e];
+          }
+#pragma unroll
+          for (int e = 0; e < 4; ++e) out[o][4 * j + e] = acc[e] * l4[e];
+        }
+      }
+#pragma unroll
+      for (int o = 0; o < NO; ++o) oacc[o] = out[o];
+    } else {
+      scale_rows(l_tot > 0.f ? 1.f / l_tot : 0.f);
+    }
+    // Direct mode: the tile's rows get all their keys in this unit, so the normalised O is the final one.
+    const bool direct = p.direct && (t.flags & kFlagQExclusive) != 0;
+    int lane_e = lane;                              // see RowStage::flush
+    asm volatile("" : "+v"(lane_e));
+    const int l32e = lane_e & 31, g2e = lane_e >> 5;
+    const int n_wave_rows = t.rows - wave_r0;
+    auto rows_of = [&](void* base, int row_bytes, int elem_bytes) {   // the wave's rows, ending with the tile's last
+      return __builtin_amdgcn_make_buffer_rsrc(base, (short)0, n_wave_rows > 0 ? (n_wave_rows - 1) * row_bytes + D * elem_bytes : 0, 0x00020000);
+    };
+    float* const po = p.o_part + (int64_t)slot * ((int64_t)p.tq * p.hq * D) + ((int64_t)(t.q_row0 + wave_r0) * p.hq + head) * D;
+    uint16_t* const pb = p.o_out + ((int64_t)(t.q_row0 + wave_r0) * p.hq + head) * D;
+    if constexpr (SPLIT > 1) {
+      // (a wave has 32 or 64 channels of every row here: stored straight from the registers)
+      if (share < C::PARTS) {
+        constexpr int NO = C::NVA / C::PARTS;
+        if (!direct) {
+          const int row_bytes = fresh_uniform(p.hq * D * 4);
+          const __amdgpu_buffer_rsrc_t ro = rows_of(po, row_bytes, 4);
+#pragma unroll
+          for (int o = 0; o < NO; ++o)
+#pragma unroll
+            for (int i = 0; i < 16; ++i)
+              __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(unsigned, (float)oacc[o][i]), ro, 4 * g2e * row_bytes + 4 * l32e,
+                                                    (8 * (i / 4) + (i % 4)) * row_bytes + 128 * (share * NO + o), 0);
+        }
+        if (p.o_out && (p.running || direct)) {
+          const int row_bytes = fresh_uniform(p.hq * D * 2);
+          const __amdgpu_buffer_rsrc_t rb = rows_of(pb, row_bytes, 2);
+#pragma unroll
+          for (int o = 0; o < NO; ++o)
+#pragma unroll
+            for (int i = 0; i < 16; ++i)
+              __builtin_amdgcn_raw_buffer_store_b16(__builtin_bit_cast(short, (__bf16)oacc[o][i]), rb, 4 * g2e * row_bytes + 2 * l32e,
+                                                    (8 * (i / 4) + (i % 4)) * row_bytes + 64 * (share * NO + o), 0);
+        }
+      }
+    } else {
+      using OUT = RowStage<D>;
+      unsigned char* const obuf = smem + wave * OUT::BYTES;
+      if (!direct) {                                  // partial O, fp32: D / 2 channels per pass
+        const int row_bytes = fresh_uniform(p.hq * D * 4);
+        const __amdgpu_buffer_rsrc_t ro = rows_of(po, row_bytes, 4);
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+#pragma unroll
+          for (int db = 0; db < D / 64; ++db)
+#pragma unroll
+            for (int i = 0; i < 16; ++i)
+              OUT::put_f32(obuf, OUT::reg_row(i, g2e), 32 * db + l32e, oacc[h * (D / 64) + db][i]);
+          OUT::flush(obuf, lane_e, ro, row_bytes, h * D * 2);
+        }
+      }
+      if (p.o_out && (p.running || direct)) {         // the final rows as bf16
+        const int row_bytes = fresh_uniform(p.hq * D * 2);
+        const __amdgpu_buffer_rsrc_t rb = rows_of(pb, row_bytes, 2);
+#pragma unroll
+        for (int db = 0; db < D / 32; ++db)
+#pragma unroll
+          for (int i = 0; i < 16; ++i) OUT::put_bf16(obuf, OUT::reg_row(i, g2e), 32 * db + l32e, oacc[db][i]);
+        OUT::flush(obuf, lane_e, rb, row_bytes, 0);
+      }
+    }
+    if (row_valid && g2 == 0 && share == 0) {
+      const float lse = l_tot > 0.f ? (m_run + __builtin_amdgcn_logf(l_tot)) * kLn2 : -INFINITY;
+      float* dst = direct ? p.lse_out : p.lse_part + (int64_t)slot * ((int64_t)p.hq * p.tq);
+      dst[(int64_t)head * p.tq + t.q_row0 + my_row] = lse;
+    }
+    uq.advance(&s_next_unit, s_rec);   // barrier: the LDS stages are free for the next unit's fills
+  }
+}
+
+template <int D, int NW, int SPLIT, int SKEYS, int OCC, int AH>
+int launch_one(const FwdParams& p, int64_t units, int n_cu, hipStream_t stream) {
+  using C = SmallCfg<D, NW, SPLIT, SKEYS>;
+  static std::atomic<uint64_t> lds_done;
+  const auto kernel = fwd_small_kernel<D, NW, SPLIT, SKEYS, OCC, AH>;
+  const int rc = raise_lds_limit((const void*)kernel, C::LDS_BYTES, lds_done);
+  if (rc != FCP_OK) return rc;
+  int64_t blocks = (int64_t)n_cu * (OCC * 4 / NW);     // as many as are resident
+  if (blocks > units) blocks = (units + 7) / 8 * 8;   // a multiple of the XCD count
+  if (blocks < 8) blocks = 8;
+  hipLaunchKernelGGL(kernel, dim3((unsigned)blocks), dim3(64 * NW), C::LDS_BYTES, stream, p);
+  FCP_HIP_CHECK(hipGetLastError());
+  return FCP_OK;
+}
+
+}  // namespace
+
+int launch_fwd_small(const FwdParams& p, int head_dim, FwdForm form, int64_t units, int n_cu, hipStream_t stream) {
+  if (head_dim == 64)
+    return form == kFwdSplit4   ? launch_one<64, 4, 4, 128, 2, 4>(p, units, n_cu, stream)
+           : form == kFwdSplit2 ? launch_one<64, 4, 2, 64, 3, 4>(p, units, n_cu, stream)
+                                : launch_one<64, 4, 1, 64, 3, 4>(p, units, n_cu, stream);
+  return form == kFwdSplit4   ? launch_one<128, 8, 4, 128, 2, 4>(p, units, n_cu, stream)
+         : form == kFwdSplit2 ? launch_one<128, 4, 2, 64, 2, 4>(p, units, n_cu, stream)
+         : form == kFwdSmall  ? launch_one<128, 4, 1, 64, 2, 4>(p, units, n_cu, stream)
+                              : launch_one<128, 4, 1, 32, 3, 3>(p, units, n_cu, stream);
+}
+
+}  // namespace fcp

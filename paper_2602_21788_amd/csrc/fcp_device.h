@@ -55,6 +55,11 @@ __device__ inline f32x16 zero16() {
   return z;
 }
 
+// A copy that the compiler cannot see through: what is derived from it inside a loop is formed there and holds no registers across
+// the loop's other parts.
+__device__ inline int fresh(int v) { asm volatile("" : "+v"(v)); return v; }
+__device__ inline int fresh_uniform(int v) { asm volatile("" : "+s"(v)); return v; }
+
 // ---- LDS tiles filled by LDS-direct buffer loads ----------------------------------------------
 // A wave-wide buffer_load_dwordx4 ... lds puts lane L's 16 bytes at (M0 base) + 16 L (verified on the
 // chip; lanes whose address is out of the resource's range write zeros), so a tile row cannot be
@@ -216,7 +221,30 @@ struct UnitQueue {
   int32_t* counter;
   const int32_t* rec_words;
   int32_t n_units, per_tile;
+  int32_t dealt = 0;               // units that went to the blocks by their numbers
 
+  // Block `block` of the `blocks` that share a queue begins with unit `block`, the counter deals out the rest: a kernel begins with one trip to
+  // memory (header and record together) instead of three in a row.  For kernels whose units never wait for each other: a unit
+  // of a block that has not begun is held back with it.  cap: tiles that the list has room for.
+  __device__ void init_dealt(SchedHeader* hdr, const Tile* tiles, int xcd, int per_tile_, int block, int blocks, int cap, int32_t* s_next, int32_t* s_rec) {
+    counter = &hdr->counter[xcd];
+    rec_words = reinterpret_cast<const int32_t*>(tiles);
+    per_tile = per_tile_;
+    dealt = blocks;
+    pend = recw = idx1 = 0;
+    if (threadIdx.x < 64) {
+      const int lane = threadIdx.x & 63;
+      int32_t rec = 0;
+      if (lane < 16) rec = rec_words[min(block / per_tile, cap - 1) * 16 + lane];
+      if (lane == 0) {
+        pend = blocks + atomicAdd(counter, 1);
+        *s_next = block;
+      }
+      if (lane < 16) s_rec[lane] = rec;
+    }
+    n_units = hdr->n_tiles * per_tile_;
+    __syncthreads();
+  }
   __device__ void init(SchedHeader* hdr, const Tile* tiles, int xcd, int per_tile_, int32_t* s_next, int32_t* s_rec) {
     counter = &hdr->counter[xcd];
     rec_words = reinterpret_cast<const int32_t*>(tiles);
@@ -241,7 +269,7 @@ struct UnitQueue {
     if (threadIdx.x < 64) {
       const int lane = threadIdx.x & 63;
       idx1 = __builtin_amdgcn_readfirstlane(pend);
-      if (lane == 0) pend = atomicAdd(counter, 1);
+      if (lane == 0) pend = dealt + atomicAdd(counter, 1);
       recw = (lane < 16 && idx1 < n_units) ? rec_words[(idx1 / per_tile) * 16 + lane] : 0;
     }
   }

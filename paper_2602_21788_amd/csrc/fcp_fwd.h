@@ -1,0 +1,39 @@
+// Declarations shared by the forward kernels' translation units (not installed).
+#pragma once
+#include "fcp_device.h"
+
+namespace fcp {
+
+struct FwdParams {
+  const uint16_t* q;
+  const uint16_t* k;
+  const uint16_t* v;
+  SchedHeader* hdr;
+  const Tile* tiles;
+  float* o_part;
+  float* lse_part;
+  const int32_t* q_limit;   // [tq] last key position each local query row sees, NULL = its own position (causal)
+  uint16_t* o_out;          // running and direct mode: final O as bf16 [tq,hq,D], or NULL
+  float* lse_out;           // direct mode: final LSE [hq,tq]
+  int32_t running;          // 1: slot 0 of o_part / lse_part is the caller's running result, continued and rewritten
+  int32_t direct;           // 1: a tile whose rows no other item of the launch covers writes o_out / lse_out, no partial
+  int32_t tq, hq, hkv;
+  int32_t head_pair;  // 1: a unit is a tile for TWO heads of one KV head; 0: a tile of twice the rows for one head
+  int32_t tile_cap;   // tiles that the list has room for
+  float scale_log2;   // softmax_scale * log2(e)
+};
+
+constexpr float kRescaleThreshold = 8.f;   // log2 units
+
+// The forms of the forward.  Rows per unit (of two heads each half as many where the heads of a KV head pair up):
+enum FwdForm {
+  kFwdWide,      // 256 rows: eight waves in lock step, one block per CU (csrc/fcp_attn_fwd.hip, 128 channels)
+  kFwdSmall,     // 128 rows: four waves, two blocks per CU (64 channels: three; csrc/fcp_attn_fwd_small.hip, as those below)
+  kFwdShort,     // 128 rows: four waves, three blocks per CU (128 channels)
+  kFwdSplit2,    // 64 rows: two waves share 32 rows and divide the keys
+  kFwdSplit4,    // four waves do; 64 rows of eight waves with 128 channels, 32 rows of four waves and one head with 64
+};
+inline int fwd_unit_rows(FwdForm f, int head_dim) { return f == kFwdWide ? kFwdBM : f == kFwdSplit2 ? 64 : f == kFwdSplit4 ? (head_dim == 64 ? 32 : 64) : 128; }
+int launch_fwd_small(const FwdParams& p, int head_dim, FwdForm form, int64_t units, int n_cu, hipStream_t stream);
+
+}  // namespace fcp

@@ -87,7 +87,8 @@ constexpr int kDqBM = 128;       // query rows per dQ unit (two heads of a KV he
 constexpr int kDqBN = 32;        // keys per dQ inner step
 constexpr int kBwdBN = 128;      // keys per dK/dV unit
 constexpr int kBwdBM = 32;       // query rows per dK/dV inner step
-constexpr int kMinQTile = 128;   // smallest query tile of any kernel (sizes the tile lists)
+constexpr int kMinQTile = 128;   // smallest query tile of the backward (sizes its tile lists)
+constexpr int kMinFwdTile = 32;  // ... and of the forward
 
 // Longest key segment of a work item the kernels take.  Byte offsets into a segment travel in 32-bit scalar
 // offsets of buffer instructions, and the fills run a few tiles past a segment's end (those land outside the
@@ -98,7 +99,7 @@ inline int32_t max_segment_keys(int64_t kv_row_bytes) { return (int32_t)(((int64
 // counted as rejected).  Query tiles: every (row, slot) belongs to at most one item, and over
 // a rank's items the query chunks of a sequence add up to at most its length.  Key tiles:
 // over a rank's items the key segments of a sequence add up to at most twice its length.
-int64_t q_tile_cap(int32_t tq, int32_t tkv, int64_t n_work, int32_t n_parts);
+int64_t q_tile_cap(int32_t tq, int32_t tkv, int64_t n_work, int32_t n_parts, int32_t rows = kMinQTile);   // rows: least rows of a tile
 int64_t kv_tile_cap(int32_t tkv, int64_t n_work);
 // Room for the backward's lists when tiles are split: a tile has two pieces more than its share of the steps asks for at most, and
 // all shares together make two pieces per CU.
@@ -222,7 +223,7 @@ inline int32_t* bwd_chain(void* scratch, int64_t n_work, int32_t tq, int32_t tkv
 
 // The forward's row states follow its tile list in its scratch buffer.
 inline uint8_t* fwd_q_state(void* scratch, int64_t n_work, int32_t tq, int32_t tkv, int32_t n_parts) {
-  return static_cast<uint8_t*>(scratch) + sched_region_bytes(n_work, q_tile_cap(tq, tkv, n_work, n_parts));
+  return static_cast<uint8_t*>(scratch) + sched_region_bytes(n_work, q_tile_cap(tq, tkv, n_work, n_parts, kMinFwdTile));
 }
 
 }  // namespace fcp
