@@ -1,6 +1,6 @@
 // dQ, dK and dV in one pass over key tiles: the backward kernel of lists of whole, mostly short sequences with 128 channels per head.
 //
-// Same function as dkv_kernel + dq_kernel (csrc/fcp_attn_dkv.hip, csrc/fcp_attn_bwd.hip), which both recompute S and dP: seven contractions
+// Same function as the kernel that works two lists (csrc/fcp_attn_bwd_lists.hip), which forms S and dP twice: seven contractions
 // where the mathematics has five, two sets of units that each begin by waiting for their first rows, and Q, dO, K and V read
 // twice.  On sequences of one or two key tiles those beginnings are most of the time.  One pass needs the dQ contributions of the key
 // tiles added up cheaply.  fp32 atomics cannot do that (about one element per L2 channel and clock); plain loads
@@ -69,12 +69,6 @@ __device__ inline void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_b
 template <int N>
 __device__ inline void wait_vmem() { asm volatile("s_waitcnt vmcnt(%0)" :: "n"(N) : "memory"); }
 
-// The lane, formed anew: no register holds it, or the thread's number, from the kernel's beginning on.
-__device__ inline int lane_id() {
-  int l;
-  asm volatile("v_mbcnt_lo_u32_b32 %0, -1, 0\n\tv_mbcnt_hi_u32_b32 %0, -1, %0" : "=v"(l));
-  return l;
-}
 constexpr int kCacheBypass = 16;   // sc1: the load goes past the CU's vector cache, which may hold what the line was when this CU last read it
 // Two wave-wide LDS-direct loads of 16 bytes per lane (see lds_fill_b128), 1 KB apart in LDS and `step` bytes apart in memory; v0, v1 = lane offsets.
 template <bool Bypass>
@@ -403,7 +397,7 @@ __global__ __launch_bounds__(768, 1) void bwd_fused_kernel(const BwdParams p0) {
         for (int i = 0; i < 8; ++i)
           lds_fill_b128(r, lds0 + (m ? C::XOFF : 3 * C::STAGE) + DT::row_base(32 * pw + 4 * i), fill_voff<DT>(32, pw, i, lane, kv_row_bytes), 0);
       }
-      // ---- dV or dK [32-channel block][key group of the pair] as [key x channel], see dkv_kernel
+      // ---- dV or dK [32-channel block][key group of the pair] as [key x channel], see key_units
       f32x16 acc[C::NVA][2];
       const float mul = m ? p.scale : 1.f;
       const int n_pair_keys = n_keys - 64 * kp;

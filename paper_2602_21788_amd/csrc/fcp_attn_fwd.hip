@@ -481,7 +481,7 @@ using fcp::fail;
 
 // What the static work area must hold: the tile list of the eight-wave kernel (the lists of smaller tiles are taken where they fit too).
 static size_t static_need(int32_t tq, int32_t tkv, int64_t n_work, int32_t n_parts) {
-  return fcp::sched_region_bytes(n_work, fcp::q_tile_cap(tq, tkv, n_work, n_parts)) + fcp::pad_to((size_t)tq, 256);
+  return fcp::sched_region_bytes(n_work, fcp::q_tile_cap(tq, tkv, n_work, n_parts, fcp::kFwdBM / 2)) + fcp::pad_to((size_t)tq, 256);
 }
 
 // Which form works a list.  The items are in device memory; the host has their mean length and the work per CU (units of 128 rows of one head, a
@@ -537,7 +537,7 @@ static int fwd_step(const void* q, const void* k, const void* v, const int32_t* 
     return fail(FCP_ERR_UNSUPPORTED, "fcp_attn_fwd_step: partial output too large");
 
   hipStream_t st = (hipStream_t)stream;
-  if (fcp::q_tile_cap(tq, tkv, n_work, n_parts) > INT32_MAX / 64) return fail(FCP_ERR_UNSUPPORTED, "fcp_attn_fwd_step: too many tiles");
+  if (fcp::q_tile_cap(tq, tkv, n_work, n_parts, fcp::kFwdBM / 2) > INT32_MAX / 64) return fail(FCP_ERR_UNSUPPORTED, "fcp_attn_fwd_step: too many tiles");
   if (lse_out) { const int rcs = fcp::check_row_states(n_work); if (rcs != FCP_OK) return rcs; }
   int dev = 0, n_cu = 256;                          // (arguments are refused without a device)
   FCP_HIP_CHECK(hipGetDevice(&dev));

@@ -31,6 +31,10 @@ struct BwdParams {
   // Split tiles: turn words of the kernel's tiles (see wait_turn), and the word that counts waits which ran out.
   int32_t* turns;
   int32_t* n_stalled;
+  // The query-tile list.
+  SchedHeader* hdr_q;
+  const Tile* tiles_q;
+  int32_t* turns_q;
   int32_t tq, hq, hkv;
   int32_t either;            // the list decided which kernels work it (path word): the others of the launches have nothing to do
   float scale, scale_log2;
@@ -39,7 +43,7 @@ struct BwdParams {
 // The pieces of a split tile add to its rows one after the other, so that the sums do not depend on the run: each adding wave of a unit has a
 // word per (tile, head) that counts the pieces whose same wave, with the same part of the rows, has added; that of piece n begins once the word stands at n.  The adds
 // are atomics, performed when the memory has acknowledged them.  A piece only waits for pieces ahead of it in the list, which blocks take
-// units from in order: the earliest unfinished unit never waits.  (One word for all eight waves, each turn as long as the slowest of
+// units from in order: the earliest unfinished unit never waits.  (One word for all waves, each turn as long as the slowest of
 // them: 315 -> 400 us on one sequence of 4096 tokens, 8 query heads on one KV head.)
 constexpr int kTurnPolls = 1 << 18;      // about half a second: a wait that does not end is given up (fcp_scratch_status reports it)
 __device__ inline bool wait_turn(const int32_t* word, int piece) {
@@ -55,8 +59,9 @@ __device__ inline void pass_turn(int32_t* word) {
   if ((threadIdx.x & 63) == 0) __hip_atomic_fetch_add(word, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
-// dK / dV over key tiles (csrc/fcp_attn_dkv.hip).  `units` = upper bound of (key tile, KV head) units.
-int launch_dkv(const BwdParams& p, int head_dim, int64_t units, int n_cu, hipStream_t stream);
+// dK / dV over key tiles and dQ over query tiles (csrc/fcp_attn_bwd_lists.hip).  `units` = upper bound of the units of both lists.
+constexpr int lists_blocks_per_cu(int head_dim) { return head_dim == 64 ? 3 : 2; }
+int launch_bwd_lists(const BwdParams& p, int head_dim, int head_pair, int64_t units, int n_cu, hipStream_t stream);
 
 // dQ, dK and dV in one pass over key tiles (csrc/fcp_attn_bwd_fused.hip), 128 channels per head.
 int launch_bwd_fused(const BwdParams& p, int64_t units, int n_cu, hipStream_t stream);

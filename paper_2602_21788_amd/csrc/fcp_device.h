@@ -59,6 +59,12 @@ __device__ inline f32x16 zero16() {
 // the loop's other parts.
 __device__ inline int fresh(int v) { asm volatile("" : "+v"(v)); return v; }
 __device__ inline int fresh_uniform(int v) { asm volatile("" : "+s"(v)); return v; }
+// The lane, formed anew: no register holds it, or the thread's number, from the kernel's beginning on.
+__device__ inline int lane_id() {
+  int l;
+  asm volatile("v_mbcnt_lo_u32_b32 %0, -1, 0\n\tv_mbcnt_hi_u32_b32 %0, -1, %0" : "=v"(l));
+  return l;
+}
 
 // ---- LDS tiles filled by LDS-direct buffer loads ----------------------------------------------
 // A wave-wide buffer_load_dwordx4 ... lds puts lane L's 16 bytes at (M0 base) + 16 L (verified on the
@@ -283,6 +289,67 @@ struct UnitQueue {
     // LDS-only barrier: the unit's last stores and atomics to global memory stay in flight (a __syncthreads() would
     // wait for them here, several microseconds per unit); nothing in the block reads them back.
     __builtin_amdgcn_s_waitcnt(0xC07F);      // lgkmcnt(0)
+    __builtin_amdgcn_s_barrier();
+  }
+};
+
+// Unit queue of the kernels whose blocks are smaller than a CU's share (several hundred of them): as UnitQueue, with what so many blocks need.
+//   * The heads of a launch that do not divide among the XCDs (`per_xcd` false) have one numbering, and the XCDs' counters deal it out in turn:
+//     number = 8 i + XCD.  (One counter for 768 blocks: an atomic on one address takes about 18 ns, 200 sequences of 60 tokens 30 us longer.)
+//   * `first` >= 0: the block begins with that number of its queue and the counter deals out those from `dealt` on.  Only for lists whose units never
+//     wait for each other: a unit of a block that has not begun is held back with it.
+//   * The last `n_half` units are worked in halves, numbered on: the end of a launch is as long as a unit.
+struct PartQueue {
+  int32_t pend, recw, idx1;
+  int32_t* counter;
+  const int32_t* rec_words;
+  int32_t n_full, n_all, per_tile, mul, add, dealt;
+
+  static __device__ int place() { return blockIdx.x / kNumXcd; }      // of the block in its queue
+  static __device__ int places() { return gridDim.x / kNumXcd; }
+  // how many of n numbers are this block's queue's
+  static __device__ int mine(int n, bool per_xcd) { return per_xcd ? n : (n + kNumXcd - 1 - (int)(blockIdx.x % kNumXcd)) / kNumXcd; }
+  __device__ int tile_of(int u) const { return (u < n_full ? u : n_full + ((u - n_full) >> 1)) / per_tile; }
+  __device__ void open(SchedHeader* hdr, const Tile* tiles, int n_units, int n_half, int per_tile_, bool per_xcd, int first, int dealt_, int32_t* s_next, int32_t* s_rec) {
+    counter = &hdr->counter[blockIdx.x % kNumXcd];
+    rec_words = reinterpret_cast<const int32_t*>(tiles);
+    per_tile = per_tile_;
+    n_full = n_units - n_half;
+    n_all = n_units + n_half;
+    mul = per_xcd ? 1 : kNumXcd;
+    add = per_xcd ? 0 : (int)(blockIdx.x % kNumXcd);
+    dealt = dealt_;
+    pend = recw = idx1 = 0;
+    if (threadIdx.x < 64) {
+      const int lane = threadIdx.x & 63;
+      int32_t v0 = first;
+      if (first < 0) {
+        if (lane == 0) v0 = dealt + atomicAdd(counter, 1);
+        v0 = __builtin_amdgcn_readfirstlane(v0);
+      }
+      const int32_t u0 = v0 * mul + add;
+      if (lane == 0) pend = (dealt + atomicAdd(counter, 1)) * mul + add;
+      if (lane < 16) s_rec[lane] = u0 < n_all ? rec_words[tile_of(u0) * 16 + lane] : 0;
+      if (lane == 0) *s_next = u0;
+    }
+    __syncthreads();
+  }
+  __device__ int32_t current(const int32_t* s_next) const { return __builtin_amdgcn_readfirstlane(*s_next); }
+  __device__ void prefetch() {
+    if (threadIdx.x < 64) {
+      const int lane = threadIdx.x & 63;
+      idx1 = __builtin_amdgcn_readfirstlane(pend);
+      if (lane == 0) pend = (dealt + atomicAdd(counter, 1)) * mul + add;
+      recw = (lane < 16 && idx1 < n_all) ? rec_words[tile_of(idx1) * 16 + lane] : 0;
+    }
+  }
+  __device__ void advance(int32_t* s_next, int32_t* s_rec) {
+    if (threadIdx.x < 64) {
+      const int lane = threadIdx.x & 63;
+      if (lane < 16) s_rec[lane] = recw;
+      if (lane == 0) *s_next = idx1;
+    }
+    __builtin_amdgcn_s_waitcnt(0xC07F);      // (see UnitQueue)
     __builtin_amdgcn_s_barrier();
   }
 };

@@ -83,12 +83,11 @@ struct Tile { int32_t w[16]; };  // storage type of the list
 
 constexpr int kFwdBM = 256;      // query rows per forward unit
 constexpr int kFwdBN = 64;       // keys per forward inner step
-constexpr int kDqBM = 128;       // query rows per dQ unit (two heads of a KV head), twice that for a single head
+constexpr int kDqBM = 64;        // query rows per dQ unit (two heads of a KV head), twice that for a single head
 constexpr int kDqBN = 32;        // keys per dQ inner step
 constexpr int kBwdBN = 128;      // keys per dK/dV unit
 constexpr int kBwdBM = 32;       // query rows per dK/dV inner step
-constexpr int kMinQTile = 128;   // smallest query tile of the backward (sizes its tile lists)
-constexpr int kMinFwdTile = 32;  // ... and of the forward
+constexpr int kMinFwdTile = 32;  // smallest query tile of the forward (sizes its tile list; the backward's is kDqBM)
 
 // Longest key segment of a work item the kernels take.  Byte offsets into a segment travel in 32-bit scalar
 // offsets of buffer instructions, and the fills run a few tiles past a segment's end (those land outside the
@@ -99,12 +98,12 @@ inline int32_t max_segment_keys(int64_t kv_row_bytes) { return (int32_t)(((int64
 // counted as rejected).  Query tiles: every (row, slot) belongs to at most one item, and over
 // a rank's items the query chunks of a sequence add up to at most its length.  Key tiles:
 // over a rank's items the key segments of a sequence add up to at most twice its length.
-int64_t q_tile_cap(int32_t tq, int32_t tkv, int64_t n_work, int32_t n_parts, int32_t rows = kMinQTile);   // rows: least rows of a tile
+int64_t q_tile_cap(int32_t tq, int32_t tkv, int64_t n_work, int32_t n_parts, int32_t rows);   // rows: least rows of a tile
 int64_t kv_tile_cap(int32_t tkv, int64_t n_work);
 // Room for the backward's lists when tiles are split: a tile has two pieces more than its share of the steps asks for at most, and
 // all shares together make two pieces per CU.
 inline int64_t bwd_kv_cap(int32_t tkv, int64_t n_work) { return 2 * kv_tile_cap(tkv, n_work) + 2048; }
-inline int64_t bwd_q_cap(int32_t tq, int32_t tkv, int64_t n_work) { return 2 * q_tile_cap(tq, tkv, n_work, 1 << 20) + 2048; }
+inline int64_t bwd_q_cap(int32_t tq, int32_t tkv, int64_t n_work) { return 2 * q_tile_cap(tq, tkv, n_work, 1 << 20, kDqBM) + 2048; }
 
 // One schedule region: SchedHeader | item offsets int32[n_work+1] | Tile[cap]; every part padded to 64 bytes, the region to 256.
 constexpr int32_t kFlagQExclusive = 1;    // no other item of the launch covers these query rows
@@ -128,8 +127,8 @@ static_assert(kBwdBN == 4 * 32, "KTile keeps four key groups");
 
 struct RowStates;   // direct modes, see below
 // Splitting of the backward's tiles on small problems (csrc/fcp_sched.hip): query heads per KV head, units per key tile and per query tile, CUs, least
-// piece in 32-row blocks (of all heads together) and in 32-key blocks; numbers that the turn words have room for; whether tiles may be split.
-struct SplitTiles { int32_t group, kv_units, q_units, n_cu, min_steps, key_turns, row_turns; bool cuts; };
+// piece in 32-row blocks (of all heads together) and in 32-key blocks; numbers that the turn words have room for; blocks of the attention kernel per CU; whether tiles may be split.
+struct SplitTiles { int32_t group, kv_units, q_units, n_cu, min_steps, key_turns, row_turns, blocks_per_cu; bool cuts; };
 
 // Builds one tile list in `region` (tiles of `tile` keys if `key_tiles`, else of `tile` query rows;
 // `inner` is the block size of the other dimension used for the cost; kv_row_bytes = hkv*D*2 bounds
@@ -185,11 +184,11 @@ inline uint8_t* bwd_kv_state(void* scratch, int64_t n_work, int32_t tq, int32_t 
 
 // Turn words of split tiles: kTurnWaves per (key tile, KV head), then as many per (query tile, head).  Only tiles whose rows one item owns have them: the
 // key segments of these do not overlap, nor do their query rows, so there are at most this many (a tile begins every kBwdBN keys or
-// kMinQTile rows and at every segment or item).
-constexpr int kTurnWaves = 8;                // waves of a unit that add
+// kDqBM rows and at every segment or item).
+constexpr int kTurnWaves = 4;                // waves of a unit that add
 constexpr int32_t kMaxFlaggedItems = 1024;   // longer lists have no exclusivity flags
 inline int64_t key_turns(int32_t tkv, int64_t n_work) { return tkv / kBwdBN + 2 * (n_work < kMaxFlaggedItems ? n_work : kMaxFlaggedItems); }
-inline int64_t row_turns(int32_t tq, int64_t n_work) { return tq / kMinQTile + (n_work < kMaxFlaggedItems ? n_work : kMaxFlaggedItems); }
+inline int64_t row_turns(int32_t tq, int64_t n_work) { return tq / kDqBM + (n_work < kMaxFlaggedItems ? n_work : kMaxFlaggedItems); }
 inline int64_t turn_words(int32_t tq, int32_t tkv, int32_t hq, int32_t hkv, int64_t n_work) {
   return (key_turns(tkv, n_work) * hkv + row_turns(tq, n_work) * hq) * kTurnWaves;
 }

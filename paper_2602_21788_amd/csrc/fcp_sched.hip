@@ -314,10 +314,15 @@ enum ListMode { kWhole, kChained, kSplit };
 // than sqrt(kTurnSteps longest loop), where the loop of a piece and the turns of its tile take the same time; not less
 // than min_steps, a unit's own beginning and end.  Nothing is split unless the longest loop is clearly longer than what the pieces
 // take: the share, half a piece at the end of the list, the atomics of the items whose tiles are longer than a piece, the turns.
-struct SplitArgs { int32_t group, kv_units, q_units, dq_tile, n_cu, min_steps, key_turns, row_turns; };
+struct SplitArgs { int32_t group, kv_units, q_units, dq_tile, n_cu, min_steps, key_turns, row_turns, blocks_per_cu; };
 struct SplitSizes { int32_t rows, keys; };
 constexpr int32_t kNoPieces = 1 << 24;
-constexpr float kSplitGain = 1.15f;
+// Least ratio of the longest loop to what the pieces take.  Key tiles, two blocks per CU and three (64 channels): the blocks share the CU's matrix units, so
+// that on a filled chip a loop takes longer than its steps say (64 channels, at 1.15 / 0.85 / 0.6: 8192 tokens, 4 heads 222 / 186 / 186 us; 30 sequences of
+// 20011 tokens, the longest over 3 ranks, 110 / 110 / 132; 8192 tokens, 40 heads on 8 1207 / 1207 / 1507).  Query tiles have a second way to
+// shorten their loops, halves (see bwd_lists_kernel), which lists with pieces of query tiles do without: 24 sequences of 32768 tokens, 4 heads of 64
+// channels, just below 1.18, 350 us whole and 422 in pieces.
+constexpr float kSplitGainKeys2 = 1.12f, kSplitGainKeys3 = 0.85f, kSplitGainRows = 1.18f;
 constexpr float kTurnSteps = 4.f;      // one piece's turn, in steps: its atomics, their acknowledgement, the word (1.5 to 6 within 5 % of each other)
 
 // Called by every thread of the block, with its item (rejected: none).  Every block that asks gets the same answer: sums are formed in a fixed
@@ -341,7 +346,8 @@ __device__ inline SplitSizes split_sizes(const SplitArgs& a, const MaskTables& m
     const int32_t nq = ceil_div(it.q_len, a.dq_tile);
     longest[1] = ceil_div(it.vis0, kDqBN) + ceil_div(it.vis1, kDqBN);
     if (fl & kFlagQExclusive) owned[1] = longest[1];
-    steps[1] = 0.5f * nq * (fwd_cost(m, it, 0, a.dq_tile, kDqBN) + longest[1]) * a.q_units;
+    // (a row unit's step is half of what a CU does at a time)
+    steps[1] = 0.25f * nq * (fwd_cost(m, it, 0, a.dq_tile, kDqBN) + longest[1]) * a.q_units;
   }
   auto wave_sum = [](float v) { for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64); return v; };
   auto wave_max = [](float v) { for (int o = 32; o > 0; o >>= 1) v = fmaxf(v, __shfl_xor(v, o, 64)); return v; };
@@ -373,7 +379,8 @@ __device__ inline SplitSizes split_sizes(const SplitArgs& a, const MaskTables& m
     float heavy = 0.f;
     for (int w = 0; w < n_waves; ++w) heavy += s_part[w][6 + l];
     const float pieces = all[l] / a.n_cu + 0.5f * piece[l] + 0.125f * heavy / piece[l] + turns[l] / piece[l] + 4.f;
-    if (top[l] < kSplitGain * pieces) piece[l] = kNoPieces;
+    const float gain = l ? kSplitGainRows : a.blocks_per_cu > 2 ? kSplitGainKeys3 : kSplitGainKeys2;
+    if (top[l] < gain * pieces) piece[l] = kNoPieces;
   }
   return {piece[0] < kNoPieces ? 32 * max(1, (int32_t)piece[0] / a.group) : 32 * kNoPieces, 32 * (int32_t)piece[1]};
 }
@@ -466,6 +473,7 @@ __device__ void build_list(
     SortArea* area, int32_t* s_fl,       // LDS: sort keys (later the histogram and the offsets), one flag word per item
     int32_t* chain,                      // kChained: the tiles' chain records
     const SplitArgs& sargs,              // kSplit
+    bool stable,                         // tiles of one bucket in the order of their numbers (chains and pieces always)
     const Item& mine) {                  // staged lists: the thread's item, or a rejected one
   __shared__ int32_t s_wave[kSchedThreads / 64];
   __shared__ int32_t s_max, s_rej;
@@ -746,7 +754,7 @@ __device__ void build_list(
     s_hist[b_lo] = ex + h_hi;
   }
   __syncthreads();
-  if (Mode == kWhole || (Mode == kSplit && !cut)) {
+  if (!stable && (Mode == kWhole || (Mode == kSplit && !cut))) {
     for (int32_t t = tid; t < n_tiles; t += kSchedThreads) {
       Tile tl;
       int32_t c;
@@ -757,7 +765,7 @@ __device__ void build_list(
     }
   } else {
     // The tiles of a chain, and the pieces of a tile, must stand in the list in the order in which they take turns: by bucket, then in the
-    // order of the flat tile numbers, i.e. the scatter has to be stable.  A wave groups its lanes by bucket, the waves
+    // order of the flat tile numbers, i.e. the scatter has to be stable; so has that of the backward's query tiles, whose place says whether they are worked in halves.  A wave groups its lanes by bucket, the waves
     // take their places one after the other.
     for (int32_t base = 0; base < n_tiles; base += kSchedThreads) {
       const int32_t t = base + tid;
@@ -996,7 +1004,7 @@ __global__ __launch_bounds__(kSchedThreads) void sched_kernel(
   __shared__ SortArea s_area;
   const int b = blockIdx.x;
   if (b == 0) {
-    build_list<kWhole>(backward != 0, j.tile, j.inner, args, m, j.tile_cap, j.hdr, j.item_off, j.tiles, s_item, &s_area, s_fl, nullptr, SplitArgs{}, my_item(args, m));
+    build_list<kWhole>(backward != 0, j.tile, j.inner, args, m, j.tile_cap, j.hdr, j.item_off, j.tiles, s_item, &s_area, s_fl, nullptr, SplitArgs{}, false, my_item(args, m));
   } else if (b <= fill_blocks) {
     const int64_t stride = (int64_t)fill_blocks * kSchedThreads;
     for (int64_t i = (int64_t)(b - 1) * kSchedThreads + threadIdx.x; i < lse_fill_n; i += stride)
@@ -1025,14 +1033,14 @@ __global__ __launch_bounds__(kSchedThreads) void sched_bwd_kernel(
     const ListJob& j = b == 0 ? kv : qt;
     const Item mine = my_item(args, m);
     if (Other != Mode && !one_pass_pays(split, m, mine, args.n_work)) {
-      build_list<Other>(b == 0, j.tile, j.inner, args, m, j.tile_cap, j.hdr, j.item_off, j.tiles, s_item, &s_area, s_fl, nullptr, split, mine);
+      build_list<Other>(b == 0, j.tile, j.inner, args, m, j.tile_cap, j.hdr, j.item_off, j.tiles, s_item, &s_area, s_fl, nullptr, split, b == 1, mine);
     } else if (Mode == kChained && b == 1) {        // the one-pass kernel has key tiles only
       if (Other != Mode && threadIdx.x == 0) {
         j.hdr->n_tiles = 0;
         j.hdr->path = kPathOnePass;
       }
     } else {
-      build_list<Mode>(b == 0, j.tile, j.inner, args, m, j.tile_cap, j.hdr, j.item_off, j.tiles, s_item, &s_area, s_fl, chain, split, mine);
+      build_list<Mode>(b == 0, j.tile, j.inner, args, m, j.tile_cap, j.hdr, j.item_off, j.tiles, s_item, &s_area, s_fl, chain, split, b == 1, mine);
     }
   } else if (b < 2 + stat_blocks) {
     const int64_t stride = (int64_t)stat_blocks * kSchedThreads;
@@ -1145,7 +1153,7 @@ int launch_schedule_bwd(int64_t kv_row_bytes, const int32_t* q_limit, const int3
   if (stat_blocks < 1) stat_blocks = 1;
   const int state_blocks = states ? row_state_blocks(tq, states->kv_state ? tkv : 0) : 0;
   SplitArgs sp{};
-  if (split) sp = {split->group, split->kv_units, split->q_units, dq_tile, split->n_cu, split->min_steps, split->key_turns, split->row_turns};
+  if (split) sp = {split->group, split->kv_units, split->q_units, dq_tile, split->n_cu, split->min_steps, split->key_turns, split->row_turns, split->blocks_per_cu};
   // (a kernel of its own for each mode: a longer one begins later)
   const bool cuts = split && split->cuts;
   const auto kernel = chain && either ? (cuts ? sched_bwd_kernel<kChained, kSplit> : sched_bwd_kernel<kChained, kWhole>)
