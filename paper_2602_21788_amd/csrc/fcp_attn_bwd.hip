@@ -76,8 +76,13 @@ static int bwd_step(const void* q, const void* k, const void* v, const void* d_o
   // (The kernel's queues are those of eight XCDs: not on a part of the chip.)
   const bool fused = fcp::one_pass_heads(hkv, head_dim) && n_work >= 1 && n_work <= 1024 && tq == tkv && n_cu == 256 &&
                      ((tkv <= 256 * n_work && (group <= 2 || key_units >= n_cu)) || (group == 1 && key_units <= 4 * n_cu));
+  // Many short sequences, 2.5 key tiles per CU and more, go to blocks of four waves (csrc/fcp_attn_bwd_short.hip), scheduling and attention launches, twelve waves /
+  // four: 200 sequences of 60 tokens on average, 32 query heads on 8, 158 / 125 us, 1000 of 40 534 / 375, 1000 of 128 1419 / 1295; with fewer tiles there are
+  // few blocks for the chip (30 of 100, 16 on 8, 43 / 48; 60 of 160 137 / 141), and with means above 192 rows most tiles are in chains, whose steps take longer there
+  // (400 of 256, 40 on 8, 1608 / 1590).  One long sequence sets the time there sooner (a step of its chain 2.5 us), so the scheduler always decides.
+  const bool many_short = fused && tkv <= 192 * n_work && 2 * key_units >= 5 * n_cu;
   const int64_t longest_item = (int64_t)tkv - n_work + 1;      // (with a row at least in each of the others)
-  const bool either = fused && group * longest_item > (group == 1 ? 16384 : group == 2 ? 4096 : 2048) && (group > 2 || key_units >= 2 * n_cu);
+  const bool either = many_short || (fused && group * longest_item > (group == 1 ? 16384 : group == 2 ? 4096 : 2048) && (group > 2 || key_units >= 2 * n_cu));
   // direct mode: where every row's result comes from (and the accumulator rows that are accumulated into cleared),
   // on extra blocks of the scheduling launch
   fcp::RowStates rs{};
@@ -110,7 +115,7 @@ static int bwd_step(const void* q, const void* k, const void* v, const void* d_o
   const int64_t longest = std::max((int64_t)tq * group / fcp::kBwdBM, (int64_t)tkv / fcp::kDqBN);
   const bool split = (!fused || either) && key_units <= 1024 && n_work <= 1024 && longest >= (tq == tkv ? 24 : 64);
   const fcp::SplitTiles sp{group, hkv, hq / (head_pair ? 2 : 1), n_cu, 12,         // (12 steps at least)
-                           (int32_t)fcp::key_turns(tkv, n_work), (int32_t)fcp::row_turns(tq, n_work), fcp::lists_blocks_per_cu(head_dim), split};
+                           (int32_t)fcp::key_turns(tkv, n_work), (int32_t)fcp::row_turns(tq, n_work), fcp::lists_blocks_per_cu(head_dim), split, many_short};
   int32_t* const turns = fcp::bwd_turns(scratch, n_work, tq, tkv, hq);
   int32_t* const flags = fcp::bwd_chain_flags(scratch, n_work, tq, tkv, hq, hkv);
   const int64_t n_flags = fused ? fcp::chain_flag_words(tq, hq, n_work) : 0;
@@ -136,7 +141,8 @@ static int bwd_step(const void* q, const void* k, const void* v, const void* d_o
     p.flags = flags;
     p.hdr = (fcp::SchedHeader*)region_kv;
     p.tiles = fcp::sched_tiles(region_kv, n_work);
-    rc = fcp::launch_bwd_fused(p, fcp::kv_tile_cap(tkv, n_work) * hkv, n_cu, st);     // (more units, of keys shared by many items: the blocks take them in turn)
+    const int64_t units = fcp::kv_tile_cap(tkv, n_work) * hkv;      // (more units, of keys shared by many items: the blocks take them in turn)
+    rc = many_short ? fcp::launch_bwd_short(p, units, n_cu, st) : fcp::launch_bwd_fused(p, units, n_cu, st);
     if (rc != FCP_OK || !either) return rc;
   }
   // both lists

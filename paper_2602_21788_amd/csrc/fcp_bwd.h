@@ -1,4 +1,4 @@
-// Declarations shared by the two backward kernels' translation units (not installed).
+// Declarations shared by the backward kernels' translation units (not installed).
 #pragma once
 #include "fcp_device.h"
 
@@ -63,7 +63,9 @@ __device__ inline void pass_turn(int32_t* word) {
 constexpr int lists_blocks_per_cu(int head_dim) { return head_dim == 64 ? 3 : 2; }
 int launch_bwd_lists(const BwdParams& p, int head_dim, int head_pair, int64_t units, int n_cu, hipStream_t stream);
 
-// dQ, dK and dV in one pass over key tiles (csrc/fcp_attn_bwd_fused.hip), 128 channels per head.
+// dQ, dK and dV in one pass over key tiles, 128 channels per head: one block of twelve waves per CU (csrc/fcp_attn_bwd_fused.hip), or two of four
+// for many short sequences (csrc/fcp_attn_bwd_short.hip).
 int launch_bwd_fused(const BwdParams& p, int64_t units, int n_cu, hipStream_t stream);
+int launch_bwd_short(const BwdParams& p, int64_t units, int n_cu, hipStream_t stream);
 
 }  // namespace fcp

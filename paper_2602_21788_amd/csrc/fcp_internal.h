@@ -48,7 +48,7 @@ struct SchedHeader {
   int32_t pad2[8];
 };                               // 128 bytes
 static_assert(sizeof(SchedHeader) == 128, "header size");
-constexpr int32_t kPathOnePass = 1;     // one pass over key tiles (csrc/fcp_attn_bwd_fused.hip)
+constexpr int32_t kPathOnePass = 1;     // one pass over key tiles (csrc/fcp_attn_bwd_fused.hip, csrc/fcp_attn_bwd_short.hip)
 constexpr int32_t kPathSplitKeys = 2;   // key tiles in pieces of rows
 constexpr int32_t kPathSplitRows = 4;   // query tiles in pieces of keys
 
@@ -128,7 +128,7 @@ static_assert(kBwdBN == 4 * 32, "KTile keeps four key groups");
 struct RowStates;   // direct modes, see below
 // Splitting of the backward's tiles on small problems (csrc/fcp_sched.hip): query heads per KV head, units per key tile and per query tile, CUs, least
 // piece in 32-row blocks (of all heads together) and in 32-key blocks; numbers that the turn words have room for; blocks of the attention kernel per CU; whether tiles may be split.
-struct SplitTiles { int32_t group, kv_units, q_units, n_cu, min_steps, key_turns, row_turns, blocks_per_cu; bool cuts; };
+struct SplitTiles { int32_t group, kv_units, q_units, n_cu, min_steps, key_turns, row_turns, blocks_per_cu; bool cuts; bool many_short; };
 
 // Builds one tile list in `region` (tiles of `tile` keys if `key_tiles`, else of `tile` query rows;
 // `inner` is the block size of the other dimension used for the cost; kv_row_bytes = hkv*D*2 bounds

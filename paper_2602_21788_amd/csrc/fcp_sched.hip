@@ -314,7 +314,7 @@ enum ListMode { kWhole, kChained, kSplit };
 // than sqrt(kTurnSteps longest loop), where the loop of a piece and the turns of its tile take the same time; not less
 // than min_steps, a unit's own beginning and end.  Nothing is split unless the longest loop is clearly longer than what the pieces
 // take: the share, half a piece at the end of the list, the atomics of the items whose tiles are longer than a piece, the turns.
-struct SplitArgs { int32_t group, kv_units, q_units, dq_tile, n_cu, min_steps, key_turns, row_turns, blocks_per_cu; };
+struct SplitArgs { int32_t group, kv_units, q_units, dq_tile, n_cu, min_steps, key_turns, row_turns, blocks_per_cu, many_short; };
 struct SplitSizes { int32_t rows, keys; };
 constexpr int32_t kNoPieces = 1 << 24;
 // Least ratio of the longest loop to what the pieces take.  Key tiles, two blocks per CU and three (64 channels): the blocks share the CU's matrix units, so
@@ -391,6 +391,8 @@ __device__ inline SplitSizes split_sizes(const SplitArgs& a, const MaskTables& m
 // against it.  Fitted to 124 lists of 30 to 1000 short sequences and one of 512 to 65536 tokens, 1, 2 and 4 heads per KV head (5 and 10 % off on
 // average).  On these and on 117 others (log-normal lengths, several long ones, 1 to 8 heads per KV head) the way chosen takes 0.4 % longer than the
 // faster one on average and 17 % at most; one pass for all of them 4 % and 57 %.
+// The kernel of many short sequences (a.many_short), fitted to 60 lists of 120 to 1000 short sequences with and without one of 512 to 16384 tokens, 1 to 5 heads per
+// KV head: the way chosen takes 0.2 % longer than the faster one on average and 9 % at most; one pass for all of them 19 %.
 // Called by every thread of the block, with its item.  Every block that asks gets the same answer.
 __device__ inline bool one_pass_pays(const SplitArgs& a, const MaskTables& m, const Item& it, int32_t n_work) {
 #pragma clang fp contract(off)
@@ -427,6 +429,10 @@ __device__ inline bool one_pass_pays(const SplitArgs& a, const MaskTables& m, co
     longest = fmaxf(longest, s_part[w][3]);
   }
   const float per_cu = (float)a.kv_units / a.n_cu;
+  if (a.many_short) {
+    const float work = (4.04f * units + 1.17f * steps + 1.02f * idle) * per_cu, chain = 2.72f * longest;
+    return 25.f + sqrtf(sqrtf(work * work * work * work + chain * chain * chain * chain)) <= 18.5f + (6.9f * units + 1.74f * steps) * per_cu;
+  }
   const float one = 21.f + fmaxf((7.9f * units + 1.36f * steps + (a.group > 1 ? 0.64f : 0.41f) * idle) * per_cu, 1.46f * longest);
   const float two = 47.f + fmaxf((12.9f * units + 1.65f * steps) * per_cu, 1.12f * longest);
   return one <= two;
@@ -569,6 +575,19 @@ __device__ void build_list(
     return lo;
   };
   auto bucket_of = [&](int32_t cost) { return min(cost >> shift, kBuckets - 1); };
+  // What a tile is sorted by: its cost.  For the kernel of many short sequences, in lists of four units per block and more, the chained tiles of an item with
+  // one segment all stand where its longest does, one after the other: the Q and dO rows, and what a tile leaves of dQ, are then still in the caches for
+  // the next tile, which works a step behind it.  (By their own cost the second tiles come after all first ones.  Scheduling and one-pass launch, by cost / by
+  // item: 400 sequences of 256 tokens, 32 query heads on 8 1322 / 1203 us, 1000 of 128 on average 1289 / 1294, with 8 heads 527 / 507; but 60 of 160, less than
+  // two units per block, 137 / 156: second tiles then wait for first ones that begin with them.)
+  const bool by_item = Chain && sargs.many_short && (int64_t)n_tiles * sargs.kv_units >= 8 * sargs.n_cu;
+  auto place_of = [&](int32_t t, int32_t cost) {
+    if (Chain && by_item) {
+      const Item it = get_item(s_item[item_of(t)]);
+      if (it.vis0 == 0 || it.vis1 == 0) return bucket_of(ceil_div(it.q_len, inner));
+    }
+    return bucket_of(cost);
+  };
   auto decode = [&](int32_t t, Tile& out) -> int32_t {
     const int32_t at = item_of(t);
     const Item it = fetch(at);
@@ -689,7 +708,8 @@ __device__ void build_list(
 
   // Place of key tile t in the chain of its item, if the item owns its query rows (else the tile adds with atomics, rank -1):
   // rank = number of the item's tiles before it, `next` = first query block of the tile after it (or past the last block),
-  // `first` = its own first block, flag0 = the item's first flag block.  Order: by bucket (decreasing), then by flat number.  Inside a
+  // `first` = its own first block, flag0 = the item's first flag block.  Order: by place (see place_of), then by flat number, which for an item of one
+  // segment is that of its tiles' buckets too; for one of two segments: by bucket (decreasing), then by flat number.  Inside a
   // segment the buckets do not grow with the key, so the tiles of the other segment that come before are found by bisection.
   // Blocks are counted so that tiles of one bucket start at the same one: a tile later in the chain never starts at an earlier block.
   auto chain_place = [&](int32_t t, int32_t bucket, int32_t& rank, int32_t& next, int32_t& first, int32_t& flag0) {
@@ -739,7 +759,7 @@ __device__ void build_list(
     Tile tl;
     const int32_t c = decode(t, tl);
     if (t == tid) { first_tile = tl; first_cost = c; }
-    if (Mode != kSplit || c >= 0) atomicAdd(&s_hist[bucket_of(c)], 1);   // (-1: no such piece)
+    if (Mode != kSplit || c >= 0) atomicAdd(&s_hist[place_of(t, c)], 1);   // (-1: no such piece)
   }
   __syncthreads();
   // Descending-cost start offset of every bucket: scan the histogram from the top.
@@ -765,7 +785,7 @@ __device__ void build_list(
     }
   } else {
     // The tiles of a chain, and the pieces of a tile, must stand in the list in the order in which they take turns: by bucket, then in the
-    // order of the flat tile numbers, i.e. the scatter has to be stable; so has that of the backward's query tiles, whose place says whether they are worked in halves.  A wave groups its lanes by bucket, the waves
+    // order of the flat tile numbers, i.e. the scatter has to be stable (chained: by place, see above); so has that of the backward's query tiles, whose place says whether they are worked in halves.  A wave groups its lanes by bucket, the waves
     // take their places one after the other.
     for (int32_t base = 0; base < n_tiles; base += kSchedThreads) {
       const int32_t t = base + tid;
@@ -777,8 +797,8 @@ __device__ void build_list(
       }
       const bool live = c >= 0;                       // (kSplit, -1: no such piece)
       if (live) {
-        bucket = bucket_of(c);
-        if constexpr (Chain) chain_place(t, bucket, rank, next, first, flag0);
+        if constexpr (Chain) chain_place(t, bucket_of(c), rank, next, first, flag0);
+        bucket = place_of(t, c);
       }
       const int lane = tid & 63;
       uint64_t mine = 0;                              // lanes of the wave with this lane's bucket
@@ -1153,7 +1173,7 @@ int launch_schedule_bwd(int64_t kv_row_bytes, const int32_t* q_limit, const int3
   if (stat_blocks < 1) stat_blocks = 1;
   const int state_blocks = states ? row_state_blocks(tq, states->kv_state ? tkv : 0) : 0;
   SplitArgs sp{};
-  if (split) sp = {split->group, split->kv_units, split->q_units, dq_tile, split->n_cu, split->min_steps, split->key_turns, split->row_turns, split->blocks_per_cu};
+  if (split) sp = {split->group, split->kv_units, split->q_units, dq_tile, split->n_cu, split->min_steps, split->key_turns, split->row_turns, split->blocks_per_cu, split->many_short ? 1 : 0};
   // (a kernel of its own for each mode: a longer one begins later)
   const bool cuts = split && split->cuts;
   const auto kernel = chain && either ? (cuts ? sched_bwd_kernel<kChained, kSplit> : sched_bwd_kernel<kChained, kWhole>)
