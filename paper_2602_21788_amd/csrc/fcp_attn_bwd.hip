@@ -56,26 +56,24 @@ static int bwd_step(const void* q, const void* k, const void* v, const void* d_o
   int dev = 0, n_cu = 0;                            // (arguments are refused without a device)
   FCP_HIP_CHECK(hipGetDevice(&dev));
   FCP_HIP_CHECK(hipDeviceGetAttribute(&n_cu, hipDeviceAttributeMultiprocessorCount, dev));
-  // One pass or two.  The one-pass kernel (csrc/fcp_attn_bwd_fused.hip) forms S and dP once and needs no query-tile launch; it has the
-  // units of key tiles only, which take turns at the dQ rows of a sequence.  That pays where sequences are short, and not where many
-  // tiles follow each other through the same rows.  Lists of whole sequences (tq == tkv), measured:
-  //   256 rows or less per item: 1.1 to 2.4 times as fast at 8 to 64 query heads, down to a handful of items, except for
-  //       three or more heads per KV head and fewer tiles than CUs, where one longer sequence of the list sets the
-  //       time (0.82 to 1.0 there); at 333 to 400 rows 0.96 to 1.1;
-  //   one query head per KV head, up to 1024 tiles: 1.06 to 1.6 times as fast at any length; at 1500 tiles 1.0.
-  // Sharded lists (tq < tkv) have the whole sequence's tiles over a part of its rows: 0.63 to 1.1, they stay with two passes.
+  // One pass or two lists.  The one-pass kernel (csrc/fcp_attn_bwd_fused.hip) forms S and dP once and needs no query tiles; it has the
+  // units of key tiles only, which take turns at the dQ rows of a sequence.  That pays where sequences are short and few of them follow each
+  // other through the same rows: whole sequences (tq == tkv) with 256 rows or less per item, one or two heads per KV head or a tile per CU.  Scheduling and
+  // attention launches, one pass / two lists, 8 query heads on 8: 30 sequences of 100 tokens on average 41 / 43 us, 200 of 60 83 / 89; 32 on 8: 200 of 60
+  // 159 / 169, 1000 of 128 1417 / 1713.  With one query head per KV head, up to four tiles per CU, also a dozen sequences and more with a mean of 768 rows at most (8
+  // heads: 16 of 512 tokens 71 / 73, 20 of 700 118 / 129), and, where the tiles are nearly four per CU, longer ones (one of 16384 tokens 1771 / 1805); not a few
+  // long ones (one of 512 tokens 37 / 33, 1000 59 / 52, 4096 210 / 171, 8192 518 / 462, 8 sequences of 4000 in all 120 / 96).
+  // Sharded lists (tq < tkv) have the whole sequence's tiles over a part of its rows: they stay with two lists.
   // The rows per item are an average, and the items are in device memory: where one of them could be long enough to turn the comparison
   // round (16384 rows with one query head per KV head, else 2048 and 512 rows of two and four heads), the scheduler decides when it sees them
   // (one_pass_pays in csrc/fcp_sched.hip), and the launches of the other way end at once: 3 to 5 us, which lists of two heads per KV
-  // head and less than 8 K tokens on 8 KV heads are spared (0.92 to 0.95 at worst).
-  // One sequence among 30 short ones (mean 64 and 128 tokens), 32 query heads on 8, one pass / two: 512 tokens 99 / 110 and 105 / 140 us, 1024 187 / 144
-  // and 193 / 162, 2048 375 / 243 and 380 / 250; among 1000 (mean 128), 4096 tokens 2177 / 2560, 16384 10611 / 8846; 8 heads on 8 among 1000,
-  // 16384 tokens 2435 / 2496, 32768 7978 / 7367.
+  // head and less than 8 K tokens on 8 KV heads are spared.
   const int group = hq / hkv;
   const int64_t key_units = (int64_t)tkv * hkv / fcp::kBwdBN;
   // (The kernel's queues are those of eight XCDs: not on a part of the chip.)
   const bool fused = fcp::one_pass_heads(hkv, head_dim) && n_work >= 1 && n_work <= 1024 && tq == tkv && n_cu == 256 &&
-                     ((tkv <= 256 * n_work && (group <= 2 || key_units >= n_cu)) || (group == 1 && key_units <= 4 * n_cu));
+                     ((tkv <= 256 * n_work && (group <= 2 || key_units >= n_cu)) ||
+                      (group == 1 && key_units <= 4 * n_cu && (2 * key_units > 7 * n_cu || (n_work >= 12 && tkv <= 768 * n_work))));
   // Many short sequences, 2.5 key tiles per CU and more, go to blocks of four waves (csrc/fcp_attn_bwd_short.hip), scheduling and attention launches, twelve waves /
   // four: 200 sequences of 60 tokens on average, 32 query heads on 8, 158 / 125 us, 1000 of 40 534 / 375, 1000 of 128 1419 / 1295; with fewer tiles there are
   // few blocks for the chip (30 of 100, 16 on 8, 43 / 48; 60 of 160 137 / 141), and with means above 192 rows most tiles are in chains, whose steps take longer there
@@ -108,7 +106,8 @@ static int bwd_step(const void* q, const void* k, const void* v, const void* d_o
   const int dq_rows = 2 * fcp::kDqBM >> head_pair;
   // Split tiles (see csrc/fcp_sched.hip): worth the scheduler's time where there are a few tiles per CU at most and a serial loop can be
   // long, in 32-row blocks of all heads of a KV head or in 32-key blocks.  In sharded lists a tile's loop is the shorter for
-  // the sharding, and its accumulators are mostly shared already.  Measured, scheduling and attention launches: one sequence of 4096 tokens, 8 query
+  // the sharding, and its accumulators are mostly shared already.  Measured, scheduling and attention launches, whole and split (with one kernel per list;
+  // split_sizes in csrc/fcp_sched.hip has the estimate as fitted to one kernel for both): one sequence of 4096 tokens, 8 query
   // heads on one KV head, 128 channels 952 -> 296 us; 6 on 2, 64 channels 445 -> 175 us; 30 sequences of 20011 tokens in all, 6 on 2, 489 -> 357 us
   // whole and 316 -> 245 us with the longest one over 3 ranks; 4096 tokens over 3 ranks, 4 on 4, 106 -> 86 us; 4096 tokens, 32 on 8, 609 -> 575 us.
   // (At the edge the estimate can miss: 9000 tokens over 4 ranks, 12 on 4, 128 channels 367 -> 375 us.)

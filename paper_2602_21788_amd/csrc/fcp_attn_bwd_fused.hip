@@ -31,9 +31,8 @@
 // Other splits of the work were slower: dQ by one of two kinds of waves in turn (every other step too long for the barrier that
 // ends it), 8 waves of 256 registers (370 instructions each), dQ on 32 x 32 x 16 instructions with dQ in flight in registers.
 //
-// Measured against the two kernels, scheduling and attention launches, 32 query heads on 8 KV heads: 1000 sequences of 128 tokens on average
-// 2.11 -> 1.42 ms, 1000 of 40 tokens 950 -> 532 us, 400 of 256 tokens 2.04 -> 1.72 ms; 8 heads on 8, 30 of 40 tokens 48 -> 26 us; on
-// sequences of 800 tokens 1.20 -> 1.32 ms and on one of 26 K of 131 K keys 82 -> 102 ms (units wait for each other at the shared rows
+// Measured against the two lists, scheduling and attention launches: 32 query heads on 8 KV heads, 200 sequences of 60 tokens on average 169 -> 159 us;
+// 8 heads on 8, 30 of 100 43 -> 41 us, 200 of 60 89 -> 83; on one sequence of 4096 tokens 167 -> 211 us (units wait for each other at the shared rows
 // and the stores of dQ compete for the L2): the rule of dispatch is at the call (csrc/fcp_attn_bwd.hip).
 #include "fcp_bwd.h"
 

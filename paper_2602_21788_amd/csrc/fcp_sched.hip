@@ -471,7 +471,7 @@ struct SortArea {
 };
 
 // One tile list, built by one block.
-template <ListMode Mode>
+template <ListMode Mode, bool ManyShort = false>
 __device__ void build_list(
     bool backward, int32_t tile, int32_t inner, const ListArgs& args, const MaskTables& m,
     int32_t tile_cap, SchedHeader* hdr, int32_t* item_off, Tile* tiles,
@@ -580,9 +580,10 @@ __device__ void build_list(
   // the next tile, which works a step behind it.  (By their own cost the second tiles come after all first ones.  Scheduling and one-pass launch, by cost / by
   // item: 400 sequences of 256 tokens, 32 query heads on 8 1322 / 1203 us, 1000 of 128 on average 1289 / 1294, with 8 heads 527 / 507; but 60 of 160, less than
   // two units per block, 137 / 156: second tiles then wait for first ones that begin with them.)
-  const bool by_item = Chain && sargs.many_short && (int64_t)n_tiles * sargs.kv_units >= 8 * sargs.n_cu;
+  // (Compiled only into the launches that can be followed by that kernel: a longer one begins later, 1 us of 40 on 30 sequences of 100.)
+  const bool by_item = ManyShort && sargs.many_short && (int64_t)n_tiles * sargs.kv_units >= 8 * sargs.n_cu;
   auto place_of = [&](int32_t t, int32_t cost) {
-    if (Chain && by_item) {
+    if (ManyShort && by_item) {
       const Item it = get_item(s_item[item_of(t)]);
       if (it.vis0 == 0 || it.vis1 == 0) return bucket_of(ceil_div(it.q_len, inner));
     }
@@ -1034,8 +1035,8 @@ __global__ __launch_bounds__(kSchedThreads) void sched_kernel(
   }
 }
 
-// Backward: one launch for everything that precedes the two attention kernels.  Block 0 builds the key-tile list
-// (dK/dV kernel), block 1 the query-tile list (dQ kernel), the other blocks write the row statistics in the form
+// Backward: one launch for everything that precedes the attention kernels.  Block 0 builds the key-tile list
+// (dK, dV), block 1 the query-tile list (dQ), the other blocks write the row statistics in the form
 // the kernels consume: plane 0 = -LSE log2 e (-inf for a row without keys, so that its probabilities vanish),
 // plane 1 = -delta.
 // Other != Mode: the list decides which of the two it is (see one_pass_pays).
@@ -1060,7 +1061,7 @@ __global__ __launch_bounds__(kSchedThreads) void sched_bwd_kernel(
         j.hdr->path = kPathOnePass;
       }
     } else {
-      build_list<Mode>(b == 0, j.tile, j.inner, args, m, j.tile_cap, j.hdr, j.item_off, j.tiles, s_item, &s_area, s_fl, chain, split, b == 1, mine);
+      build_list<Mode, Mode == kChained && Other != Mode>(b == 0, j.tile, j.inner, args, m, j.tile_cap, j.hdr, j.item_off, j.tiles, s_item, &s_area, s_fl, chain, split, b == 1, mine);
     }
   } else if (b < 2 + stat_blocks) {
     const int64_t stride = (int64_t)stat_blocks * kSchedThreads;
@@ -1191,7 +1192,7 @@ int launch_schedule_bwd(int64_t kv_row_bytes, const int32_t* q_limit, const int3
 extern "C" size_t fcp_scratch_bytes(int which, int32_t tq, int32_t tkv, int32_t hq, int32_t hkv,
                                     int32_t head_dim, int64_t n_work, int32_t n_parts) {
   if (tq < 0 || tkv < 0 || n_work < 0 || n_parts < 0) return 0;
-  if (which == FCP_SCRATCH_BWD)   // key-tile list (dK/dV kernel), query-tile list (dQ kernel), packed row statistics,
+  if (which == FCP_SCRATCH_BWD)   // key-tile list, query-tile list, packed row statistics,
                                   // row states
     return fcp::sched_region_bytes(n_work, fcp::bwd_kv_cap(tkv, n_work)) +
            fcp::sched_region_bytes(n_work, fcp::bwd_q_cap(tq, tkv, n_work)) +

@@ -99,3 +99,19 @@ def test_rows_do_not_see_what_later_keys_hold(what):
     a, b = got[0].float().to(dev).view(80, 150, hq, D), ref[0].view(80, 150, hq, D)
     assert not torch.isfinite(a[:, bad:]).all(dim=-1).any()
     assert torch.isfinite(a[:, :seen]).all() and float((a - b)[:, :seen].abs().max() / b[:, :seen].abs().max()) <= TOL_BF16_REL
+
+
+@pytest.mark.parametrize("lens,path", [
+    ([500] * 12, listed.ONE_PASS), ([500] * 11, 0), ([800] * 12, 0),           # a dozen sequences, a mean of 768 rows
+    ([900], 0), ([255, 257], listed.ONE_PASS), ([256, 257], 0),                # a mean of 256 rows
+])
+def test_one_pass_or_two_lists_by_the_mean(lens, path):
+    import paper_2602_21788_amd.binding as B
+    hq, hkv, D = 8, 8, 128
+    items = [(s, 0, n, [(0, n)]) for s, n in enumerate(lens)]
+    q, k, v, do = listed.draw(lens, hq, hkv, D, 34)
+    lse, delta, ref = listed.reference(lens, items, q, k, v, do, D ** -0.5)
+    print(f"one pass or two lists: {lens}", flush=True)
+    got, scratch = listed.run_backward(B, "direct", lens, listed.work_list(B, lens, items), q, k, v, do, lse, delta, D ** -0.5)
+    assert B.fcp_scratch_status(scratch)[1] == 0 and listed.backward_path(scratch) & listed.ONE_PASS == path
+    listed.check(got, ref, TOL_BF16_REL, str(lens))

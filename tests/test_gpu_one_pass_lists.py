@@ -241,9 +241,8 @@ def test_one_pass_with_costs_of_several_blocks_in_one_bucket(family):
 
 
 def test_one_pass_is_no_less_exact_than_two():
-    """dQ, dK and dV against 64 bits.  The two kernels see the same eight heads in two calls of four KV heads, which one pass does not take.
-    5 % is left for the rounding of the results, a mean over 340 000 elements and more; dS is formed from P in fp32 in one pass, in
-    dkv_kernel from P as bf16 (2.56e-3 and 3.05e-3 in dK on 1000 sequences of 128 tokens)."""
+    """dQ, dK and dV against 64 bits.  The kernel of two lists sees the same eight heads in two calls of four KV heads, which one pass does not take.
+    5 % is left for the rounding of the results, a mean over 340 000 elements and more."""
     import torch
     import paper_2602_21788_amd.binding as B
     lens, hq, hkv, D = [300, 40, 129, 64, 500, 90, 200], 8, 8, 128
