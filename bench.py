@@ -13,7 +13,7 @@ and head; masked pairs are not counted).  --mask mixed times the same path throu
 
 Prints ONE JSON line.  `value` / `ms_per_step` come from the wall clock around the K timed steps; every segment is
 also timed per step with events on the stream the kernels run on and reported as mean, median and min.  `roofline`
-is for the dominant launch (the backward step: its scheduling launch and the two attention kernels), `cpu_baseline`
+is for the dominant launch (the backward step: its scheduling launch and the attention kernel), `cpu_baseline`
 times the fp64 CPU oracle on a bounded sample of the same workload, and `secondary` (default run only) holds the
 other workloads, the CP-degree sweep and the merge on a bandwidth-sized input, a few steps each, device-side random
 inputs.
