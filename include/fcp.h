@@ -131,8 +131,10 @@ int fcp_attn_fwd_step(const void* q, const void* k, const void* v, const int32_t
  * function, arguments, results and errors as fcp_attn_fwd_step, except that the scheduler's work area is a static
  * device array inside the library (FCP_STATIC_SCRATCH_BYTES, held on every GPU the library runs on until the
  * process ends) instead of `scratch`.  The call allocates nothing and frees nothing.
- *   - a call that needs more than FCP_STATIC_SCRATCH_BYTES (see fcp_scratch_bytes(FCP_SCRATCH_FWD, ...)) returns
- *     FCP_ERR_CAPACITY and launches nothing;
+ *   - a call whose list of query tiles could need more than FCP_STATIC_SCRATCH_BYTES returns FCP_ERR_CAPACITY and launches
+ *     nothing: 128 bytes, 4 per work item, 64 per tile of 128 rows (at most n_work + min(n_parts * ceil(tq / 128),
+ *     ceil(tkv / 128)) of them) and tq bytes, each rounded up to 256.  (fcp_scratch_bytes(FCP_SCRATCH_FWD, ...) is more: a
+ *     caller's buffer has room for tiles of 32 rows.  Here a list of smaller tiles that would not fit is built of larger ones.);
  *   - every call on a GPU uses that GPU's one array: calls that overlap in time on one GPU (two streams, two threads)
  *     race and give undefined results; calls on one stream are ordered and safe.  Nothing has to be cleared between
  *     calls;

@@ -5,7 +5,7 @@
 // packed sequences of heterogeneous length (Sec. 4.1).  Per row the kernel emits the
 // locally normalised output and LSE = ln sum exp(scaled scores).
 //
-// gfx950 design (128 channels per head, long items; the other lists: csrc/fcp_attn_fwd_small.hip, the rule is at fwd_form below)
+// gfx950 design (128 channels per head, long items; the other lists: csrc/fcp_attn_fwd_small.hip, the rule is fwd_form in csrc/fcp_sizes.h)
 //   * persistent 512-thread blocks (8 wave64, one block per CU, two waves per SIMD) pull
 //     (query tile, head) units from per-XCD counters; the tile list is sorted longest-first by
 //     the scheduler kernel;
@@ -34,8 +34,6 @@
 //     wave's rows are not computed by that wave (it only keeps the barriers).
 
 #include "fcp_fwd.h"
-
-#include <algorithm>
 
 namespace fcp {
 namespace {
@@ -479,36 +477,6 @@ __global__ __launch_bounds__(512, 1) void fwd_kernel(const FwdParams p) {
 
 using fcp::fail;
 
-// What the static work area must hold: the tile list of the eight-wave kernel (the lists of smaller tiles are taken where they fit too).
-static size_t static_need(int32_t tq, int32_t tkv, int64_t n_work, int32_t n_parts) {
-  return fcp::sched_region_bytes(n_work, fcp::q_tile_cap(tq, tkv, n_work, n_parts, fcp::kFwdBM / 2)) + fcp::pad_to((size_t)tq, 256);
-}
-
-// Which form works a list.  The items are in device memory; the host has their mean length and the work per CU (units of 128 rows of one head, a
-// row counted once per item that covers it).  Measured, forward step with its scheduling launch, wide / the form chosen, us:
-//   few units, and loops long enough to be divided: the longest unit's loop sets the time.  128 channels, 8 heads: 2000 tokens 56 / 36 (four waves
-//     a row), 4096 tokens 98 / 73 (two), 4096 tokens over 3 ranks 47 / 39.  64 channels, 4 heads: 512 tokens 23 / 18, 4096 82 / 41; several sequences
-//     have a longer longest loop for the same work: 16 of 16384 tokens 125 / 82.  (At twice the bounds the divided form is slower: 16384
-//     tokens over 5 ranks, 6 heads on 2 of 64 channels 75 / 88.)
-//   64 channels otherwise: blocks of four waves, three per CU, at every size: 60000 tokens in 16 sequences, 40 heads on 8 4100 / 3760; 1000 of 128 1050 / 737.
-//   128 channels: short items are mostly beginnings and ends of units, which other blocks of the CU cover: 1000 of 128, 32 heads on 8 922 / 694, 200
-//     of 400 690 / 608, 30 of 667 over 3 ranks 317 / 300; with few units per CU two blocks with 64-key tiles do better than three with 32-key tiles: 4000
-//     tokens in 8 sequences 84 / 77 (three: 85), 8192 tokens of 8 heads 190 / 182 (205).  Long items: the wide form (60000 tokens in 16
-//     sequences 4900; 5020 with three blocks, 5180 with two).
-static fcp::FwdForm fwd_form(int head_dim, int hq, int64_t tq, int64_t tkv, int64_t n_work, int64_t n_parts, int n_cu) {
-  const int64_t rows = std::min(n_parts * tq, tkv);          // of all items together, at most
-  const int64_t mean = n_work > 0 ? rows / n_work : 0;
-  const double per_cu = (double)rows * hq / (128. * n_cu);
-  if (head_dim == 64) {
-    if (mean >= 256 && (per_cu <= 0.5 || (per_cu <= 1. && mean >= 1024))) return fcp::kFwdSplit4;
-    return mean >= 256 && per_cu <= (tq == tkv && n_work >= 8 ? 2.5 : 1.6) ? fcp::kFwdSplit2 : fcp::kFwdSmall;
-  }
-  if (mean >= 256 && per_cu <= 1.1) return per_cu <= 0.55 ? fcp::kFwdSplit4 : fcp::kFwdSplit2;
-  const int64_t units = (rows / 128 + n_work) * hq;
-  if (mean <= 640) return units <= 12 * (int64_t)n_cu ? fcp::kFwdSmall : fcp::kFwdShort;
-  return units <= 6 * (int64_t)n_cu ? fcp::kFwdSmall : fcp::kFwdWide;
-}
-
 // Both entry points; q_limit == NULL is the causal mask.
 static int fwd_step(const void* q, const void* k, const void* v, const int32_t* cu_seqlens_kv,
                     int32_t n_seqs, const fcp_work_desc* work, int64_t n_work, int32_t n_parts,
@@ -530,24 +498,21 @@ static int fwd_step(const void* q, const void* k, const void* v, const int32_t* 
                                reinterpret_cast<uintptr_t>(v) | reinterpret_cast<uintptr_t>(o_part);
   if (align_mask & 15u) return fail(FCP_ERR_INVALID_ARG, "fcp_attn_fwd_step: q/k/v/o_part must be 16-byte aligned");
   if (reinterpret_cast<uintptr_t>(scratch) & 255u) return fail(FCP_ERR_INVALID_ARG, "fcp_attn_fwd_step: scratch must be 256-byte aligned");
-  const size_t need = static_area ? static_need(tq, tkv, n_work, n_parts)
-                                  : fcp_scratch_bytes(FCP_SCRATCH_FWD, tq, tkv, hq, hkv, head_dim, n_work, n_parts);
+  const size_t need = static_area ? fcp::fwd_static_bytes(tq, tkv, n_work, n_parts) : fcp::fwd_scratch_bytes(tq, tkv, n_work, n_parts);
   if (scratch_bytes < need) return fail(FCP_ERR_CAPACITY, "fcp_attn_fwd_step: scratch %zu < %zu bytes", scratch_bytes, need);
   if ((int64_t)tq * hq * head_dim * (int64_t)n_parts > ((int64_t)1 << 40))
     return fail(FCP_ERR_UNSUPPORTED, "fcp_attn_fwd_step: partial output too large");
 
   hipStream_t st = (hipStream_t)stream;
-  if (fcp::q_tile_cap(tq, tkv, n_work, n_parts, fcp::kFwdBM / 2) > INT32_MAX / 64) return fail(FCP_ERR_UNSUPPORTED, "fcp_attn_fwd_step: too many tiles");
+  if (fcp::q_tile_cap(tq, tkv, n_work, n_parts, fcp::kFwdBM / 2) > fcp::kMaxTiles) return fail(FCP_ERR_UNSUPPORTED, "fcp_attn_fwd_step: too many tiles");
   if (lse_out) { const int rcs = fcp::check_row_states(n_work); if (rcs != FCP_OK) return rcs; }
   int dev = 0, n_cu = 256;                          // (arguments are refused without a device)
   FCP_HIP_CHECK(hipGetDevice(&dev));
   FCP_HIP_CHECK(hipDeviceGetAttribute(&n_cu, hipDeviceAttributeMultiprocessorCount, dev));
-  const fcp::FwdForm form = fwd_form(head_dim, hq, tq, tkv, n_work, n_parts, n_cu);
-  const int unit_rows = fcp::fwd_unit_rows(form, head_dim);
-  // two heads of one KV head per unit when the heads pair up, else twice the rows for one head
-  const int head_pair = ((hq / hkv) % 2 == 0) && unit_rows > 32 ? 1 : 0;
-  const int32_t tile = unit_rows >> head_pair;
-  const int64_t cap = fcp::q_tile_cap(tq, tkv, n_work, n_parts, tile);
+  const size_t area = static_area ? scratch_bytes : fcp::fwd_area_bytes(tq, tkv, n_work, n_parts);   // (row states behind it)
+  const auto [form, head_pair, tile, cap] = fcp::fwd_plan(head_dim, hq, hkv, tq, tkv, n_work, n_parts, n_cu, area);
+  if (fcp::sched_region_bytes(n_work, cap) > area)
+    return fail(FCP_ERR_CAPACITY, "fcp_attn_fwd_step: the tile list needs %zu bytes of %zu", fcp::sched_region_bytes(n_work, cap), area);
   const bool direct = lse_out != nullptr;
   // direct mode: which rows get their final result from one unit and which are merged from partials is worked out on
   // extra blocks of the scheduling launch
@@ -617,7 +582,7 @@ extern "C" int fcp_attn_fwd_step_static(const void* q, const void* k, const void
   fcp::clear_error();
   if (tq < 0 || tkv < 1 || n_work < 0 || n_parts < 1 || hq < 1 || hkv < 1)
     return fail(FCP_ERR_INVALID_ARG, "fcp_attn_fwd_step_static: bad sizes");
-  const size_t need = static_need(tq, tkv, n_work, n_parts);
+  const size_t need = fcp::fwd_static_bytes(tq, tkv, n_work, n_parts);
   if (need > (size_t)FCP_STATIC_SCRATCH_BYTES)
     return fail(FCP_ERR_CAPACITY, "fcp_attn_fwd_step_static: this call needs a work area of %zu bytes, the static one has %zu "
                                   "(use fcp_attn_fwd_step with a caller-owned scratch buffer)", need, (size_t)FCP_STATIC_SCRATCH_BYTES);

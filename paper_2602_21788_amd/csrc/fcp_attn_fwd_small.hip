@@ -15,7 +15,7 @@
 //     that would otherwise leave CUs without a unit.  A stage's fills then serve fewer matrix instructions, so it does not pay where units
 //     abound (60000 tokens in 16 sequences, 32 heads on 8: 5180 -> 6300 us with two).
 // Priorities as in fwd_kernel (matrix stream first) gain 1 % on long items and lose 1 to 3 % elsewhere; none are set.
-// Times of the forms beside each other and where each is taken: fwd_form in csrc/fcp_attn_fwd.hip.
+// Times of the forms beside each other and where each is taken: fwd_form in csrc/fcp_sizes.h.
 #include "fcp_fwd.h"
 
 namespace fcp {

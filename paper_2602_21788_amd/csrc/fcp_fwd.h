@@ -25,15 +25,6 @@ struct FwdParams {
 
 constexpr float kRescaleThreshold = 8.f;   // log2 units
 
-// The forms of the forward.  Rows per unit (of two heads each half as many where the heads of a KV head pair up):
-enum FwdForm {
-  kFwdWide,      // 256 rows: eight waves in lock step, one block per CU (csrc/fcp_attn_fwd.hip, 128 channels)
-  kFwdSmall,     // 128 rows: four waves, two blocks per CU (64 channels: three; csrc/fcp_attn_fwd_small.hip, as those below)
-  kFwdShort,     // 128 rows: four waves, three blocks per CU (128 channels)
-  kFwdSplit2,    // 64 rows: two waves share 32 rows and divide the keys
-  kFwdSplit4,    // four waves do; 64 rows of eight waves with 128 channels, 32 rows of four waves and one head with 64
-};
-inline int fwd_unit_rows(FwdForm f, int head_dim) { return f == kFwdWide ? kFwdBM : f == kFwdSplit2 ? 64 : f == kFwdSplit4 ? (head_dim == 64 ? 32 : 64) : 128; }
 int launch_fwd_small(const FwdParams& p, int head_dim, FwdForm form, int64_t units, int n_cu, hipStream_t stream);
 
 }  // namespace fcp

@@ -5,6 +5,7 @@
 
 #include <atomic>
 #include "fcp.h"
+#include "fcp_sizes.h"
 
 namespace fcp {
 
@@ -47,7 +48,7 @@ struct SchedHeader {
   int32_t claimed[kNumXcd];     // one-pass backward: next unit of a queue that another XCD's blocks have claimed
   int32_t pad2[8];
 };                               // 128 bytes
-static_assert(sizeof(SchedHeader) == 128, "header size");
+static_assert(sizeof(SchedHeader) == kSchedHeaderBytes, "header size");
 constexpr int32_t kPathOnePass = 1;     // one pass over key tiles (csrc/fcp_attn_bwd_fused.hip, csrc/fcp_attn_bwd_short.hip)
 constexpr int32_t kPathSplitKeys = 2;   // key tiles in pieces of rows
 constexpr int32_t kPathSplitRows = 4;   // query tiles in pieces of keys
@@ -80,43 +81,28 @@ struct KTile {                   // a block of keys of one segment of one work i
 };
 static_assert(sizeof(QTile) == 64 && sizeof(KTile) == 64, "tile records are 16 words");
 struct Tile { int32_t w[16]; };  // storage type of the list
+static_assert(sizeof(Tile) == kTileBytes, "tile size");
 
-constexpr int kFwdBM = 256;      // query rows per forward unit
 constexpr int kFwdBN = 64;       // keys per forward inner step
 constexpr int kDqBM = 64;        // query rows per dQ unit (two heads of a KV head), twice that for a single head
 constexpr int kDqBN = 32;        // keys per dQ inner step
-constexpr int kBwdBN = 128;      // keys per dK/dV unit
 constexpr int kBwdBM = 32;       // query rows per dK/dV inner step
-constexpr int kMinFwdTile = 32;  // smallest query tile of the forward (sizes its tile list; the backward's is kDqBM)
 
 // Longest key segment of a work item the kernels take.  Byte offsets into a segment travel in 32-bit scalar
 // offsets of buffer instructions, and the fills run a few tiles past a segment's end (those land outside the
 // resource's range and read as zero): with a segment below 2^30 bytes the offsets stay far from 2^31.
 inline int32_t max_segment_keys(int64_t kv_row_bytes) { return (int32_t)(((int64_t)1 << 30) / kv_row_bytes); }
 
-// Upper bounds on the number of tiles of a valid plan (anything beyond is dropped and
-// counted as rejected).  Query tiles: every (row, slot) belongs to at most one item, and over
-// a rank's items the query chunks of a sequence add up to at most its length.  Key tiles:
-// over a rank's items the key segments of a sequence add up to at most twice its length.
-int64_t q_tile_cap(int32_t tq, int32_t tkv, int64_t n_work, int32_t n_parts, int32_t rows);   // rows: least rows of a tile
-int64_t kv_tile_cap(int32_t tkv, int64_t n_work);
 // Room for the backward's lists when tiles are split: a tile has two pieces more than its share of the steps asks for at most, and
 // all shares together make two pieces per CU.
 inline int64_t bwd_kv_cap(int32_t tkv, int64_t n_work) { return 2 * kv_tile_cap(tkv, n_work) + 2048; }
 inline int64_t bwd_q_cap(int32_t tq, int32_t tkv, int64_t n_work) { return 2 * q_tile_cap(tq, tkv, n_work, 1 << 20, kDqBM) + 2048; }
 
-// One schedule region: SchedHeader | item offsets int32[n_work+1] | Tile[cap]; every part padded to 64 bytes, the region to 256.
 constexpr int32_t kFlagQExclusive = 1;    // no other item of the launch covers these query rows
 constexpr int32_t kFlagSeg0Exclusive = 2; // no other item's key segment overlaps segment 0 / 1
 constexpr int32_t kFlagSeg1Exclusive = 4;
 constexpr int32_t kFlagInTurn = 8;        // tile records only: the unit is piece (flags >> kPieceShift) of a tile that the launch owns (split tiles)
 constexpr int kPieceShift = 8;
-inline size_t pad_to(size_t x, size_t a) { return (x + a - 1) / a * a; }
-inline size_t sched_item_off_bytes(int64_t n_work) { return pad_to((size_t)(n_work + 1) * sizeof(int32_t), 64); }
-inline size_t sched_region_bytes(int64_t n_work, int64_t cap) {
-  return pad_to(sizeof(SchedHeader) + sched_item_off_bytes(n_work) +
-                (size_t)cap * sizeof(Tile), 256);
-}
 inline const SchedHeader* sched_header(const void* region) { return static_cast<const SchedHeader*>(region); }
 inline const Tile* sched_tiles(const void* region, int64_t n_work) {
   return reinterpret_cast<const Tile*>(static_cast<const char*>(region) + sizeof(SchedHeader) +
@@ -222,7 +208,7 @@ inline int32_t* bwd_chain(void* scratch, int64_t n_work, int32_t tq, int32_t tkv
 
 // The forward's row states follow its tile list in its scratch buffer.
 inline uint8_t* fwd_q_state(void* scratch, int64_t n_work, int32_t tq, int32_t tkv, int32_t n_parts) {
-  return static_cast<uint8_t*>(scratch) + sched_region_bytes(n_work, q_tile_cap(tq, tkv, n_work, n_parts, kMinFwdTile));
+  return static_cast<uint8_t*>(scratch) + fwd_area_bytes(tq, tkv, n_work, n_parts);
 }
 
 }  // namespace fcp

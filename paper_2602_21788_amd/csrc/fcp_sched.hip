@@ -1132,16 +1132,6 @@ int launch_row_states(int64_t kv_row_bytes, const RowStates& rs, const int32_t* 
   return FCP_OK;
 }
 
-int64_t q_tile_cap(int32_t tq, int32_t tkv, int64_t n_work, int32_t n_parts, int32_t rows) {
-  const int64_t by_slots = (int64_t)n_parts * ((tq + (int64_t)rows - 1) / rows);
-  const int64_t by_tokens = (tkv + (int64_t)rows - 1) / rows;
-  return n_work + (by_slots < by_tokens ? by_slots : by_tokens);
-}
-
-int64_t kv_tile_cap(int32_t tkv, int64_t n_work) {
-  return 2 * n_work + 2 * (int64_t)((tkv + kBwdBN - 1) / kBwdBN);
-}
-
 int launch_schedule(bool backward, int32_t tile, int32_t inner, int64_t kv_row_bytes,
                     const int32_t* q_limit, const int32_t* k_from,
                     const fcp_work_desc* work, int64_t n_work,
@@ -1200,8 +1190,7 @@ extern "C" size_t fcp_scratch_bytes(int which, int32_t tq, int32_t tkv, int32_t 
            fcp::pad_to((size_t)tq, 256) + fcp::pad_to((size_t)tkv, 256) +  // + row states of the direct mode
            fcp::turn_bytes(tq, tkv, hq, hkv, n_work) +                     // + turns of split tiles
            fcp::chain_bytes(tq, tkv, hq, hkv, head_dim, n_work);                // + chains of the one-pass kernel
-  return fcp::sched_region_bytes(n_work, fcp::q_tile_cap(tq, tkv, n_work, n_parts, fcp::kMinFwdTile)) +
-         fcp::pad_to((size_t)tq, 256);                                  // + row states of the direct mode
+  return fcp::fwd_scratch_bytes(tq, tkv, n_work, n_parts);
 }
 
 extern "C" int fcp_scratch_status(const void* scratch, void* stream, int32_t* n_tiles, int32_t* n_rejected) {

@@ -1,0 +1,103 @@
+// Sizes and choices that follow from a call's arguments alone: room in the tile lists, the forward's form and its list (not installed).
+// Plain C++, so that they can be checked without a device.
+#pragma once
+#include <stddef.h>
+#include <stdint.h>
+
+#include <algorithm>
+
+namespace fcp {
+
+constexpr int kFwdBM = 256;      // query rows per forward unit
+constexpr int kMinFwdTile = 32;  // smallest query tile of the forward (sizes its tile list; the backward's is kDqBM)
+constexpr int kBwdBN = 128;      // keys per dK/dV unit
+
+constexpr size_t kSchedHeaderBytes = 128, kTileBytes = 64;
+constexpr int64_t kMaxTiles = INT32_MAX / 64;   // of a list
+
+inline size_t pad_to(size_t x, size_t a) { return (x + a - 1) / a * a; }
+
+// Upper bounds on the number of tiles of a valid plan (anything beyond is dropped and
+// counted as rejected).  Query tiles: every (row, slot) belongs to at most one item, and over
+// a rank's items the query chunks of a sequence add up to at most its length.  Key tiles:
+// over a rank's items the key segments of a sequence add up to at most twice its length.
+inline int64_t q_tile_cap(int32_t tq, int32_t tkv, int64_t n_work, int32_t n_parts, int32_t rows) {   // rows: least rows of a tile
+  const int64_t by_slots = (int64_t)n_parts * ((tq + (int64_t)rows - 1) / rows);
+  const int64_t by_tokens = (tkv + (int64_t)rows - 1) / rows;
+  return n_work + std::min(by_slots, by_tokens);
+}
+inline int64_t kv_tile_cap(int32_t tkv, int64_t n_work) {
+  return 2 * n_work + 2 * (int64_t)((tkv + kBwdBN - 1) / kBwdBN);
+}
+
+// One schedule region: SchedHeader | item offsets int32[n_work+1] | Tile[cap]; every part padded to 64 bytes, the region to 256.
+inline size_t sched_item_off_bytes(int64_t n_work) { return pad_to((size_t)(n_work + 1) * sizeof(int32_t), 64); }
+inline size_t sched_region_bytes(int64_t n_work, int64_t cap) {
+  return pad_to(kSchedHeaderBytes + sched_item_off_bytes(n_work) + (size_t)cap * kTileBytes, 256);
+}
+
+// ---- the forward ------------------------------------------------------------------------
+// The forms of the forward.  Rows per unit (of two heads each half as many where the heads of a KV head pair up):
+enum FwdForm {
+  kFwdWide,      // 256 rows: eight waves in lock step, one block per CU (csrc/fcp_attn_fwd.hip, 128 channels)
+  kFwdSmall,     // 128 rows: four waves, two blocks per CU (64 channels: three; csrc/fcp_attn_fwd_small.hip, as those below)
+  kFwdShort,     // 128 rows: four waves, three blocks per CU (128 channels)
+  kFwdSplit2,    // 64 rows: two waves share 32 rows and divide the keys
+  kFwdSplit4,    // four waves do; 64 rows of eight waves with 128 channels, 32 rows of four waves and one head with 64
+};
+inline int fwd_unit_rows(FwdForm f, int head_dim) { return f == kFwdWide ? kFwdBM : f == kFwdSplit2 ? 64 : f == kFwdSplit4 ? (head_dim == 64 ? 32 : 64) : 128; }
+
+// Which form works a list.  The items are in device memory; the host has their mean length and the work per CU (units of 128 rows of one head, a
+// row counted once per item that covers it).  Measured, forward step with its scheduling launch, wide / the form chosen, us:
+//   few units, and loops long enough to be divided: the longest unit's loop sets the time.  128 channels, 8 heads: 2000 tokens 56 / 36 (four waves
+//     a row), 4096 tokens 98 / 73 (two), 4096 tokens over 3 ranks 47 / 39.  64 channels, 4 heads: 512 tokens 23 / 18, 4096 82 / 41; several sequences
+//     have a longer longest loop for the same work: 16 of 16384 tokens 125 / 82.  (At twice the bounds the divided form is slower: 16384
+//     tokens over 5 ranks, 6 heads on 2 of 64 channels 75 / 88.)
+//   64 channels otherwise: blocks of four waves, three per CU, at every size: 60000 tokens in 16 sequences, 40 heads on 8 4100 / 3760; 1000 of 128 1050 / 737.
+//   128 channels: short items are mostly beginnings and ends of units, which other blocks of the CU cover: 1000 of 128, 32 heads on 8 922 / 694, 200
+//     of 400 690 / 608, 30 of 667 over 3 ranks 317 / 300; with few units per CU two blocks with 64-key tiles do better than three with 32-key tiles: 4000
+//     tokens in 8 sequences 84 / 77 (three: 85), 8192 tokens of 8 heads 190 / 182 (205).  Long items: the wide form (60000 tokens in 16
+//     sequences 4900; 5020 with three blocks, 5180 with two).
+inline FwdForm fwd_form(int head_dim, int hq, int64_t tq, int64_t tkv, int64_t n_work, int64_t n_parts, int n_cu) {
+  const int64_t rows = std::min(n_parts * tq, tkv);          // of all items together, at most
+  const int64_t mean = n_work > 0 ? rows / n_work : 0;
+  const double per_cu = (double)rows * hq / (128. * n_cu);
+  if (head_dim == 64) {
+    if (mean >= 256 && (per_cu <= 0.5 || (per_cu <= 1. && mean >= 1024))) return kFwdSplit4;
+    return mean >= 256 && per_cu <= (tq == tkv && n_work >= 8 ? 2.5 : 1.6) ? kFwdSplit2 : kFwdSmall;
+  }
+  if (mean >= 256 && per_cu <= 1.1) return per_cu <= 0.55 ? kFwdSplit4 : kFwdSplit2;
+  const int64_t units = (rows / 128 + n_work) * hq;
+  if (mean <= 640) return units <= 12 * (int64_t)n_cu ? kFwdSmall : kFwdShort;
+  return units <= 6 * (int64_t)n_cu ? kFwdSmall : kFwdWide;
+}
+
+// The form and its list: two heads of one KV head per unit when the heads pair up (and a unit has rows for two), else twice the rows for one head.
+// The list has to fit `area` bytes.  Where that of the form's tiles does not (the static work area is checked for tiles of 128 rows), units
+// of 128 rows of one head take their place, whose tiles are the largest that every head layout and both widths have.
+struct FwdPlan { FwdForm form; int32_t head_pair, tile; int64_t cap; };
+inline FwdPlan fwd_plan(int head_dim, int hq, int hkv, int32_t tq, int32_t tkv, int64_t n_work, int32_t n_parts, int n_cu, size_t area) {
+  auto with = [&](FwdForm f, bool pair) {
+    const int rows = fwd_unit_rows(f, head_dim);
+    const int32_t tile = pair ? rows / 2 : rows;
+    return FwdPlan{f, pair ? 1 : 0, tile, q_tile_cap(tq, tkv, n_work, n_parts, tile)};
+  };
+  const FwdForm form = fwd_form(head_dim, hq, tq, tkv, n_work, n_parts, n_cu);
+  const FwdPlan p = with(form, (hq / hkv) % 2 == 0 && fwd_unit_rows(form, head_dim) > 32);
+  if (p.cap <= kMaxTiles && sched_region_bytes(n_work, p.cap) <= area) return p;
+  return with(kFwdSmall, false);
+}
+
+// What a call must bring: the list of the smallest tiles and the direct mode's row states; for the static area (no row states, and the plan goes by
+// what fits) the list of 128-row tiles, with tq bytes to spare.
+inline size_t fwd_area_bytes(int32_t tq, int32_t tkv, int64_t n_work, int32_t n_parts) {
+  return sched_region_bytes(n_work, q_tile_cap(tq, tkv, n_work, n_parts, kMinFwdTile));
+}
+inline size_t fwd_scratch_bytes(int32_t tq, int32_t tkv, int64_t n_work, int32_t n_parts) {
+  return fwd_area_bytes(tq, tkv, n_work, n_parts) + pad_to((size_t)tq, 256);
+}
+inline size_t fwd_static_bytes(int32_t tq, int32_t tkv, int64_t n_work, int32_t n_parts) {
+  return sched_region_bytes(n_work, q_tile_cap(tq, tkv, n_work, n_parts, kFwdBM / 2)) + pad_to((size_t)tq, 256);
+}
+
+}  // namespace fcp

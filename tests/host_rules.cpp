@@ -1,0 +1,15 @@
+// What csrc/fcp_sizes.h computes, for tests/host_rules.py.
+#include "fcp_sizes.h"
+
+extern "C" {
+// out: tile rows, paired heads, list capacity, bytes of the list's region
+void forward_plan(int head_dim, int hq, int hkv, int32_t tq, int32_t tkv, int64_t n_work, int32_t n_parts, int n_cu, int64_t area, int64_t* out) {
+  const fcp::FwdPlan p = fcp::fwd_plan(head_dim, hq, hkv, tq, tkv, n_work, n_parts, n_cu, (size_t)area);
+  out[0] = p.tile;
+  out[1] = p.head_pair;
+  out[2] = p.cap;
+  out[3] = (int64_t)fcp::sched_region_bytes(n_work, p.cap);
+}
+int64_t static_bytes(int32_t tq, int32_t tkv, int64_t n_work, int32_t n_parts) { return (int64_t)fcp::fwd_static_bytes(tq, tkv, n_work, n_parts); }
+int64_t scratch_area_bytes(int32_t tq, int32_t tkv, int64_t n_work, int32_t n_parts) { return (int64_t)fcp::fwd_area_bytes(tq, tkv, n_work, n_parts); }
+}

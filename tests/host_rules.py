@@ -1,0 +1,30 @@
+"""The library's rules on sizes (csrc/fcp_sizes.h, plain C++), compiled by themselves for the tests."""
+import ctypes
+import functools
+import os
+import subprocess
+import tempfile
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+
+
+@functools.lru_cache(None)
+def lib():
+    with tempfile.TemporaryDirectory() as d:
+        so = os.path.join(d, "host_rules.so")
+        subprocess.check_call(["g++", "-std=c++17", "-O1", "-Wall", "-shared", "-fPIC", "-I", os.path.join(ROOT, "paper_2602_21788_amd", "csrc"),
+                               "-o", so, os.path.join(ROOT, "tests", "host_rules.cpp")])
+        L = ctypes.CDLL(so)
+    i32, i64, P = ctypes.c_int32, ctypes.c_int64, ctypes.POINTER(ctypes.c_int64)
+    L.forward_plan.argtypes = [i32, i32, i32, i32, i32, i64, i32, i32, i64, P]
+    L.forward_plan.restype = None
+    for f in (L.static_bytes, L.scratch_area_bytes):
+        f.argtypes, f.restype = [i32, i32, i64, i32], i64
+    return L
+
+
+def forward_plan(head_dim, hq, hkv, tq, tkv, n_work, n_parts, area, n_cu=256):
+    """(tile rows, two heads per unit, tiles the list has room for, bytes of its region)."""
+    out = (ctypes.c_int64 * 4)()
+    lib().forward_plan(head_dim, hq, hkv, tq, tkv, n_work, n_parts, n_cu, area, out)
+    return tuple(out)

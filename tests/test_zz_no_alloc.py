@@ -64,3 +64,29 @@ def test_static_work_area_rejects_what_does_not_fit():
     p = ctypes.c_void_p(t.data_ptr())
     rc = B.lib().fcp_attn_fwd_step_static(p, p, p, p, 1, p, 100000, 4, 1 << 22, 1 << 22, 8, 8, 128, 0.1, p, p, None)
     assert rc == B.FCP_ERR_CAPACITY and b"static" in B.lib().fcp_last_error()
+
+
+def test_static_work_area_takes_larger_tiles_where_its_own_would_not_fit():
+    """16 sequences of 131072 tokens over 4 ranks, two heads on one KV head of 64 channels: the list of 64-row tiles that a caller's buffer would hold is
+    longer than the static area, a list of 128-row tiles is not.  Every wave has the same 32 rows of the same head either way: equal results."""
+    import torch
+    import paper_2602_21788_amd as fcp
+    from paper_2602_21788_amd.rank import RankAttention
+    from host_rules import forward_plan
+    lens, hq, hkv, D = [1 << 17] * 16, 2, 1, 64
+    ra = RankAttention(lens, [4] * 16, 3, hq, hkv, D)
+    n_cu = torch.cuda.get_device_properties(0).multi_processor_count
+    plan = [forward_plan(D, hq, hkv, ra.tq, ra.tkv, ra.n_work, ra.n_parts, area, n_cu) for area in (1 << 40, 2 * 1024 * 1024)]
+    assert plan[0][0] == 64 and plan[0][3] > 2 * 1024 * 1024 and plan[1][0] == 128 and plan[1][3] <= 2 * 1024 * 1024
+    ra.set_random_inputs(7)
+    print(f"static work area: {ra.tq} rows, {ra.tkv} keys, {ra.n_work} items, {ra.n_parts} steps", flush=True)
+    ra.forward_steps()
+    torch.cuda.synchronize()
+    assert fcp.fcp_scratch_status(ra.scratch_f) == (sum(-(-int(n) // 64) for n in ra.work["q_len"]), 0)
+    want_o, want_l = ra.o_part.clone(), ra.lse_part.clone()
+    ra.o_part.fill_(float("nan")); ra.lse_part.fill_(float("nan"))
+    fcp.fcp_attn_fwd_step_static(ra.q, ra.k, ra.v, ra.cu_d, ra.work_d, ra.n_parts, ra.scale, ra.o_part, ra.lse_part)
+    torch.cuda.synchronize()
+    assert torch.equal(ra.lse_part, want_l)
+    covered = torch.isfinite(want_l).transpose(1, 2).unsqueeze(-1)      # [parts, tq, hq, 1]
+    assert torch.equal(torch.where(covered, ra.o_part, 0.), torch.where(covered, want_o, 0.))
