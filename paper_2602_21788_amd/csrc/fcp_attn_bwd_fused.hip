@@ -636,9 +636,7 @@ __global__ __launch_bounds__(768, 1) void bwd_fused_kernel(const BwdParams p0) {
 }  // namespace
 
 int launch_bwd_fused(const BwdParams& p, int64_t units, int n_cu, hipStream_t stream) {
-  int64_t blocks = n_cu;                               // one 768-thread block per CU
-  if (blocks > units) blocks = (units + 7) / 8 * 8;    // a multiple of the XCD count
-  if (blocks < 8) blocks = 8;
+  const int64_t blocks = persistent_blocks(n_cu, units);               // one 768-thread block per CU
   static std::atomic<uint64_t> lds_done;
   const int rc = raise_lds_limit((const void*)bwd_fused_kernel<128>, FusedCfg<128>::LDS_BYTES, lds_done);
   if (rc != FCP_OK) return rc;

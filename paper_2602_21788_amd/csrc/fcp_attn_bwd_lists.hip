@@ -699,14 +699,7 @@ __global__ __launch_bounds__(256, lists_blocks_per_cu(D)) void bwd_lists_kernel(
     }
   }
   n_long = min(n_long, min(kv_mine, places));
-  // The blocks' first units: the long key tiles, then key tiles and query tiles in turn, then query tiles.
-  const int kv_dealt = min(kv_mine, n_long + (places - n_long + 1) / 2);
-  int kv_first = -1, q_first = -1;                 // the block's
-  const int k = place - n_long, pairs = 2 * (kv_dealt - n_long);
-  if (k < 0) kv_first = place;
-  else if (k >= pairs) q_first = k - pairs / 2;
-  else if (k & 1) q_first = k >> 1;
-  else kv_first = n_long + (k >> 1);
+  const auto [kv_dealt, kv_first, q_first] = first_unit(place, places, kv_mine, n_long);
   if (kv_first < 0 && q_first >= PartQueue::mine(q_units + q_half, q_xcd) && kv_dealt == kv_mine) return;   // the others are enough
   bool keys = kv_first >= 0;
 #pragma unroll 1
@@ -731,9 +724,7 @@ int launch_one(const BwdParams& p, int head_pair, int64_t units, int n_cu, hipSt
   const auto kernel = bwd_lists_kernel<D, AHEAD>;
   const int rc = raise_lds_limit((const void*)kernel, C::LDS_BYTES, lds_done);
   if (rc != FCP_OK) return rc;
-  int64_t blocks = (int64_t)n_cu * lists_blocks_per_cu(D);   // as many as are resident
-  if (blocks > units) blocks = (units + 7) / 8 * 8;   // a multiple of the XCD count
-  if (blocks < 8) blocks = 8;
+  const int64_t blocks = persistent_blocks((int64_t)n_cu * lists_blocks_per_cu(D), units);
   hipLaunchKernelGGL(kernel, dim3((unsigned)blocks), dim3(256), C::LDS_BYTES, stream, p, head_pair);
   FCP_HIP_CHECK(hipGetLastError());
   return FCP_OK;

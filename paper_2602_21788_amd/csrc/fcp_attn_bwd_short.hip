@@ -547,9 +547,7 @@ __global__ __launch_bounds__(256, 2) void bwd_short_kernel(const BwdParams p) {
 }  // namespace
 
 int launch_bwd_short(const BwdParams& p, int64_t units, int n_cu, hipStream_t stream) {
-  int64_t blocks = 2 * (int64_t)n_cu;                  // as many as are resident
-  if (blocks > units) blocks = (units + 7) / 8 * 8;    // a multiple of the XCD count
-  if (blocks < 8) blocks = 8;
+  const int64_t blocks = persistent_blocks(2 * (int64_t)n_cu, units);   // as many as are resident
   static std::atomic<uint64_t> lds_done;
   const int rc = raise_lds_limit((const void*)bwd_short_kernel<128>, ShortCfg<128>::LDS_BYTES, lds_done);
   if (rc != FCP_OK) return rc;

@@ -544,9 +544,7 @@ static int fwd_step(const void* q, const void* k, const void* v, const int32_t* 
 
   int64_t units = cap * (hq / (head_pair ? 2 : 1));
   if (form != fcp::kFwdWide) return fcp::launch_fwd_small(p, head_dim, form, units, n_cu, st);
-  int64_t blocks = n_cu;                               // one 512-thread block per CU
-  if (blocks > units) blocks = (units + 7) / 8 * 8;   // keep a multiple of the XCD count
-  if (blocks < 8) blocks = 8;
+  const int64_t blocks = fcp::persistent_blocks(n_cu, units);   // one 512-thread block per CU
   static std::atomic<uint64_t> lds_done;
   if ((rc = fcp::raise_lds_limit((const void*)fcp::fwd_kernel<128>, fcp::FwdCfg<128>::LDS_BYTES, lds_done)) != FCP_OK) return rc;
   hipLaunchKernelGGL(fcp::fwd_kernel<128>, dim3((unsigned)blocks), dim3(512), fcp::FwdCfg<128>::LDS_BYTES, st, p);

@@ -444,9 +444,7 @@ int launch_one(const FwdParams& p, int64_t units, int n_cu, hipStream_t stream) 
   const auto kernel = fwd_small_kernel<D, NW, SPLIT, SKEYS, OCC, AH>;
   const int rc = raise_lds_limit((const void*)kernel, C::LDS_BYTES, lds_done);
   if (rc != FCP_OK) return rc;
-  int64_t blocks = (int64_t)n_cu * (OCC * 4 / NW);     // as many as are resident
-  if (blocks > units) blocks = (units + 7) / 8 * 8;   // a multiple of the XCD count
-  if (blocks < 8) blocks = 8;
+  const int64_t blocks = persistent_blocks((int64_t)n_cu * (OCC * 4 / NW), units);
   hipLaunchKernelGGL(kernel, dim3((unsigned)blocks), dim3(64 * NW), C::LDS_BYTES, stream, p);
   FCP_HIP_CHECK(hipGetLastError());
   return FCP_OK;

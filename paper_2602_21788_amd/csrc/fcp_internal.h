@@ -36,7 +36,6 @@ inline int raise_lds_limit(const void* kernel, int bytes, std::atomic<uint64_t>&
 // Both attention kernels are persistent: blocks pull (tile, head) units from counters
 // until the list is exhausted.  There is one counter per XCD so that the blocks of one
 // XCD (blockIdx % 8) walk the heads of the same KV heads and share K/V in that XCD's L2.
-constexpr int kNumXcd = 8;
 struct SchedHeader {
   int32_t n_tiles;              // tiles in the list (sorted by decreasing cost)
   int32_t n_rejected;           // work items that failed validation

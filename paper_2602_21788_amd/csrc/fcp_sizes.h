@@ -6,6 +6,12 @@
 
 #include <algorithm>
 
+#ifdef __HIPCC__
+#define FCP_HD __host__ __device__
+#else
+#define FCP_HD
+#endif
+
 namespace fcp {
 
 constexpr int kFwdBM = 256;      // query rows per forward unit
@@ -34,6 +40,29 @@ inline int64_t kv_tile_cap(int32_t tkv, int64_t n_work) {
 inline size_t sched_item_off_bytes(int64_t n_work) { return pad_to((size_t)(n_work + 1) * sizeof(int32_t), 64); }
 inline size_t sched_region_bytes(int64_t n_work, int64_t cap) {
   return pad_to(kSchedHeaderBytes + sched_item_off_bytes(n_work) + (size_t)cap * kTileBytes, 256);
+}
+
+// ---- grids of the persistent kernels and the first units of their blocks ----------------
+constexpr int kNumXcd = 8;
+
+// Blocks of a launch: as many as are resident, or as there are units, and a multiple of the XCD count: block b is number b / 8 of the grid / 8 blocks
+// of queue b % 8.  With 300 resident blocks a 38th block of some queues would begin with a unit that the counter deals out too.
+inline int64_t persistent_blocks(int64_t resident, int64_t units) {
+  const int64_t most = resident / kNumXcd * kNumXcd, wanted = (units + kNumXcd - 1) / kNumXcd * kNumXcd;
+  return std::max<int64_t>(kNumXcd, std::min(most, wanted));
+}
+
+// Two lists worked by the same blocks (csrc/fcp_attn_bwd_lists.hip): what block `place` of the `places` of its queue begins with, the key units of the queue
+// being `key_units`, `n_long` of them (`places` at most) longer than any row unit.  The long key units go to the first blocks, then key units and row
+// units in turn, then row units.  The counters deal out the rest: key units from `key_dealt` on, row units from places - key_dealt on.
+struct FirstUnit { int key_dealt, key, row; };     // (-1: none of that list)
+FCP_HD inline FirstUnit first_unit(int place, int places, int key_units, int n_long) {
+  const int alternate = n_long + (places - n_long + 1) / 2;
+  const int key_dealt = key_units < alternate ? key_units : alternate;
+  const int k = place - n_long, pairs = 2 * (key_dealt - n_long);
+  if (k < 0) return {key_dealt, place, -1};
+  if (k >= pairs) return {key_dealt, -1, k - pairs / 2};
+  return (k & 1) ? FirstUnit{key_dealt, -1, k >> 1} : FirstUnit{key_dealt, n_long + (k >> 1), -1};
 }
 
 // ---- the forward ------------------------------------------------------------------------

@@ -20,6 +20,8 @@ def lib():
     L.forward_plan.restype = None
     for f in (L.static_bytes, L.scratch_area_bytes):
         f.argtypes, f.restype = [i32, i32, i64, i32], i64
+    L.persistent_blocks.argtypes, L.persistent_blocks.restype = [i64, i64], i64
+    L.first_unit.argtypes, L.first_unit.restype = [i32, i32, i32, i32, P], None
     return L
 
 
@@ -27,4 +29,15 @@ def forward_plan(head_dim, hq, hkv, tq, tkv, n_work, n_parts, area, n_cu=256):
     """(tile rows, two heads per unit, tiles the list has room for, bytes of its region)."""
     out = (ctypes.c_int64 * 4)()
     lib().forward_plan(head_dim, hq, hkv, tq, tkv, n_work, n_parts, n_cu, area, out)
+    return tuple(out)
+
+
+def persistent_blocks(resident, units):
+    return lib().persistent_blocks(resident, units)
+
+
+def first_unit(place, places, key_units, n_long):
+    """(key units dealt, the block's first key unit, its first row unit); -1: none of that list."""
+    out = (ctypes.c_int64 * 3)()
+    lib().first_unit(place, places, key_units, n_long, out)
     return tuple(out)
