@@ -61,7 +61,7 @@ struct KeyCfg {
 template <int D> constexpr int kTr8 = (DualTile<D>::key(0) ^ DualTile<D>::key(8)) << 4;
 
 template <int D, int AHEAD>
-__device__ inline void key_units(const BwdParams& p, PartQueue& uq, unsigned char* const smem, int32_t* const s_next_unit, int32_t* const s_rec) {
+__device__ inline void key_units(const BwdParams& p, const int queues, PartQueue& uq, unsigned char* const smem, int32_t* const s_next_unit, int32_t* const s_rec) {
   using C = KeyCfg<D>;
   using DT = typename C::DT;
   using VT = typename C::VT;
@@ -70,9 +70,7 @@ __device__ inline void key_units(const BwdParams& p, PartQueue& uq, unsigned cha
   const int l32 = lane & 31, g2 = lane >> 5;
   const int G = p.hq / p.hkv;
   const uint32_t lds0 = lds_offset(smem);
-  const bool per_xcd = (p.hkv % kNumXcd) == 0;
-  const int xcd = per_xcd ? (int)(blockIdx.x % kNumXcd) : 0;
-  const int kvh_here = per_xcd ? p.hkv / kNumXcd : p.hkv;
+  const int kvh_here = p.hkv / queues, kvh0 = (int)(blockIdx.x % queues) * kvh_here;    // the queue's heads
 
   const int q_row_bytes = p.hq * D * 2;
   const int kv_row_bytes = p.hkv * D * 2;
@@ -93,7 +91,7 @@ __device__ inline void key_units(const BwdParams& p, PartQueue& uq, unsigned cha
     const int unit = uq.current(s_next_unit);
     if (unit >= uq.n_all) break;
     const KTile t = read_record<KTile, 16>(s_rec);
-    const int kvh = xcd * kvh_here + unit % kvh_here;
+    const int kvh = kvh0 + unit % kvh_here;
     uq.prefetch();
 
     const bool exclusive = (t.flags & kFlagSeg0Exclusive) != 0;
@@ -366,7 +364,7 @@ struct RowCfg {
 };
 
 template <int D, int SPLIT, int SKEYS, int AHEAD>
-__device__ inline void row_units(const BwdParams& p, const int head_pair, PartQueue& uq, unsigned char* const smem, int32_t* const s_next_unit, int32_t* const s_rec) {
+__device__ inline void row_units(const BwdParams& p, const int head_pair, const int queues, PartQueue& uq, unsigned char* const smem, int32_t* const s_next_unit, int32_t* const s_rec) {
   using C = RowCfg<D, SPLIT, SKEYS>;
   using DT = typename C::DT;
   const int tid = threadIdx.x;
@@ -376,9 +374,7 @@ __device__ inline void row_units(const BwdParams& p, const int head_pair, PartQu
   const int G = p.hq / p.hkv;
   const uint32_t lds0 = lds_offset(smem);
   const int hpu = head_pair ? 2 : 1;
-  const bool per_xcd = (p.hq % (kNumXcd * hpu)) == 0;
-  const int xcd = per_xcd ? (int)(blockIdx.x % kNumXcd) : 0;
-  const int heads_here = per_xcd ? p.hq / kNumXcd : p.hq;
+  const int heads_here = p.hq / queues, head0 = (int)(blockIdx.x % queues) * heads_here;
   const int units_per_tile = heads_here / hpu;
 
   const int kv_row_bytes = p.hkv * D * 2;
@@ -414,7 +410,7 @@ __device__ inline void row_units(const BwdParams& p, const int head_pair, PartQu
         continue;
       }
     }
-    const int head = xcd * heads_here + (whole % units_per_tile) * hpu + (head_pair ? group / RGP : 0);
+    const int head = head0 + (whole % units_per_tile) * hpu + (head_pair ? group / RGP : 0);
     const int kvh = head / G;
 
     const bool exclusive = (t.flags & kFlagQExclusive) != 0;
@@ -665,23 +661,25 @@ __global__ __launch_bounds__(256, lists_blocks_per_cu(D)) void bwd_lists_kernel(
   __shared__ int32_t s_rec[16];
   const int path = p.hdr->path;
   if (p.either && (path & kPathOnePass)) return;
-  const bool ordered = (path & (kPathSplitKeys | kPathSplitRows)) != 0;   // units wait for earlier ones
+  const bool kv_turns = (path & kPathSplitKeys) != 0, q_turns = (path & kPathSplitRows) != 0;   // units wait for earlier ones of their list
+  const bool turns = kv_turns || q_turns;
   const int place = PartQueue::place(), places = PartQueue::places();
   const bool kv_xcd = (p.hkv % kNumXcd) == 0;
   const int kv_per_tile = kv_xcd ? p.hkv / kNumXcd : p.hkv;
-  const int kv_units = p.hdr->n_tiles * kv_per_tile;
+  const int kv_tiles = p.hdr->n_tiles, q_tiles = p.hdr_q->n_tiles;      // (read here once: the counters beside them are busy later)
+  const int kv_units = kv_tiles * kv_per_tile;
   const int kv_mine = PartQueue::mine(kv_units, kv_xcd);
   const int hpu = head_pair ? 2 : 1;
   const bool q_xcd = (p.hq % (kNumXcd * hpu)) == 0;
   const int q_per_tile = (q_xcd ? p.hq / kNumXcd : p.hq) / hpu;
-  const int q_units = p.hdr_q->n_tiles * q_per_tile;
+  const int q_units = q_tiles * q_per_tile;
 
   // How many of the key tiles that could come first take longer than the longest query tile (lists are sorted).
   const QTile* const q_list = reinterpret_cast<const QTile*>(p.tiles_q);
   const int lane = threadIdx.x & 63;
   int q_half = 0, n_long = kv_mine;
   if (q_units > 0) {
-    if (!(path & kPathSplitRows)) {
+    if (!q_turns) {
       q_half = min(q_units, q_xcd ? places : (int)gridDim.x);
       const QTile& t = q_list[(q_units - q_half) / q_per_tile];
       if (t.vis[0] + t.vis[1] < kHalfKeys) q_half = 0;
@@ -706,13 +704,20 @@ __global__ __launch_bounds__(256, lists_blocks_per_cu(D)) void bwd_lists_kernel(
   for (int turn = 0; turn < 2; ++turn, keys = !keys) {
     PartQueue uq;
     if (turn) __syncthreads();                     // (everybody has seen the end of the other list)
+    const bool dealt = !turns && turn == 0;
     if (keys) {
-      uq.open(p.hdr, p.tiles, kv_units, 0, kv_per_tile, kv_xcd, ordered || turn ? -1 : kv_first, ordered ? 0 : kv_dealt, &s_next_unit, s_rec);
-      key_units<D, AHEAD>(p, uq, smem, &s_next_unit, s_rec);
+      const int queues = head_queues(p.hkv, kv_turns);
+      const int per_tile = p.hkv / queues;
+      uq.open(p.hdr, p.tiles, kv_tiles * per_tile, 0, per_tile, unit_numbers(blockIdx.x, queues, kv_turns), turns, dealt ? kv_first : -1,
+              turns ? 0 : kv_dealt, &s_next_unit, s_rec);
+      key_units<D, AHEAD>(p, queues, uq, smem, &s_next_unit, s_rec);
     } else {
-      uq.open(p.hdr_q, p.tiles_q, q_units, q_half, q_per_tile, q_xcd, ordered || turn ? -1 : q_first, ordered ? 0 : places - kv_dealt, &s_next_unit, s_rec);
-      row_units<D, 1, 64, 4>(p, head_pair, uq, smem, &s_next_unit, s_rec);
-      row_units<D, 2, 64, 4>(p, head_pair, uq, smem, &s_next_unit, s_rec);
+      const int queues = head_queues(p.hq / hpu, q_turns);
+      const int per_tile = p.hq / hpu / queues;
+      uq.open(p.hdr_q, p.tiles_q, q_tiles * per_tile, q_half, per_tile, unit_numbers(blockIdx.x, queues, q_turns), turns, dealt ? q_first : -1,
+              turns ? 0 : places - kv_dealt, &s_next_unit, s_rec);
+      row_units<D, 1, 64, 4>(p, head_pair, queues, uq, smem, &s_next_unit, s_rec);
+      row_units<D, 2, 64, 4>(p, head_pair, queues, uq, smem, &s_next_unit, s_rec);
     }
   }
 }

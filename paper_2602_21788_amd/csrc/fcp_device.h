@@ -294,8 +294,13 @@ struct UnitQueue {
 };
 
 // Unit queue of the kernels whose blocks are smaller than a CU's share (several hundred of them): as UnitQueue, with what so many blocks need.
-//   * The heads of a launch that do not divide among the XCDs (`per_xcd` false) have one numbering, and the XCDs' counters deal it out in turn:
-//     number = 8 i + XCD.  (One counter for 768 blocks: an atomic on one address takes about 18 ns, 200 sequences of 60 tokens 30 us longer.)
+//   * The heads of a launch that do not divide among the XCDs have one numbering, and the XCDs' counters deal it out in turn:
+//     number = 8 i + XCD (unit_numbers).  (One counter for 768 blocks: an atomic on one address takes about 18 ns, 200 sequences of 60 tokens 30 us longer.)
+//     Not where units wait for each other: see head_queues.
+//   * `late`, for launches with pieces of tiles: a block takes its next unit when it has worked the one before, and has none in reserve.  A piece in reserve
+//     holds up the pieces after it, and half of the atomics when the launch begins fall away.  Backward step, one unit in reserve / none, us: 8192
+//     tokens, 3 heads on 3, 128 channels 413 / 227; 6 sequences of 6000 tokens in all, 8 heads on 8, 219 / 153; 4096 tokens, 32 heads on 8, 482 / 445;
+//     30 of 20011 tokens, the longest over 3 ranks, 6 heads on 2, 234 / 214.
 //   * `first` >= 0: the block begins with that number of its queue and the counter deals out those from `dealt` on.  Only for lists whose units never
 //     wait for each other: a unit of a block that has not begun is held back with it.
 //   * The last `n_half` units are worked in halves, numbered on: the end of a launch is as long as a unit.
@@ -304,21 +309,23 @@ struct PartQueue {
   int32_t* counter;
   const int32_t* rec_words;
   int32_t n_full, n_all, per_tile, mul, add, dealt;
+  bool late;
 
   static __device__ int place() { return blockIdx.x / kNumXcd; }      // of the block in its queue
   static __device__ int places() { return gridDim.x / kNumXcd; }
   // how many of n numbers are this block's queue's
   static __device__ int mine(int n, bool per_xcd) { return per_xcd ? n : (n + kNumXcd - 1 - (int)(blockIdx.x % kNumXcd)) / kNumXcd; }
   __device__ int tile_of(int u) const { return (u < n_full ? u : n_full + ((u - n_full) >> 1)) / per_tile; }
-  __device__ void open(SchedHeader* hdr, const Tile* tiles, int n_units, int n_half, int per_tile_, bool per_xcd, int first, int dealt_, int32_t* s_next, int32_t* s_rec) {
-    counter = &hdr->counter[blockIdx.x % kNumXcd];
+  __device__ void open(SchedHeader* hdr, const Tile* tiles, int n_units, int n_half, int per_tile_, UnitNumbers numbers, bool late_, int first, int dealt_, int32_t* s_next, int32_t* s_rec) {
+    counter = &hdr->counter[numbers.counter];
     rec_words = reinterpret_cast<const int32_t*>(tiles);
     per_tile = per_tile_;
     n_full = n_units - n_half;
     n_all = n_units + n_half;
-    mul = per_xcd ? 1 : kNumXcd;
-    add = per_xcd ? 0 : (int)(blockIdx.x % kNumXcd);
+    mul = numbers.mul;
+    add = numbers.add;
     dealt = dealt_;
+    late = late_;
     pend = recw = idx1 = 0;
     if (threadIdx.x < 64) {
       const int lane = threadIdx.x & 63;
@@ -328,7 +335,7 @@ struct PartQueue {
         v0 = __builtin_amdgcn_readfirstlane(v0);
       }
       const int32_t u0 = v0 * mul + add;
-      if (lane == 0) pend = (dealt + atomicAdd(counter, 1)) * mul + add;
+      if (lane == 0 && !late) pend = (dealt + atomicAdd(counter, 1)) * mul + add;
       if (lane < 16) s_rec[lane] = u0 < n_all ? rec_words[tile_of(u0) * 16 + lane] : 0;
       if (lane == 0) *s_next = u0;
     }
@@ -336,7 +343,7 @@ struct PartQueue {
   }
   __device__ int32_t current(const int32_t* s_next) const { return __builtin_amdgcn_readfirstlane(*s_next); }
   __device__ void prefetch() {
-    if (threadIdx.x < 64) {
+    if (threadIdx.x < 64 && !late) {
       const int lane = threadIdx.x & 63;
       idx1 = __builtin_amdgcn_readfirstlane(pend);
       if (lane == 0) pend = (dealt + atomicAdd(counter, 1)) * mul + add;
@@ -346,6 +353,12 @@ struct PartQueue {
   __device__ void advance(int32_t* s_next, int32_t* s_rec) {
     if (threadIdx.x < 64) {
       const int lane = threadIdx.x & 63;
+      if (late) {
+        int32_t v = 0;
+        if (lane == 0) v = (dealt + atomicAdd(counter, 1)) * mul + add;
+        idx1 = __builtin_amdgcn_readfirstlane(v);
+        recw = (lane < 16 && idx1 < n_all) ? rec_words[tile_of(idx1) * 16 + lane] : 0;
+      }
       if (lane < 16) s_rec[lane] = recw;
       if (lane == 0) *s_next = idx1;
     }

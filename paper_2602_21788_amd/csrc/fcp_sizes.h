@@ -52,6 +52,22 @@ inline int64_t persistent_blocks(int64_t resident, int64_t units) {
   return std::max<int64_t>(kNumXcd, std::min(most, wanted));
 }
 
+// The heads of a tile (`per_tile`: heads, or pairs of them) and the queues.  `queues` > 1, or a list whose units wait for each other (`in_turn`): every queue
+// has as many heads as every other and works all tiles for them, in list order; its blocks are b = queue mod `queues`.  A unit then waits for units of its
+// own queue only (the pieces of a tile for one head), which running blocks have taken before it: blocks that cannot start, because something else
+// holds their CUs, hold up nobody who runs.  (A power of two: as many blocks for every queue.)  `queues` = 1 else: one numbering, which the eight counters
+// deal out in turn.
+FCP_HD inline int head_queues(int per_tile, bool in_turn) {
+  if (per_tile % kNumXcd == 0) return kNumXcd;
+  return !in_turn ? 1 : per_tile % 4 == 0 ? 4 : per_tile % 2 == 0 ? 2 : 1;
+}
+// Which counter a block takes numbers from, and the unit that number i is of the queue's heads: mul i + add.
+struct UnitNumbers { int counter, mul, add; };
+FCP_HD inline UnitNumbers unit_numbers(int block, int queues, bool in_turn) {
+  if (queues > 1 || in_turn) return {block % queues, 1, 0};
+  return {block % kNumXcd, kNumXcd, block % kNumXcd};
+}
+
 // Two lists worked by the same blocks (csrc/fcp_attn_bwd_lists.hip): what block `place` of the `places` of its queue begins with, the key units of the queue
 // being `key_units`, `n_long` of them (`places` at most) longer than any row unit.  The long key units go to the first blocks, then key units and row
 // units in turn, then row units.  The counters deal out the rest: key units from `key_dealt` on, row units from places - key_dealt on.

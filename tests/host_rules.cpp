@@ -19,4 +19,11 @@ void first_unit(int place, int places, int key_units, int n_long, int64_t* out) 
   out[1] = f.key;
   out[2] = f.row;
 }
+int head_queues(int per_tile, int in_turn) { return fcp::head_queues(per_tile, in_turn != 0); }
+void unit_numbers(int block, int queues, int in_turn, int64_t* out) {
+  const fcp::UnitNumbers n = fcp::unit_numbers(block, queues, in_turn != 0);
+  out[0] = n.counter;
+  out[1] = n.mul;
+  out[2] = n.add;
+}
 }

@@ -22,6 +22,8 @@ def lib():
         f.argtypes, f.restype = [i32, i32, i64, i32], i64
     L.persistent_blocks.argtypes, L.persistent_blocks.restype = [i64, i64], i64
     L.first_unit.argtypes, L.first_unit.restype = [i32, i32, i32, i32, P], None
+    L.head_queues.argtypes, L.head_queues.restype = [i32, i32], i32
+    L.unit_numbers.argtypes, L.unit_numbers.restype = [i32, i32, i32, P], None
     return L
 
 
@@ -40,4 +42,15 @@ def first_unit(place, places, key_units, n_long):
     """(key units dealt, the block's first key unit, its first row unit); -1: none of that list."""
     out = (ctypes.c_int64 * 3)()
     lib().first_unit(place, places, key_units, n_long, out)
+    return tuple(out)
+
+
+def head_queues(per_tile, in_turn):
+    return lib().head_queues(per_tile, in_turn)
+
+
+def unit_numbers(block, queues, in_turn):
+    """(counter, mul, add): number i of the counter is unit mul i + add of the queue's heads."""
+    out = (ctypes.c_int64 * 3)()
+    lib().unit_numbers(block, queues, in_turn, out)
     return tuple(out)

@@ -1,8 +1,9 @@
-"""Every unit of a persistent launch is taken once, whatever the number of CUs: blocks begin with units by their numbers, counters deal out the rest."""
+"""Every unit of a persistent launch is taken once, whatever the number of CUs: blocks begin with units by their numbers, counters deal out the rest.  A unit that
+waits for others does so inside its own queue."""
 import numpy as np
 import pytest
 
-from host_rules import first_unit, persistent_blocks
+from host_rules import first_unit, head_queues, persistent_blocks, unit_numbers
 
 XCDS = 8
 
@@ -42,3 +43,30 @@ def test_a_grid_that_is_no_multiple_takes_units_twice():
 def test_grids():
     assert persistent_blocks(256, 10 ** 9) == 256 and persistent_blocks(768, 767) == 768 and persistent_blocks(768, 41) == 48
     assert persistent_blocks(300, 10 ** 9) == 296 and persistent_blocks(4, 10) == 8 and persistent_blocks(256, 0) == 8
+
+
+def _list(block, per_tile, in_turn, n_tiles):
+    """The (tile, head) units that the block's counter deals out, in that order, and the counter."""
+    queues = head_queues(per_tile, in_turn)
+    here = per_tile // queues
+    assert here * queues == per_tile
+    counter, mul, add = unit_numbers(block, queues, in_turn)
+    return counter, [(u // here, block % queues * here + u % here) for u in range(add, n_tiles * here, mul)]
+
+
+@pytest.mark.parametrize("in_turn", [0, 1])
+@pytest.mark.parametrize("per_tile", [1, 2, 3, 4, 5, 6, 7, 8, 9, 10, 12, 15, 20, 24, 11, 13, 40, 64])
+def test_queues_cover_every_unit_and_pieces_wait_in_their_own(per_tile, in_turn):
+    n_tiles = 37
+    queue = {}                                               # counter -> its units
+    for block in range(24):                                  # (the first eight have a block in every queue)
+        counter, units = _list(block, per_tile, in_turn, n_tiles)
+        assert 0 <= counter < XCDS and queue.setdefault(counter, units) == units
+    assert sorted(u for units in queue.values() for u in units) == [(t, h) for t in range(n_tiles) for h in range(per_tile)]
+    for counter, units in queue.items():
+        assert units == sorted(units)                        # list order
+        if in_turn:                                          # a head's tiles, pieces among them, are all here
+            heads = {h for _, h in units}
+            assert len(units) == n_tiles * len(heads)
+            assert len(heads) * head_queues(per_tile, 1) == per_tile
+    assert {_list(b, per_tile, in_turn, n_tiles)[0] for b in range(XCDS)} == set(queue)
