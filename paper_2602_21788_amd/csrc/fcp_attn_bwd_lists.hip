@@ -21,7 +21,7 @@
 //     of the contractions; the exponentials stand between the instructions of dP, dS between those of dV.  AHEAD = 3 with 128 channels and 2 with
 //     64 is what 256 and 168 registers hold without spills inside the loops;
 //   * ONE launch for both lists.  Neither fills the chip on small problems, and each has an end in which CUs run dry.  A block takes units of
-//     one list, then of the other; the first units are dealt out longest first over both lists (a step of a key unit has 32 matrix instructions per
+//     one list, then of the other; blocks begin with the longest units of both lists (a step of a key unit has 32 matrix instructions per
 //     wave, one of a row unit 24), half of the blocks go on with key tiles and half with query tiles once those are as long;
 //   * the last row units of the list, one per block, are worked in halves (two waves share 32 rows and divide the keys, 32 each, dQ added up in
 //     LDS): the end of the launch is as long as a unit.  On small problems these are all of them.
@@ -92,7 +92,6 @@ __device__ inline void key_units(const BwdParams& p, const int queues, PartQueue
     if (unit >= uq.n_all) break;
     const KTile t = read_record<KTile, 16>(s_rec);
     const int kvh = kvh0 + unit % kvh_here;
-    uq.prefetch();
 
     const bool exclusive = (t.flags & kFlagSeg0Exclusive) != 0;
     const bool direct = exclusive && p.dk_out != nullptr;
@@ -298,6 +297,7 @@ __device__ inline void key_units(const BwdParams& p, const int queues, PartQueue
       if constexpr (D == 128) __builtin_amdgcn_s_setprio(0);
     }
     __syncthreads();                                // the stages are free
+    uq.prefetch();
     // ---- epilogue
     int lane_e = lane;
     asm volatile("" : "+v"(lane_e));
@@ -698,24 +698,26 @@ __global__ __launch_bounds__(256, lists_blocks_per_cu(D)) void bwd_lists_kernel(
   }
   n_long = min(n_long, min(kv_mine, places));
   const auto [kv_dealt, kv_first, q_first] = first_unit(place, places, kv_mine, n_long);
-  if (kv_first < 0 && q_first >= PartQueue::mine(q_units + q_half, q_xcd) && kv_dealt == kv_mine) return;   // the others are enough
+  const int q_mine = PartQueue::mine(q_units + q_half, q_xcd);
+  if (kv_first < 0 && q_first >= q_mine && kv_dealt == kv_mine) return;   // the others are enough
+  const bool deal = !turns && deals_first(kv_mine + q_mine, places, kDealLists);
   bool keys = kv_first >= 0;
 #pragma unroll 1
   for (int turn = 0; turn < 2; ++turn, keys = !keys) {
     PartQueue uq;
     if (turn) __syncthreads();                     // (everybody has seen the end of the other list)
-    const bool dealt = !turns && turn == 0;
+    const bool dealt = deal && turn == 0;
     if (keys) {
       const int queues = head_queues(p.hkv, kv_turns);
       const int per_tile = p.hkv / queues;
       uq.open(p.hdr, p.tiles, kv_tiles * per_tile, 0, per_tile, unit_numbers(blockIdx.x, queues, kv_turns), turns, dealt ? kv_first : -1,
-              turns ? 0 : kv_dealt, &s_next_unit, s_rec);
+              deal ? kv_dealt : 0, &s_next_unit, s_rec);
       key_units<D, AHEAD>(p, queues, uq, smem, &s_next_unit, s_rec);
     } else {
       const int queues = head_queues(p.hq / hpu, q_turns);
       const int per_tile = p.hq / hpu / queues;
       uq.open(p.hdr_q, p.tiles_q, q_tiles * per_tile, q_half, per_tile, unit_numbers(blockIdx.x, queues, q_turns), turns, dealt ? q_first : -1,
-              turns ? 0 : places - kv_dealt, &s_next_unit, s_rec);
+              deal ? places - kv_dealt : 0, &s_next_unit, s_rec);
       row_units<D, 1, 64, 4>(p, head_pair, queues, uq, smem, &s_next_unit, s_rec);
       row_units<D, 2, 64, 4>(p, head_pair, queues, uq, smem, &s_next_unit, s_rec);
     }

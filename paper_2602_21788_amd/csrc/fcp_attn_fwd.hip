@@ -89,8 +89,7 @@ __global__ __launch_bounds__(512, 1) void fwd_kernel(const FwdParams p) {
   const int heads_here = per_xcd ? p.hq / kNumXcd : p.hq;
   const int units_per_tile = heads_here / hpu;
   UnitQueue uq;
-  uq.init_dealt(p.hdr, p.tiles, xcd, units_per_tile, per_xcd ? blockIdx.x / kNumXcd : blockIdx.x, per_xcd ? gridDim.x / kNumXcd : gridDim.x, p.tile_cap,
-                &s_next_unit, s_rec);
+  uq.init(p.hdr, p.tiles, xcd, units_per_tile, per_xcd ? gridDim.x / kNumXcd : gridDim.x, &s_next_unit, s_rec);
 
   // ---- per-lane constants -----------------------------------------------------------------
   const int kv_row_bytes = p.hkv * D * 2;

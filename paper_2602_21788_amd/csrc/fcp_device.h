@@ -227,44 +227,47 @@ struct UnitQueue {
   int32_t* counter;
   const int32_t* rec_words;
   int32_t n_units, per_tile;
-  int32_t dealt = 0;               // units that went to the blocks by their numbers
+  int32_t dealt;                   // units that went to the blocks by their numbers
+  int32_t tail;                    // from this unit on a block holds none in reserve
 
-  // Block `block` of the `blocks` that share a queue begins with unit `block`, the counter deals out the rest: a kernel begins with one trip to
-  // memory (header and record together) instead of three in a row.  For kernels whose units never wait for each other: a unit
-  // of a block that has not begun is held back with it.  cap: tiles that the list has room for.
-  __device__ void init_dealt(SchedHeader* hdr, const Tile* tiles, int xcd, int per_tile_, int block, int blocks, int cap, int32_t* s_next, int32_t* s_rec) {
-    counter = &hdr->counter[xcd];
-    rec_words = reinterpret_cast<const int32_t*>(tiles);
-    per_tile = per_tile_;
-    dealt = blocks;
-    pend = recw = idx1 = 0;
-    if (threadIdx.x < 64) {
-      const int lane = threadIdx.x & 63;
-      int32_t rec = 0;
-      if (lane < 16) rec = rec_words[min(block / per_tile, cap - 1) * 16 + lane];
-      if (lane == 0) {
-        pend = blocks + atomicAdd(counter, 1);
-        *s_next = block;
-      }
-      if (lane < 16) s_rec[lane] = rec;
-    }
-    n_units = hdr->n_tiles * per_tile_;
-    __syncthreads();
-  }
-  __device__ void init(SchedHeader* hdr, const Tile* tiles, int xcd, int per_tile_, int32_t* s_next, int32_t* s_rec) {
+  __device__ void init(SchedHeader* hdr, const Tile* tiles, int xcd, int per_tile_, int blocks, int32_t* s_next, int32_t* s_rec) {
     counter = &hdr->counter[xcd];
     rec_words = reinterpret_cast<const int32_t*>(tiles);
     per_tile = per_tile_;
     n_units = hdr->n_tiles * per_tile_;
-    pend = recw = idx1 = 0;
+    recw = idx1 = dealt = 0;
+    tail = n_units - kReserve * blocks;
+    pend = -1;
     const int lane = threadIdx.x & 63;
     if (threadIdx.x < 64) {
       int32_t v0 = 0;
       if (lane == 0) v0 = atomicAdd(counter, 1);
       const int32_t u0 = __builtin_amdgcn_readfirstlane(v0);
-      if (lane == 0) pend = atomicAdd(counter, 1);
       if (lane < 16) s_rec[lane] = u0 < n_units ? rec_words[(u0 / per_tile) * 16 + lane] : 0;
       if (lane == 0) *s_next = u0;
+    }
+    __syncthreads();
+  }
+  // Block `block` of the `blocks` that share a queue begins with unit `block`, the counter deals out the rest: a kernel begins with one trip to
+  // memory (header and record together) instead of three in a row.  Where deals_first says so.  cap: tiles that the list has room for.
+  __device__ void init_dealt(SchedHeader* hdr, const Tile* tiles, int xcd, int per_tile_, int block, int blocks, int cap, int32_t* s_next, int32_t* s_rec) {
+    int32_t rec = 0;
+    if (threadIdx.x < 16) rec = reinterpret_cast<const int32_t*>(tiles)[min(block / per_tile_, cap - 1) * 16 + threadIdx.x];
+    if (!deals_first(hdr->n_tiles * per_tile_, blocks, kDealForward)) return init(hdr, tiles, xcd, per_tile_, blocks, s_next, s_rec);
+    counter = &hdr->counter[xcd];
+    rec_words = reinterpret_cast<const int32_t*>(tiles);
+    per_tile = per_tile_;
+    n_units = hdr->n_tiles * per_tile_;
+    dealt = blocks;
+    tail = n_units;
+    pend = recw = idx1 = 0;
+    if (threadIdx.x < 64) {
+      const int lane = threadIdx.x & 63;
+      if (lane == 0) {
+        pend = blocks + atomicAdd(counter, 1);
+        *s_next = block;
+      }
+      if (lane < 16) s_rec[lane] = rec;
     }
     __syncthreads();
   }
@@ -274,8 +277,9 @@ struct UnitQueue {
   __device__ void prefetch() {
     if (threadIdx.x < 64) {
       const int lane = threadIdx.x & 63;
+      if (__builtin_amdgcn_readfirstlane(pend) < 0 && lane == 0) pend = dealt + atomicAdd(counter, 1);
       idx1 = __builtin_amdgcn_readfirstlane(pend);
-      if (lane == 0) pend = dealt + atomicAdd(counter, 1);
+      if (lane == 0) pend = idx1 < tail ? dealt + atomicAdd(counter, 1) : -1;
       recw = (lane < 16 && idx1 < n_units) ? rec_words[(idx1 / per_tile) * 16 + lane] : 0;
     }
   }
@@ -301,14 +305,14 @@ struct UnitQueue {
 //     holds up the pieces after it, and half of the atomics when the launch begins fall away.  Backward step, one unit in reserve / none, us: 8192
 //     tokens, 3 heads on 3, 128 channels 413 / 227; 6 sequences of 6000 tokens in all, 8 heads on 8, 219 / 153; 4096 tokens, 32 heads on 8, 482 / 445;
 //     30 of 20011 tokens, the longest over 3 ranks, 6 heads on 2, 234 / 214.
-//   * `first` >= 0: the block begins with that number of its queue and the counter deals out those from `dealt` on.  Only for lists whose units never
-//     wait for each other: a unit of a block that has not begun is held back with it.
+//   * `first` >= 0: the block begins with that number of its queue and the counter deals out those from `dealt` on (see deals_first).
 //   * The last `n_half` units are worked in halves, numbered on: the end of a launch is as long as a unit.
 struct PartQueue {
   int32_t pend, recw, idx1;
   int32_t* counter;
   const int32_t* rec_words;
   int32_t n_full, n_all, per_tile, mul, add, dealt;
+  int32_t tail;                    // from this unit on a block holds none in reserve
   bool late;
 
   static __device__ int place() { return blockIdx.x / kNumXcd; }      // of the block in its queue
@@ -326,7 +330,9 @@ struct PartQueue {
     add = numbers.add;
     dealt = dealt_;
     late = late_;
-    pend = recw = idx1 = 0;
+    tail = first >= 0 ? n_all : n_all - kReserve * (mul == 1 ? places() : (int)gridDim.x);
+    recw = idx1 = 0;
+    pend = -1;
     if (threadIdx.x < 64) {
       const int lane = threadIdx.x & 63;
       int32_t v0 = first;
@@ -335,7 +341,7 @@ struct PartQueue {
         v0 = __builtin_amdgcn_readfirstlane(v0);
       }
       const int32_t u0 = v0 * mul + add;
-      if (lane == 0 && !late) pend = (dealt + atomicAdd(counter, 1)) * mul + add;
+      if (lane == 0 && first >= 0) pend = (dealt + atomicAdd(counter, 1)) * mul + add;
       if (lane < 16) s_rec[lane] = u0 < n_all ? rec_words[tile_of(u0) * 16 + lane] : 0;
       if (lane == 0) *s_next = u0;
     }
@@ -345,8 +351,10 @@ struct PartQueue {
   __device__ void prefetch() {
     if (threadIdx.x < 64 && !late) {
       const int lane = threadIdx.x & 63;
+      if (__builtin_amdgcn_readfirstlane(pend) < 0 && lane == 0) pend = (dealt + atomicAdd(counter, 1)) * mul + add;
+      if (__builtin_amdgcn_readfirstlane(pend) < 0 && lane == 0) pend = (dealt + atomicAdd(counter, 1)) * mul + add;
       idx1 = __builtin_amdgcn_readfirstlane(pend);
-      if (lane == 0) pend = (dealt + atomicAdd(counter, 1)) * mul + add;
+      if (lane == 0) pend = idx1 < tail ? (dealt + atomicAdd(counter, 1)) * mul + add : -1;
       recw = (lane < 16 && idx1 < n_all) ? rec_words[tile_of(idx1) * 16 + lane] : 0;
     }
   }

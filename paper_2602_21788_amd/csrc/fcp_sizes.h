@@ -68,6 +68,23 @@ FCP_HD inline UnitNumbers unit_numbers(int block, int queues, bool in_turn) {
   return {block % kNumXcd, kNumXcd, block % kNumXcd};
 }
 
+// Do the blocks of a queue begin with units by their numbers, instead of taking them from the queue's counter?  A launch then begins with one trip to memory
+// instead of three in a row, on lines that all blocks are after.  But the first units are the longest, and one of a block that cannot start, because
+// something else holds its CU, waits until a block of the launch has run dry.  So only in launches of few units per block (of few short ones, for the
+// forward's four-wave forms), where the beginning counts.  By number / by counter, us: forward, 300 sequences of 120 tokens, 8 heads (6 units per block) 94 / 101,
+// 32 heads on 8 (12) 199 / 209, 412 of 149, 40 on 8 (30) 460 / 471; both lists, 36 sequences of 104, 40 on 8 of 64 channels (3) 67 / 71, 340 of 67, 8 on
+// one (3) 68 / 72, 43864 tokens in 11 sequences over 8 ranks, 32 on 8 (14) equal.  While 16 of 256 CUs are held: both lists, 32768 tokens in 24
+// sequences, 32 on 8 (20) 2950 / 2620, 65536 over 4 ranks (16) 29420 / 28370; the forward's wide form there 9590 / 9210, which never begins by
+// number.  Never for units that wait for each other.
+constexpr int kDealForward = 32, kDealLists = 4;
+FCP_HD inline bool deals_first(int units, int blocks, int per_block) { return units <= per_block * blocks; }
+// A block has its next unit in reserve, so that neither the counter's trip nor the record's is waited for.  Not from the beginning where it did not begin
+// by number (early blocks would hold long units in reserve while later ones begin with shorter ones), and not in the last units, this many
+// per block: one that a busy block holds is begun late.  Forward, 40000 tokens over 3 ranks, 6 heads on 2, 648 units, reserve from the beginning to
+// the end / so 799 / 725 us; 42000 tokens in 60 sequences 272 / 247; 28000 in 40, 8 heads on one 163 / 135.  (One per block: 952 on the first; four: the trips
+// that are waited for cost 10356 tokens in 4 sequences over 6 ranks, 40 heads on 8, 383 us instead of 375, by number 363.)
+constexpr int kReserve = 3;
+
 // Two lists worked by the same blocks (csrc/fcp_attn_bwd_lists.hip): what block `place` of the `places` of its queue begins with, the key units of the queue
 // being `key_units`, `n_long` of them (`places` at most) longer than any row unit.  The long key units go to the first blocks, then key units and row
 // units in turn, then row units.  The counters deal out the rest: key units from `key_dealt` on, row units from places - key_dealt on.

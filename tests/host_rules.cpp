@@ -26,4 +26,5 @@ void unit_numbers(int block, int queues, int in_turn, int64_t* out) {
   out[1] = n.mul;
   out[2] = n.add;
 }
+int deals_first(int units, int blocks, int per_block) { return fcp::deals_first(units, blocks, per_block); }
 }

@@ -24,6 +24,7 @@ def lib():
     L.first_unit.argtypes, L.first_unit.restype = [i32, i32, i32, i32, P], None
     L.head_queues.argtypes, L.head_queues.restype = [i32, i32], i32
     L.unit_numbers.argtypes, L.unit_numbers.restype = [i32, i32, i32, P], None
+    L.deals_first.argtypes, L.deals_first.restype = [i32, i32, i32], i32
     return L
 
 
@@ -54,3 +55,7 @@ def unit_numbers(block, queues, in_turn):
     out = (ctypes.c_int64 * 3)()
     lib().unit_numbers(block, queues, in_turn, out)
     return tuple(out)
+
+
+def deals_first(units, blocks, per_block):
+    return bool(lib().deals_first(units, blocks, per_block))

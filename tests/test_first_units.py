@@ -1,9 +1,12 @@
 """Every unit of a persistent launch is taken once, whatever the number of CUs: blocks begin with units by their numbers, counters deal out the rest.  A unit that
 waits for others does so inside its own queue."""
+import heapq
+import itertools
+
 import numpy as np
 import pytest
 
-from host_rules import first_unit, head_queues, persistent_blocks, unit_numbers
+from host_rules import deals_first, first_unit, head_queues, persistent_blocks, unit_numbers
 
 XCDS = 8
 
@@ -38,6 +41,48 @@ def test_a_grid_that_is_no_multiple_takes_units_twice():
     """Why: 300 blocks, a 38th block in queues 0 to 3."""
     keys, rows = _taken(300, 200, 200, 0)
     assert len(rows) > len(set(rows))
+
+
+def _makespan(units, blocks, held, per_block=4, reserve=3):
+    """When a launch ends whose units, longest first, are taken as the kernels take them, and `held` of whose blocks can only begin when another has run dry.
+    per_block: of deals_first.  reserve: the last units per block that no block holds ahead."""
+    n, deal = len(units), deals_first(len(units), blocks, per_block)
+    tail = n if deal else n - reserve * blocks
+    counter = itertools.count(blocks if deal else 0)
+    late = list(range(blocks - held, blocks))
+    events, ahead, end = [(0., b) for b in range(blocks - held)], {}, 0.
+    while events:
+        t, b = heapq.heappop(events)
+        if b not in ahead:                                   # it begins
+            unit, ahead[b] = (b, next(counter)) if deal else (next(counter), -1)
+        else:
+            unit = ahead[b] if ahead[b] >= 0 else next(counter)
+            ahead[b] = next(counter) if unit < tail else -1
+        if unit < n:
+            end = t + units[unit]
+            heapq.heappush(events, (end, b))
+        elif late:
+            heapq.heappush(events, (t, late.pop(0)))
+    return max(end, t)
+
+
+@pytest.mark.parametrize("n,blocks,held", [(600, 32, 2), (300, 64, 4), (2000, 96, 6)])
+def test_blocks_that_cannot_start_hold_no_long_unit_back(n, blocks, held):
+    """A launch of many units ends within the length of a unit of the tail of the least time on the blocks that can start: the last unit that a block has in
+    reserve may be begun after all others.  With first units by number it ends with a unit of the longest."""
+    units = [100. - 99. * i / n for i in range(n)]
+    least = sum(units) / (blocks - held)
+    by_number = _makespan(units, blocks, held, per_block=n)
+    assert _makespan(units, blocks, held) <= min(least + units[n - 3 * blocks], by_number - 0.4 * units[0])
+    assert by_number >= least + 0.5 * units[0]
+    assert not deals_first(n, blocks, 4) and deals_first(4 * blocks, blocks, 4) and not deals_first(4 * blocks + 1, blocks, 4) and not deals_first(1, 0, 4)
+
+
+def test_units_in_reserve_do_not_make_the_end_uneven():
+    """648 units of a sharded sequence on 256 blocks: two and a half units per block."""
+    units = [min(331., 331. * (648 - i) / 300) for i in range(648)]
+    least = sum(units) / 256
+    assert _makespan(units, 256, 0, per_block=0) <= 1.1 * least < _makespan(units, 256, 0, per_block=0, reserve=1)
 
 
 def test_grids():
