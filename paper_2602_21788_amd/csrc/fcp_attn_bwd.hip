@@ -56,31 +56,9 @@ static int bwd_step(const void* q, const void* k, const void* v, const void* d_o
   int dev = 0, n_cu = 0;                            // (arguments are refused without a device)
   FCP_HIP_CHECK(hipGetDevice(&dev));
   FCP_HIP_CHECK(hipDeviceGetAttribute(&n_cu, hipDeviceAttributeMultiprocessorCount, dev));
-  // One pass or two lists.  The one-pass kernel (csrc/fcp_attn_bwd_fused.hip) forms S and dP once and needs no query tiles; it has the
-  // units of key tiles only, which take turns at the dQ rows of a sequence.  That pays where sequences are short and few of them follow each
-  // other through the same rows: whole sequences (tq == tkv) with 256 rows or less per item, one or two heads per KV head or a tile per CU.  Scheduling and
-  // attention launches, one pass / two lists, 8 query heads on 8: 30 sequences of 100 tokens on average 41 / 43 us, 200 of 60 83 / 89; 32 on 8: 200 of 60
-  // 159 / 169, 1000 of 128 1417 / 1713.  With one query head per KV head, up to four tiles per CU, also a dozen sequences and more with a mean of 768 rows at most (8
-  // heads: 16 of 512 tokens 71 / 73, 20 of 700 118 / 129), and, where the tiles are nearly four per CU, longer ones (one of 16384 tokens 1771 / 1805); not a few
-  // long ones (one of 512 tokens 37 / 33, 1000 59 / 52, 4096 210 / 171, 8192 518 / 462, 8 sequences of 4000 in all 120 / 96).
-  // Sharded lists (tq < tkv) have the whole sequence's tiles over a part of its rows: they stay with two lists.
-  // The rows per item are an average, and the items are in device memory: where one of them could be long enough to turn the comparison
-  // round (16384 rows with one query head per KV head, else 2048 and 512 rows of two and four heads), the scheduler decides when it sees them
-  // (one_pass_pays in csrc/fcp_sched.hip), and the launches of the other way end at once: 3 to 5 us, which lists of two heads per KV
-  // head and less than 8 K tokens on 8 KV heads are spared.
   const int group = hq / hkv;
   const int64_t key_units = (int64_t)tkv * hkv / fcp::kBwdBN;
-  // (The kernel's queues are those of eight XCDs: not on a part of the chip.)
-  const bool fused = fcp::one_pass_heads(hkv, head_dim) && n_work >= 1 && n_work <= 1024 && tq == tkv && n_cu == 256 &&
-                     ((tkv <= 256 * n_work && (group <= 2 || key_units >= n_cu)) ||
-                      (group == 1 && key_units <= 4 * n_cu && (2 * key_units > 7 * n_cu || (n_work >= 12 && tkv <= 768 * n_work))));
-  // Many short sequences, 2.5 key tiles per CU and more, go to blocks of four waves (csrc/fcp_attn_bwd_short.hip), scheduling and attention launches, twelve waves /
-  // four: 200 sequences of 60 tokens on average, 32 query heads on 8, 158 / 125 us, 1000 of 40 534 / 375, 1000 of 128 1419 / 1295; with fewer tiles there are
-  // few blocks for the chip (30 of 100, 16 on 8, 43 / 48; 60 of 160 137 / 141), and with means above 192 rows most tiles are in chains, whose steps take longer there
-  // (400 of 256, 40 on 8, 1608 / 1590).  One long sequence sets the time there sooner (a step of its chain 2.5 us), so the scheduler always decides.
-  const bool many_short = fused && tkv <= 192 * n_work && 2 * key_units >= 5 * n_cu;
-  const int64_t longest_item = (int64_t)tkv - n_work + 1;      // (with a row at least in each of the others)
-  const bool either = many_short || (fused && group * longest_item > (group == 1 ? 16384 : group == 2 ? 4096 : 2048) && (group > 2 || key_units >= 2 * n_cu));
+  const auto [fused, many_short, either] = fcp::bwd_way(hq, hkv, head_dim, tq, tkv, n_work, n_cu);
   // direct mode: where every row's result comes from (and the accumulator rows that are accumulated into cleared),
   // on extra blocks of the scheduling launch
   fcp::RowStates rs{};

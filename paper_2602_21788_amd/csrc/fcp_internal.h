@@ -189,8 +189,8 @@ inline int32_t* bwd_turns(void* scratch, int64_t n_work, int32_t tq, int32_t tkv
 constexpr int kChainWords = 4;            // rank (-1: atomics), first block of the next tile, the chain's first flag block, first block
 constexpr int kChainSlices = 8;
 inline int64_t chain_flag_words(int32_t tq, int32_t hq, int64_t n_work) { return ((int64_t)tq / 32 + 1 + n_work) * hq * kChainSlices; }
-// Only head layouts that the kernel takes have this area.  (No other argument decides: a buffer sized for the largest call has room for any smaller one.)
-inline bool one_pass_heads(int32_t hkv, int32_t head_dim) { return head_dim == 128 && hkv % kNumXcd == 0; }
+// Only head layouts that the kernel takes (one_pass_heads) have this area.  (No other argument decides: a buffer sized for the largest call has room for any
+// smaller one.)
 // (a record for every tile that the key-tile list has room for)
 inline size_t chain_table_bytes(int32_t tkv, int64_t n_work) { return pad_to((size_t)bwd_kv_cap(tkv, n_work) * kChainWords * sizeof(int32_t), 256); }
 inline size_t chain_bytes(int32_t tq, int32_t tkv, int32_t hq, int32_t hkv, int32_t head_dim, int64_t n_work) {

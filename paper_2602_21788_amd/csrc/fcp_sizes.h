@@ -162,4 +162,40 @@ inline size_t fwd_static_bytes(int32_t tq, int32_t tkv, int64_t n_work, int32_t 
   return sched_region_bytes(n_work, q_tile_cap(tq, tkv, n_work, n_parts, kFwdBM / 2)) + pad_to((size_t)tq, 256);
 }
 
+// ---- the backward -----------------------------------------------------------------------
+inline bool one_pass_heads(int32_t hkv, int32_t head_dim) { return head_dim == 128 && hkv % kNumXcd == 0; }
+
+// One pass or two lists.  The one-pass kernel (csrc/fcp_attn_bwd_fused.hip) forms S and dP once and needs no query tiles; it has the
+// units of key tiles only, which take turns at the dQ rows of a sequence.  That pays where sequences are short and few of them follow each
+// other through the same rows: whole sequences (tq == tkv) with 256 rows or less per item, one or two heads per KV head or a tile per CU.  Scheduling and
+// attention launches, one pass / two lists, us: 8 query heads on 8: 60 sequences of 130 tokens on average 54 / 58, 100 of 130 75 / 83, 30 of 190 49 / 56; 16 on 8:
+// 60 of 130 67 / 75; 32 on 8: 60 of 100 74 / 79, 100 of 130 158 / 179; 40 on 8: 60 of 160 176 / 194.  With one query head per KV head, up to four tiles per
+// CU, also a dozen sequences and more with a mean of 768 rows at most (as the kernels are now 9 to 12 % slower there: 12 of 6000 tokens in all 111 / 99); not
+// longer ones (one of 512 tokens 37 / 33, 4096 210 / 160, 8192 518 / 466, 14400 1378 / 1301, 16384 1772 / 1616, 4 of 15000 798 / 744).
+// Sharded lists (tq < tkv) have the whole sequence's tiles over a part of its rows: they stay with two lists.
+// The rows per item are an average, and the items are in device memory: where one of them could be long enough to turn the comparison
+// round (16384 rows with one query head per KV head, else 2048 and 512 rows of two and four heads), the scheduler decides when it sees them
+// (one_pass_pays in csrc/fcp_sched.hip), and the launches of the other way end at once: 3 to 5 us, which lists of two heads per KV
+// head and less than 8 K tokens on 8 KV heads are spared.
+// Many short sequences, 2.5 key tiles per CU and more, go to blocks of four waves (csrc/fcp_attn_bwd_short.hip), scheduling and attention launches, twelve waves /
+// four: 200 sequences of 60 tokens on average, 32 query heads on 8, 154 / 126 us, 1000 of 40 534 / 375, 1000 of 128 1419 / 1295; with fewer tiles there are
+// few blocks for the chip (30 of 100, 16 on 8, 47 / 51), and with means above 192 rows most tiles are in chains, whose steps take longer there
+// (400 of 256, 40 on 8, 1608 / 1590).  Below four tiles per CU that is so from smaller means on, the smaller the more heads a chain's steps have: 70 of 155, 8 on
+// 8 70 / 72, 32 on 8 146 / 161, 40 on 8 177 / 203; 75 of 158, 24 on 8 144 / 156; 80 of 133, 40 on 8 173 / 200, 64 on 8 239 / 271; but 110 of 95, 40 on 8 155 / 146,
+// 85 of 132, 24 on 8 132 / 122, 75 of 158, 8 on 8 77 / 72.  One long sequence sets the time there sooner (a step of its chain 2.5 us), so the scheduler always decides.
+struct BwdWay { bool one_pass, many_short, either; };     // either: the scheduler decides between one pass and two lists
+inline BwdWay bwd_way(int32_t hq, int32_t hkv, int32_t head_dim, int32_t tq, int32_t tkv, int64_t n_work, int n_cu) {
+  const int group = hq / hkv;
+  const int64_t key_units = (int64_t)tkv * hkv / kBwdBN;
+  // (The kernel's queues are those of eight XCDs: not on a part of the chip.)
+  const bool one_pass = one_pass_heads(hkv, head_dim) && n_work >= 1 && n_work <= 1024 && tq == tkv && n_cu == 256 &&
+                        ((tkv <= 256 * n_work && (group <= 2 || key_units >= n_cu)) ||
+                         (group == 1 && key_units <= 4 * n_cu && n_work >= 12 && tkv <= 768 * n_work));
+  const bool many_short = one_pass && tkv <= 192 * n_work && 2 * key_units >= 5 * n_cu &&
+                          (tkv <= (group <= 4 ? 144 : 112) * n_work || 4 * key_units >= (group <= 2 ? 11 : 16) * n_cu);
+  const int64_t longest_item = (int64_t)tkv - n_work + 1;      // (with a row at least in each of the others)
+  const bool either = many_short || (one_pass && group * longest_item > (group == 1 ? 16384 : group == 2 ? 4096 : 2048) && (group > 2 || key_units >= 2 * n_cu));
+  return {one_pass, many_short, either};
+}
+
 }  // namespace fcp

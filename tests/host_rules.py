@@ -25,6 +25,7 @@ def lib():
     L.head_queues.argtypes, L.head_queues.restype = [i32, i32], i32
     L.unit_numbers.argtypes, L.unit_numbers.restype = [i32, i32, i32, P], None
     L.deals_first.argtypes, L.deals_first.restype = [i32, i32, i32], i32
+    L.backward_way.argtypes, L.backward_way.restype = [i32, i32, i32, i32, i32, i64, i32], i32
     return L
 
 
@@ -59,3 +60,10 @@ def unit_numbers(block, queues, in_turn):
 
 def deals_first(units, blocks, per_block):
     return bool(lib().deals_first(units, blocks, per_block))
+
+
+ONE_PASS, MANY_SHORT, EITHER = 1, 2, 4
+
+
+def backward_way(hq, hkv, head_dim, tq, tkv, n_work, n_cu=256):
+    return lib().backward_way(hq, hkv, head_dim, tq, tkv, n_work, n_cu)
