@@ -201,7 +201,7 @@ __device__ inline void key_units(const BwdParams& p, const int queues, PartQueue
     for (int it = 0; it < n_iter; ++it) {
       __builtin_amdgcn_s_waitcnt(kWaitVm0);
       __syncthreads();
-      if (it + 1 < n_iter) fill_next();
+      if (__builtin_expect(it + 1 < n_iter, 1)) fill_next(); else uq.take(wave);
       const int jb = j, at0 = st;
       if (++j == nqb) j = 0;
       st = C::STAGE - st;
@@ -297,6 +297,7 @@ __device__ inline void key_units(const BwdParams& p, const int queues, PartQueue
       if constexpr (D == 128) __builtin_amdgcn_s_setprio(0);
     }
     __syncthreads();                                // the stages are free
+    if (n_iter == 0) uq.take(wave);
     uq.prefetch();
     // ---- epilogue
     int lane_e = lane;
@@ -404,6 +405,7 @@ __device__ inline void row_units(const BwdParams& p, const int head_pair, const 
       t.q_pos0 += first;
       t.rows = min(t.rows - first, 32 * C::RG / hpu);
       if (t.rows <= 0) {
+        uq.take(wave);
         uq.prefetch();
         __syncthreads();                            // (everybody has read the record)
         uq.advance(s_next_unit, s_rec);
@@ -501,7 +503,7 @@ __device__ inline void row_units(const BwdParams& p, const int head_pair, const 
     for (int it = 0; it < n_iter; ++it) {
       __builtin_amdgcn_s_waitcnt(kWaitVm0);
       __syncthreads();
-      if (it + 1 < n_iter) fill_next();
+      if (__builtin_expect(it + 1 < n_iter, 1)) fill_next(); else uq.take(wave);
       const bool seg1 = it >= nt0;
       const int base = (it - (seg1 ? nt0 : 0)) * C::SK + 32 * C::NB * share;
       for (int b = 0; b < C::NB; ++b) {
@@ -572,6 +574,7 @@ __device__ inline void row_units(const BwdParams& p, const int head_pair, const 
       }
     }
     __syncthreads();
+    if (n_iter == 0) uq.take(wave);
     uq.prefetch();
     // ---- epilogue
     int lane_e = lane;
@@ -700,7 +703,8 @@ __global__ __launch_bounds__(256, lists_blocks_per_cu(D)) void bwd_lists_kernel(
   const auto [kv_dealt, kv_first, q_first] = first_unit(place, places, kv_mine, n_long);
   const int q_mine = PartQueue::mine(q_units + q_half, q_xcd);
   if (kv_first < 0 && q_first >= q_mine && kv_dealt == kv_mine) return;   // the others are enough
-  const bool deal = !turns && deals_first(kv_mine + q_mine, places, kDealLists);
+  const int longest_row = q_units > 0 ? q_list->vis[0] + q_list->vis[1] : 0;
+  const bool deal = !turns && deals_first(kv_mine + q_mine, places, kDealLists, longest_row), reserve = keeps_reserve(deal, longest_row);
   bool keys = kv_first >= 0;
 #pragma unroll 1
   for (int turn = 0; turn < 2; ++turn, keys = !keys) {
@@ -710,13 +714,13 @@ __global__ __launch_bounds__(256, lists_blocks_per_cu(D)) void bwd_lists_kernel(
     if (keys) {
       const int queues = head_queues(p.hkv, kv_turns);
       const int per_tile = p.hkv / queues;
-      uq.open(p.hdr, p.tiles, kv_tiles * per_tile, 0, per_tile, unit_numbers(blockIdx.x, queues, kv_turns), turns, dealt ? kv_first : -1,
+      uq.open(p.hdr, p.tiles, kv_tiles * per_tile, 0, per_tile, unit_numbers(blockIdx.x, queues, kv_turns), turns, reserve, dealt ? kv_first : -1,
               deal ? kv_dealt : 0, &s_next_unit, s_rec);
       key_units<D, AHEAD>(p, queues, uq, smem, &s_next_unit, s_rec);
     } else {
       const int queues = head_queues(p.hq / hpu, q_turns);
       const int per_tile = p.hq / hpu / queues;
-      uq.open(p.hdr_q, p.tiles_q, q_tiles * per_tile, q_half, per_tile, unit_numbers(blockIdx.x, queues, q_turns), turns, dealt ? q_first : -1,
+      uq.open(p.hdr_q, p.tiles_q, q_tiles * per_tile, q_half, per_tile, unit_numbers(blockIdx.x, queues, q_turns), turns, reserve, dealt ? q_first : -1,
               deal ? places - kv_dealt : 0, &s_next_unit, s_rec);
       row_units<D, 1, 64, 4>(p, head_pair, queues, uq, smem, &s_next_unit, s_rec);
       row_units<D, 2, 64, 4>(p, head_pair, queues, uq, smem, &s_next_unit, s_rec);

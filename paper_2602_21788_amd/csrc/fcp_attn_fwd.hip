@@ -89,7 +89,7 @@ __global__ __launch_bounds__(512, 1) void fwd_kernel(const FwdParams p) {
   const int heads_here = per_xcd ? p.hq / kNumXcd : p.hq;
   const int units_per_tile = heads_here / hpu;
   UnitQueue uq;
-  uq.init(p.hdr, p.tiles, xcd, units_per_tile, per_xcd ? gridDim.x / kNumXcd : gridDim.x, &s_next_unit, s_rec);
+  uq.init(p.hdr, p.tiles, xcd, units_per_tile, &s_next_unit, s_rec);
 
   // ---- per-lane constants -----------------------------------------------------------------
   const int kv_row_bytes = p.hkv * D * 2;
@@ -411,14 +411,14 @@ __global__ __launch_bounds__(512, 1) void fwd_kernel(const FwdParams p) {
       // slot boundary: this wave's fills (issued a step ago) have landed, then everybody meets
       __builtin_amdgcn_s_waitcnt(kWaitVm0);
       __syncthreads();
-      if (it + 2 < n_iter) fill_next();      // (nothing in flight when the loop ends: the epilogue reuses the stages)
+      if (__builtin_expect(it + 2 < n_iter, 1)) fill_next();      // (no fill in flight when the loop ends: the epilogue reuses the stages)
+      else if (it == max(n_iter - 2, 0)) uq.take(wave);
       if (do_s) vector_slot(it);
       __syncthreads();
     }
     if (grp == 0) __syncthreads();
 
-    // The next unit's record and the number of the unit after it start their trips here, ahead of the epilogue's
-    // stores (waiting for them later must not mean waiting for those stores).
+    // The next unit's record starts its trip here, ahead of the epilogue's stores (waiting for it later must not mean waiting for those stores).
     uq.prefetch();
     // ---- epilogue: normalise, write partial O (fp32) and LSE --------------------------------
     const float l_tot = lane32_partner_sum(l_run);

@@ -222,7 +222,7 @@ __global__ __launch_bounds__(64 * NW, OCC) void fwd_small_kernel(const FwdParams
     for (int it = 0; it < n_iter; ++it) {
       __builtin_amdgcn_s_waitcnt(kWaitVm0);
       __syncthreads();
-      if (it + 1 < n_iter) fill_next();
+      if (__builtin_expect(it + 1 < n_iter, 1)) fill_next(); else uq.take(wave);
       const bool seg1 = it >= nt0;
       const int k0 = (it - (seg1 ? nt0 : 0)) * C::SK + (SPLIT > 1 ? 32 * share : 0);    // the wave's first key of the segment
       const int k_pos = (seg1 ? kpos1 : kpos0) + k0;
@@ -302,6 +302,7 @@ __global__ __launch_bounds__(64 * NW, OCC) void fwd_small_kernel(const FwdParams
       }
     }
     __syncthreads();                                // the stages are free
+    if (n_iter == 0) uq.take(wave);
     uq.prefetch();                                  // ahead of the epilogue's stores, see fwd_kernel
 
     // ---- epilogue

@@ -218,25 +218,25 @@ struct RowStage {
 };
 
 // Unit queue of a persistent block.  Units are numbered per XCD counter; unit u of an XCD is
-// (tile u / per_tile, sub-index u % per_tile).  Wave 0 keeps the atomic for the unit after next
-// and the 64-byte record of the next unit in flight while the block computes the current one,
-// so neither the atomic's nor the record's latency is paid between units.  LDS: s_next (1 word),
-// s_rec (16 words).  Every thread of the block calls every function.
+// (tile u / per_tile, sub-index u % per_tile).  Wave 0 asks for the next unit in the last step of the current one (take),
+// or has its number from the unit before (reserve: keeps_reserve), and the 64-byte record is in flight during the epilogue
+// (prefetch), so neither latency is paid between units.  LDS: s_next (1 word), s_rec (16 words).  Every thread of the block
+// calls every function; each unit calls take once before prefetch, also one without steps.
 struct UnitQueue {
   int32_t pend, recw, idx1;
   int32_t* counter;
   const int32_t* rec_words;
   int32_t n_units, per_tile;
   int32_t dealt;                   // units that went to the blocks by their numbers
-  int32_t tail;                    // from this unit on a block holds none in reserve
+  bool reserve;                    // a block has its next unit in reserve (see keeps_reserve)
 
-  __device__ void init(SchedHeader* hdr, const Tile* tiles, int xcd, int per_tile_, int blocks, int32_t* s_next, int32_t* s_rec) {
+  __device__ void init(SchedHeader* hdr, const Tile* tiles, int xcd, int per_tile_, int32_t* s_next, int32_t* s_rec) {
     counter = &hdr->counter[xcd];
     rec_words = reinterpret_cast<const int32_t*>(tiles);
     per_tile = per_tile_;
     n_units = hdr->n_tiles * per_tile_;
     recw = idx1 = dealt = 0;
-    tail = n_units - kReserve * blocks;
+    reserve = false;
     pend = -1;
     const int lane = threadIdx.x & 63;
     if (threadIdx.x < 64) {
@@ -253,18 +253,18 @@ struct UnitQueue {
   __device__ void init_dealt(SchedHeader* hdr, const Tile* tiles, int xcd, int per_tile_, int block, int blocks, int cap, int32_t* s_next, int32_t* s_rec) {
     int32_t rec = 0;
     if (threadIdx.x < 16) rec = reinterpret_cast<const int32_t*>(tiles)[min(block / per_tile_, cap - 1) * 16 + threadIdx.x];
-    if (!deals_first(hdr->n_tiles * per_tile_, blocks, kDealForward)) return init(hdr, tiles, xcd, per_tile_, blocks, s_next, s_rec);
+    if (!deals_first(hdr->n_tiles * per_tile_, blocks, kDealForward, hdr->max_cost * kFwdBN)) return init(hdr, tiles, xcd, per_tile_, s_next, s_rec);
     counter = &hdr->counter[xcd];
     rec_words = reinterpret_cast<const int32_t*>(tiles);
     per_tile = per_tile_;
     n_units = hdr->n_tiles * per_tile_;
     dealt = blocks;
-    tail = n_units;
+    reserve = keeps_reserve(true, hdr->max_cost * kFwdBN);
     pend = recw = idx1 = 0;
     if (threadIdx.x < 64) {
       const int lane = threadIdx.x & 63;
       if (lane == 0) {
-        pend = blocks + atomicAdd(counter, 1);
+        if (reserve) pend = blocks + atomicAdd(counter, 1);
         *s_next = block;
       }
       if (lane < 16) s_rec[lane] = rec;
@@ -273,13 +273,16 @@ struct UnitQueue {
   }
   // current unit number (>= n_units: the list is exhausted); wave-uniform
   __device__ int32_t current(const int32_t* s_next) const { return __builtin_amdgcn_readfirstlane(*s_next); }
-  // after the record has been read from s_rec: start the trips for the next two units
+  // in the unit's last step: ask for the next one
+  __device__ void take(int wave) {
+    if (wave == 0 && !reserve && lane_id() == 0) pend = dealt + atomicAdd(counter, 1);
+  }
+  // at the unit's end, ahead of its stores: start the record's trip (and, with a reserve, that for the unit after it)
   __device__ void prefetch() {
     if (threadIdx.x < 64) {
       const int lane = threadIdx.x & 63;
-      if (__builtin_amdgcn_readfirstlane(pend) < 0 && lane == 0) pend = dealt + atomicAdd(counter, 1);
       idx1 = __builtin_amdgcn_readfirstlane(pend);
-      if (lane == 0) pend = idx1 < tail ? dealt + atomicAdd(counter, 1) : -1;
+      if (lane == 0 && reserve && idx1 < n_units) pend = dealt + atomicAdd(counter, 1);
       recw = (lane < 16 && idx1 < n_units) ? rec_words[(idx1 / per_tile) * 16 + lane] : 0;
     }
   }
@@ -312,7 +315,7 @@ struct PartQueue {
   int32_t* counter;
   const int32_t* rec_words;
   int32_t n_full, n_all, per_tile, mul, add, dealt;
-  int32_t tail;                    // from this unit on a block holds none in reserve
+  bool reserve;                    // a block has its next unit in reserve (see keeps_reserve)
   bool late;
 
   static __device__ int place() { return blockIdx.x / kNumXcd; }      // of the block in its queue
@@ -320,7 +323,7 @@ struct PartQueue {
   // how many of n numbers are this block's queue's
   static __device__ int mine(int n, bool per_xcd) { return per_xcd ? n : (n + kNumXcd - 1 - (int)(blockIdx.x % kNumXcd)) / kNumXcd; }
   __device__ int tile_of(int u) const { return (u < n_full ? u : n_full + ((u - n_full) >> 1)) / per_tile; }
-  __device__ void open(SchedHeader* hdr, const Tile* tiles, int n_units, int n_half, int per_tile_, UnitNumbers numbers, bool late_, int first, int dealt_, int32_t* s_next, int32_t* s_rec) {
+  __device__ void open(SchedHeader* hdr, const Tile* tiles, int n_units, int n_half, int per_tile_, UnitNumbers numbers, bool late_, bool reserve_, int first, int dealt_, int32_t* s_next, int32_t* s_rec) {
     counter = &hdr->counter[numbers.counter];
     rec_words = reinterpret_cast<const int32_t*>(tiles);
     per_tile = per_tile_;
@@ -330,7 +333,7 @@ struct PartQueue {
     add = numbers.add;
     dealt = dealt_;
     late = late_;
-    tail = first >= 0 ? n_all : n_all - kReserve * (mul == 1 ? places() : (int)gridDim.x);
+    reserve = reserve_;
     recw = idx1 = 0;
     pend = -1;
     if (threadIdx.x < 64) {
@@ -341,20 +344,21 @@ struct PartQueue {
         v0 = __builtin_amdgcn_readfirstlane(v0);
       }
       const int32_t u0 = v0 * mul + add;
-      if (lane == 0 && first >= 0) pend = (dealt + atomicAdd(counter, 1)) * mul + add;
+      if (lane == 0 && reserve) pend = (dealt + atomicAdd(counter, 1)) * mul + add;
       if (lane < 16) s_rec[lane] = u0 < n_all ? rec_words[tile_of(u0) * 16 + lane] : 0;
       if (lane == 0) *s_next = u0;
     }
     __syncthreads();
   }
   __device__ int32_t current(const int32_t* s_next) const { return __builtin_amdgcn_readfirstlane(*s_next); }
+  __device__ void take(int wave) {
+    if (wave == 0 && !reserve && !late && lane_id() == 0) pend = (dealt + atomicAdd(counter, 1)) * mul + add;
+  }
   __device__ void prefetch() {
     if (threadIdx.x < 64 && !late) {
       const int lane = threadIdx.x & 63;
-      if (__builtin_amdgcn_readfirstlane(pend) < 0 && lane == 0) pend = (dealt + atomicAdd(counter, 1)) * mul + add;
-      if (__builtin_amdgcn_readfirstlane(pend) < 0 && lane == 0) pend = (dealt + atomicAdd(counter, 1)) * mul + add;
       idx1 = __builtin_amdgcn_readfirstlane(pend);
-      if (lane == 0) pend = idx1 < tail ? (dealt + atomicAdd(counter, 1)) * mul + add : -1;
+      if (lane == 0 && reserve && idx1 < n_all) pend = (dealt + atomicAdd(counter, 1)) * mul + add;
       recw = (lane < 16 && idx1 < n_all) ? rec_words[tile_of(idx1) * 16 + lane] : 0;
     }
   }

@@ -70,20 +70,22 @@ FCP_HD inline UnitNumbers unit_numbers(int block, int queues, bool in_turn) {
 
 // Do the blocks of a queue begin with units by their numbers, instead of taking them from the queue's counter?  A launch then begins with one trip to memory
 // instead of three in a row, on lines that all blocks are after.  But the first units are the longest, and one of a block that cannot start, because
-// something else holds its CU, waits until a block of the launch has run dry.  So only in launches of few units per block (of few short ones, for the
-// forward's four-wave forms), where the beginning counts.  By number / by counter, us: forward, 300 sequences of 120 tokens, 8 heads (6 units per block) 94 / 101,
-// 32 heads on 8 (12) 199 / 209, 412 of 149, 40 on 8 (30) 460 / 471; both lists, 36 sequences of 104, 40 on 8 of 64 channels (3) 67 / 71, 340 of 67, 8 on
-// one (3) 68 / 72, 43864 tokens in 11 sequences over 8 ranks, 32 on 8 (14) equal.  While 16 of 256 CUs are held: both lists, 32768 tokens in 24
-// sequences, 32 on 8 (20) 2950 / 2620, 65536 over 4 ranks (16) 29420 / 28370; the forward's wide form there 9590 / 9210, which never begins by
+// something else holds its CU, waits until a block of the launch has run dry.  So only in launches of few units per block, fewer of long ones (`longest`:
+// the key rows of the longest loop, at most), where the beginning counts.  By number / by counter, us: forward, 300 sequences of 120 tokens, 8 heads (6 units per
+// block) 94 / 101, 32 heads on 8 (12) 199 / 209, 412 of 149, 40 on 8 (30) 460 / 471; both lists, 36 sequences of 104, 40 on 8 of 64 channels (3) 67 / 71,
+// 340 of 67, 8 on one (3) 68 / 72, 43864 tokens in 11 sequences over 8 ranks, 32 on 8 (14) equal.  While 16 of 256 CUs are held: both lists, 32768 tokens
+// in 24 sequences, 32 on 8 (20) 2950 / 2700, 65536 over 4 ranks (16) 29420 / 28790; the forward's wide form there 9590 / 9030, which never begins by
 // number.  Never for units that wait for each other.
-constexpr int kDealForward = 32, kDealLists = 4;
-FCP_HD inline bool deals_first(int units, int blocks, int per_block) { return units <= per_block * blocks; }
-// A block has its next unit in reserve, so that neither the counter's trip nor the record's is waited for.  Not from the beginning where it did not begin
-// by number (early blocks would hold long units in reserve while later ones begin with shorter ones), and not in the last units, this many
-// per block: one that a busy block holds is begun late.  Forward, 40000 tokens over 3 ranks, 6 heads on 2, 648 units, reserve from the beginning to
-// the end / so 799 / 725 us; 42000 tokens in 60 sequences 272 / 247; 28000 in 40, 8 heads on one 163 / 135.  (One per block: 952 on the first; four: the trips
-// that are waited for cost 10356 tokens in 4 sequences over 6 ranks, 40 heads on 8, 383 us instead of 375, by number 363.)
-constexpr int kReserve = 3;
+constexpr int kDealForward = 32, kDealLists = 4, kDealKeys = 1024;
+FCP_HD inline bool deals_first(int units, int blocks, int per_block, int longest) { return units <= (longest > kDealKeys ? 2 : per_block) * blocks; }
+// When does a block ask the counter for its next unit?  With loops of some length in the unit's last step (`take`): the trip is over before the epilogue is,
+// and what is left goes to whoever comes first.  Blocks that begin by number, with short loops, have it in reserve from the unit before: their
+// units are too short to cover the trip, and too short for the end to become uneven.  A long unit in reserve is begun late, after the block's own long
+// one.  In reserve / taken in the last step, us: forward, 35768 tokens in 53 sequences over 2 ranks, 8 heads on one 418 / 358; 42000 in 60, 6
+// on 2 269 / 236; 28000 in 40 over 4 ranks, 10 on 2 200 / 191; 18000 tokens, 8 of 64 channels (by number) 413 / 398; 9 sequences of 1000, 8 heads (by
+// number) 87 / 77; both lists, 18000 tokens, 8 of 64 channels 1220 / 1171.  (In reserve but for the last three units per block: 53860 tokens in 5 sequences
+// over 3 ranks, 8 on one 684, where reserve 597, last step 589.)
+FCP_HD inline bool keeps_reserve(bool dealt, int longest) { return dealt && longest <= kDealKeys; }
 
 // Two lists worked by the same blocks (csrc/fcp_attn_bwd_lists.hip): what block `place` of the `places` of its queue begins with, the key units of the queue
 // being `key_units`, `n_long` of them (`places` at most) longer than any row unit.  The long key units go to the first blocks, then key units and row

@@ -26,7 +26,8 @@ void unit_numbers(int block, int queues, int in_turn, int64_t* out) {
   out[1] = n.mul;
   out[2] = n.add;
 }
-int deals_first(int units, int blocks, int per_block) { return fcp::deals_first(units, blocks, per_block); }
+int deals_first(int units, int blocks, int per_block, int longest) { return fcp::deals_first(units, blocks, per_block, longest); }
+int keeps_reserve(int dealt, int longest) { return fcp::keeps_reserve(dealt != 0, longest); }
 int backward_way(int32_t hq, int32_t hkv, int32_t head_dim, int32_t tq, int32_t tkv, int64_t n_work, int n_cu) {
   const fcp::BwdWay w = fcp::bwd_way(hq, hkv, head_dim, tq, tkv, n_work, n_cu);
   return (w.one_pass ? 1 : 0) | (w.many_short ? 2 : 0) | (w.either ? 4 : 0);

@@ -24,7 +24,8 @@ def lib():
     L.first_unit.argtypes, L.first_unit.restype = [i32, i32, i32, i32, P], None
     L.head_queues.argtypes, L.head_queues.restype = [i32, i32], i32
     L.unit_numbers.argtypes, L.unit_numbers.restype = [i32, i32, i32, P], None
-    L.deals_first.argtypes, L.deals_first.restype = [i32, i32, i32], i32
+    L.deals_first.argtypes, L.deals_first.restype = [i32, i32, i32, i32], i32
+    L.keeps_reserve.argtypes, L.keeps_reserve.restype = [i32, i32], i32
     L.backward_way.argtypes, L.backward_way.restype = [i32, i32, i32, i32, i32, i64, i32], i32
     return L
 
@@ -58,8 +59,12 @@ def unit_numbers(block, queues, in_turn):
     return tuple(out)
 
 
-def deals_first(units, blocks, per_block):
-    return bool(lib().deals_first(units, blocks, per_block))
+def deals_first(units, blocks, per_block, longest):
+    return bool(lib().deals_first(units, blocks, per_block, longest))
+
+
+def keeps_reserve(dealt, longest):
+    return bool(lib().keeps_reserve(dealt, longest))
 
 
 ONE_PASS, MANY_SHORT, EITHER = 1, 2, 4

@@ -6,7 +6,7 @@ import itertools
 import numpy as np
 import pytest
 
-from host_rules import deals_first, first_unit, head_queues, persistent_blocks, unit_numbers
+from host_rules import deals_first, first_unit, head_queues, keeps_reserve, persistent_blocks, unit_numbers
 
 XCDS = 8
 
@@ -43,21 +43,20 @@ def test_a_grid_that_is_no_multiple_takes_units_twice():
     assert len(rows) > len(set(rows))
 
 
-def _makespan(units, blocks, held, per_block=4, reserve=3):
+def _makespan(units, blocks, held, deal, reserve):
     """When a launch ends whose units, longest first, are taken as the kernels take them, and `held` of whose blocks can only begin when another has run dry.
-    per_block: of deals_first.  reserve: the last units per block that no block holds ahead."""
-    n, deal = len(units), deals_first(len(units), blocks, per_block)
-    tail = n if deal else n - reserve * blocks
+    deal: blocks begin by number.  reserve: a block has its next unit from the unit before."""
+    n = len(units)
     counter = itertools.count(blocks if deal else 0)
     late = list(range(blocks - held, blocks))
     events, ahead, end = [(0., b) for b in range(blocks - held)], {}, 0.
     while events:
         t, b = heapq.heappop(events)
         if b not in ahead:                                   # it begins
-            unit, ahead[b] = (b, next(counter)) if deal else (next(counter), -1)
+            unit = b if deal else next(counter)
         else:
-            unit = ahead[b] if ahead[b] >= 0 else next(counter)
-            ahead[b] = next(counter) if unit < tail else -1
+            unit = ahead[b] if reserve else next(counter)
+        ahead[b] = next(counter) if reserve else -1
         if unit < n:
             end = t + units[unit]
             heapq.heappush(events, (end, b))
@@ -66,23 +65,43 @@ def _makespan(units, blocks, held, per_block=4, reserve=3):
     return max(end, t)
 
 
+def _rule(n, blocks, per_block, longest):
+    deal = deals_first(n, blocks, per_block, longest)
+    return deal, keeps_reserve(deal, longest)
+
+
 @pytest.mark.parametrize("n,blocks,held", [(600, 32, 2), (300, 64, 4), (2000, 96, 6)])
 def test_blocks_that_cannot_start_hold_no_long_unit_back(n, blocks, held):
-    """A launch of many units ends within the length of a unit of the tail of the least time on the blocks that can start: the last unit that a block has in
-    reserve may be begun after all others.  With first units by number it ends with a unit of the longest."""
+    """A launch of many units ends within the length of the last units of the least time on the blocks that can start (a block that runs dry begins no unit
+    after the others' last ones).  With first units by number it ends with a unit of the longest."""
     units = [100. - 99. * i / n for i in range(n)]
     least = sum(units) / (blocks - held)
-    by_number = _makespan(units, blocks, held, per_block=n)
-    assert _makespan(units, blocks, held) <= min(least + units[n - 3 * blocks], by_number - 0.4 * units[0])
+    by_number = _makespan(units, blocks, held, True, True)
+    assert _makespan(units, blocks, held, *_rule(n, blocks, 4, 4096)) <= min(least + units[n - blocks], by_number - 0.4 * units[0])
     assert by_number >= least + 0.5 * units[0]
-    assert not deals_first(n, blocks, 4) and deals_first(4 * blocks, blocks, 4) and not deals_first(4 * blocks + 1, blocks, 4) and not deals_first(1, 0, 4)
 
 
-def test_units_in_reserve_do_not_make_the_end_uneven():
-    """648 units of a sharded sequence on 256 blocks: two and a half units per block."""
+@pytest.mark.parametrize("per_block", [4, 32])
+@pytest.mark.parametrize("longest", [0, 64, 1024, 1025, 65536])
+def test_when_blocks_begin_by_number(per_block, longest):
+    most = (per_block if longest <= 1024 else 2) * 96
+    assert deals_first(most, 96, per_block, longest) and not deals_first(most + 1, 96, per_block, longest) and not deals_first(1, 0, per_block, longest)
+    assert keeps_reserve(True, longest) == (longest <= 1024) and not keeps_reserve(False, longest)
+
+
+@pytest.mark.parametrize("n,blocks", [(648, 256), (1128, 768), (300, 256)])
+def test_long_units_end_evenly(n, blocks):
+    """Units of a long sequence, one to two and a half per block: list scheduling, as no block has a unit that another could begin, which ends within a
+    longest unit of the mean load (the unit that ends last began when no block was free before)."""
+    units = [min(331., 331. * (n - i) / 300) for i in range(n)]
+    deal, reserve = _rule(n, blocks, 32, 40000)
+    assert not reserve and _makespan(units, blocks, 0, deal, reserve) <= sum(units) / blocks + units[0]
+
+
+def test_units_in_reserve_make_the_end_uneven():
+    """Why: 648 units of a sharded sequence on 256 blocks."""
     units = [min(331., 331. * (648 - i) / 300) for i in range(648)]
-    least = sum(units) / 256
-    assert _makespan(units, 256, 0, per_block=0) <= 1.1 * least < _makespan(units, 256, 0, per_block=0, reserve=1)
+    assert _makespan(units, 256, 0, False, False) <= 1.1 * sum(units) / 256 < _makespan(units, 256, 0, False, True)
 
 
 def test_grids():
