@@ -83,7 +83,6 @@ struct Tile { int32_t w[16]; };  // storage type of the list
 static_assert(sizeof(Tile) == kTileBytes, "tile size");
 
 constexpr int kFwdBN = 64;       // keys per forward inner step
-constexpr int kDqBM = 64;        // query rows per dQ unit (two heads of a KV head), twice that for a single head
 constexpr int kDqBN = 32;        // keys per dQ inner step
 constexpr int kBwdBM = 32;       // query rows per dK/dV inner step
 
@@ -91,11 +90,6 @@ constexpr int kBwdBM = 32;       // query rows per dK/dV inner step
 // offsets of buffer instructions, and the fills run a few tiles past a segment's end (those land outside the
 // resource's range and read as zero): with a segment below 2^30 bytes the offsets stay far from 2^31.
 inline int32_t max_segment_keys(int64_t kv_row_bytes) { return (int32_t)(((int64_t)1 << 30) / kv_row_bytes); }
-
-// Room for the backward's lists when tiles are split: a tile has two pieces more than its share of the steps asks for at most, and
-// all shares together make two pieces per CU.
-inline int64_t bwd_kv_cap(int32_t tkv, int64_t n_work) { return 2 * kv_tile_cap(tkv, n_work) + 2048; }
-inline int64_t bwd_q_cap(int32_t tq, int32_t tkv, int64_t n_work) { return 2 * q_tile_cap(tq, tkv, n_work, 1 << 20, kDqBM) + 2048; }
 
 constexpr int32_t kFlagQExclusive = 1;    // no other item of the launch covers these query rows
 constexpr int32_t kFlagSeg0Exclusive = 2; // no other item's key segment overlaps segment 0 / 1

@@ -17,6 +17,7 @@ namespace fcp {
 constexpr int kFwdBM = 256;      // query rows per forward unit
 constexpr int kMinFwdTile = 32;  // smallest query tile of the forward (sizes its tile list; the backward's is kDqBM)
 constexpr int kBwdBN = 128;      // keys per dK/dV unit
+constexpr int kDqBM = 64;        // query rows per dQ unit (two heads of a KV head), twice that for a single head
 
 constexpr size_t kSchedHeaderBytes = 128, kTileBytes = 64;
 constexpr int64_t kMaxTiles = INT32_MAX / 64;   // of a list
@@ -35,6 +36,14 @@ inline int64_t q_tile_cap(int32_t tq, int32_t tkv, int64_t n_work, int32_t n_par
 inline int64_t kv_tile_cap(int32_t tkv, int64_t n_work) {
   return 2 * n_work + 2 * (int64_t)((tkv + kBwdBN - 1) / kBwdBN);
 }
+
+// Room for the backward's lists when tiles are split (split_sizes, csrc/fcp_sched.hip).  A tile has at most two pieces more than its loop divided by the size of a
+// piece.  Over all tiles that quotient is 4 per CU at most: a piece is no less than a CU's share of all steps, which counts a key tile's loop at half its
+// length or more (the average of the first and the last tile), and a query tile's at a quarter (a row unit's step is half of what a CU does at a
+// time); and a piece in whole steps is half of its size at least (key tiles, whose pieces are whole blocks of 32 rows for all heads of the group), 12 / 13
+// of it (query tiles, by the least size).  So 2048 is enough for 472 CUs.
+inline int64_t bwd_kv_cap(int32_t tkv, int64_t n_work) { return 2 * kv_tile_cap(tkv, n_work) + 2048; }
+inline int64_t bwd_q_cap(int32_t tq, int32_t tkv, int64_t n_work) { return 2 * q_tile_cap(tq, tkv, n_work, 1 << 20, kDqBM) + 2048; }
 
 // One schedule region: SchedHeader | item offsets int32[n_work+1] | Tile[cap]; every part padded to 64 bytes, the region to 256.
 inline size_t sched_item_off_bytes(int64_t n_work) { return pad_to((size_t)(n_work + 1) * sizeof(int32_t), 64); }

@@ -12,6 +12,8 @@ void forward_plan(int head_dim, int hq, int hkv, int32_t tq, int32_t tkv, int64_
 }
 int64_t static_bytes(int32_t tq, int32_t tkv, int64_t n_work, int32_t n_parts) { return (int64_t)fcp::fwd_static_bytes(tq, tkv, n_work, n_parts); }
 int64_t scratch_area_bytes(int32_t tq, int32_t tkv, int64_t n_work, int32_t n_parts) { return (int64_t)fcp::fwd_area_bytes(tq, tkv, n_work, n_parts); }
+int64_t bwd_kv_cap(int32_t tkv, int64_t n_work) { return fcp::bwd_kv_cap(tkv, n_work); }
+int64_t bwd_q_cap(int32_t tq, int32_t tkv, int64_t n_work) { return fcp::bwd_q_cap(tq, tkv, n_work); }
 int64_t persistent_blocks(int64_t resident, int64_t units) { return fcp::persistent_blocks(resident, units); }
 void first_unit(int place, int places, int key_units, int n_long, int64_t* out) {
   const fcp::FirstUnit f = fcp::first_unit(place, places, key_units, n_long);

@@ -24,6 +24,8 @@ def lib():
     L.first_unit.argtypes, L.first_unit.restype = [i32, i32, i32, i32, P], None
     L.head_queues.argtypes, L.head_queues.restype = [i32, i32], i32
     L.unit_numbers.argtypes, L.unit_numbers.restype = [i32, i32, i32, P], None
+    L.bwd_kv_cap.argtypes, L.bwd_kv_cap.restype = [i32, i64], i64
+    L.bwd_q_cap.argtypes, L.bwd_q_cap.restype = [i32, i32, i64], i64
     L.deals_first.argtypes, L.deals_first.restype = [i32, i32, i32, i32], i32
     L.keeps_reserve.argtypes, L.keeps_reserve.restype = [i32, i32], i32
     L.backward_way.argtypes, L.backward_way.restype = [i32, i32, i32, i32, i32, i64, i32], i32
@@ -65,6 +67,11 @@ def deals_first(units, blocks, per_block, longest):
 
 def keeps_reserve(dealt, longest):
     return bool(lib().keeps_reserve(dealt, longest))
+
+
+def backward_caps(tq, tkv, n_work):
+    """Tiles that the key-tile and the query-tile list have room for."""
+    return lib().bwd_kv_cap(tkv, n_work), lib().bwd_q_cap(tq, tkv, n_work)
 
 
 ONE_PASS, MANY_SHORT, EITHER = 1, 2, 4
