@@ -93,7 +93,8 @@ int fcp_shard_plan(const int32_t* seq_lens, const int32_t* cp_degree, const int3
                    int32_t n_seqs, fcp_chunk_desc* chunks, int64_t chunk_cap, int64_t* n_chunks,
                    fcp_work_desc* work, int64_t work_cap, int64_t* n_work);
 
-/* Scratch size in bytes for `which` = FCP_SCRATCH_FWD or FCP_SCRATCH_BWD. */
+/* Scratch size in bytes for `which` = FCP_SCRATCH_FWD or FCP_SCRATCH_BWD.  Another build of the library may need another size for the
+ * same arguments (smaller tiles, more lists): ask the library that is used, keep no size from before. */
 #define FCP_SCRATCH_FWD 0
 #define FCP_SCRATCH_BWD 1
 size_t fcp_scratch_bytes(int which, int32_t tq, int32_t tkv, int32_t hq, int32_t hkv,
@@ -134,7 +135,7 @@ int fcp_attn_fwd_step(const void* q, const void* k, const void* v, const int32_t
  *   - a call whose list of query tiles could need more than FCP_STATIC_SCRATCH_BYTES returns FCP_ERR_CAPACITY and launches
  *     nothing: 128 bytes, 4 per work item, 64 per tile of 128 rows (at most n_work + min(n_parts * ceil(tq / 128),
  *     ceil(tkv / 128)) of them) and tq bytes, each rounded up to 256.  (fcp_scratch_bytes(FCP_SCRATCH_FWD, ...) is more: a
- *     caller's buffer has room for tiles of 32 rows.  Here a list of smaller tiles that would not fit is built of larger ones.);
+ *     caller's buffer has room for tiles of 32 rows.  Here a list of smaller tiles that would not fit is built of larger ones);
  *   - every call on a GPU uses that GPU's one array: calls that overlap in time on one GPU (two streams, two threads)
  *     race and give undefined results; calls on one stream are ordered and safe.  Nothing has to be cleared between
  *     calls;

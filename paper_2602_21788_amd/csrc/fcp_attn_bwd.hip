@@ -5,8 +5,8 @@
 // probabilities of a step are recomputed exactly, P = exp(scale s - LSE), so each step adds
 // its own share:  dV += P^T dO,  dS = P o (dO V^T - delta),  dQ += scale dS K,  dK += scale dS^T Q.
 //
-// Entry points, checks and the choice between two ways: key tiles and query tiles in one launch (csrc/fcp_attn_bwd_lists.hip), or one pass over key
-// tiles for lists of short whole sequences (csrc/fcp_attn_bwd_fused.hip).
+// Entry points, checks and the launches of the way that bwd_way (csrc/fcp_sizes.h) chooses: key tiles and query tiles in one launch (csrc/fcp_attn_bwd_lists.hip),
+// or one pass over key tiles for lists of short whole sequences (csrc/fcp_attn_bwd_fused.hip; many of them: csrc/fcp_attn_bwd_short.hip).
 #include "fcp_bwd.h"
 
 #include <algorithm>

@@ -33,7 +33,7 @@
 //
 // Measured against the two lists, scheduling and attention launches: 32 query heads on 8 KV heads, 200 sequences of 60 tokens on average 169 -> 159 us;
 // 8 heads on 8, 30 of 100 43 -> 41 us, 200 of 60 89 -> 83; on one sequence of 4096 tokens 167 -> 211 us (units wait for each other at the shared rows
-// and the stores of dQ compete for the L2): the rule of dispatch is at the call (csrc/fcp_attn_bwd.hip).
+// and the stores of dQ compete for the L2): the rule of dispatch is bwd_way in csrc/fcp_sizes.h.
 #include "fcp_bwd.h"
 
 namespace fcp {

@@ -21,8 +21,8 @@
 //     of the contractions; the exponentials stand between the instructions of dP, dS between those of dV.  AHEAD = 3 with 128 channels and 2 with
 //     64 is what 256 and 168 registers hold without spills inside the loops;
 //   * ONE launch for both lists.  Neither fills the chip on small problems, and each has an end in which CUs run dry.  A block takes units of
-//     one list, then of the other; blocks begin with the longest units of both lists (a step of a key unit has 32 matrix instructions per
-//     wave, one of a row unit 24), half of the blocks go on with key tiles and half with query tiles once those are as long;
+//     one list, then of the other; the first blocks begin with the key units that are longer than any row unit (a step of a key unit has 32
+//     matrix instructions per wave, one of a row unit 24), of the others half begin with key units and half with row units;
 //   * the last row units of the list, one per block, are worked in halves (two waves share 32 rows and divide the keys, 32 each, dQ added up in
 //     LDS): the end of the launch is as long as a unit.  On small problems these are all of them.
 // Backward step with its scheduling launch, two kernels one after the other / this one, us: 4096 tokens over 3 ranks, 8 heads 138 / 91; 8192 tokens,
