@@ -25,7 +25,7 @@
 //     matrix instructions per wave, one of a row unit 24), of the others half begin with key units and half with row units;
 //   * the last row units of the list, one per block, are worked in halves (two waves share 32 rows and divide the keys, 32 each, dQ added up in
 //     LDS): the end of the launch is as long as a unit.  On small problems these are all of them.
-// Backward step with its scheduling launch, two kernels one after the other / this one, us: 4096 tokens over 3 ranks, 8 heads 138 / 91; 8192 tokens,
+// Backward step with its scheduling launch, two kernels one after the other / this one, us: 4096 tokens over 3 ranks, 8 heads 138 / 83; 8192 tokens,
 // 32 heads on 8 1900 / 1650; 24 sequences of 32768 tokens, 32 on 8 4170 / 3950, 8 heads 1115 / 1020; 131072 tokens over 8 ranks, 32 on 8 51200 /
 // 50100; 64 channels: 4096 tokens, 4 heads 133 / 85, 16 sequences of 60000 tokens, 40 on 8 15900 / 12100.
 // Tried: the key tiles first and then the query tiles in every block (24 sequences of 32768 tokens, 8 heads 1230: the longest query tile begins

@@ -11,8 +11,8 @@
 //     to stores of 16 bytes; the final rows of a sequence of one tile go straight to bf16;
 //   * the flag of a chain's step is set most of a step later, when its stores have arrived anyway.
 // What bounds it: memory.  1000 sequences of 128 tokens, 32 query heads on 8 KV heads, are 4.2 GB of Q, dO, dQ, K, V, dK and dV: 0.89 ms with the scheduling launch
-// (4.7 TB/s, what a large copy reaches), 64 tokens each 0.45 ms; the twelve-wave kernel 1.01 and 0.64.  Sequences of two tiles move a part of dQ as fp32 and
-// read Q and dO again: 1000 of 128 on average 1.42 -> 1.29 ms (8 heads 667 -> 508 us), 1000 of 40 534 -> 376 us (8 heads 318 -> 206).
+// (4.7 TB/s, what a large copy reaches, by count), 64 tokens each 0.45 ms; the twelve-wave kernel 1.01 and 0.64.  Sequences of two tiles move a part of dQ as fp32 and
+// read Q and dO again: 1000 of 128 on average 1.42 -> 1.29 ms (5.2 GB by the counters; 8 heads 667 -> 508 us), 1000 of 40 534 -> 376 us (8 heads 318 -> 206).
 // Where one chain sets the time a step takes 2.5 us against 1.5: the rule is bwd_way in csrc/fcp_sizes.h.
 // Tried: the sums of earlier tiles requested before the barrier (a chain's step 2.5 -> 2.2 us, but many short sequences 2 % slower: the extra loads
 // are issued for every step); fragments two or four instructions ahead, no priority for the matrix stream: equal.

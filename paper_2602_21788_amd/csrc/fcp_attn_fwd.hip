@@ -412,7 +412,7 @@ __global__ __launch_bounds__(512, 1) void fwd_kernel(const FwdParams p) {
       __builtin_amdgcn_s_waitcnt(kWaitVm0);
       __syncthreads();
       if (__builtin_expect(it + 2 < n_iter, 1)) fill_next();      // (no fill in flight when the loop ends: the epilogue reuses the stages)
-      else if (it == max(n_iter - 2, 0)) uq.take(wave);
+      if (it == max(n_iter - 3, 0)) uq.take(wave);      // (two steps sooner than the forms of four waves, whose blocks cover each other: 0.5 % here)
       if (do_s) vector_slot(it);
       __syncthreads();
     }

@@ -13,7 +13,7 @@
 //   * SPLIT = 2, 4: groups of SPLIT waves own the same 32 rows and divide the keys of every stage among them, 32 keys each; their
 //     (maximum, sum, O) meet in LDS at the unit's end.  Half (a quarter) of the rows per unit, half (a quarter) of the serial loop, for problems
 //     that would otherwise leave CUs without a unit.  A stage's fills then serve fewer matrix instructions, so it does not pay where units
-//     abound (60000 tokens in 16 sequences, 32 heads on 8: 5180 -> 6300 us with two).
+//     abound (60000 tokens in 16 sequences, 32 heads on 8: 4180 -> 5230 us with two).
 // Priorities as in fwd_kernel (matrix stream first) gain 1 % on long items and lose 1 to 3 % elsewhere; none are set.
 // Times of the forms beside each other and where each is taken: fwd_form in csrc/fcp_sizes.h.
 #include "fcp_fwd.h"

@@ -218,7 +218,7 @@ struct RowStage {
 };
 
 // Unit queue of a persistent block.  Units are numbered per XCD counter; unit u of an XCD is
-// (tile u / per_tile, sub-index u % per_tile).  Wave 0 asks for the next unit in the last step of the current one (take),
+// (tile u / per_tile, sub-index u % per_tile).  Wave 0 asks for the next unit in the last steps of the current one (take),
 // or has its number from the unit before (reserve: keeps_reserve), and the 64-byte record is in flight during the epilogue
 // (prefetch), so neither latency is paid between units.  LDS: s_next (1 word), s_rec (16 words).  Every thread of the block
 // calls every function; each unit calls take once before prefetch, also one without steps.
@@ -273,7 +273,7 @@ struct UnitQueue {
   }
   // current unit number (>= n_units: the list is exhausted); wave-uniform
   __device__ int32_t current(const int32_t* s_next) const { return __builtin_amdgcn_readfirstlane(*s_next); }
-  // in the unit's last step: ask for the next one
+  // in the unit's last steps: ask for the next one
   __device__ void take(int wave) {
     if (wave == 0 && !reserve && lane_id() == 0) pend = dealt + atomicAdd(counter, 1);
   }

@@ -122,15 +122,16 @@ inline int fwd_unit_rows(FwdForm f, int head_dim) { return f == kFwdWide ? kFwdB
 
 // Which form works a list.  The items are in device memory; the host has their mean length and the work per CU (units of 128 rows of one head, a
 // row counted once per item that covers it).  Measured, forward step with its scheduling launch, wide / the form chosen, us:
-//   few units, and loops long enough to be divided: the longest unit's loop sets the time.  128 channels, 8 heads: 2000 tokens 56 / 36 (four waves
-//     a row), 4096 tokens 98 / 73 (two), 4096 tokens over 3 ranks 47 / 39.  64 channels, 4 heads: 512 tokens 23 / 18, 4096 82 / 41; several sequences
-//     have a longer longest loop for the same work: 16 of 16384 tokens 125 / 82.  (At twice the bounds the divided form is slower: 16384
-//     tokens over 5 ranks, 6 heads on 2 of 64 channels 75 / 88.)
-//   64 channels otherwise: blocks of four waves, three per CU, at every size: 60000 tokens in 16 sequences, 40 heads on 8 4100 / 3760; 1000 of 128 1050 / 737.
-//   128 channels: short items are mostly beginnings and ends of units, which other blocks of the CU cover: 1000 of 128, 32 heads on 8 922 / 694, 200
-//     of 400 690 / 608, 30 of 667 over 3 ranks 317 / 300; with few units per CU two blocks with 64-key tiles do better than three with 32-key tiles: 4000
-//     tokens in 8 sequences 84 / 77 (three: 85), 8192 tokens of 8 heads 190 / 182 (205).  Long items: the wide form (60000 tokens in 16
-//     sequences 4900; 5020 with three blocks, 5180 with two).
+//   few units, and loops long enough to be divided: the longest unit's loop sets the time.  128 channels, 8 heads: 2000 tokens 59 / 38 (four waves
+//     a row; two 44), 4096 tokens 102 / 75 (two), 4096 tokens over 3 ranks 53 / 43.  64 channels, 4 heads, undivided / divided: 512 tokens 23 / 23, 4096 68 /
+//     38 (four; two 50); several sequences have a longer longest loop for the same work: 16 of 16384 tokens 72 / 57 (two).  Where units abound it is slower:
+//     60000 tokens in 16 sequences, 32 heads on 8 of 128 channels 3940 / 5230.
+//   64 channels otherwise: blocks of four waves, three per CU, at every size (against the wide form when it had 64 channels: 60000 tokens in 16 sequences,
+//     40 heads on 8 4100 / 3760; 1000 of 128 1050 / 737).
+//   128 channels: short items are mostly beginnings and ends of units, which other blocks of the CU cover: 1000 of 128, 32 heads on 8 956 / 681 (two
+//     blocks per CU 718), 200 of 80000 tokens 1172 / 1071 (1157); with few units per CU two blocks with 64-key tiles do better than three with
+//     32-key tiles: 4000 tokens in 8 sequences, 32 heads on 8, 62 / 62 (three: 64), 8192 tokens of 8 heads 193 / 183 (206).  Long items: the wide form (60000
+//     tokens in 16 sequences 3940; 4030 with three blocks, 4180 with two).
 inline FwdForm fwd_form(int head_dim, int hq, int64_t tq, int64_t tkv, int64_t n_work, int64_t n_parts, int n_cu) {
   const int64_t rows = std::min(n_parts * tq, tkv);          // of all items together, at most
   const int64_t mean = n_work > 0 ? rows / n_work : 0;
