@@ -368,7 +368,7 @@ __global__ __launch_bounds__(64 * NW, OCC) void fwd_small_kernel(const FwdParams
       scale_rows(l_tot > 0.f ? 1.f / l_tot : 0.f);
     }
     // Direct mode: the tile's rows get all their keys in this unit, so the normalised O is the final one.
-    const bool direct = p.direct && (t.flags & kFlagQExclusive) != 0;
+    const bool direct = p.direct > 1 || (p.direct && (t.flags & kFlagQExclusive) != 0);
     int lane_e = lane;                              // see RowStage::flush
     asm volatile("" : "+v"(lane_e));
     const int l32e = lane_e & 31, g2e = lane_e >> 5;

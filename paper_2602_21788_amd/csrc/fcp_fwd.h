@@ -16,7 +16,7 @@ struct FwdParams {
   uint16_t* o_out;          // running and direct mode: final O as bf16 [tq,hq,D], or NULL
   float* lse_out;           // direct mode: final LSE [hq,tq]
   int32_t running;          // 1: slot 0 of o_part / lse_part is the caller's running result, continued and rewritten
-  int32_t direct;           // 1: a tile whose rows no other item of the launch covers writes o_out / lse_out, no partial
+  int32_t direct;           // 1: a tile whose rows no other item of the launch covers writes o_out / lse_out, no partial; 2: every tile (one partial slot)
   int32_t tq, hq, hkv;
   int32_t head_pair;  // 1: a unit is a tile for TWO heads of one KV head; 0: a tile of twice the rows for one head
   int32_t tile_cap;   // tiles that the list has room for

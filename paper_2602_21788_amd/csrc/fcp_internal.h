@@ -146,6 +146,9 @@ struct RowStates {
   int32_t q_row_elems, kv_row_elems;
   int32_t n_parts;
   bool check_step;
+  void* o_none;          // forward with one partial slot: state 1 does not occur, and the results of rows of state 0 are written here (O [tq,hq,D], LSE [hq,tq])
+  float* lse_none;
+  int32_t hq;
 };
 int check_row_states(int64_t n_work);   // error of a list that is too long for them
 int launch_row_states(int64_t kv_row_bytes, const RowStates& rs, const int32_t* q_limit, const int32_t* k_from,

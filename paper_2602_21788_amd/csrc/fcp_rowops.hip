@@ -215,7 +215,7 @@ static int lse_merge(const float* o_part, const float* lse_part, int32_t n_parts
   if (head_dim != 64 && head_dim != 128) return fail(FCP_ERR_UNSUPPORTED, "fcp_lse_merge: head_dim %d not 64/128", head_dim);
   if (hq > 65535) return fail(FCP_ERR_UNSUPPORTED, "fcp_lse_merge: hq > 65535");
   if (!aligned16(o_part) || !aligned16(o)) return fail(FCP_ERR_INVALID_ARG, "fcp_lse_merge: o_part/o must be 16-byte aligned");
-  if (tq == 0) return FCP_OK;
+  if (tq == 0 || (q_state && n_parts == 1)) return FCP_OK;      // (one slot: the direct forward has written every row)
   hipStream_t st = (hipStream_t)stream;
   if (q_state) {
     const int hpw = 64 / (head_dim / 8);

@@ -852,6 +852,9 @@ struct RowStateJob {
   float* dv_acc;
   int32_t q_row_elems, kv_row_elems;
   int32_t n_parts, check_step;   // the validity rules of the list the states go with
+  uint32_t* o_none;        // forward with one partial slot (see RowStates), or NULL
+  float* lse_none;
+  int32_t hq;
 };
 // The blocks `first` .. `first + count - 1` of the launch share the rows; LDS arrays come from the kernel.  `split`: the rows of split tiles are
 // accumulated into.
@@ -966,13 +969,13 @@ __device__ void row_states(int first, int count, const RowStateJob& job, const L
         }
       }
     }
-    const int state = cnt == 0 ? 0 : (cnt == 1 && own != 0) ? 2 : 1;
+    const int state = cnt == 0 ? 0 : (cnt == 1 && own != 0) || job.o_none ? 2 : 1;
     if (live) {
       if (r < tq) q_state[r] = (uint8_t)state;
       else kv_state[r - tq] = (uint8_t)state;
     }
     __syncthreads();
-    const bool clear = live && state == 1 && (r >= tq || dq_acc != nullptr);
+    const bool clear = live && (job.o_none ? state == 0 : state == 1 && (r >= tq || dq_acc != nullptr));
     const uint64_t todo = __builtin_amdgcn_ballot_w64(clear);
     if (todo) {
       int32_t base = 0;
@@ -986,6 +989,12 @@ __device__ void row_states(int first, int count, const RowStateJob& job, const L
     const int32_t n_clear = s_cnt[1];
     for (int32_t c = wave; c < n_clear; c += kSchedThreads / 64) {
       const int64_t rr = s_clear[c];
+      if (job.o_none) {
+        uint4* row = reinterpret_cast<uint4*>(job.o_none + rr * (q_row_elems / 2));
+        for (int32_t e = lane; e < q_row_elems / 8; e += 64) row[e] = make_uint4(0, 0, 0, 0);
+        for (int32_t h = lane; h < job.hq; h += 64) job.lse_none[(int64_t)h * tq + rr] = -INFINITY;
+        continue;
+      }
       if (rr < tq) {
         float4* row = reinterpret_cast<float4*>(dq_acc + rr * q_row_elems);
         for (int32_t e = lane; e < q_row_elems / 4; e += 64) row[e] = zero;
@@ -1101,6 +1110,7 @@ static RowStateJob make_job(const RowStates* rs) {
     j.dq_acc = rs->dq_acc; j.dk_acc = rs->dk_acc; j.dv_acc = rs->dv_acc;
     j.q_row_elems = rs->q_row_elems; j.kv_row_elems = rs->kv_row_elems;
     j.n_parts = rs->n_parts; j.check_step = rs->check_step ? 1 : 0;
+    j.o_none = (uint32_t*)rs->o_none; j.lse_none = rs->lse_none; j.hq = rs->hq;
   }
   return j;
 }
@@ -1148,7 +1158,7 @@ int launch_schedule(bool backward, int32_t tile, int32_t inner, int64_t kv_row_b
   const int state_blocks = states ? row_state_blocks(tq, states->kv_state ? tkv : 0) : 0;
   hipLaunchKernelGGL(sched_kernel, dim3(1 + fill_blocks + state_blocks), dim3(kSchedThreads), 0, stream,
                      backward ? 1 : 0, list_job(region, n_work, tile, inner, tile_cap),
-                     list_args(kv_row_bytes, work, n_work, cu_seqlens_kv, n_seqs, tq, tkv, n_parts, lse_fill != nullptr),
+                     list_args(kv_row_bytes, work, n_work, cu_seqlens_kv, n_seqs, tq, tkv, n_parts, lse_fill != nullptr || states != nullptr),
                      MaskTables{q_limit, k_from}, lse_fill, lse_fill_n, fill_blocks, make_job(states));
   FCP_HIP_CHECK(hipGetLastError());
   return FCP_OK;
