@@ -15,7 +15,7 @@ CSRC = os.path.join(PKG, "csrc")
 OBJ = os.path.join(PKG, "_build")
 LIB = os.path.join(PKG, "libfcp.so")
 SOURCES = ["fcp_host.cpp", "fcp_planner.cpp", "fcp_sched.hip", "fcp_rowops.hip", "fcp_attn_fwd.hip", "fcp_attn_fwd_small.hip", "fcp_attn_bwd_lists.hip", "fcp_attn_bwd.hip", "fcp_attn_bwd_fused.hip", "fcp_attn_bwd_short.hip"]
-HEADERS = [os.path.join(CSRC, "fcp_internal.h"), os.path.join(CSRC, "fcp_sizes.h"), os.path.join(CSRC, "fcp_device.h"), os.path.join(CSRC, "fcp_bwd.h"), os.path.join(CSRC, "fcp_fwd.h"),
+HEADERS = [os.path.join(CSRC, "fcp_internal.h"), os.path.join(CSRC, "fcp_sizes.h"), os.path.join(CSRC, "fcp_device.h"), os.path.join(CSRC, "fcp_items.h"), os.path.join(CSRC, "fcp_bwd.h"), os.path.join(CSRC, "fcp_fwd.h"),
            os.path.join(ROOT, "include", "fcp.h")]
 # packed fp32 VALU ops are switched off for all device code (see the note in the package docs)
 # Loops begin on a cache line: a step loop is entered some thousand times by each of a block's waves and fits a step of 1000 to 3000 clocks, and

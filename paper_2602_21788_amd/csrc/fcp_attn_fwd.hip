@@ -524,12 +524,15 @@ static int fwd_step(const void* q, const void* k, const void* v, const int32_t* 
     rs.n_parts = n_parts; rs.check_step = true;
     if (n_parts == 1) { rs.o_none = o_out; rs.lse_none = lse_out; rs.hq = hq; }
   }
-  int rc = fcp::launch_schedule(false, tile, fcp::kFwdBN, (int64_t)hkv * head_dim * 2, q_limit, nullptr, work, n_work, cu_seqlens_kv, n_seqs, tq, tkv, n_parts, cap, scratch,
+  int64_t units = cap * (hq / (head_pair ? 2 : 1));
+  const bool alone = tq > 0 && fcp::fwd_alone(form, head_dim, n_work, n_parts, units, n_cu);
+  int rc = FCP_OK;
+  if (!alone) rc = fcp::launch_schedule(false, tile, fcp::kFwdBN, (int64_t)hkv * head_dim * 2, q_limit, nullptr, work, n_work, cu_seqlens_kv, n_seqs, tq, tkv, n_parts, cap, scratch,
                                 running || (direct && n_parts == 1) ? nullptr : lse_part, (int64_t)n_parts * hq * tq, st, direct ? &rs : nullptr);
   if (rc != FCP_OK) return rc;
   if (tq == 0 || n_work == 0) return FCP_OK;
 
-  fcp::FwdParams p;
+  fcp::FwdParams p{};
   p.q = (const uint16_t*)q; p.k = (const uint16_t*)k; p.v = (const uint16_t*)v;
   p.hdr = (fcp::SchedHeader*)scratch;
   p.tiles = fcp::sched_tiles(scratch, n_work);
@@ -544,8 +547,10 @@ static int fwd_step(const void* q, const void* k, const void* v, const int32_t* 
   p.head_pair = head_pair;
   p.scale_log2 = softmax_scale * 1.4426950408889634f;
 
-  int64_t units = cap * (hq / (head_pair ? 2 : 1));
-  if (form != fcp::kFwdWide) return fcp::launch_fwd_small(p, head_dim, form, units, n_cu, st);
+  p.tile = tile;
+  p.q_state = rs.q_state;
+  p.list = {work, cu_seqlens_kv, (int32_t)n_work, n_seqs, tq, tkv, n_parts, fcp::max_segment_keys((int64_t)hkv * head_dim * 2), !running};
+  if (form != fcp::kFwdWide) return fcp::launch_fwd_small(p, head_dim, form, units, alone, n_cu, st);
   const int64_t blocks = fcp::persistent_blocks(n_cu, units);   // one 512-thread block per CU
   static std::atomic<uint64_t> lds_done;
   if ((rc = fcp::raise_lds_limit((const void*)fcp::fwd_kernel<128>, fcp::FwdCfg<128>::LDS_BYTES, lds_done)) != FCP_OK) return rc;

@@ -14,6 +14,8 @@
 //     (maximum, sum, O) meet in LDS at the unit's end.  Half (a quarter) of the rows per unit, half (a quarter) of the serial loop, for problems
 //     that would otherwise leave CUs without a unit.  A stage's fills then serve fewer matrix instructions, so it does not pay where units
 //     abound (60000 tokens in 16 sequences, 32 heads on 8: 4180 -> 5230 us with two).
+//   * small launches have no list (fwd_alone in csrc/fcp_sizes.h): a block finds its unit from the work items, and further blocks do what else the
+//     scheduling launch does (row states, empty slots, the header's counts).  No block waits for another one.
 // Priorities as in fwd_kernel (matrix stream first) gain 1 % on long items and lose 1 to 3 % elsewhere; none are set.
 // Times of the forms beside each other and where each is taken: fwd_form in csrc/fcp_sizes.h.
 #include "fcp_fwd.h"
@@ -45,6 +47,97 @@ struct SmallCfg {
   static_assert(RPW % KT::RPI == 0 && KT::row_base(RPW * 3 + KT::RPI) == KT::row_base(RPW * 3) + KT::row_base(KT::RPI), "a wave's rows start on a padding group boundary");
 };
 
+// ---- launches without a list (fwd_alone): one item per lane -------------------------------
+static_assert(kAloneItems == 64 && kAloneParts == 32, "a lane per item, a bit per slot");
+__device__ inline Item lane_item(const FwdParams& p, int lane) {
+  Item it{-1, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0};
+  if (lane < p.list.n_work) it = load_item(p.list, MaskTables{p.q_limit, nullptr}, lane);
+  return it;
+}
+// One wave writes the record of the launch's tile `number`.  The items stand by the cost of their last tile, which sees the most keys, the tiles of an item from its end
+// on: long units begin first, and a short one beside each.  (In the order of the list 8000 tokens over 3 ranks, 8 heads, take 87 instead of 72 us.)
+__device__ inline bool alone_record(const FwdParams& p, int number, i32x4* s_lists, int32_t* s_rec) {
+  const int lane = lane_id();
+  const Item it = lane_item(p, lane);
+  const int32_t tiles = it.seq >= 0 ? ceil_div(it.q_len, p.tile) : 0, cost = ceil_div(it.vis0, kFwdBN) + ceil_div(it.vis1, kFwdBN);
+  const int32_t key = min(cost, 1 << 24) * 64 + 63 - lane;    // (no two are alike)
+  int32_t before = 0;                               // tiles of the items that stand before the lane's
+  reinterpret_cast<int32_t*>(s_lists)[lane] = key;
+  reinterpret_cast<int32_t*>(s_lists)[64 + lane] = tiles;     // (none past the list's end)
+#pragma unroll 4
+  for (int j = 0; j < (p.list.n_work + 3) / 4; ++j) {
+    const i32x4 k = s_lists[j], n = s_lists[16 + j];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) before += k[e] > key ? n[e] : 0;
+  }
+  const uint64_t mine = __builtin_amdgcn_ballot_w64(number >= before && number < before + tiles);
+  if (mine == 0) return false;
+  const int at = __builtin_ctzll(mine);
+  auto of = [&](int32_t v) { return __builtin_amdgcn_readlane(v, at); };
+  const Item u{0, of(it.q_off), of(it.q_len), of(it.q_pos), of(it.k0), of(it.n0), of(it.k1), of(it.n1), of(it.base), 0, 0, of(it.step)};
+  const bool shared = __builtin_amdgcn_ballot_w64(lane != at && it.seq >= 0 && it.q_off < u.q_off + u.q_len && u.q_off < it.q_off + it.q_len) != 0;
+  const int32_t r0 = (of(before) + of(tiles) - 1 - number) * p.tile;
+  const int32_t rows = min(p.tile, u.q_len - r0);
+  const int64_t limit = MaskTables{p.q_limit, nullptr}.limit(u, r0 + rows - 1);
+  if (lane == 0) {
+    const int32_t w[12] = {u.q_off + r0, u.q_pos + r0, rows, u.step, u.base + u.k0, u.n1 > 0 ? u.base + u.k1 : 0, u.k0, u.k1,
+                           seen_keys(u, 0, limit), u.n1 > 0 ? seen_keys(u, 1, limit) : 0, shared ? 0 : kFlagQExclusive, 0};
+#pragma unroll
+    for (int i = 0; i < 12; ++i) s_rec[i] = w[i];
+  }
+  return true;
+}
+// What the scheduling launch does beside the list: the rows' states (direct mode), -inf in the partial slots of rows that no item covers there, O = 0 and
+// LSE = -inf of rows without an item where no merge follows, and the counts of the header.  A row per thread.
+template <int D>
+__device__ inline void alone_rows(const FwdParams& p, i32x4* s_lists) {
+  const int lane = lane_id(), n_work = p.list.n_work;
+  s_lists += 64 * (threadIdx.x >> 6);
+  const Item it = lane_item(p, lane);
+  const int block = (int)blockIdx.x - p.unit_blocks;
+  if (block == 0 && threadIdx.x < 64) {
+    int32_t n_tiles = it.seq >= 0 ? ceil_div(it.q_len, p.tile) : 0;
+    for (int off = 32; off > 0; off >>= 1) n_tiles += __shfl_xor(n_tiles, off, 64);
+    const int n_bad = __builtin_popcountll(__builtin_amdgcn_ballot_w64(lane < n_work && it.seq < 0));
+    if (lane < (int)(sizeof(SchedHeader) / 4))
+      reinterpret_cast<int32_t*>(p.hdr)[lane] = lane == 0 ? n_tiles : lane == 1 ? n_bad : 0;
+  }
+  if (p.running) return;
+  const int32_t row = block * (int)blockDim.x + (int)threadIdx.x;
+  const int32_t len = it.seq >= 0 ? it.q_len : 0;
+  int32_t shared = 0, hits = 0, lost = 0;
+  uint32_t slots = 0;
+  s_lists[lane] = i32x4{it.q_off, len, it.step & 31, 0};
+#pragma unroll 4
+  for (int j = 0; j < n_work; ++j) {
+    const i32x4 o = s_lists[j];
+    shared |= j != lane && o[1] > 0 && it.q_off < o[0] + o[1] && o[0] < it.q_off + len;
+  }
+  s_lists[lane][3] = shared;
+#pragma unroll 4
+  for (int j = 0; j < n_work; ++j) {
+    const i32x4 o = s_lists[j];
+    const bool hit = (uint32_t)(row - o[0]) < (uint32_t)o[1];
+    hits += hit;
+    lost |= hit ? o[3] : 0;
+    slots |= hit ? 1u << o[2] : 0;
+  }
+  if (row >= p.tq) return;
+  const int state = hits == 0 ? 0 : p.direct > 1 || (hits == 1 && !lost) ? 2 : 1;
+  if (p.direct) p.q_state[row] = (uint8_t)state;
+  if (p.direct > 1) {
+    if (state != 0) return;
+    u32x4* const o = reinterpret_cast<u32x4*>(p.o_out + (int64_t)row * p.hq * D);
+    for (int e = 0; e < p.hq * D / 8; ++e) o[e] = u32x4{0, 0, 0, 0};
+    for (int h = 0; h < p.hq; ++h) p.lse_out[(int64_t)h * p.tq + row] = -INFINITY;
+  } else if (!p.direct || state != 2) {            // (the slots of a row that has its result are not read)
+    for (int s = 0; s < p.list.n_parts; ++s) {
+      if (slots >> s & 1) continue;
+      for (int h = 0; h < p.hq; ++h) p.lse_part[((int64_t)s * p.hq + h) * p.tq + row] = -INFINITY;
+    }
+  }
+}
+
 template <int D, int NW, int SPLIT, int SKEYS, int OCC, int AH>
 __global__ __launch_bounds__(64 * NW, OCC) void fwd_small_kernel(const FwdParams p) {
   using C = SmallCfg<D, NW, SPLIT, SKEYS>;
@@ -72,8 +165,16 @@ __global__ __launch_bounds__(64 * NW, OCC) void fwd_small_kernel(const FwdParams
   const int heads_here = per_xcd ? p.hq / kNumXcd : p.hq;
   const int units_per_tile = heads_here / hpu;
   UnitQueue uq;
-  uq.init_dealt(p.hdr, p.tiles, xcd, units_per_tile, per_xcd ? blockIdx.x / kNumXcd : blockIdx.x, per_xcd ? gridDim.x / kNumXcd : gridDim.x, p.tile_cap,
-                &s_next_unit, s_rec);
+  if (p.unit_blocks > 0) {
+    if ((int)blockIdx.x >= p.unit_blocks) return alone_rows<D>(p, reinterpret_cast<i32x4*>(smem));
+    const int place = per_xcd ? blockIdx.x / kNumXcd : blockIdx.x;
+    bool found = false;
+    if (tid < 64) found = alone_record(p, place / units_per_tile, reinterpret_cast<i32x4*>(smem), s_rec);
+    uq.init_alone(units_per_tile, place % units_per_tile, found, &s_next_unit);
+  } else {
+    uq.init_dealt(p.hdr, p.tiles, xcd, units_per_tile, per_xcd ? blockIdx.x / kNumXcd : blockIdx.x, per_xcd ? gridDim.x / kNumXcd : gridDim.x, p.tile_cap,
+                  &s_next_unit, s_rec);
+  }
 
   const int kv_row_bytes = p.hkv * D * 2;
   int kfill[C::NKF];
@@ -439,13 +540,15 @@ __global__ __launch_bounds__(64 * NW, OCC) void fwd_small_kernel(const FwdParams
 }
 
 template <int D, int NW, int SPLIT, int SKEYS, int OCC, int AH>
-int launch_one(const FwdParams& p, int64_t units, int n_cu, hipStream_t stream) {
+int launch_one(FwdParams p, int64_t units, bool alone, int n_cu, hipStream_t stream) {
   using C = SmallCfg<D, NW, SPLIT, SKEYS>;
   static std::atomic<uint64_t> lds_done;
   const auto kernel = fwd_small_kernel<D, NW, SPLIT, SKEYS, OCC, AH>;
   const int rc = raise_lds_limit((const void*)kernel, C::LDS_BYTES, lds_done);
   if (rc != FCP_OK) return rc;
-  const int64_t blocks = persistent_blocks((int64_t)n_cu * (OCC * 4 / NW), units);
+  int64_t blocks = persistent_blocks((int64_t)n_cu * (OCC * 4 / NW), units);
+  p.unit_blocks = alone ? (int32_t)units : 0;
+  if (alone) blocks = units + (p.running ? 1 : (p.tq + 64 * NW - 1) / (64 * NW));
   hipLaunchKernelGGL(kernel, dim3((unsigned)blocks), dim3(64 * NW), C::LDS_BYTES, stream, p);
   FCP_HIP_CHECK(hipGetLastError());
   return FCP_OK;
@@ -453,15 +556,15 @@ int launch_one(const FwdParams& p, int64_t units, int n_cu, hipStream_t stream) 
 
 }  // namespace
 
-int launch_fwd_small(const FwdParams& p, int head_dim, FwdForm form, int64_t units, int n_cu, hipStream_t stream) {
+int launch_fwd_small(FwdParams p, int head_dim, FwdForm form, int64_t units, bool alone, int n_cu, hipStream_t stream) {
   if (head_dim == 64)
-    return form == kFwdSplit4   ? launch_one<64, 4, 4, 128, 2, 4>(p, units, n_cu, stream)
-           : form == kFwdSplit2 ? launch_one<64, 4, 2, 64, 3, 4>(p, units, n_cu, stream)
-                                : launch_one<64, 4, 1, 64, 3, 4>(p, units, n_cu, stream);
-  return form == kFwdSplit4   ? launch_one<128, 8, 4, 128, 2, 4>(p, units, n_cu, stream)
-         : form == kFwdSplit2 ? launch_one<128, 4, 2, 64, 2, 4>(p, units, n_cu, stream)
-         : form == kFwdSmall  ? launch_one<128, 4, 1, 64, 2, 4>(p, units, n_cu, stream)
-                              : launch_one<128, 4, 1, 32, 3, 3>(p, units, n_cu, stream);
+    return form == kFwdSplit4   ? launch_one<64, 4, 4, 128, 2, 4>(p, units, alone, n_cu, stream)
+           : form == kFwdSplit2 ? launch_one<64, 4, 2, 64, 3, 4>(p, units, alone, n_cu, stream)
+                                : launch_one<64, 4, 1, 64, 3, 4>(p, units, alone, n_cu, stream);
+  return form == kFwdSplit4   ? launch_one<128, 8, 4, 128, 2, 4>(p, units, alone, n_cu, stream)
+         : form == kFwdSplit2 ? launch_one<128, 4, 2, 64, 2, 4>(p, units, alone, n_cu, stream)
+         : form == kFwdSmall  ? launch_one<128, 4, 1, 64, 2, 4>(p, units, alone, n_cu, stream)
+                              : launch_one<128, 4, 1, 32, 3, 3>(p, units, alone, n_cu, stream);
 }
 
 }  // namespace fcp

@@ -271,6 +271,17 @@ struct UnitQueue {
     }
     __syncthreads();
   }
+  // Without a list: the block has one unit, sub-index `sub` of the tile whose record is in s_rec (found: there is such a tile), and no counter.
+  __device__ void init_alone(int per_tile_, int sub, bool found, int32_t* s_next) {
+    counter = nullptr;
+    rec_words = nullptr;
+    n_units = per_tile = per_tile_;
+    reserve = true;                                // (nothing is asked for: the unit in reserve is past the last)
+    pend = n_units;
+    recw = idx1 = dealt = 0;
+    if (threadIdx.x == 0) *s_next = found ? sub : n_units;
+    __syncthreads();
+  }
   // current unit number (>= n_units: the list is exhausted); wave-uniform
   __device__ int32_t current(const int32_t* s_next) const { return __builtin_amdgcn_readfirstlane(*s_next); }
   // in the unit's last steps: ask for the next one

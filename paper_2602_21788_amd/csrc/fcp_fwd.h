@@ -1,6 +1,7 @@
 // Declarations shared by the forward kernels' translation units (not installed).
 #pragma once
 #include "fcp_device.h"
+#include "fcp_items.h"
 
 namespace fcp {
 
@@ -21,10 +22,16 @@ struct FwdParams {
   int32_t head_pair;  // 1: a unit is a tile for TWO heads of one KV head; 0: a tile of twice the rows for one head
   int32_t tile_cap;   // tiles that the list has room for
   float scale_log2;   // softmax_scale * log2(e)
+  // A launch without a list (fwd_alone in csrc/fcp_sizes.h): block b < unit_blocks finds unit b by itself, the blocks behind them classify the rows.
+  int32_t unit_blocks;      // 0: the list tells
+  int32_t tile;             // query rows per tile
+  uint8_t* q_state;         // direct mode
+  ListArgs list;
 };
 
 constexpr float kRescaleThreshold = 8.f;   // log2 units
 
-int launch_fwd_small(const FwdParams& p, int head_dim, FwdForm form, int64_t units, int n_cu, hipStream_t stream);
+// (p.unit_blocks is set by the launch: `alone`)
+int launch_fwd_small(FwdParams p, int head_dim, FwdForm form, int64_t units, bool alone, int n_cu, hipStream_t stream);
 
 }  // namespace fcp

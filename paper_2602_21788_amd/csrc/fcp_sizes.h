@@ -162,6 +162,22 @@ inline FwdPlan fwd_plan(int head_dim, int hq, int hkv, int32_t tq, int32_t tkv, 
   return with(kFwdSmall, false);
 }
 
+// Blocks of the form that a CU holds.
+inline int fwd_blocks_per_cu(FwdForm f, int head_dim) {
+  if (head_dim == 64) return f == kFwdSplit4 ? 2 : 3;
+  return f == kFwdWide || f == kFwdSplit4 ? 1 : f == kFwdShort ? 3 : 2;
+}
+// Does the launch do without a list?  Its blocks then have one unit each, which they find from the items themselves (one item per lane, the slots of a row in
+// one word), and as many blocks as there can be units are launched: there is no scheduling launch to wait for (7 to 10 us), but a block begins with one or
+// two trips to memory more, and long units of different items begin in the order of the items, not of all tiles.  With up to 2.5 units per resident block that
+// pays.  The two calls of the direct forward in a graph, with a list / without, us: 512 tokens, 4 heads of 64 channels (0.13 units per block) 15.9 / 9.7; 4096, the same heads (1.0)
+// 36.0 / 30.3; 4096 over 3 ranks, 8 heads (1.1) 45.4 / 38.6; 40 sequences of 300, 6 heads on 2 of 64 (1.8) 35.6 / 25.2; 30 of 100, 32 on 8 (2.2) 31.3 / 23.8; 4096 over 8 ranks,
+// 32 on 8 (2.4) 60.9 / 51.1; past that 20000 over 8 ranks, 8 heads (2.6) 135.7 / 139.3, 64 of 300, 8 heads (3.2) 52.4 / 57.9, 60 of 500, 10 on 2 of 64 (3.7) 63 / 68.
+constexpr int kAloneItems = 64, kAloneParts = 32;
+inline bool fwd_alone(FwdForm f, int head_dim, int64_t n_work, int32_t n_parts, int64_t units, int n_cu) {
+  return f != kFwdWide && n_work >= 1 && n_work <= kAloneItems && n_parts <= kAloneParts && 2 * units <= 5 * (int64_t)n_cu * fwd_blocks_per_cu(f, head_dim);
+}
+
 // What a call must bring: the list of the smallest tiles and the direct mode's row states; for the static area (no row states, and the plan goes by
 // what fits) the list of 128-row tiles, with tq bytes to spare.
 inline size_t fwd_area_bytes(int32_t tq, int32_t tkv, int64_t n_work, int32_t n_parts) {
