@@ -315,7 +315,7 @@ __device__ inline void key_units(const BwdParams& p, const int queues, PartQueue
         for (int db = 0; db < C::NVA; ++db)
 #pragma unroll
           for (int i = 0; i < 16; ++i) OUT::put_bf16(obuf, OUT::reg_row(i, g2e), 32 * db + l32e, (m ? dk : dv)[db][i] * mul);
-        OUT::flush(obuf, lane_e, r, row_bytes, 0);
+        OUT::template flush<true>(obuf, lane_e, r, row_bytes, 0);
       }
     } else {
       const bool in_turn = (t.flags & kFlagInTurn) != 0;

@@ -517,7 +517,7 @@ __global__ __launch_bounds__(256, 2) void bwd_short_kernel(const BwdParams p) {
         for (int db = 0; db < C::NVA; ++db)
 #pragma unroll
           for (int i = 0; i < 16; ++i) OUT::put_bf16(obuf, OUT::reg_row(i, g2e), 32 * db + l32e, (m ? dk : dv)[db][i] * mul);
-        OUT::flush(obuf, lane_e, r, row_bytes, 0);
+        OUT::template flush<true>(obuf, lane_e, r, row_bytes, 0);
       }
     } else {
       const int row_bytes = fresh_uniform(p.hkv * D * 4);

@@ -527,7 +527,7 @@ __global__ __launch_bounds__(64 * NW, OCC) void fwd_small_kernel(const FwdParams
         for (int db = 0; db < D / 32; ++db)
 #pragma unroll
           for (int i = 0; i < 16; ++i) OUT::put_bf16(obuf, OUT::reg_row(i, g2e), 32 * db + l32e, oacc[db][i]);
-        OUT::flush(obuf, lane_e, rb, row_bytes, 0);
+        OUT::template flush<true>(obuf, lane_e, rb, row_bytes, 0);
       }
     }
     if (row_valid && g2 == 0 && share == 0) {

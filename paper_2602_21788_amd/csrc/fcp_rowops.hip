@@ -120,8 +120,10 @@ __global__ __launch_bounds__(256) void delta_kernel(const uint32_t* __restrict__
   float s = 0.f;
   if (row < tq) {
     const int64_t off = (((int64_t)row * hq + h) * D + c8 * 8) / 2;
-    const u32x4 a = *reinterpret_cast<const u32x4*>(o + off);
-    const u32x4 b = *reinterpret_cast<const u32x4*>(d_o + off);
+    // (Non-temporal: read once, they do not have to push what the caches hold, much of it still to be written back, out of them.  128000 rows of 32 heads
+    // 344 us, 6.1 TB/s, instead of 400, 25003 rows after another kernel's 512 MB of stores 77 instead of 122.)
+    const u32x4 a = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(o + off));
+    const u32x4 b = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(d_o + off));
 #pragma unroll
     for (int i = 0; i < 4; ++i) s += bf16_lo(a[i]) * bf16_lo(b[i]) + bf16_hi(a[i]) * bf16_hi(b[i]);
   }
