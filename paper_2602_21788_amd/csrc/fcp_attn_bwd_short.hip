@@ -10,9 +10,12 @@
 //   * dQ^T as [channel x query]: a lane has four consecutive channels of a query in four registers, exchanged with the other half of the wave
 //     to stores of 16 bytes; the final rows of a sequence of one tile go straight to bf16;
 //   * the flag of a chain's step is set most of a step later, when its stores have arrived anyway.
+//   * a store or load takes about a clock for every line it touches, however little of it: the final rows leave 64 bytes of a row at a time, and a sum on its way
+//     from one tile to the next lies where an instruction's lines are whole, not where row and channel belong (scheduling and one-pass launch, us, before / now: 1000
+//     sequences of 128 on average, 32 query heads on 8 KV heads 1247 / 1210, 8 heads 504 / 464, 1000 of 60 482 / 465, 120 of 150 235 / 219).
 // What bounds it: memory.  1000 sequences of 128 tokens, 32 query heads on 8 KV heads, are 4.2 GB of Q, dO, dQ, K, V, dK and dV: 0.89 ms with the scheduling launch
 // (4.7 TB/s, what a large copy reaches, by count), 64 tokens each 0.45 ms; the twelve-wave kernel 1.01 and 0.64.  Sequences of two tiles move a part of dQ as fp32 and
-// read Q and dO again: 1000 of 128 on average 1.42 -> 1.29 ms (5.2 GB by the counters; 8 heads 667 -> 508 us), 1000 of 40 534 -> 376 us (8 heads 318 -> 206).
+// read Q and dO again: 1000 of 128 on average 1.42 -> 1.21 ms (5.2 GB by the counters; 8 heads 667 -> 464 us), 1000 of 40 534 -> 376 us (8 heads 318 -> 206).
 // Where one chain sets the time a step takes 2.5 us against 1.5: the rule is bwd_way in csrc/fcp_sizes.h.
 // Tried: the sums of earlier tiles requested before the barrier (a chain's step 2.5 -> 2.2 us, but many short sequences 2 % slower: the extra loads
 // are issued for every step); fragments two or four instructions ahead, no priority for the matrix stream: equal.
@@ -444,10 +447,16 @@ __global__ __launch_bounds__(256, 2) void bwd_short_kernel(const BwdParams p) {
       }
       const float dq_mul = spin_left > 0 ? p.scale : NAN;            // (see kSpinLimit)
       const int dq_voff = (l & 31) * dq_row_bytes + 16 * (l >> 5);
+      // Sums on their way from one tile to the next lie where an instruction's lines are whole: 16 bytes per lane of eight rows x 128 bytes.  In their own
+      // places they lie where they come from and go to the caller, and in a last block of less than 32 rows.
+      const bool whole = 32 * (qb0 + j + 1) <= t.q_len, get_lines = whole && rank > 0, put_lines = whole && qb0 + j >= qb_next;
+      const int lines = (l >> 3) * dq_row_bytes + 16 * (l & 7);
       if (loads) {
         f32x4 v[4];
+        const int at = get_lines ? lines : dq_voff, step = get_lines ? 8 * dq_row_bytes : 32;
 #pragma unroll
-        for (int q = 0; q < 4; ++q) v[q] = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(rq, dq_voff + 32 * q, so, kCacheBypass));
+        for (int q = 0; q < 4; ++q) v[q] = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(rq, at, so + q * step, kCacheBypass));
+        if (get_lines != put_lines) wait_vmem<0>(); // (all of it is read before any of it is written)
 #pragma unroll
         for (int q = 0; q < 4; ++q)
 #pragma unroll
@@ -462,19 +471,30 @@ __global__ __launch_bounds__(256, 2) void bwd_short_kernel(const BwdParams p) {
 #pragma unroll
         for (int q = 0; q < 4; ++q)
           w[q] = __builtin_bit_cast(u32x2, bf16x4{(__bf16)dq[4 * q], (__bf16)dq[4 * q + 1], (__bf16)dq[4 * q + 2], (__bf16)dq[4 * q + 3]});
+        u32x4 x[2];
 #pragma unroll
         for (int q = 0; q < 2; ++q) {               // lanes below 32 end up with channels 8 q .. 8 q + 7, the others with 16 + 8 q ..
           const auto a = __builtin_amdgcn_permlane32_swap(w[q][0], w[q + 2][0], false, false);
           const auto b = __builtin_amdgcn_permlane32_swap(w[q][1], w[q + 2][1], false, false);
-          const u32x4 x = {(uint32_t)a[0], (uint32_t)b[0], (uint32_t)a[1], (uint32_t)b[1]};
-          __builtin_amdgcn_raw_buffer_store_b128(x, rb, (l & 31) * (dq_row_bytes / 2) + 32 * (l >> 5) + 16 * q + (int)((uint32_t)so / 2), 0, 0);
-          asm volatile("s_nop 1" :: "v"(x));        // (see RowStage::flush)
+          x[q] = u32x4{(uint32_t)a[0], (uint32_t)b[0], (uint32_t)a[1], (uint32_t)b[1]};
+        }
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {               // x[0]: all 32 channels of the first sixteen rows, x[1]: of the others (64 bytes of a row an instruction, not twice 16)
+          const auto a = __builtin_amdgcn_permlane16_swap(x[0][e], x[1][e], false, false);
+          x[0][e] = (uint32_t)a[0];
+          x[1][e] = (uint32_t)a[1];
+        }
+#pragma unroll
+        for (int q = 0; q < 2; ++q) {
+          __builtin_amdgcn_raw_buffer_store_b128(x[q], rb, (16 * q + (l & 15)) * (dq_row_bytes / 2) + 32 * (l >> 5) + (l & 16) + (int)((uint32_t)so / 2), 0, 0);
+          asm volatile("s_nop 1" :: "v"(x[q]));        // (see RowStage::flush)
         }
       } else if (chained) {
+        const int at = (put_lines ? lines : dq_voff) + so, step = put_lines ? 8 * dq_row_bytes : 32;
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
           const u32x4 x = __builtin_bit_cast(u32x4, f32x4{dq[4 * q], dq[4 * q + 1], dq[4 * q + 2], dq[4 * q + 3]});
-          __builtin_amdgcn_raw_buffer_store_b128(x, rq, dq_voff + 32 * q + so, 0, 0);
+          __builtin_amdgcn_raw_buffer_store_b128(x, rq, at + q * step, 0, 0);
           asm volatile("s_nop 1" :: "v"(x));
         }
         fo_done = fo;
