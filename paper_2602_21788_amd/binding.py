@@ -122,16 +122,22 @@ def _dev_ptr(t):
     """Device pointer of a torch tensor (must be contiguous and on a GPU)."""
     if t is None:
         return None
-    if not t.is_cuda or not t.is_contiguous():
-        raise ValueError("expected a contiguous device tensor")
-    return ctypes.c_void_p(t.data_ptr())
+    if t.is_cuda and t.is_contiguous():
+        return t.data_ptr()                       # (an int: ctypes makes the pointer of it)
+    raise ValueError("expected a contiguous device tensor")
 
 
+# A forward of one short prompt takes the GPU 10 us, so what a call costs on the host shows: pointers and streams are passed as plain integers, and
+# the current stream is asked for by its handle, without a stream object (0.3 instead of 3 us; the two calls of the direct forward 9.5 instead of 16.5).
 def _stream(stream):
-    if stream is None:
-        import torch
-        stream = torch.cuda.current_stream()
-    return ctypes.c_void_p(int(getattr(stream, "cuda_stream", stream)))
+    """Handle of a stream (torch's, or a handle); None: torch's current one on the current device."""
+    if stream is not None:
+        return int(getattr(stream, "cuda_stream", stream))
+    import torch
+    try:
+        return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
+    except AttributeError:                        # (a torch that has no such call)
+        return torch.cuda.current_stream().cuda_stream
 
 
 # ---------------------------------------------------------------------------------------
