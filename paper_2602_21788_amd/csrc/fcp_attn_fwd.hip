@@ -526,7 +526,7 @@ static int fwd_step(const void* q, const void* k, const void* v, const int32_t* 
     if (n_parts == 1) { rs.o_none = o_out; rs.lse_none = lse_out; rs.hq = hq; }
   }
   int64_t units = cap * (hq / (head_pair ? 2 : 1));
-  const bool alone = tq > 0 && fcp::fwd_alone(form, head_dim, n_work, n_parts, units, n_cu);
+  const bool alone = tq > 0 && tq < (1 << 30) && fcp::fwd_alone(form, head_dim, n_work, n_parts, units, n_cu);
   int rc = FCP_OK;
   if (!alone) rc = fcp::launch_schedule(false, tile, fcp::kFwdBN, (int64_t)hkv * head_dim * 2, q_limit, nullptr, work, n_work, cu_seqlens_kv, n_seqs, tq, tkv, n_parts, cap, scratch,
                                 running || (direct && n_parts == 1) ? nullptr : lse_part, (int64_t)n_parts * hq * tq, st, direct ? &rs : nullptr,
