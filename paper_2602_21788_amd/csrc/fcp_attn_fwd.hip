@@ -88,7 +88,6 @@ __global__ __launch_bounds__(512, 1) void fwd_kernel(const FwdParams p) {
   const int xcd = per_xcd ? (int)(blockIdx.x % kNumXcd) : 0;
   const int heads_here = per_xcd ? p.hq / kNumXcd : p.hq;
   const int units_per_tile = heads_here / hpu;
-  if (p.either && p.hdr->path != 0) return;
   UnitQueue uq;
   uq.init(p.hdr, p.tiles, xcd, units_per_tile, &s_next_unit, s_rec);
 
@@ -510,7 +509,7 @@ static int fwd_step(const void* q, const void* k, const void* v, const int32_t* 
   FCP_HIP_CHECK(hipGetDevice(&dev));
   FCP_HIP_CHECK(hipDeviceGetAttribute(&n_cu, hipDeviceAttributeMultiprocessorCount, dev));
   const size_t area = static_area ? scratch_bytes : fcp::fwd_area_bytes(tq, tkv, n_work, n_parts);   // (row states behind it)
-  const auto [form, head_pair, tile, cap, tile_short] = fcp::fwd_plan(head_dim, hq, hkv, tq, tkv, n_work, n_parts, n_cu, area);
+  const auto [form, head_pair, tile, cap] = fcp::fwd_plan(head_dim, hq, hkv, tq, tkv, n_work, n_parts, n_cu, area);
   if (fcp::sched_region_bytes(n_work, cap) > area)
     return fail(FCP_ERR_CAPACITY, "fcp_attn_fwd_step: the tile list needs %zu bytes of %zu", fcp::sched_region_bytes(n_work, cap), area);
   const bool direct = lse_out != nullptr;
@@ -523,14 +522,14 @@ static int fwd_step(const void* q, const void* k, const void* v, const int32_t* 
     rs.q_state = fcp::fwd_q_state(scratch, n_work, tq, tkv, n_parts);
     rs.q_row_elems = hq * head_dim; rs.kv_row_elems = hkv * head_dim;
     rs.n_parts = n_parts; rs.check_step = true;
+    if (n_parts > 1) { rs.join_heads = hq; rs.n_cu = n_cu; }
     if (n_parts == 1) { rs.o_none = o_out; rs.lse_none = lse_out; rs.hq = hq; }
   }
   int64_t units = cap * (hq / (head_pair ? 2 : 1));
   const bool alone = tq > 0 && tq < (1 << 30) && fcp::fwd_alone(form, head_dim, n_work, n_parts, units, n_cu);
   int rc = FCP_OK;
   if (!alone) rc = fcp::launch_schedule(false, tile, fcp::kFwdBN, (int64_t)hkv * head_dim * 2, q_limit, nullptr, work, n_work, cu_seqlens_kv, n_seqs, tq, tkv, n_parts, cap, scratch,
-                                running || (direct && n_parts == 1) ? nullptr : lse_part, (int64_t)n_parts * hq * tq, st, direct ? &rs : nullptr,
-                                fcp::ForwardList{direct && n_parts > 1, hq, n_cu, tile_short});
+                                running || (direct && n_parts == 1) ? nullptr : lse_part, (int64_t)n_parts * hq * tq, st, direct ? &rs : nullptr);
   if (rc != FCP_OK) return rc;
   if (tq == 0 || n_work == 0) return FCP_OK;
 
@@ -551,10 +550,8 @@ static int fwd_step(const void* q, const void* k, const void* v, const int32_t* 
 
   p.tile = tile;
   p.q_state = rs.q_state;
-  p.list = {work, cu_seqlens_kv, (int32_t)n_work, n_seqs, tq, tkv, n_parts, fcp::max_segment_keys((int64_t)hkv * head_dim * 2), !running, false, hq, n_cu};
+  p.list = {work, cu_seqlens_kv, (int32_t)n_work, n_seqs, tq, tkv, n_parts, fcp::max_segment_keys((int64_t)hkv * head_dim * 2), !running, 0, 0};
   if (form != fcp::kFwdWide) return fcp::launch_fwd_small(p, head_dim, form, units, alone, n_cu, st);
-  p.either = tile_short > 0;
-  if (p.either && (rc = fcp::launch_fwd_small(p, head_dim, fcp::kFwdShort, units, false, n_cu, st)) != FCP_OK) return rc;   // (the one or the other ends at once)
   const int64_t blocks = fcp::persistent_blocks(n_cu, units);   // one 512-thread block per CU
   static std::atomic<uint64_t> lds_done;
   if ((rc = fcp::raise_lds_limit((const void*)fcp::fwd_kernel<128>, fcp::FwdCfg<128>::LDS_BYTES, lds_done)) != FCP_OK) return rc;

@@ -172,7 +172,6 @@ __global__ __launch_bounds__(64 * NW, OCC) void fwd_small_kernel(const FwdParams
     if (tid < 64) found = alone_record(p, place / units_per_tile, reinterpret_cast<i32x4*>(smem), s_rec);
     uq.init_alone(units_per_tile, place % units_per_tile, found, &s_next_unit);
   } else {
-    if (p.either && p.hdr->path == 0) return;
     uq.init_dealt(p.hdr, p.tiles, xcd, units_per_tile, per_xcd ? blockIdx.x / kNumXcd : blockIdx.x, per_xcd ? gridDim.x / kNumXcd : gridDim.x, p.tile_cap,
                   &s_next_unit, s_rec);
   }

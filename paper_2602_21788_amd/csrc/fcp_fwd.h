@@ -22,7 +22,6 @@ struct FwdParams {
   int32_t head_pair;  // 1: a unit is a tile for TWO heads of one KV head; 0: a tile of twice the rows for one head
   int32_t tile_cap;   // tiles that the list has room for
   float scale_log2;   // softmax_scale * log2(e)
-  int32_t either;     // the list decided between the wide form and that of short documents (its header's path word): the other's launch has nothing to do
   // A launch without a list (fwd_alone in csrc/fcp_sizes.h): block b < unit_blocks finds unit b by itself, the blocks behind them classify the rows.
   int32_t unit_blocks;      // 0: the list tells
   int32_t tile;             // query rows per tile

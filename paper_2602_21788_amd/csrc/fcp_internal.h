@@ -52,7 +52,6 @@ static_assert(sizeof(SchedHeader) == kSchedHeaderBytes, "header size");
 constexpr int32_t kPathOnePass = 1;     // one pass over key tiles (csrc/fcp_attn_bwd_fused.hip, csrc/fcp_attn_bwd_short.hip)
 constexpr int32_t kPathSplitKeys = 2;   // key tiles in pieces of rows
 constexpr int32_t kPathSplitRows = 4;   // query tiles in pieces of keys
-constexpr int32_t kPathShortForm = 1;   // forward: the list decided for the form of short documents
 
 // One schedulable tile, fully resolved by the scheduler so that an attention kernel needs a
 // single 64-byte read per unit (no dependent loads of work item and cu_seqlens).
@@ -107,9 +106,6 @@ inline const Tile* sched_tiles(const void* region, int64_t n_work) {
 static_assert(kBwdBN == 4 * 32, "KTile keeps four key groups");
 
 struct RowStates;   // direct modes, see below
-// What the forward's list needs to know beside its tiles: whether items may be joined, query heads, CUs, and the tile of the form for short documents, where the
-// list decides between that and the wide one (0: the caller has decided).
-struct ForwardList { bool join; int32_t heads, n_cu, tile_short; };
 // Splitting of the backward's tiles on small problems (csrc/fcp_sched.hip): query heads per KV head, units per key tile and per query tile, CUs, least
 // piece in 32-row blocks (of all heads together) and in 32-key blocks; numbers that the turn words have room for; blocks of the attention kernel per CU; whether tiles may be split.
 struct SplitTiles { int32_t group, kv_units, q_units, n_cu, min_steps, key_turns, row_turns, blocks_per_cu; bool cuts; bool many_short; };
@@ -125,7 +121,7 @@ int launch_schedule(bool key_tiles, int32_t tile, int32_t inner, int64_t kv_row_
                     const fcp_work_desc* work, int64_t n_work,
                     const int32_t* cu_seqlens_kv, int32_t n_seqs, int32_t tq, int32_t tkv,
                     int32_t n_parts, int64_t tile_cap, void* region, float* lse_fill,
-                    int64_t lse_fill_n, hipStream_t stream, const RowStates* states = nullptr, const ForwardList& fwd = {});
+                    int64_t lse_fill_n, hipStream_t stream, const RowStates* states = nullptr);
 
 // Everything that precedes the backward's attention kernels in one launch: both tile lists (key tiles of kBwdBN
 // keys in region_kv, query tiles of dq_tile rows in region_q) and the row statistics (stats: two planes of n_stats
@@ -151,6 +147,7 @@ struct RowStates {
   int32_t q_row_elems, kv_row_elems;
   int32_t n_parts;
   bool check_step;
+  int32_t join_heads, n_cu;   // forward: see ListArgs
   void* o_none;          // forward with one partial slot: state 1 does not occur, and the results of rows of state 0 are written here (O [tq,hq,D], LSE [hq,tq])
   float* lse_none;
   int32_t hq;

@@ -44,8 +44,7 @@ struct ListArgs {                   // what a list is built from
   const int32_t* cu;
   int32_t n_work, n_seqs, tq, tkv, n_parts, max_seg_keys;
   bool check_step;
-  bool join;                        // forward: items may be joined (join_items)
-  int32_t heads, n_cu;              // forward: query heads and CUs
+  int32_t join_heads, n_cu;         // join_items: query heads (0: items stay as they are) and CUs
 };
 __device__ inline Item load_item(const ListArgs& a, const MaskTables& m, int32_t i) {
   const fcp_work_desc w = a.work[i];

@@ -407,13 +407,6 @@ struct SortArea {
   uint64_t wmax[kSchedThreads / 64];
 };
 
-// Rows of an item times the steps (64 keys) of its first and of its last row: twice the steps of all (causal; what a mask adds does not matter here).
-__device__ inline int64_t row_steps(const Item& it) {
-  const int32_t last = ceil_div(it.vis0, kFwdBN) + ceil_div(it.vis1, kFwdBN);
-  const int32_t first = ceil_div(seen_keys(it, 0, it.q_pos), kFwdBN) + (it.n1 > 0 ? ceil_div(seen_keys(it, 1, it.q_pos), kFwdBN) : 0);
-  return (int64_t)it.q_len * (first + last);
-}
-
 // Joined items (direct forward).  In a sharded list a query chunk has one item per ring step, so that its rows would be the sum of several units, through partial results
 // and a merge.  The call brings all steps, and the keys of a chunk over all of them are one run of the pool: items of the same query rows whose key segments are one run,
 // without gap or overlap, become one item (the first of them).  Its rows then have one unit, which writes their final result.
@@ -436,7 +429,11 @@ __device__ inline void join_items(const ListArgs& args, ItemSlot* s_item, int32_
   }
   if (tid == 0) s_steps = 0;
   __syncthreads();
-  if (tid < n_work && mine.seq >= 0) atomicAdd(&s_steps, (unsigned long long)row_steps(mine));
+  if (tid < n_work && mine.seq >= 0) {            // rows times the average of the first and the last row's steps (causal; what a mask adds does not matter here)
+    const int32_t last = ceil_div(mine.vis0, kFwdBN) + ceil_div(mine.vis1, kFwdBN);
+    const int32_t first = ceil_div(seen_keys(mine, 0, mine.q_pos), kFwdBN) + (mine.n1 > 0 ? ceil_div(seen_keys(mine, 1, mine.q_pos), kFwdBN) : 0);
+    atomicAdd(&s_steps, (unsigned long long)((int64_t)mine.q_len * (first + last)));
+  }
   {
     // thread = (item, share of the others), as in exclusive_flags_all
     int32_t p = 1;
@@ -463,7 +460,7 @@ __device__ inline void join_items(const ListArgs& args, ItemSlot* s_item, int32_
   const bool live = tid < n_work && mine.seq >= 0;
   if (live && s_lost[tid]) atomicOr(&s_lost[s_leader[tid]], 1);
   __syncthreads();
-  const float share = 0.5f * (float)s_steps * args.heads / (256.f * args.n_cu);
+  const float share = 0.5f * (float)s_steps * args.join_heads / (256.f * args.n_cu);
   const bool join = live && !s_lost[s_leader[tid]] && s_total[tid] > (uint32_t)mine.n0 && (uint32_t)(s_hi[tid] - s_lo[tid]) == s_total[tid] &&
                     s_total[tid] <= (uint32_t)args.max_seg_keys && (float)s_seen[tid] <= kJoinLoop * kFwdBN * share;
   if (join) {
@@ -478,28 +475,6 @@ __device__ inline void join_items(const ListArgs& args, ItemSlot* s_item, int32_
   if (__syncthreads_or(join)) exclusive_flags_all(s_item, n_work, area->key, area->wmax, s_fl);
 }
 
-// The forward's wide form or that of short documents (three blocks of four waves per CU), where the mean length leaves it open (fwd_either in csrc/fcp_sizes.h): short where a
-// row has up to 1300 keys on average and the longest loop is no longer than a CU's share.  Wide / short, us (keys a row, longest loop over share), 32 heads on 8
-// unless said otherwise: 16384 tokens in 16 sequences 246 / 216 (660, 0.4), 40 of 1000 548 / 502 (630, 0.2), 30 of 1400 611 / 570 (830, 0.2), 32768 in 24 over 2 ranks
-// 578 / 553 (1160, 0.3), 30 of 1000, 8 heads 100 / 91 (590, 0.9); 12000 over 3 ranks and 16 of 1000 516 / 546 (1900, 0.8), 8000 and 16 of 1000 over 2, 10 heads on 2
-// 589 / 748 (4400, 1.2), 65536 tokens, one of 44814, 40 heads on 8 3230 / 3334 (6100, 0.4).
-// Called by every thread of the block with its item.
-constexpr int kShortKeys = 1300;
-__device__ inline bool short_form_pays(const ListArgs& args, const Item& mine) {
-  __shared__ unsigned long long s_steps, s_rows;
-  __shared__ int32_t s_top;
-  if (threadIdx.x == 0) { s_steps = s_rows = 0; s_top = 0; }
-  __syncthreads();
-  if ((int32_t)threadIdx.x < args.n_work && mine.seq >= 0) {
-    atomicAdd(&s_steps, (unsigned long long)row_steps(mine));
-    atomicAdd(&s_rows, (unsigned long long)mine.q_len);
-    atomicMax(&s_top, ceil_div(mine.vis0, kFwdBN) + ceil_div(mine.vis1, kFwdBN));
-  }
-  __syncthreads();
-  const float steps = 0.5f * (float)s_steps;
-  return steps * kFwdBN <= (float)kShortKeys * (float)s_rows && (float)s_top <= steps * args.heads / (256.f * args.n_cu);
-}
-
 // One tile list, built by one block.
 template <ListMode Mode, bool ManyShort = false, bool Join = false>
 __device__ void build_list(
@@ -510,8 +485,7 @@ __device__ void build_list(
     int32_t* chain,                      // kChained: the tiles' chain records
     const SplitArgs& sargs,              // kSplit
     bool stable,                         // tiles of one bucket in the order of their numbers (chains and pieces always)
-    Item mine,                           // staged lists: the thread's item, or a rejected one
-    int32_t tile_short = 0) {            // forward: the tile of the other form, if the list decides
+    Item mine) {                         // staged lists: the thread's item, or a rejected one
   __shared__ int32_t s_wave[kSchedThreads / 64];
   __shared__ int32_t s_max, s_rej, s_taken;
   constexpr bool Chain = Mode == kChained;
@@ -528,11 +502,7 @@ __device__ void build_list(
   __syncthreads();                                 // (for every list: the other waves add to s_max and s_rej below)
   if (staged) {
     const bool in_order = exclusive_flags_all(s_item, n_work, area->key, area->wmax, s_fl);
-    if (Join && !in_order && args.join && n_work <= kSmallList) join_items(args, s_item, s_fl, area, mine);
-    if (Join && tile_short > 0 && short_form_pays(args, mine)) {
-      tile = tile_short;
-      path = kPathShortForm;
-    }
+    if (Join && !in_order && args.join_heads > 0 && n_work <= kSmallList) join_items(args, s_item, s_fl, area, mine);
     if constexpr (Mode == kSplit) {
       split = split_sizes(sargs, m, mine, tid < n_work ? s_fl[tid] : 0, n_work);
       cut = (backward ? split.rows : split.keys) < 32 * kNoPieces;
@@ -910,7 +880,7 @@ __device__ void row_states(int first, int count, const RowStateJob& job, const L
   if (tid < n_work) put_item(s_item[tid], item);
   __syncthreads();
   const bool in_order = exclusive_flags_all(s_item, n_work, area->key, area->wmax, s_fl);
-  if (Join && !in_order && args.join && n_work <= kSmallList) {
+  if (Join && !in_order && args.join_heads > 0 && n_work <= kSmallList) {
     join_items(args, s_item, s_fl, area, item);
     if (tid < n_work && item.seq < 0) s_item[tid][2] = 0;    // (its rows are another item's)
   }
@@ -1070,13 +1040,13 @@ struct ListJob {
 // the blocks after those classify the rows (direct mode).
 __global__ __launch_bounds__(kSchedThreads) void sched_kernel(
     int backward, const ListJob j, const ListArgs args, const MaskTables m,
-    float* lse_fill, int64_t lse_fill_n, int fill_blocks, const RowStateJob states, int32_t tile_short) {
+    float* lse_fill, int64_t lse_fill_n, int fill_blocks, const RowStateJob states) {
   __shared__ ItemSlot s_item[kMaxExclusiveScan];
   __shared__ int32_t s_fl[kMaxExclusiveScan];
   __shared__ SortArea s_area;
   const int b = blockIdx.x;
   if (b == 0) {
-    build_list<kWhole, false, true>(backward != 0, j.tile, j.inner, args, m, j.tile_cap, j.hdr, j.item_off, j.tiles, s_item, &s_area, s_fl, nullptr, SplitArgs{}, false, my_item(args, m), tile_short);
+    build_list<kWhole, false, true>(backward != 0, j.tile, j.inner, args, m, j.tile_cap, j.hdr, j.item_off, j.tiles, s_item, &s_area, s_fl, nullptr, SplitArgs{}, false, my_item(args, m));
   } else if (b <= fill_blocks) {
     const int64_t stride = (int64_t)fill_blocks * kSchedThreads;
     for (int64_t i = (int64_t)(b - 1) * kSchedThreads + threadIdx.x; i < lse_fill_n; i += stride)
@@ -1158,8 +1128,8 @@ static RowStateJob make_job(const RowStates* rs) {
 }
 
 static ListArgs list_args(int64_t kv_row_bytes, const fcp_work_desc* work, int64_t n_work, const int32_t* cu, int32_t n_seqs, int32_t tq,
-                          int32_t tkv, int32_t n_parts, bool check_step, const ForwardList& fwd = {}) {
-  return {work, cu, (int32_t)n_work, n_seqs, tq, tkv, n_parts, max_segment_keys(kv_row_bytes), check_step, fwd.join, fwd.heads, fwd.n_cu};
+                          int32_t tkv, int32_t n_parts, bool check_step, int32_t join_heads = 0, int32_t n_cu = 0) {
+  return {work, cu, (int32_t)n_work, n_seqs, tq, tkv, n_parts, max_segment_keys(kv_row_bytes), check_step, join_heads, n_cu};
 }
 static ListJob list_job(void* region, int64_t n_work, int32_t tile, int32_t inner, int64_t cap) {
   return {tile, inner, (int32_t)cap, reinterpret_cast<SchedHeader*>(region),
@@ -1189,7 +1159,7 @@ int launch_schedule(bool backward, int32_t tile, int32_t inner, int64_t kv_row_b
                     const fcp_work_desc* work, int64_t n_work,
                     const int32_t* cu_seqlens_kv, int32_t n_seqs, int32_t tq, int32_t tkv,
                     int32_t n_parts, int64_t tile_cap, void* region, float* lse_fill,
-                    int64_t lse_fill_n, hipStream_t stream, const RowStates* states, const ForwardList& fwd) {
+                    int64_t lse_fill_n, hipStream_t stream, const RowStates* states) {
   if (states) { const int rcs = check_row_states(n_work); if (rcs != FCP_OK) return rcs; }
   int fill_blocks = 0;
   if (lse_fill && lse_fill_n > 0) {
@@ -1200,8 +1170,9 @@ int launch_schedule(bool backward, int32_t tile, int32_t inner, int64_t kv_row_b
   const int state_blocks = states ? row_state_blocks(tq, states->kv_state ? tkv : 0) : 0;
   hipLaunchKernelGGL(sched_kernel, dim3(1 + fill_blocks + state_blocks), dim3(kSchedThreads), 0, stream,
                      backward ? 1 : 0, list_job(region, n_work, tile, inner, tile_cap),
-                     list_args(kv_row_bytes, work, n_work, cu_seqlens_kv, n_seqs, tq, tkv, n_parts, lse_fill != nullptr || states != nullptr, fwd),
-                     MaskTables{q_limit, k_from}, lse_fill, lse_fill_n, fill_blocks, make_job(states), fwd.tile_short);
+                     list_args(kv_row_bytes, work, n_work, cu_seqlens_kv, n_seqs, tq, tkv, n_parts, lse_fill != nullptr || states != nullptr,
+                               states ? states->join_heads : 0, states ? states->n_cu : 0),
+                     MaskTables{q_limit, k_from}, lse_fill, lse_fill_n, fill_blocks, make_job(states));
   FCP_HIP_CHECK(hipGetLastError());
   return FCP_OK;
 }

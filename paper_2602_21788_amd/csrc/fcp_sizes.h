@@ -149,28 +149,15 @@ inline FwdForm fwd_form(int head_dim, int hq, int64_t tq, int64_t tkv, int64_t n
 // The form and its list: two heads of one KV head per unit when the heads pair up (and a unit has rows for two), else twice the rows for one head.
 // The list has to fit `area` bytes.  Where that of the form's tiles does not (the static work area is checked for tiles of 128 rows), units
 // of 128 rows of one head take their place, whose tiles are the largest that every head layout and both widths have.
-// Mean rows per item up to which the list decides (on the device, which sees the lengths: short_form_pays in csrc/fcp_sched.hip) whether the wide form or that of
-// short documents works it; both are launched and one ends at once (3 to 8 us with the decision).  Above, the longer ones of the list take most of the time and the wide form is
-// the faster one or as fast (10 sequences of 2000, 32 heads on 8, 373 / 361 us, 4 of 4000 516 / 522); with fewer units of 128 rows per CU than 12 the launch
-// costs what the form gains (5746 tokens in 5 sequences, 40 heads on 8, decided by the host / by the list 145 / 152, 40057 in 47 over 7 ranks, 6 on 2, 203 / 209).
-constexpr int kEitherRows = 1500, kEitherUnits = 12;
-// (tile_short: its tile, 0 where the host decides)
-struct FwdPlan { FwdForm form; int32_t head_pair, tile; int64_t cap; int32_t tile_short; };
+struct FwdPlan { FwdForm form; int32_t head_pair, tile; int64_t cap; };
 inline FwdPlan fwd_plan(int head_dim, int hq, int hkv, int32_t tq, int32_t tkv, int64_t n_work, int32_t n_parts, int n_cu, size_t area) {
   auto with = [&](FwdForm f, bool pair) {
     const int rows = fwd_unit_rows(f, head_dim);
     const int32_t tile = pair ? rows / 2 : rows;
-    return FwdPlan{f, pair ? 1 : 0, tile, q_tile_cap(tq, tkv, n_work, n_parts, tile), 0};
+    return FwdPlan{f, pair ? 1 : 0, tile, q_tile_cap(tq, tkv, n_work, n_parts, tile)};
   };
   const FwdForm form = fwd_form(head_dim, hq, tq, tkv, n_work, n_parts, n_cu);
   const FwdPlan p = with(form, (hq / hkv) % 2 == 0 && fwd_unit_rows(form, head_dim) > 32);
-  const int64_t rows = std::min((int64_t)n_parts * tq, (int64_t)tkv);
-  if (p.form == kFwdWide && n_work <= 1024 && rows <= kEitherRows * n_work && (rows / 128 + n_work) * hq >= kEitherUnits * (int64_t)n_cu) {
-    FwdPlan either = p;
-    either.tile_short = p.tile / 2;
-    either.cap = q_tile_cap(tq, tkv, n_work, n_parts, either.tile_short);
-    if (either.cap <= kMaxTiles && sched_region_bytes(n_work, either.cap) <= area) return either;
-  }
   if (p.cap <= kMaxTiles && sched_region_bytes(n_work, p.cap) <= area) return p;
   return with(kFwdSmall, false);
 }
