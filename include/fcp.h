@@ -165,8 +165,7 @@ int fcp_lse_merge(const float* o_part, const float* lse_part, int32_t n_parts, i
  * carries ALL ring steps.  Rows that get all their keys from one work item (every sequence that is not sharded,
  * paper Sec. 4.1; no other item of the call covers the item's query rows) need no partial result and no merge
  * (Sec. 3.2: the rescaling combines the steps of a ring): the kernel writes their normalised O as bf16 into o and
- * their LSE into lse.  So it does for rows of several items where it works these as one (items of the same rows whose key
- * segments are one run of the sequence).  The other rows get partial results in o_part / lse_part as in fcp_attn_fwd_step;
+ * their LSE into lse.  The other rows get partial results in o_part / lse_part as in fcp_attn_fwd_step;
  * fcp_lse_merge_direct merges those, gives rows that no item covers O = 0 and LSE = -inf, and leaves the directly
  * written rows alone.  The row states stay in `scratch` between the two calls.
  *   o [tq,hq,D] bf16, lse [hq,tq] fp32: device, complete after fcp_lse_merge_direct;  o_part / lse_part: defined only

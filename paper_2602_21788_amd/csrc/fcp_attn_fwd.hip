@@ -522,7 +522,6 @@ static int fwd_step(const void* q, const void* k, const void* v, const int32_t* 
     rs.q_state = fcp::fwd_q_state(scratch, n_work, tq, tkv, n_parts);
     rs.q_row_elems = hq * head_dim; rs.kv_row_elems = hkv * head_dim;
     rs.n_parts = n_parts; rs.check_step = true;
-    if (n_parts > 1) { rs.join_heads = hq; rs.n_cu = n_cu; }
     if (n_parts == 1) { rs.o_none = o_out; rs.lse_none = lse_out; rs.hq = hq; }
   }
   int64_t units = cap * (hq / (head_pair ? 2 : 1));
@@ -550,7 +549,7 @@ static int fwd_step(const void* q, const void* k, const void* v, const int32_t* 
 
   p.tile = tile;
   p.q_state = rs.q_state;
-  p.list = {work, cu_seqlens_kv, (int32_t)n_work, n_seqs, tq, tkv, n_parts, fcp::max_segment_keys((int64_t)hkv * head_dim * 2), !running, 0, 0};
+  p.list = {work, cu_seqlens_kv, (int32_t)n_work, n_seqs, tq, tkv, n_parts, fcp::max_segment_keys((int64_t)hkv * head_dim * 2), !running};
   if (form != fcp::kFwdWide) return fcp::launch_fwd_small(p, head_dim, form, units, alone, n_cu, st);
   const int64_t blocks = fcp::persistent_blocks(n_cu, units);   // one 512-thread block per CU
   static std::atomic<uint64_t> lds_done;

@@ -43,8 +43,7 @@ struct SchedHeader {
   int32_t path;                 // backward, key-tile list: how the call is worked (kPath* bits), for tests and profiles
   int32_t counter[kNumXcd];     // next unit per XCD (or counter[0] alone)
   int32_t n_stalled;            // backward, key-tile list: waits for another unit's turn that ran out (their rows are NaN)
-  int32_t n_taken_over;         // forward: tiles of items whose keys others have taken over: listed by the caller, not worked by themselves
-  int32_t pad[2];
+  int32_t pad[3];
   int32_t claimed[kNumXcd];     // one-pass backward: next unit of a queue that another XCD's blocks have claimed
   int32_t pad2[8];
 };                               // 128 bytes
@@ -147,7 +146,6 @@ struct RowStates {
   int32_t q_row_elems, kv_row_elems;
   int32_t n_parts;
   bool check_step;
-  int32_t join_heads, n_cu;   // forward: see ListArgs
   void* o_none;          // forward with one partial slot: state 1 does not occur, and the results of rows of state 0 are written here (O [tq,hq,D], LSE [hq,tq])
   float* lse_none;
   int32_t hq;

@@ -11,7 +11,7 @@ __device__ inline int32_t ceil_div(int32_t a, int32_t b) { return (a + b - 1) / 
 // is built of many short dependent steps, and trips to global memory for descriptor, cu_seqlens and mask in each of them
 // were most of its time.  (No arrays: indexed by a run-time segment number they would live in scratch memory.)
 struct Item {
-  int32_t seq;                      // -1: rejected, -2: another item has taken its keys over (join_items in csrc/fcp_sched.hip)
+  int32_t seq;                      // -1: rejected
   int32_t q_off, q_len, q_pos;      // query rows: first local row, count, position of the first
   int32_t k0, n0, k1, n1;           // key segments: position of the first key, keys (n1 = 0: one segment)
   int32_t base;                     // pool row of the sequence's first key
@@ -44,7 +44,6 @@ struct ListArgs {                   // what a list is built from
   const int32_t* cu;
   int32_t n_work, n_seqs, tq, tkv, n_parts, max_seg_keys;
   bool check_step;
-  int32_t join_heads, n_cu;         // join_items: query heads (0: items stay as they are) and CUs
 };
 __device__ inline Item load_item(const ListArgs& a, const MaskTables& m, int32_t i) {
   const fcp_work_desc w = a.work[i];

@@ -131,8 +131,7 @@ __device__ inline void block_running_max(uint64_t v0, uint64_t v1, uint64_t* s_w
 
 constexpr int kSmallList = 256;   // (all pairs take about 5 us there, the two sorts 25 at any length)
 
-// True: the list is in row order.
-__device__ inline bool exclusive_flags_all(const ItemSlot* item, int32_t n_work, uint64_t* key, uint64_t* s_wmax, int32_t* fl) {
+__device__ inline void exclusive_flags_all(const ItemSlot* item, int32_t n_work, uint64_t* key, uint64_t* s_wmax, int32_t* fl) {
   const int tid = threadIdx.x;
   constexpr uint64_t kNone = ~(uint64_t)0;
   constexpr int32_t kAll = kFlagQExclusive | kFlagSeg0Exclusive | kFlagSeg1Exclusive;
@@ -147,7 +146,7 @@ __device__ inline bool exclusive_flags_all(const ItemSlot* item, int32_t n_work,
       in_order &= a.q_off >= b.q_off + b.q_len && (a.seq > b.seq || (a.seq == b.seq && a.k0 >= (b.n1 > 0 ? b.k1 + b.n1 : b.k0 + b.n0)));
     }
   }
-  if (__syncthreads_and(in_order)) return true;
+  if (__syncthreads_and(in_order)) return;
   if (n_work <= kSmallList) {
     // thread = (item, share of the others); the lanes of a wave look at the same other item
     int32_t p = 1;
@@ -168,7 +167,7 @@ __device__ inline bool exclusive_flags_all(const ItemSlot* item, int32_t n_work,
       if (lost) atomicAnd(&fl[ia], ~lost);
     }
     __syncthreads();
-    return false;
+    return;
   }
   // ---- query rows: key = start << 11 | item
   int32_t np = 2;
@@ -233,7 +232,6 @@ __device__ inline bool exclusive_flags_all(const ItemSlot* item, int32_t n_work,
     test(k1, v1, q1, st1, sl1, b1, k2);
   }
   __syncthreads();
-  return false;
 }
 
 // What the key-tile and query-tile lists of a backward are like: one unit per tile; the chains of the one-pass kernel; tiles split where
@@ -407,76 +405,8 @@ struct SortArea {
   uint64_t wmax[kSchedThreads / 64];
 };
 
-// Joined items (direct forward).  In a sharded list a query chunk has one item per ring step, so that its rows would be the sum of several units, through partial results
-// and a merge.  The call brings all steps, and the keys of a chunk over all of them are one run of the pool: items of the same query rows whose key segments are one run,
-// without gap or overlap, become one item (the first of them).  Its rows then have one unit, which writes their final result.
-// Not where the loop over all those keys would be longer than kJoinLoop times a CU's share of all steps (256 rows and heads by 64 keys): there the longest
-// loop, not the sum of the work, would set the time.  The two calls of the direct forward, as listed / joined, us (loop over share): 32 heads on 8: 16000 tokens over 4 ranks 547 / 464
-// (0.7), 8000 over 2 307 / 269 (0.8), 8000 over 3 226 / 195 (1.3), 48000 over 6 2870 / 2601, 12000 over 3 and 16 sequences of 1000 567 / 514; all of them joined: 16000 over 8 313 / 316
-// (1.7), 24000 over 3 and 20 of 800, 8 heads, 437 / 527 (1.9), 8000 over 2 and 16 of 1000, 10 heads on 2, 152 / 201 (2.2).  Joining takes the scheduling launch 4 us.
-// Called by every thread of the block with its item, which it gives back; the flags are known.  Every block that asks gets the same answer.
-constexpr float kJoinLoop = 1.3f;
-__device__ inline void join_items(const ListArgs& args, ItemSlot* s_item, int32_t* s_fl, SortArea* area, Item& mine) {
-  __shared__ int32_t s_leader[kSmallList], s_lo[kSmallList], s_hi[kSmallList], s_lost[kSmallList];
-  __shared__ uint32_t s_total[kSmallList], s_seen[kSmallList];
-  __shared__ unsigned long long s_steps;
-  const int tid = threadIdx.x;
-  const int32_t n_work = args.n_work;
-  if (tid < kSmallList) {
-    s_leader[tid] = s_lo[tid] = INT32_MAX;
-    s_hi[tid] = s_lost[tid] = 0;
-    s_total[tid] = s_seen[tid] = 0;
-  }
-  if (tid == 0) s_steps = 0;
-  __syncthreads();
-  if (tid < n_work && mine.seq >= 0) {            // rows times the average of the first and the last row's steps (causal; what a mask adds does not matter here)
-    const int32_t last = ceil_div(mine.vis0, kFwdBN) + ceil_div(mine.vis1, kFwdBN);
-    const int32_t first = ceil_div(seen_keys(mine, 0, mine.q_pos), kFwdBN) + (mine.n1 > 0 ? ceil_div(seen_keys(mine, 1, mine.q_pos), kFwdBN) : 0);
-    atomicAdd(&s_steps, (unsigned long long)((int64_t)mine.q_len * (first + last)));
-  }
-  {
-    // thread = (item, share of the others), as in exclusive_flags_all
-    int32_t p = 1;
-    while (p < n_work) p <<= 1;
-    const int32_t ia = tid & (p - 1), parts = kSchedThreads / p;
-    if (ia < n_work && s_item[ia][0] >= 0) {
-      const Item a = get_item(s_item[ia]);
-      for (int32_t ib = tid / p; ib < n_work; ib += parts) {
-        const Item b = get_item(s_item[ib]);
-        if (b.seq != a.seq || b.q_off != a.q_off || b.q_len != a.q_len || b.q_pos != a.q_pos) continue;
-        auto meets = [](int32_t k, int32_t n, int32_t ks, int32_t ns) { return n > 0 && ns > 0 && k < ks + ns && ks < k + n; };
-        atomicMin(&s_leader[ia], ib);
-        atomicMin(&s_lo[ia], b.n1 > 0 ? min(b.k0, b.k1) : b.k0);
-        atomicMax(&s_hi[ia], max(b.k0 + b.n0, b.k1 + b.n1));
-        atomicAdd(&s_total[ia], (uint32_t)b.n0 + (uint32_t)b.n1);
-        atomicAdd(&s_seen[ia], (uint32_t)b.vis0 + (uint32_t)b.vis1);
-        if (ia == ib ? meets(a.k0, a.n0, a.k1, a.n1)
-                     : meets(a.k0, a.n0, b.k0, b.n0) || meets(a.k0, a.n0, b.k1, b.n1) || meets(a.k1, a.n1, b.k0, b.n0) || meets(a.k1, a.n1, b.k1, b.n1))
-          atomicOr(&s_lost[ia], 1);
-      }
-    }
-  }
-  __syncthreads();
-  const bool live = tid < n_work && mine.seq >= 0;
-  if (live && s_lost[tid]) atomicOr(&s_lost[s_leader[tid]], 1);
-  __syncthreads();
-  const float share = 0.5f * (float)s_steps * args.join_heads / (256.f * args.n_cu);
-  const bool join = live && !s_lost[s_leader[tid]] && s_total[tid] > (uint32_t)mine.n0 && (uint32_t)(s_hi[tid] - s_lo[tid]) == s_total[tid] &&
-                    s_total[tid] <= (uint32_t)args.max_seg_keys && (float)s_seen[tid] <= kJoinLoop * kFwdBN * share;
-  if (join) {
-    if (s_leader[tid] == tid) {
-      mine.k0 = s_lo[tid]; mine.n0 = (int32_t)s_total[tid]; mine.vis0 = (int32_t)s_seen[tid];
-      mine.k1 = mine.n1 = mine.vis1 = 0;
-    } else {
-      mine.seq = -2;
-    }
-    put_item(s_item[tid], mine);
-  }
-  if (__syncthreads_or(join)) exclusive_flags_all(s_item, n_work, area->key, area->wmax, s_fl);
-}
-
 // One tile list, built by one block.
-template <ListMode Mode, bool ManyShort = false, bool Join = false>
+template <ListMode Mode, bool ManyShort = false>
 __device__ void build_list(
     bool backward, int32_t tile, int32_t inner, const ListArgs& args, const MaskTables& m,
     int32_t tile_cap, SchedHeader* hdr, int32_t* item_off, Tile* tiles,
@@ -485,9 +415,9 @@ __device__ void build_list(
     int32_t* chain,                      // kChained: the tiles' chain records
     const SplitArgs& sargs,              // kSplit
     bool stable,                         // tiles of one bucket in the order of their numbers (chains and pieces always)
-    Item mine) {                         // staged lists: the thread's item, or a rejected one
+    const Item& mine) {                  // staged lists: the thread's item, or a rejected one
   __shared__ int32_t s_wave[kSchedThreads / 64];
-  __shared__ int32_t s_max, s_rej, s_taken;
+  __shared__ int32_t s_max, s_rej;
   constexpr bool Chain = Mode == kChained;
   int32_t* const s_hist = area->later.hist;
   int32_t* const s_off = area->later.off;          // item_off for staged lists
@@ -497,12 +427,11 @@ __device__ void build_list(
   SplitSizes split{};
   bool cut = false;                                // tiles are split (the same for every thread)
   int32_t path = Mode == kChained ? kPathOnePass : 0;
-  if (tid == 0) s_max = s_rej = s_taken = 0;
+  if (tid == 0) { s_max = 0; s_rej = 0; }
   if (staged && tid < n_work) put_item(s_item[tid], mine);
   __syncthreads();                                 // (for every list: the other waves add to s_max and s_rej below)
   if (staged) {
-    const bool in_order = exclusive_flags_all(s_item, n_work, area->key, area->wmax, s_fl);
-    if (Join && !in_order && args.join_heads > 0 && n_work <= kSmallList) join_items(args, s_item, s_fl, area, mine);
+    exclusive_flags_all(s_item, n_work, area->key, area->wmax, s_fl);
     if constexpr (Mode == kSplit) {
       split = split_sizes(sargs, m, mine, tid < n_work ? s_fl[tid] : 0, n_work);
       cut = (backward ? split.rows : split.keys) < 32 * kNoPieces;
@@ -541,8 +470,7 @@ __device__ void build_list(
     if (i < n_work) {
       const Item it = staged ? mine : load_item(args, m, i);
       if (it.seq < 0) {
-        bad = it.seq == -1;
-        if (Join && it.seq == -2) atomicAdd(&s_taken, ceil_div(it.q_len, tile));
+        bad = 1;
       } else if (!backward) {
         cnt = ceil_div(it.q_len, tile);
         cost = ceil_div(it.vis0, inner) + ceil_div(it.vis1, inner);
@@ -842,8 +770,7 @@ __device__ void build_list(
     hdr->max_cost = s_max;
     hdr->path = path;
     hdr->n_stalled = 0;
-    hdr->n_taken_over = s_taken;
-    for (int c = 0; c < 2; ++c) hdr->pad[c] = 0;
+    for (int c = 0; c < 3; ++c) hdr->pad[c] = 0;
     for (int c = 0; c < kNumXcd; ++c) hdr->counter[c] = hdr->claimed[c] = 0;
   }
 }
@@ -866,9 +793,9 @@ struct RowStateJob {
 };
 // The blocks `first` .. `first + count - 1` of the launch share the rows; LDS arrays come from the kernel.  `split`: the rows of split tiles are
 // accumulated into.
-template <bool Split, bool Join = false>
+template <bool Split>
 __device__ void row_states(int first, int count, const RowStateJob& job, const ListArgs& args, const MaskTables& m, ItemSlot* s_item,
-                           int32_t* s_fl, SortArea* area, const SplitArgs& sargs, Item item) {
+                           int32_t* s_fl, SortArea* area, const SplitArgs& sargs, const Item& item) {
   uint8_t* __restrict__ q_state = job.q_state;
   uint8_t* __restrict__ kv_state = job.kv_state;
   float* __restrict__ dq_acc = job.dq_acc;
@@ -879,11 +806,7 @@ __device__ void row_states(int first, int count, const RowStateJob& job, const L
   const int tid = threadIdx.x, lane = tid & 63;
   if (tid < n_work) put_item(s_item[tid], item);
   __syncthreads();
-  const bool in_order = exclusive_flags_all(s_item, n_work, area->key, area->wmax, s_fl);
-  if (Join && !in_order && args.join_heads > 0 && n_work <= kSmallList) {
-    join_items(args, s_item, s_fl, area, item);
-    if (tid < n_work && item.seq < 0) s_item[tid][2] = 0;    // (its rows are another item's)
-  }
+  exclusive_flags_all(s_item, n_work, area->key, area->wmax, s_fl);
   SplitSizes split{};
   bool cut = false;
   if constexpr (Split) {
@@ -1046,13 +969,13 @@ __global__ __launch_bounds__(kSchedThreads) void sched_kernel(
   __shared__ SortArea s_area;
   const int b = blockIdx.x;
   if (b == 0) {
-    build_list<kWhole, false, true>(backward != 0, j.tile, j.inner, args, m, j.tile_cap, j.hdr, j.item_off, j.tiles, s_item, &s_area, s_fl, nullptr, SplitArgs{}, false, my_item(args, m));
+    build_list<kWhole>(backward != 0, j.tile, j.inner, args, m, j.tile_cap, j.hdr, j.item_off, j.tiles, s_item, &s_area, s_fl, nullptr, SplitArgs{}, false, my_item(args, m));
   } else if (b <= fill_blocks) {
     const int64_t stride = (int64_t)fill_blocks * kSchedThreads;
     for (int64_t i = (int64_t)(b - 1) * kSchedThreads + threadIdx.x; i < lse_fill_n; i += stride)
       lse_fill[i] = -INFINITY;
   } else {
-    row_states<false, true>(1 + fill_blocks, gridDim.x - 1 - fill_blocks, states, args, m, s_item, s_fl, &s_area, SplitArgs{}, my_item(args, m));
+    row_states<false>(1 + fill_blocks, gridDim.x - 1 - fill_blocks, states, args, m, s_item, s_fl, &s_area, SplitArgs{}, my_item(args, m));
   }
 }
 
@@ -1128,8 +1051,8 @@ static RowStateJob make_job(const RowStates* rs) {
 }
 
 static ListArgs list_args(int64_t kv_row_bytes, const fcp_work_desc* work, int64_t n_work, const int32_t* cu, int32_t n_seqs, int32_t tq,
-                          int32_t tkv, int32_t n_parts, bool check_step, int32_t join_heads = 0, int32_t n_cu = 0) {
-  return {work, cu, (int32_t)n_work, n_seqs, tq, tkv, n_parts, max_segment_keys(kv_row_bytes), check_step, join_heads, n_cu};
+                          int32_t tkv, int32_t n_parts, bool check_step) {
+  return {work, cu, (int32_t)n_work, n_seqs, tq, tkv, n_parts, max_segment_keys(kv_row_bytes), check_step};
 }
 static ListJob list_job(void* region, int64_t n_work, int32_t tile, int32_t inner, int64_t cap) {
   return {tile, inner, (int32_t)cap, reinterpret_cast<SchedHeader*>(region),
@@ -1170,8 +1093,7 @@ int launch_schedule(bool backward, int32_t tile, int32_t inner, int64_t kv_row_b
   const int state_blocks = states ? row_state_blocks(tq, states->kv_state ? tkv : 0) : 0;
   hipLaunchKernelGGL(sched_kernel, dim3(1 + fill_blocks + state_blocks), dim3(kSchedThreads), 0, stream,
                      backward ? 1 : 0, list_job(region, n_work, tile, inner, tile_cap),
-                     list_args(kv_row_bytes, work, n_work, cu_seqlens_kv, n_seqs, tq, tkv, n_parts, lse_fill != nullptr || states != nullptr,
-                               states ? states->join_heads : 0, states ? states->n_cu : 0),
+                     list_args(kv_row_bytes, work, n_work, cu_seqlens_kv, n_seqs, tq, tkv, n_parts, lse_fill != nullptr || states != nullptr),
                      MaskTables{q_limit, k_from}, lse_fill, lse_fill_n, fill_blocks, make_job(states));
   FCP_HIP_CHECK(hipGetLastError());
   return FCP_OK;
@@ -1222,7 +1144,7 @@ extern "C" int fcp_scratch_status(const void* scratch, void* stream, int32_t* n_
   fcp::SchedHeader h;
   FCP_HIP_CHECK(hipMemcpyAsync(&h, scratch, sizeof(h), hipMemcpyDeviceToHost, (hipStream_t)stream));
   FCP_HIP_CHECK(hipStreamSynchronize((hipStream_t)stream));
-  if (n_tiles) *n_tiles = h.n_tiles + h.n_taken_over;
+  if (n_tiles) *n_tiles = h.n_tiles;
   if (n_rejected) *n_rejected = h.n_rejected;
   if (h.n_stalled != 0)
     return fcp::fail(FCP_ERR_STALLED, "fcp_scratch_status: %d waits for another unit's turn ran out; the rows concerned are NaN", (int)h.n_stalled);
