@@ -54,21 +54,36 @@ __device__ inline Item lane_item(const FwdParams& p, int lane) {
   if (lane < p.list.n_work) it = load_item(p.list, MaskTables{p.q_limit, nullptr}, lane);
   return it;
 }
+// Tiles of the lane's item that the launch works.  It has blocks for tile_cap tiles; of a list with more of them, in the order of the list, the rest is dropped and
+// counted as rejected, as in a list.  `ahead`: tiles of the items that the list has before this one.
+__device__ inline int32_t alone_tiles(const FwdParams& p, int32_t tiles, int32_t ahead) { return min(tiles, max(p.tile_cap - ahead, 0)); }
 // One wave writes the record of the launch's tile `number`.  The items stand by the cost of their last tile, which sees the most keys, the tiles of an item from its end
 // on: long units begin first, and a short one beside each.  (In the order of the list 8000 tokens over 3 ranks, 8 heads, take 87 instead of 72 us.)
 __device__ inline bool alone_record(const FwdParams& p, int number, i32x4* s_lists, int32_t* s_rec) {
   const int lane = lane_id();
   const Item it = lane_item(p, lane);
-  const int32_t tiles = it.seq >= 0 ? ceil_div(it.q_len, p.tile) : 0, cost = ceil_div(it.vis0, kFwdBN) + ceil_div(it.vis1, kFwdBN);
+  const int32_t cost = ceil_div(it.vis0, kFwdBN) + ceil_div(it.vis1, kFwdBN);
   const int32_t key = min(cost, 1 << 24) * 64 + 63 - lane;    // (no two are alike)
-  int32_t before = 0;                               // tiles of the items that stand before the lane's
+  int32_t tiles = it.seq >= 0 ? ceil_div(it.q_len, p.tile) : 0;
+  int32_t before, ahead;                            // tiles of the items that stand before the lane's, by cost and in the list
   reinterpret_cast<int32_t*>(s_lists)[lane] = key;
-  reinterpret_cast<int32_t*>(s_lists)[64 + lane] = tiles;     // (none past the list's end)
+  auto count = [&]() {
+    before = ahead = 0;
+    reinterpret_cast<int32_t*>(s_lists)[64 + lane] = tiles;   // (none past the list's end)
 #pragma unroll 4
-  for (int j = 0; j < (p.list.n_work + 3) / 4; ++j) {
-    const i32x4 k = s_lists[j], n = s_lists[16 + j];
+    for (int j = 0; j < (p.list.n_work + 3) / 4; ++j) {
+      const i32x4 k = s_lists[j], n = s_lists[16 + j];
 #pragma unroll
-    for (int e = 0; e < 4; ++e) before += k[e] > key ? n[e] : 0;
+      for (int e = 0; e < 4; ++e) {
+        before += k[e] > key ? n[e] : 0;
+        ahead += 4 * j + e < lane ? n[e] : 0;
+      }
+    }
+  };
+  count();
+  if (__builtin_amdgcn_ballot_w64(ahead + tiles > p.tile_cap) != 0) {
+    tiles = alone_tiles(p, tiles, ahead);
+    count();
   }
   const uint64_t mine = __builtin_amdgcn_ballot_w64(number >= before && number < before + tiles);
   if (mine == 0) return false;
@@ -95,25 +110,28 @@ __device__ inline void alone_rows(const FwdParams& p, i32x4* s_lists) {
   s_lists += 64 * (threadIdx.x >> 6);
   const Item it = lane_item(p, lane);
   const int block = (int)blockIdx.x - p.unit_blocks;
+  const int32_t tiles = it.seq >= 0 ? ceil_div(it.q_len, p.tile) : 0;
   if (block == 0 && threadIdx.x < 64) {
-    int32_t n_tiles = it.seq >= 0 ? ceil_div(it.q_len, p.tile) : 0;
+    int32_t n_tiles = tiles;
     for (int off = 32; off > 0; off >>= 1) n_tiles += __shfl_xor(n_tiles, off, 64);
     const int n_bad = __builtin_popcountll(__builtin_amdgcn_ballot_w64(lane < n_work && it.seq < 0));
     if (lane < (int)(sizeof(SchedHeader) / 4))
-      reinterpret_cast<int32_t*>(p.hdr)[lane] = lane == 0 ? n_tiles : lane == 1 ? n_bad : 0;
+      reinterpret_cast<int32_t*>(p.hdr)[lane] = lane == 0 ? min(n_tiles, p.tile_cap) : lane == 1 ? n_bad + max(n_tiles - p.tile_cap, 0) : 0;
   }
   if (p.running) return;
   const int32_t row = block * (int)blockDim.x + (int)threadIdx.x;
   const int32_t len = it.seq >= 0 ? it.q_len : 0;
-  int32_t shared = 0, hits = 0, lost = 0;
+  int32_t shared = 0, ahead = 0, hits = 0, lost = 0;
   uint32_t slots = 0;
-  s_lists[lane] = i32x4{it.q_off, len, it.step & 31, 0};
+  s_lists[lane] = i32x4{it.q_off, len, it.step & 31, tiles};
 #pragma unroll 4
   for (int j = 0; j < n_work; ++j) {
     const i32x4 o = s_lists[j];
     shared |= j != lane && o[1] > 0 && it.q_off < o[0] + o[1] && o[0] < it.q_off + len;
+    ahead += j < lane ? o[3] : 0;
   }
-  s_lists[lane][3] = shared;
+  // (rows of dropped tiles are like rows that the item does not have)
+  s_lists[lane] = i32x4{it.q_off, min(len, alone_tiles(p, tiles, ahead) * p.tile), it.step & 31, shared};
 #pragma unroll 4
   for (int j = 0; j < n_work; ++j) {
     const i32x4 o = s_lists[j];

@@ -68,3 +68,71 @@ def test_without_a_list_and_with_one(lens, deg, rank, hq, hkv, D, spans, drop):
         assert not bool(o.isnan().any()) and float((o - o2).abs().max()) <= 2.0 ** -7 * float(o2.abs().max() + 1e-30), name
         if part is not None:
             assert torch.equal(part == float("-inf"), part2 == float("-inf")) and not bool(part.isnan().any())
+
+
+@pytest.mark.parametrize("hq,hkv,D,tq,tkv,items,tiles", [
+    # (item: rows from, rows, first key, keys, step).  Tiles of 128, 32 and 64 rows; the rows of all items together are more than the keys of the pool
+    (4, 4, 64, 512, 512, [(0, 512, 64 * s, 64, s) for s in range(8)], 12),            # the last five items have no tile
+    (2, 1, 64, 600, 1200, [(0, 600, 0, 100, 0), (100, 444, 100, 200, 1), (37, 500, 300, 30, 2)], 41),  # the third loses its end
+    (8, 4, 128, 700, 60, [(0, 700, 0, 60, 0)], 2),                                       # one slot
+])
+@pytest.mark.parametrize("how", ["direct", "partial", "running"])
+def test_more_tiles_than_the_list_bound(hq, hkv, D, tq, tkv, items, tiles, how):
+    """Tiles past the bound, in the order of the list, are not worked: they are counted as rejected and their rows have no result of that item."""
+    import torch
+    import paper_2602_21788_amd as fcp
+    B = fcp.binding
+    dev, n_parts = "cuda:0", 1 + max(s for *_, s in items)
+    if how == "running" and n_parts > 1:
+        items, n_parts = items[:1], 1                       # (one item per row and call)
+    g = torch.Generator().manual_seed(tq)
+    q = torch.randn(tq, hq, D, generator=g).to(torch.bfloat16)
+    k, v = (torch.randn(tkv, hkv, D, generator=g).to(torch.bfloat16) for _ in range(2))
+    work = np.zeros(len(items), B.WORK_DTYPE)
+    for w, (r, n, k0, kn, s) in zip(work, items):
+        w["q_local_off"], w["q_seq_start"], w["q_len"], w["n_seg"], w["step"] = r, r, n, 1, s
+        w["k_seq_start"][0], w["k_len"][0] = k0, kn
+    from host_rules import forward_plan, lib
+    tile, pair, cap, _ = forward_plan(D, hq, hkv, tq, tkv, len(items), n_parts, 1 << 40)
+    wanted = [-(-n // tile) for _, n, *_ in items]
+    assert lib().forward_alone(1, D, len(items), n_parts, cap * hq // (2 if pair else 1), 256)
+    if how != "running":
+        assert cap == tiles < sum(wanted)
+    # keys that each row sees, through the tiles within the bound
+    seen, left = np.zeros((n_parts, tq, tkv), bool), cap
+    for (r, n, k0, kn, s), t in zip(items, wanted):
+        n = min(n, max(left, 0) * tile)
+        left -= t
+        seen[s, r:r + n, k0:k0 + kn] = np.arange(k0, k0 + kn)[None] <= np.arange(r, r + n)[:, None]
+    G, scale = hq // hkv, 1 / np.sqrt(D)
+    sc = torch.stack([q[:, h].double() @ k[:, h // G].double().T.contiguous() for h in range(hq)]).numpy() * scale
+    def attend(mask):                                       # O [tq, hq, D], LSE [hq, tq]
+        with np.errstate(divide="ignore"):
+            p = np.where(mask[None], np.exp(sc), 0.)
+            lse = np.log(p.sum(-1))
+        w = p / np.maximum(p.sum(-1, keepdims=True), 1e-300)
+        return np.stack([w[h] @ v[:, h // G].double().numpy() for h in range(hq)], 1), lse
+    o_ref, lse_ref = attend(seen.any(0))
+    t = [x.to(dev) for x in (q, k, v)]
+    cu, work_d = torch.tensor([0, tkv], dtype=torch.int32, device=dev), torch.from_numpy(work.view(np.uint8).copy()).to(dev)
+    scratch = torch.full((B.fcp_scratch_bytes(B.FCP_SCRATCH_FWD, tq, tkv, hq, hkv, D, len(items), n_parts),), 0xAB, dtype=torch.uint8, device=dev)
+    o, lse = torch.full((tq, hq, D), float("nan"), device=dev, dtype=torch.bfloat16), torch.full((hq, tq), float("nan"), device=dev)
+    o_part, lse_part = torch.full((n_parts, tq, hq, D), float("nan"), device=dev), torch.full((n_parts, hq, tq), float("nan"), device=dev)
+    print(f"more tiles than the bound: {hq}/{hkv} heads of {D}, {tq} rows, {tkv} keys, {len(items)} items, {how}", flush=True)
+    if how == "direct":
+        B.fcp_attn_fwd_step_direct(*t, cu, work_d, n_parts, scale, o_part, lse_part, o, lse, scratch)
+        B.fcp_lse_merge_direct(o_part, lse_part, o, lse, tkv, scratch, len(items))
+    elif how == "partial":
+        B.fcp_attn_fwd_step(*t, cu, work_d, n_parts, scale, o_part, lse_part, scratch)
+        for s in range(n_parts):
+            assert torch.equal(lse_part[s].cpu() > float("-inf"), torch.from_numpy(attend(seen[s])[1]) > float("-inf")), s
+        B.fcp_lse_merge(o_part, lse_part, o, lse)
+    else:
+        o.zero_(); lse.fill_(float("-inf"))
+        B.fcp_attn_fwd_step_running(*t, cu, work_d, scale, o_part[0], lse, scratch, o_out=o)
+    torch.cuda.synchronize()
+    assert fcp.fcp_scratch_status(scratch) == (min(cap, sum(wanted)), max(sum(wanted) - cap, 0))
+    o, lse = o.double().cpu().numpy(), lse.double().cpu().numpy()
+    assert np.array_equal(np.isneginf(lse), np.isneginf(lse_ref)) and np.abs((lse - lse_ref)[lse_ref > -np.inf]).max() <= 1e-3
+    # (P and O are rounded to bf16: 2^-9 of the largest value each)
+    assert not np.isnan(o).any() and np.abs(o - o_ref).max() <= 2.0 ** -7 * np.abs(o_ref).max()
