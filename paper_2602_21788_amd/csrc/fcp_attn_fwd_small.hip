@@ -65,23 +65,22 @@ __device__ inline bool alone_record(const FwdParams& p, int number, i32x4* s_lis
   const int32_t cost = ceil_div(it.vis0, kFwdBN) + ceil_div(it.vis1, kFwdBN);
   const int32_t key = min(cost, 1 << 24) * 64 + 63 - lane;    // (no two are alike)
   int32_t tiles = it.seq >= 0 ? ceil_div(it.q_len, p.tile) : 0;
-  int32_t before, ahead;                            // tiles of the items that stand before the lane's, by cost and in the list
+  int32_t before;                                   // tiles of the items that stand before the lane's
   reinterpret_cast<int32_t*>(s_lists)[lane] = key;
   auto count = [&]() {
-    before = ahead = 0;
+    before = 0;
     reinterpret_cast<int32_t*>(s_lists)[64 + lane] = tiles;   // (none past the list's end)
 #pragma unroll 4
     for (int j = 0; j < (p.list.n_work + 3) / 4; ++j) {
       const i32x4 k = s_lists[j], n = s_lists[16 + j];
 #pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        before += k[e] > key ? n[e] : 0;
-        ahead += 4 * j + e < lane ? n[e] : 0;
-      }
+      for (int e = 0; e < 4; ++e) before += k[e] > key ? n[e] : 0;
     }
   };
   count();
-  if (__builtin_amdgcn_ballot_w64(ahead + tiles > p.tile_cap) != 0) {
+  if (__builtin_amdgcn_ballot_w64(before + tiles > p.tile_cap) != 0) {
+    int32_t ahead = 0;
+    for (int j = 0; j < lane; ++j) ahead += reinterpret_cast<const int32_t*>(s_lists)[64 + j];
     tiles = alone_tiles(p, tiles, ahead);
     count();
   }
