@@ -48,6 +48,8 @@ struct SmallCfg {
 };
 
 // ---- launches without a list (fwd_alone): one item per lane -------------------------------
+typedef int32_t __attribute__((may_alias)) i32_any;    // (the lists lie in the stages)
+typedef i32x4 __attribute__((may_alias)) i32x4_any;
 static_assert(kAloneItems == 64 && kAloneParts == 32, "a lane per item, a bit per slot");
 __device__ inline Item lane_item(const FwdParams& p, int lane) {
   Item it{-1, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0};
@@ -59,17 +61,18 @@ __device__ inline Item lane_item(const FwdParams& p, int lane) {
 __device__ inline int32_t alone_tiles(const FwdParams& p, int32_t tiles, int32_t ahead) { return min(tiles, max(p.tile_cap - ahead, 0)); }
 // One wave writes the record of the launch's tile `number`.  The items stand by the cost of their last tile, which sees the most keys, the tiles of an item from its end
 // on: long units begin first, and a short one beside each.  (In the order of the list 8000 tokens over 3 ranks, 8 heads, take 87 instead of 72 us.)
-__device__ inline bool alone_record(const FwdParams& p, int number, i32x4* s_lists, int32_t* s_rec) {
+__device__ inline bool alone_record(const FwdParams& p, int number, i32x4_any* s_lists, int32_t* s_rec) {
   const int lane = lane_id();
   const Item it = lane_item(p, lane);
   const int32_t cost = ceil_div(it.vis0, kFwdBN) + ceil_div(it.vis1, kFwdBN);
   const int32_t key = min(cost, 1 << 24) * 64 + 63 - lane;    // (no two are alike)
   int32_t tiles = it.seq >= 0 ? ceil_div(it.q_len, p.tile) : 0;
   int32_t before;                                   // tiles of the items that stand before the lane's
-  reinterpret_cast<int32_t*>(s_lists)[lane] = key;
+  reinterpret_cast<i32_any*>(s_lists)[lane] = key;
   auto count = [&]() {
     before = 0;
-    reinterpret_cast<int32_t*>(s_lists)[64 + lane] = tiles;   // (none past the list's end)
+    reinterpret_cast<i32_any*>(s_lists)[64 + lane] = tiles;   // (none past the list's end)
+    wave_exchange();
 #pragma unroll 4
     for (int j = 0; j < (p.list.n_work + 3) / 4; ++j) {
       const i32x4 k = s_lists[j], n = s_lists[16 + j];
@@ -80,8 +83,9 @@ __device__ inline bool alone_record(const FwdParams& p, int number, i32x4* s_lis
   count();
   if (__builtin_amdgcn_ballot_w64(before + tiles > p.tile_cap) != 0) {
     int32_t ahead = 0;
-    for (int j = 0; j < lane; ++j) ahead += reinterpret_cast<const int32_t*>(s_lists)[64 + j];
+    for (int j = 0; j < lane; ++j) ahead += reinterpret_cast<const i32_any*>(s_lists)[64 + j];
     tiles = alone_tiles(p, tiles, ahead);
+    wave_exchange();
     count();
   }
   const uint64_t mine = __builtin_amdgcn_ballot_w64(number >= before && number < before + tiles);
@@ -104,7 +108,7 @@ __device__ inline bool alone_record(const FwdParams& p, int number, i32x4* s_lis
 // What the scheduling launch does beside the list: the rows' states (direct mode), -inf in the partial slots of rows that no item covers there, O = 0 and
 // LSE = -inf of rows without an item where no merge follows, and the counts of the header.  A row per thread.
 template <int D>
-__device__ inline void alone_rows(const FwdParams& p, i32x4* s_lists) {
+__device__ inline void alone_rows(const FwdParams& p, i32x4_any* s_lists) {
   const int lane = lane_id(), n_work = p.list.n_work;
   s_lists += 64 * (threadIdx.x >> 6);
   const Item it = lane_item(p, lane);
@@ -123,14 +127,17 @@ __device__ inline void alone_rows(const FwdParams& p, i32x4* s_lists) {
   int32_t shared = 0, ahead = 0, hits = 0, lost = 0;
   uint32_t slots = 0;
   s_lists[lane] = i32x4{it.q_off, len, it.step & 31, tiles};
+  wave_exchange();
 #pragma unroll 4
   for (int j = 0; j < n_work; ++j) {
     const i32x4 o = s_lists[j];
     shared |= j != lane && o[1] > 0 && it.q_off < o[0] + o[1] && o[0] < it.q_off + len;
     ahead += j < lane ? o[3] : 0;
   }
+  wave_exchange();
   // (rows of dropped tiles are like rows that the item does not have)
   s_lists[lane] = i32x4{it.q_off, min(len, alone_tiles(p, tiles, ahead) * p.tile), it.step & 31, shared};
+  wave_exchange();
 #pragma unroll 4
   for (int j = 0; j < n_work; ++j) {
     const i32x4 o = s_lists[j];
@@ -183,10 +190,10 @@ __global__ __launch_bounds__(64 * NW, OCC) void fwd_small_kernel(const FwdParams
   const int units_per_tile = heads_here / hpu;
   UnitQueue uq;
   if (p.unit_blocks > 0) {
-    if ((int)blockIdx.x >= p.unit_blocks) return alone_rows<D>(p, reinterpret_cast<i32x4*>(smem));
+    if ((int)blockIdx.x >= p.unit_blocks) return alone_rows<D>(p, reinterpret_cast<i32x4_any*>(smem));
     const int place = per_xcd ? blockIdx.x / kNumXcd : blockIdx.x;
     bool found = false;
-    if (tid < 64) found = alone_record(p, place / units_per_tile, reinterpret_cast<i32x4*>(smem), s_rec);
+    if (tid < 64) found = alone_record(p, place / units_per_tile, reinterpret_cast<i32x4_any*>(smem), s_rec);
     uq.init_alone(units_per_tile, place % units_per_tile, found, &s_next_unit);
   } else {
     uq.init_dealt(p.hdr, p.tiles, xcd, units_per_tile, per_xcd ? blockIdx.x / kNumXcd : blockIdx.x, per_xcd ? gridDim.x / kNumXcd : gridDim.x, p.tile_cap,

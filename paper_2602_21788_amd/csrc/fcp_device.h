@@ -165,6 +165,13 @@ __device__ inline int fill_voff(int rpw, int wave, int i, int lane, int row_byte
 
 constexpr int kStreamed = 2;       // nt: the access is not expected to be repeated
 
+// Between a wave's LDS stores and its loads of what other lanes stored (or the other way round).  The hardware works them in order; this keeps the compiler to it.
+__device__ inline void wave_exchange() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
 // Wave-private LDS staging for writing a [32 rows x 2 D bytes] tile that the wave holds in the accumulator layout of
 // the 32 x 32 matrix instructions (lane = column inside a 32-column block, register i = row reg_row(i, lane / 32)).
 // Stored from that layout a wave-wide instruction carries 2 or 4 bytes per lane and the memory pipeline takes as long
@@ -200,9 +207,7 @@ struct RowStage {
     // the lane's addresses are formed here, after the unit's loop: values that the compiler can form ahead of the loop
     // would hold registers across it
     asm volatile("" : "+v"(lane));
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    wave_exchange();
     const int row = lane / CPR, chunk = lane % CPR;
     const int voff = row * row_bytes + 16 * chunk + soff0;
     u32x4 x[N];                                    // all chunks first: one LDS latency, not N
@@ -217,9 +222,7 @@ struct RowStage {
       // hazard, and the wait below does not depend on its table).
       asm volatile("s_nop 1" :: "v"(x[j]));
     }
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    wave_exchange();
   }
 };
 
