@@ -51,9 +51,10 @@ FCP_WIDE_LANES int best_fit(const int64_t* __restrict__ room, int n, int64_t s) 
     const int64_t r = room[g] < s ? INT64_MAX : room[g];
     least = r < least ? r : least;
   }
-  for (int g = 0; g < n; ++g)
-    if (room[g] == least) return least < s ? -1 : g;
-  return -1;
+  if (least == INT64_MAX) return -1;               // (a room is less than that: a sequence has been taken off it)
+  int g = 0;
+  while (room[g] != least) ++g;
+  return g;
 }
 
 // One degree of a group against adjacent rank counts: the least makespan so far and its degree.
