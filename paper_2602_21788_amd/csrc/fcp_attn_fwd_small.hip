@@ -118,8 +118,13 @@ __device__ inline void alone_rows(const FwdParams& p, i32x4_any* s_lists) {
     int32_t n_tiles = tiles;
     for (int off = 32; off > 0; off >>= 1) n_tiles += __shfl_xor(n_tiles, off, 64);
     const int n_bad = __builtin_popcountll(__builtin_amdgcn_ballot_w64(lane < n_work && it.seq < 0));
-    if (lane < (int)(sizeof(SchedHeader) / 4))
-      reinterpret_cast<int32_t*>(p.hdr)[lane] = lane == 0 ? min(n_tiles, p.tile_cap) : lane == 1 ? n_bad + max(n_tiles - p.tile_cap, 0) : 0;
+    if (lane == 0) {
+      SchedHeader h{};
+      h.n_tiles = min(n_tiles, p.tile_cap);
+      h.n_rejected = n_bad + max(n_tiles - p.tile_cap, 0);
+      h.path = kPathNoList;
+      *p.hdr = h;
+    }
   }
   if (p.running) return;
   const int32_t row = block * (int)blockDim.x + (int)threadIdx.x;

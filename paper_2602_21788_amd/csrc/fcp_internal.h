@@ -33,14 +33,15 @@ inline int raise_lds_limit(const void* kernel, int bytes, std::atomic<uint64_t>&
 }
 
 // ---- device-side schedule kept at the start of the caller's scratch buffer ----------
-// Both attention kernels are persistent: blocks pull (tile, head) units from counters
+// The attention kernels are persistent: blocks pull (tile, head) units from counters
 // until the list is exhausted.  There is one counter per XCD so that the blocks of one
 // XCD (blockIdx % 8) walk the heads of the same KV heads and share K/V in that XCD's L2.
+// (Not the forward's launches without a list, fwd_alone in csrc/fcp_sizes.h: they write the counts and the path only, no tiles, and have a block per unit.)
 struct SchedHeader {
   int32_t n_tiles;              // tiles in the list (sorted by decreasing cost)
-  int32_t n_rejected;           // work items that failed validation
+  int32_t n_rejected;           // work items that failed validation, and tiles past the list's room
   int32_t max_cost;
-  int32_t path;                 // backward, key-tile list: how the call is worked (kPath* bits), for tests and profiles
+  int32_t path;                 // backward, key-tile list, and forward: how the call is worked (kPath* bits), for tests and profiles
   int32_t counter[kNumXcd];     // next unit per XCD (or counter[0] alone)
   int32_t n_stalled;            // backward, key-tile list: waits for another unit's turn that ran out (their rows are NaN)
   int32_t pad[3];
@@ -51,6 +52,7 @@ static_assert(sizeof(SchedHeader) == kSchedHeaderBytes, "header size");
 constexpr int32_t kPathOnePass = 1;     // one pass over key tiles (csrc/fcp_attn_bwd_fused.hip, csrc/fcp_attn_bwd_short.hip)
 constexpr int32_t kPathSplitKeys = 2;   // key tiles in pieces of rows
 constexpr int32_t kPathSplitRows = 4;   // query tiles in pieces of keys
+constexpr int32_t kPathNoList = 8;      // forward without a list
 
 // One schedulable tile, fully resolved by the scheduler so that an attention kernel needs a
 // single 64-byte read per unit (no dependent loads of work item and cu_seqlens).

@@ -1,13 +1,22 @@
 """Forward launches without a list: their blocks find their units from the items themselves.  The same items among rejected ones, too many
-for that, go through the scheduler's list: the results are the same up to the order of the sums, in all forms, modes and edges of the rule."""
+for that, go through the scheduler's list: the results are the same up to the order of the sums, in all forms, modes and edges of the rule.  Which of the two
+a call went through is told by the path word of its header."""
 import numpy as np
 import pytest
 
 pytestmark = pytest.mark.gpu
 
 
+NO_LIST = 8
+
+
+def _path(scratch):
+    import torch
+    return int(scratch[:16].cpu().view(torch.int32)[3])
+
+
 def _passes(ra, work, torch, fcp):
-    """(rejected items, results) of every entry point with that work list, on poisoned buffers."""
+    """(results, rejected items, path word) of every entry point with that work list, on poisoned buffers."""
     ra.work_d, ra.n_work = torch.from_numpy(work.view(np.uint8).copy()).to(ra.device), len(work)
     nb = fcp.fcp_scratch_bytes(fcp.binding.FCP_SCRATCH_FWD, ra.tq, ra.tkv, ra.hq, ra.hkv, ra.D, len(work), ra.n_parts)
     ra.scratch_f = torch.full((nb,), 0xAB, dtype=torch.uint8, device=ra.device)
@@ -28,7 +37,7 @@ def _passes(ra, work, torch, fcp):
                 d = torch.from_numpy(np.ascontiguousarray(w).view(np.uint8).copy()).to(ra.device)
                 fcp.fcp_attn_fwd_step_running(ra.q, ra.k, ra.v, ra.cu_d, d, ra.scale, o_run, ra.lse, ra.scratch_f, o_out=ra.o, q_limit=ra.q_limit_d)
         torch.cuda.synchronize()
-        out[name] = (ra.o.float(), ra.lse.clone(), ra.lse_part.clone() if name == "partial" else None, fcp.fcp_scratch_status(ra.scratch_f)[1])
+        out[name] = (ra.o.float(), ra.lse.clone(), ra.lse_part.clone() if name == "partial" else None, fcp.fcp_scratch_status(ra.scratch_f)[1], _path(ra.scratch_f))
     return out
 
 
@@ -57,8 +66,9 @@ def test_without_a_list_and_with_one(lens, deg, rank, hq, hkv, D, spans, drop):
     many["seq"] = -1
     many = np.concatenate([many, work])
     alone, listed = _passes(ra, work, torch, fcp), _passes(ra, many, torch, fcp)
-    for name, (o, lse, part, rejected) in alone.items():
-        o2, lse2, part2, rejected2 = listed[name]
+    for name, (o, lse, part, rejected, path) in alone.items():
+        o2, lse2, part2, rejected2, path2 = listed[name]
+        assert path == NO_LIST and path2 == 0, name
         if name != "running":
             assert rejected == len(drop) and rejected2 == len(drop) + 70, name
         assert torch.equal(lse == float("-inf"), lse2 == float("-inf")), name
@@ -131,6 +141,7 @@ def test_more_tiles_than_the_list_bound(hq, hkv, D, tq, tkv, items, tiles, how):
         o.zero_(); lse.fill_(float("-inf"))
         B.fcp_attn_fwd_step_running(*t, cu, work_d, scale, o_part[0], lse, scratch, o_out=o)
     torch.cuda.synchronize()
+    assert _path(scratch) == NO_LIST
     assert fcp.fcp_scratch_status(scratch) == (min(cap, sum(wanted)), max(sum(wanted) - cap, 0))
     o, lse = o.double().cpu().numpy(), lse.double().cpu().numpy()
     fin = lse_ref > -np.inf

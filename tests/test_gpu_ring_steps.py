@@ -5,19 +5,21 @@ import pytest
 
 pytestmark = pytest.mark.gpu
 
+NO_LIST = 8          # path word of a launch without a list
 
-@pytest.mark.parametrize("lens,deg,rank,hq,hkv,D,spans,how", [
-    ([8000], 2, 1, 32, 8, 128, None, ""),
-    ([8000], 2, 1, 32, 8, 128, None, "shuffled"),
-    ([8000], 3, 2, 32, 8, 128, [(0, 2500, 400), (0, 5200, 577)], ""),
-    ([6000, 300, 2500, 41], 3, 0, 40, 8, 128, None, "shuffled"),
-    ([8003], 3, 1, 32, 8, 64, None, ""),
-    ([8000], 2, 1, 32, 8, 128, None, "gap"),                    # a key too few between two segments
-    ([8000], 2, 1, 32, 8, 128, None, "twice"),                  # a key in two items
-    ([12000], 4, 2, 8, 8, 128, None, ""),                       # few heads
-    ([2500], 3, 2, 8, 8, 128, None, "shuffled"),                # a launch without a list
+
+@pytest.mark.parametrize("lens,deg,rank,hq,hkv,D,spans,how,no_list", [
+    ([8000], 2, 1, 32, 8, 128, None, "", False),
+    ([8000], 2, 1, 32, 8, 128, None, "shuffled", False),
+    ([8000], 3, 2, 32, 8, 128, [(0, 2500, 400), (0, 5200, 577)], "", False),
+    ([6000, 300, 2500, 41], 3, 0, 40, 8, 128, None, "shuffled", False),
+    ([8003], 3, 1, 32, 8, 64, None, "", False),
+    ([8000], 2, 1, 32, 8, 128, None, "gap", False),                    # a key too few between two segments
+    ([8000], 2, 1, 32, 8, 128, None, "twice", False),                  # a key in two items
+    ([12000], 4, 2, 8, 8, 128, None, "", True),                        # few heads: a launch without a list
+    ([2500], 3, 2, 8, 8, 128, None, "shuffled", True),                 # the same
 ])
-def test_steps_have_their_own_results(lens, deg, rank, hq, hkv, D, spans, how):
+def test_steps_have_their_own_results(lens, deg, rank, hq, hkv, D, spans, how, no_list):
     import torch
     import paper_2602_21788_amd as fcp
     from paper_2602_21788_amd.rank import RankAttention
@@ -43,6 +45,7 @@ def test_steps_have_their_own_results(lens, deg, rank, hq, hkv, D, spans, how):
     ra.forward_direct()
     torch.cuda.synchronize()
     assert fcp.fcp_scratch_status(ra.scratch_f)[1] == 0
+    assert (int(ra.scratch_f[:16].cpu().view(torch.int32)[3]) == NO_LIST) == no_list
     assert torch.equal(ra.o, o) and torch.equal(ra.lse, lse)
     # rows of several items have the partial results of each
     n = np.zeros(ra.tq, int)
