@@ -515,8 +515,8 @@ static int fwd_step(const void* q, const void* k, const void* v, const int32_t* 
   const bool direct = lse_out != nullptr;
   // direct mode: which rows get their final result from one unit and which are merged from partials is worked out on
   // extra blocks of the scheduling launch.  With one partial slot no row is merged: a row has one item at most, whose unit writes its result, and
-  // these blocks write O = 0 and LSE = -inf of the others; fcp_lse_merge_direct then has nothing to do (one launch less and no partial LSE to fill: 16 sequences of
-  // 16384 tokens, 32 heads on 8, the two calls 233 -> 229 us, one of 512 tokens, 4 heads of 64 channels, 20.6 -> 16.9).
+  // these blocks write O = 0 and LSE = -inf of the others; fcp_lse_merge_direct then has nothing to do (one launch less and no partial LSE to fill: 16384 tokens in
+  // 16 sequences, 32 heads on 8, the two calls 233 -> 229 us, one of 512 tokens, 4 heads of 64 channels, 20.6 -> 16.9).
   fcp::RowStates rs{};
   if (direct) {
     rs.q_state = fcp::fwd_q_state(scratch, n_work, tq, tkv, n_parts);

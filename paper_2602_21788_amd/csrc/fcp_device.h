@@ -198,7 +198,7 @@ struct RowStage {
     *reinterpret_cast<u32_any*>(buf + at(row, 4 * col)) = __builtin_bit_cast(uint32_t, v);
   }
   // Final results leave as a stream (Stream): nothing in these kernels reads them again, and lines that they do not take stay with the keys and rows that are
-  // read again.  O and the gradients of the keys as a stream or not, us: forward of 16 sequences of 16384 tokens, 32 heads on 8 214 / 230; training pass of 1000 short sequences
+  // read again.  O and the gradients of the keys as a stream or not, us: forward of 16384 tokens in 16 sequences, 32 heads on 8 214 / 230; training pass of 1000 short sequences
   // 2285 / 2344, of 32768 packed tokens 2470 / 2488.  (Not partial sums, which are read soon, nor lines that are not written whole: dQ of the one-pass kernel +10 %.)
   // after the wave has written its staged rows: row r goes to byte offset r * row_bytes + soff0 of the resource
   // (rows past the resource's range are dropped)
