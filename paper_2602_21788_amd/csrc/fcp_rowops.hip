@@ -108,7 +108,7 @@ __global__ __launch_bounds__(256) void merge_direct_kernel(const float* __restri
   }
 }
 
-template <int D>
+template <int D, bool StreamDo>
 __global__ __launch_bounds__(256) void delta_kernel(const uint32_t* __restrict__ o,
                                                     const uint32_t* __restrict__ d_o, int tq, int hq,
                                                     float* __restrict__ delta) {
@@ -120,10 +120,11 @@ __global__ __launch_bounds__(256) void delta_kernel(const uint32_t* __restrict__
   float s = 0.f;
   if (row < tq) {
     const int64_t off = (((int64_t)row * hq + h) * D + c8 * 8) / 2;
-    // (Non-temporal: read once, they do not have to push what the caches hold, much of it still to be written back, out of them.  128000 rows of 32 heads
-    // 344 us, 6.1 TB/s, instead of 400, 25003 rows after another kernel's 512 MB of stores 77 instead of 122.)
+    // (Non-temporal: what is read once does not have to push what the caches hold, much of it still to be written back, out of them.  128000 rows of 32 heads
+    // 344 us, 6.1 TB/s, instead of 400, 25003 rows after another kernel's 512 MB of stores 77 instead of 122.  dO only where delta_streams_do says so.)
     const u32x4 a = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(o + off));
-    const u32x4 b = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(d_o + off));
+    const u32x4* const pb = reinterpret_cast<const u32x4*>(d_o + off);
+    const u32x4 b = StreamDo ? __builtin_nontemporal_load(pb) : *pb;
 #pragma unroll
     for (int i = 0; i < 4; ++i) s += bf16_lo(a[i]) * bf16_lo(b[i]) + bf16_hi(a[i]) * bf16_hi(b[i]);
   }
@@ -264,13 +265,11 @@ extern "C" int fcp_attn_bwd_delta(const void* o, const void* d_o, int32_t tq, in
   if (!aligned16(o) || !aligned16(d_o)) return fail(FCP_ERR_INVALID_ARG, "fcp_attn_bwd_delta: o/d_o must be 16-byte aligned");
   if (tq == 0) return FCP_OK;
   hipStream_t st = (hipStream_t)stream;
-  if (head_dim == 128) {
-    dim3 grid((tq + 15) / 16, hq);
-    hipLaunchKernelGGL(fcp::delta_kernel<128>, grid, dim3(256), 0, st, (const uint32_t*)o, (const uint32_t*)d_o, tq, hq, delta);
-  } else {
-    dim3 grid((tq + 31) / 32, hq);
-    hipLaunchKernelGGL(fcp::delta_kernel<64>, grid, dim3(256), 0, st, (const uint32_t*)o, (const uint32_t*)d_o, tq, hq, delta);
-  }
+  const bool streams = fcp::delta_streams_do(tq, hq, head_dim);
+  const auto kernel = head_dim == 128 ? (streams ? fcp::delta_kernel<128, true> : fcp::delta_kernel<128, false>)
+                                      : (streams ? fcp::delta_kernel<64, true> : fcp::delta_kernel<64, false>);
+  const int rows = 2048 / head_dim;
+  hipLaunchKernelGGL(kernel, dim3((tq + rows - 1) / rows, hq), dim3(256), 0, st, (const uint32_t*)o, (const uint32_t*)d_o, tq, hq, delta);
   FCP_HIP_CHECK(hipGetLastError());
   return FCP_OK;
 }

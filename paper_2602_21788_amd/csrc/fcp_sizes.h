@@ -191,6 +191,11 @@ inline size_t fwd_static_bytes(int32_t tq, int32_t tkv, int64_t n_work, int32_t 
 }
 
 // ---- the backward -----------------------------------------------------------------------
+// Does delta read dO as a stream, past the caches?  The attention kernel reads dO next.  Where the L2s (8 of 4 MB) can hold it, it is found there, and chains of short
+// sequences wait for nothing longer; larger ones would not be found anyway, and push other lines out.  Delta, lists and conversion, dO streamed / not, us: 6603 tokens in
+// 12 sequences, 8 heads on 8 (13.5 MB) 187 / 168, 4545 in 45, 32 on 8 (38 MB) 88 / 83; by bytes of dO, mean over calls of all kinds: 4 to 8 MB 1.003 / 0.995 of the time with
+// neither O nor dO streamed, 16 to 28 0.991 / 0.993, 40 to 48 0.983 / 0.991, 64 to 96 0.974 / 0.984.
+inline bool delta_streams_do(int32_t tq, int32_t hq, int32_t head_dim) { return 2 * (int64_t)tq * hq * head_dim > (int64_t)kNumXcd * 4 << 20; }
 inline bool one_pass_heads(int32_t hkv, int32_t head_dim) { return head_dim == 128 && hkv % kNumXcd == 0; }
 
 // One pass or two lists.  The one-pass kernel (csrc/fcp_attn_bwd_fused.hip) forms S and dP once and needs no query tiles; it has the
