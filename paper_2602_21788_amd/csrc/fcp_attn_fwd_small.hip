@@ -48,8 +48,7 @@ struct SmallCfg {
 };
 
 // ---- launches without a list (fwd_alone): one item per lane -------------------------------
-typedef int32_t __attribute__((may_alias)) i32_any;    // (the lists lie in the stages)
-typedef i32x4 __attribute__((may_alias)) i32x4_any;
+typedef i32x4 __attribute__((may_alias)) i32x4_any;    // (the rows' lists lie in the stages)
 static_assert(kAloneItems == 64 && kAloneParts == 32, "a lane per item, a bit per slot");
 __device__ inline Item lane_item(const FwdParams& p, int lane) {
   Item it{-1, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0};
@@ -59,42 +58,62 @@ __device__ inline Item lane_item(const FwdParams& p, int lane) {
 // Tiles of the lane's item that the launch works.  It has blocks for tile_cap tiles; of a list with more of them, in the order of the list, the rest is dropped and
 // counted as rejected, as in a list.  `ahead`: tiles of the items that the list has before this one.
 __device__ inline int32_t alone_tiles(const FwdParams& p, int32_t tiles, int32_t ahead) { return min(tiles, max(p.tile_cap - ahead, 0)); }
-// One wave writes the record of the launch's tile `number`.  The items stand by the cost of their last tile, which sees the most keys, the tiles of an item from its end
-// on: long units begin first, and a short one beside each.  (In the order of the list 8000 tokens over 3 ranks, 8 heads, take 87 instead of 72 us.)
-__device__ inline bool alone_record(const FwdParams& p, int number, i32x4_any* s_lists, int32_t* s_rec) {
-  const int lane = lane_id();
+// The block's record, of the launch's tile `number`.  Where more than one unit comes to a CU the tiles stand in the order of what they cost, so that the longest units
+// begin first and are spread over the CUs, and short ones lie beside them (AloneOrder in csrc/fcp_sizes.h, with times).  The order has to be every block's own and to need
+// no list: the costs of an item's tiles are taken as a line from its first tile (its rows' own positions, also under a mask) to its last, which tells how many of them cost
+// C or more.  A lane counts these for a C of its own over all items (the waves share long lists): the greatest C with more than `number` such tiles has the tile, among those
+// of that cost in the order of the items.
+// Every thread calls it; the answer (is there such a tile?) is wave 0's.
+constexpr int kShareItems = 8;
+template <int NW>
+__device__ inline bool alone_record(const FwdParams& p, int number, float (*s_sums)[64], int32_t* s_rec) {
+  const int lane = lane_id(), wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+  const int waves = p.order != kInListOrder && p.list.n_work > kShareItems ? NW : 1;
+  if (wave >= waves) return true;
   const Item it = lane_item(p, lane);
-  const int32_t cost = ceil_div(it.vis0, kFwdBN) + ceil_div(it.vis1, kFwdBN);
-  const int32_t key = min(cost, 1 << 24) * 64 + 63 - lane;    // (no two are alike)
   int32_t tiles = it.seq >= 0 ? ceil_div(it.q_len, p.tile) : 0;
-  int32_t before;                                   // tiles of the items that stand before the lane's
-  reinterpret_cast<i32_any*>(s_lists)[lane] = key;
-  auto count = [&]() {
-    before = 0;
-    reinterpret_cast<i32_any*>(s_lists)[64 + lane] = tiles;   // (none past the list's end)
-    wave_exchange();
+  const int32_t upto = wave_prefix_sum(tiles), ahead = upto - tiles;
+  if (number >= min(__builtin_amdgcn_readlane(upto, 63), p.tile_cap)) return false;
+  tiles = alone_tiles(p, tiles, ahead);
+  int32_t place = number - ahead, here = tiles, above = 0;    // the item's tiles from its end on: those in front, those among which `place` is
+  if (p.order != kInListOrder) {
+    const int32_t last = ceil_div(it.vis0, kFwdBN) + ceil_div(it.vis1, kFwdBN);
+    const int64_t limit = (int64_t)it.q_pos + p.tile - 1;
+    const int32_t first = ceil_div(seen_keys(it, 0, limit), kFwdBN) + (it.n1 > 0 ? ceil_div(seen_keys(it, 1, limit), kFwdBN) : 0);
+    const bool rises = p.order == kByTiles && tiles > 1 && last > first;
+    const float n = (float)tiles, per_step = rises ? (n - 1.f) / (float)(last - first) : n, from = (float)(rises ? first : last) * per_step;
+    // (C = 0: all of the item.  Past its last tile's cost: none, as the product's rounding is far less than a step's share.)
+    auto count = [](float c, float n, float from, float per_step) {
+      return __builtin_amdgcn_fmed3f(n - __builtin_ceilf(__builtin_fmaf(c, per_step, -from)), 0.f, n);
+    };
+    const float step = (float)(wave_max(last) / 64 + 1);
+    float sum = 0.f;
 #pragma unroll 4
-    for (int j = 0; j < (p.list.n_work + 3) / 4; ++j) {
-      const i32x4 k = s_lists[j], n = s_lists[16 + j];
-#pragma unroll
-      for (int e = 0; e < 4; ++e) before += k[e] > key ? n[e] : 0;
+    for (int i = wave; i < p.list.n_work; i += waves) {
+      auto of = [&](float v) { return __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int32_t, v), i)); };
+      sum += count((float)lane * step, of(n), of(from), of(per_step));
     }
-  };
-  count();
-  if (__builtin_amdgcn_ballot_w64(before + tiles > p.tile_cap) != 0) {
-    int32_t ahead = 0;
-    for (int j = 0; j < lane; ++j) ahead += reinterpret_cast<const i32_any*>(s_lists)[64 + j];
-    tiles = alone_tiles(p, tiles, ahead);
-    wave_exchange();
-    count();
+    if (waves > 1) {
+      s_sums[wave][lane] = sum;
+      __syncthreads();
+      if (wave != 0) return true;
+#pragma unroll
+      for (int w = 1; w < NW; ++w) sum += s_sums[w][lane];
+    }
+    const float c = (float)(__builtin_popcountll(__builtin_amdgcn_ballot_w64(sum > (float)number)) - 1) * step;
+    above = (int32_t)count(c + step, n, from, per_step);
+    here = (int32_t)count(c, n, from, per_step) - above;
+    place = number - __builtin_amdgcn_readlane(wave_prefix_sum(above), 63) - (wave_prefix_sum(here) - here);
   }
-  const uint64_t mine = __builtin_amdgcn_ballot_w64(number >= before && number < before + tiles);
-  if (mine == 0) return false;
+  const uint64_t mine = __builtin_amdgcn_ballot_w64(place >= 0 && place < here);
+  if (mine == 0) return false;                      // (does not occur: one lane has the place)
   const int at = __builtin_ctzll(mine);
+  int32_t tile = tiles - 1 - above - place;
+  tile = __builtin_amdgcn_readlane(tile, at);
   auto of = [&](int32_t v) { return __builtin_amdgcn_readlane(v, at); };
   const Item u{0, of(it.q_off), of(it.q_len), of(it.q_pos), of(it.k0), of(it.n0), of(it.k1), of(it.n1), of(it.base), 0, 0, of(it.step)};
   const bool shared = __builtin_amdgcn_ballot_w64(lane != at && it.seq >= 0 && it.q_off < u.q_off + u.q_len && u.q_off < it.q_off + it.q_len) != 0;
-  const int32_t r0 = (of(before) + of(tiles) - 1 - number) * p.tile;
+  const int32_t r0 = tile * p.tile;
   const int32_t rows = min(p.tile, u.q_len - r0);
   const int64_t limit = MaskTables{p.q_limit, nullptr}.limit(u, r0 + rows - 1);
   if (lane == 0) {
@@ -114,9 +133,9 @@ __device__ inline void alone_rows(const FwdParams& p, i32x4_any* s_lists) {
   const Item it = lane_item(p, lane);
   const int block = (int)blockIdx.x - p.unit_blocks;
   const int32_t tiles = it.seq >= 0 ? ceil_div(it.q_len, p.tile) : 0;
+  const int32_t upto = wave_prefix_sum(tiles);
   if (block == 0 && threadIdx.x < 64) {
-    int32_t n_tiles = tiles;
-    for (int off = 32; off > 0; off >>= 1) n_tiles += __shfl_xor(n_tiles, off, 64);
+    const int32_t n_tiles = __builtin_amdgcn_readlane(upto, 63);
     const int n_bad = __builtin_popcountll(__builtin_amdgcn_ballot_w64(lane < n_work && it.seq < 0));
     if (lane == 0) {
       SchedHeader h{};
@@ -129,19 +148,18 @@ __device__ inline void alone_rows(const FwdParams& p, i32x4_any* s_lists) {
   if (p.running) return;
   const int32_t row = block * (int)blockDim.x + (int)threadIdx.x;
   const int32_t len = it.seq >= 0 ? it.q_len : 0;
-  int32_t shared = 0, ahead = 0, hits = 0, lost = 0;
+  int32_t shared = 0, hits = 0, lost = 0;
   uint32_t slots = 0;
-  s_lists[lane] = i32x4{it.q_off, len, it.step & 31, tiles};
+  s_lists[lane] = i32x4{it.q_off, len, it.step & 31, 0};
   wave_exchange();
 #pragma unroll 4
   for (int j = 0; j < n_work; ++j) {
     const i32x4 o = s_lists[j];
     shared |= j != lane && o[1] > 0 && it.q_off < o[0] + o[1] && o[0] < it.q_off + len;
-    ahead += j < lane ? o[3] : 0;
   }
   wave_exchange();
   // (rows of dropped tiles are like rows that the item does not have)
-  s_lists[lane] = i32x4{it.q_off, min(len, alone_tiles(p, tiles, ahead) * p.tile), it.step & 31, shared};
+  s_lists[lane] = i32x4{it.q_off, min(len, alone_tiles(p, tiles, upto - tiles) * p.tile), it.step & 31, shared};
   wave_exchange();
 #pragma unroll 4
   for (int j = 0; j < n_work; ++j) {
@@ -197,8 +215,7 @@ __global__ __launch_bounds__(64 * NW, OCC) void fwd_small_kernel(const FwdParams
   if (p.unit_blocks > 0) {
     if ((int)blockIdx.x >= p.unit_blocks) return alone_rows<D>(p, reinterpret_cast<i32x4_any*>(smem));
     const int place = per_xcd ? blockIdx.x / kNumXcd : blockIdx.x;
-    bool found = false;
-    if (tid < 64) found = alone_record(p, place / units_per_tile, reinterpret_cast<i32x4_any*>(smem), s_rec);
+    const bool found = alone_record<NW>(p, place / units_per_tile, reinterpret_cast<float (*)[64]>(smem), s_rec);
     uq.init_alone(units_per_tile, place % units_per_tile, found, &s_next_unit);
   } else {
     uq.init_dealt(p.hdr, p.tiles, xcd, units_per_tile, per_xcd ? blockIdx.x / kNumXcd : blockIdx.x, per_xcd ? gridDim.x / kNumXcd : gridDim.x, p.tile_cap,
@@ -586,6 +603,7 @@ int launch_one(FwdParams p, int64_t units, bool alone, int n_cu, hipStream_t str
 }  // namespace
 
 int launch_fwd_small(FwdParams p, int head_dim, FwdForm form, int64_t units, bool alone, int n_cu, hipStream_t stream) {
+  p.order = alone_order(form, p.list.n_work, units, n_cu);
   if (head_dim == 64)
     return form == kFwdSplit4   ? launch_one<64, 4, 4, 128, 2, 4>(p, units, alone, n_cu, stream)
            : form == kFwdSplit2 ? launch_one<64, 4, 2, 64, 3, 4>(p, units, alone, n_cu, stream)

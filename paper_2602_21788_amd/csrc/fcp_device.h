@@ -165,6 +165,20 @@ __device__ inline int fill_voff(int rpw, int wave, int i, int lane, int row_byte
 
 constexpr int kStreamed = 2;       // nt: the access is not expected to be repeated
 
+// Sum of the values of the lanes up to this one (the last lane's: of all), and the greatest of all (of values >= 0).  Every lane of the wave calls them.
+template <class Op>
+__device__ inline int32_t wave_prefix(int32_t v, Op op) {
+  v = op(v, __builtin_amdgcn_update_dpp(0, v, 0x111, 0xf, 0xf, false));   // from 1, 2, 4 and 8 lanes below, inside 16 lanes
+  v = op(v, __builtin_amdgcn_update_dpp(0, v, 0x112, 0xf, 0xf, false));
+  v = op(v, __builtin_amdgcn_update_dpp(0, v, 0x114, 0xf, 0xf, false));
+  v = op(v, __builtin_amdgcn_update_dpp(0, v, 0x118, 0xf, 0xf, false));
+  v = op(v, __builtin_amdgcn_update_dpp(0, v, 0x142, 0xa, 0xf, false));   // lane 15 to the second, lane 47 to the fourth 16
+  v = op(v, __builtin_amdgcn_update_dpp(0, v, 0x143, 0xc, 0xf, false));   // lane 31 to the upper 32
+  return v;
+}
+__device__ inline int32_t wave_prefix_sum(int32_t v) { return wave_prefix(v, [](int32_t a, int32_t b) { return a + b; }); }
+__device__ inline int32_t wave_max(int32_t v) { return __builtin_amdgcn_readlane(wave_prefix(v, [](int32_t a, int32_t b) { return max(a, b); }), 63); }
+
 // Between a wave's LDS stores and its loads of what other lanes stored (or the other way round).  The hardware works them in order; this keeps the compiler to it.
 __device__ inline void wave_exchange() {
   __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");

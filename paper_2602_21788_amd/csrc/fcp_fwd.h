@@ -25,13 +25,14 @@ struct FwdParams {
   // A launch without a list (fwd_alone in csrc/fcp_sizes.h): block b < unit_blocks finds unit b by itself, the blocks behind them classify the rows.
   int32_t unit_blocks;      // 0: the list tells
   int32_t tile;             // query rows per tile
+  AloneOrder order;         // of the units
   uint8_t* q_state;         // direct mode
   ListArgs list;
 };
 
 constexpr float kRescaleThreshold = 8.f;   // log2 units
 
-// (p.unit_blocks is set by the launch: `alone`)
+// (p.unit_blocks and p.order are set by the launch: `alone`)
 int launch_fwd_small(FwdParams p, int head_dim, FwdForm form, int64_t units, bool alone, int n_cu, hipStream_t stream);
 
 }  // namespace fcp

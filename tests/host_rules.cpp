@@ -35,6 +35,7 @@ int backward_way(int32_t hq, int32_t hkv, int32_t head_dim, int32_t tq, int32_t 
   return (w.one_pass ? 1 : 0) | (w.many_short ? 2 : 0) | (w.either ? 4 : 0);
 }
 int delta_streams_do(int32_t tq, int32_t hq, int32_t head_dim) { return fcp::delta_streams_do(tq, hq, head_dim); }
+int alone_order(int form, int64_t n_work, int64_t units, int n_cu) { return fcp::alone_order((fcp::FwdForm)form, n_work, units, n_cu); }
 int forward_alone(int form, int head_dim, int64_t n_work, int32_t n_parts, int64_t units, int n_cu) {
   return fcp::fwd_alone((fcp::FwdForm)form, head_dim, n_work, n_parts, units, n_cu);
 }

@@ -28,6 +28,7 @@ def lib():
     L.bwd_q_cap.argtypes, L.bwd_q_cap.restype = [i32, i32, i64], i64
     L.forward_alone.argtypes, L.forward_alone.restype = [i32, i32, i64, i32, i64, i32], i32
     L.delta_streams_do.argtypes, L.delta_streams_do.restype = [i32, i32, i32], i32
+    L.alone_order.argtypes, L.alone_order.restype = [i32, i64, i64, i32], i32
     L.deals_first.argtypes, L.deals_first.restype = [i32, i32, i32, i32], i32
     L.keeps_reserve.argtypes, L.keeps_reserve.restype = [i32, i32], i32
     L.backward_way.argtypes, L.backward_way.restype = [i32, i32, i32, i32, i32, i64, i32], i32

@@ -51,6 +51,11 @@ def _passes(ra, work, torch, fcp):
     ([1900, 77, 300], 4, 1, 8, 2, 128, [(0, 400, 900), (2, 5, 64)], []),
     ([1500], 5, 4, 16, 8, 64, None, [3]),                   # a slot less for some rows
     ([4097], 3, 1, 32, 8, 128, None, []),                   # several units per resident block
+    ([4600], 4, 1, 32, 8, 128, [(0, 700, 900)], []),        # tiles in the order of their costs, which a mask makes estimates of
+    ([260 + 97 * i for i in range(11)], 1, 0, 10, 2, 128, None, [3]),       # the waves share the items
+    ([6000, 31, 64, 900, 2000, 129, 1, 700, 333, 65], 1, 0, 6, 2, 64, [(0, 100, 3000), (4, 0, 2000)], []),
+    ([90, 8] * 32, 1, 0, 10, 2, 128, None, list(range(0, 64, 5))),
+    ([1200, 1200], 1, 0, 8, 1, 64, None, []),               # keys divided among the waves: items in the order of their costs
 ])
 def test_without_a_list_and_with_one(lens, deg, rank, hq, hkv, D, spans, drop):
     import torch
@@ -83,6 +88,7 @@ def test_without_a_list_and_with_one(lens, deg, rank, hq, hkv, D, spans, drop):
 @pytest.mark.parametrize("hq,hkv,D,tq,tkv,items,tiles", [
     # (item: rows from, rows, first key, keys, step).  Tiles of 128, 32 and 64 rows; the rows of all items together are more than the keys of the pool
     (4, 4, 64, 512, 512, [(0, 512, 64 * s, 64, s) for s in range(8)], 12),            # the last five items have no tile
+    (32, 32, 64, 512, 512, [(0, 512, 64 * s, 64, s) for s in range(8)], 12),          # the same with more units than CUs
     (2, 1, 64, 600, 1200, [(0, 600, 0, 100, 0), (100, 444, 100, 200, 1), (37, 500, 300, 30, 2)], 41),  # the third loses its end
     (8, 4, 128, 700, 60, [(0, 700, 0, 60, 0)], 2),                                       # one slot
 ])
