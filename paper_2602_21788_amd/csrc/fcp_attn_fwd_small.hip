@@ -81,10 +81,11 @@ __device__ inline bool alone_record(const FwdParams& p, int number, float (*s_su
     const int64_t limit = (int64_t)it.q_pos + p.tile - 1;
     const int32_t first = ceil_div(seen_keys(it, 0, limit), kFwdBN) + (it.n1 > 0 ? ceil_div(seen_keys(it, 1, limit), kFwdBN) : 0);
     const bool rises = p.order == kByTiles && tiles > 1 && last > first;
-    const float n = (float)tiles, per_step = rises ? (n - 1.f) / (float)(last - first) : n, from = (float)(rises ? first : last) * per_step;
-    // (C = 0: all of the item.  Past its last tile's cost: none, as the product's rounding is far less than a step's share.)
+    const float n = (float)tiles, from = (float)(rises ? first : last), per_step = rises ? (n - 1.f) / (float)(last - first) : n;
+    // (C = 0: all of the item.  Past its last tile's cost: none.  A segment has 2^23 keys at most, max_segment_keys, so costs are below 2^19 and their differences exact, and
+    // the product's rounding, 2^-23 of n at most, is less than per_step.)
     auto count = [](float c, float n, float from, float per_step) {
-      return __builtin_amdgcn_fmed3f(n - __builtin_ceilf(__builtin_fmaf(c, per_step, -from)), 0.f, n);
+      return __builtin_amdgcn_fmed3f(n - __builtin_ceilf((c - from) * per_step), 0.f, n);
     };
     const float step = (float)(wave_max(last) / 64 + 1);
     float sum = 0.f;
