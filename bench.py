@@ -53,7 +53,9 @@ def rank_pairs(ra) -> int:
 def merge_bytes(ra, direct: bool) -> int:
     """Algorithmic bytes of the merge: per row and head, each contributing slot is read once (D fp32 + its LSE),
     every slot's LSE is read, and O (bf16) + LSE are written.  direct: fcp_lse_merge_direct skips the rows that
-    exactly one work item feeds (one state byte per row is read)."""
+    exactly one work item feeds (one state byte per row is read), and with one partial slot it launches nothing."""
+    if direct and ra.n_parts == 1:
+        return 0
     parts_per_row = np.zeros(ra.tq, np.int64)
     for w in ra.work:
         parts_per_row[int(w["q_local_off"]):int(w["q_local_off"]) + int(w["q_len"])] += 1
