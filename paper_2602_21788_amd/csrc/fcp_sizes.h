@@ -169,24 +169,25 @@ inline int fwd_blocks_per_cu(FwdForm f, int head_dim) {
 }
 // Does the launch do without a list?  Its blocks then have one unit each, which they find from the items themselves (one item per lane, the slots of a row in
 // one word), and as many blocks as there can be units are launched: there is no scheduling launch to wait for (7 to 10 us), but a block begins with one or
-// two trips to memory more, and the order of the tiles is an estimate (alone_order).  With up to 2.5 units per resident block that
-// pays.  The two calls of the direct forward in a graph, with a list / without, us: 512 tokens, 4 heads of 64 channels (0.13 units per block) 15.9 / 9.7; 4096, the same heads (1.0)
-// 36.0 / 30.3; 4096 over 3 ranks, 8 heads (1.1) 45.4 / 38.6; 40 sequences of 300, 6 heads on 2 of 64 (1.8) 35.6 / 25.2; 30 of 100, 32 on 8 (2.2) 31.3 / 23.8; 4096 over 8 ranks,
-// 32 on 8 (2.4) 60.9 / 51.1; past that 20000 over 8 ranks, 8 heads (2.6) 135.7 / 139.3, 64 of 300, 8 heads (3.2) 52.4 / 57.9, 60 of 500, 10 on 2 of 64 (3.7) 63 / 68.
+// two trips to memory more, and the order of the tiles is an estimate (alone_order).  With up to 2.5 units per resident block that pays.  The two calls of the direct
+// forward in a graph, with a list / without, us: 512 tokens, 4 heads of 64 channels (0.13 units per block) 16.0 / 9.3; 4096, the same heads (1.0) 33.6 / 27.9; 4096 over 3
+// ranks, 8 heads (1.1) 43.7 / 37.0; 30 of 667, 6 on 2 of 64 (1.5) 41.6 / 29.2; 40 sequences of 300, the same heads (1.8) 35.3 / 24.5; 30 of 100, 32 on 8 (2.2) 29.7 / 22.6; 4096 over 8,
+// 32 on 8 (2.4) 57.0 / 47.8.  Past that less, and not always: 20000 over 8 ranks, 8 heads (2.6) 133 / 129, 64 of 300, 8 heads (3.2) 53.6 / 52.3, 60 of 500, 10 on 2 of 64 (3.7)
+// 57.0 / 54.6, 6 of 2000, 32 on 8 of 64 134.6 / 134.8; of 149 lists of more than 8192 tokens with 2.5 to 3 units per block 21 take more than 1 % longer without, the worst 6 %.
 constexpr int kAloneItems = 64, kAloneParts = 32;
 inline bool fwd_alone(FwdForm f, int head_dim, int64_t n_work, int32_t n_parts, int64_t units, int n_cu) {
   return f != kFwdWide && n_work >= 1 && n_work <= kAloneItems && n_parts <= kAloneParts && 2 * units <= 5 * (int64_t)n_cu * fwd_blocks_per_cu(f, head_dim);
 }
 
 // In which order such a launch has its tiles (alone_record in csrc/fcp_attn_fwd_small.hip).  Blocks begin in the order of their numbers, so that with more than one unit
-// per CU the order decides which units share a CU and which begin late.  Direct forward, us, with a list / by items, an item's tiles from its end on and the item with the
-// costliest last tile first / by tiles, each by its own cost:
-//   128 rows a unit: 25834 tokens, one sequence of 16481 over 2 ranks, 4 heads 193 / 231 / 192; 18232 over 2, 4 of 64 channels 143 / 173 / 139; 9580 over 2, 4 heads 230 / 275 /
-//     219; 30 of 667, 6 on 2 of 64 45 / 35 / 29; 16 of 200, 32 on 8 of 64 33 / 18.6 / 16.4; 55 of 80, 8 of 64 26.4 / 10.3 / 11.0.  Of 1992 calls of all kinds 123 / 25 by
-//     items / by tiles are more than 1 % slower than with a list, the worst 24 / 9 %;
-//   keys divided among the waves (64 and 32 rows a unit): the units that begin last are the shortest of all, and several short ones one after the other are as long as a long
-//     one: 2 of 1200, 8 on one of 64 25.2 / 18.9 / 21.8, 5096 over 2, 6 on 2 of 64 42.9 / 35.7 / 39.5;
-//   up to a unit per CU any order does, and none has to be found: 512 tokens, 4 of 64 9.5 / 9.4 (in the order of the list).
+// per CU the order decides which units share a CU and which begin late.  The two calls of the direct forward in a graph, us, with a list / by items, the one with the
+// costliest last tile first, its tiles from the end on / by tiles, each by its own cost:
+//   128 rows a unit: 25834 tokens, one sequence of 16481 over 2 ranks, 4 heads 184 / 226 / 177; 18232 over 2, 4 of 64 channels 141 / 172 / 135; 8642 over 2, 8 heads 108 / 127 /
+//     102; 30 of 667, 6 on 2 of 64 42 / 35 / 30; 16 of 200, 32 on 8 of 64 29 / 19 / 17; but 55 of 80, 8 of 64 22.8 / 10.3 / 11.1 (the search, about 0.3 us for few items and 0.8
+//     for many).  Of 1992 calls of all kinds 123 by items and 25 by tiles took more than 1 % longer than before there were launches without a list, the worst 24 and 9 %;
+//   keys divided among the waves (64 and 32 rows a unit): several short units one after the other take as long as a long one, and by tiles the short ones of all items come
+//     last: 2 of 1200, 8 on one of 64 23.7 / 19.9 / 22.6, 5096 over 2, 6 on 2 of 64 43.8 / 36.8 / 40.1;
+//   up to a unit per CU any order does, and none has to be found.
 enum AloneOrder { kInListOrder, kByItems, kByTiles };
 inline AloneOrder alone_order(FwdForm f, int64_t n_work, int64_t units, int n_cu) {
   if (n_work == 1 || units <= n_cu) return kInListOrder;
